@@ -123,7 +123,9 @@ typedef struct {
   double delta_m, delta_i, delta_s, grad_norm, loss;
   int32_t status;         /* 0 ok, 1 converged (gradient exactly zero), -1 gradient not finite,
                              -2 exchange wait ran out (w~ unchanged)                        */
-  int32_t inner_variant;  /* kernel that ran the last inner loop: 1 generic, 2 register-resident */
+  int32_t inner_variant;  /* kernel that ran the last inner loop: 1 general (softmax rows past the
+                             register-resident kernels: its form cut across workgroups, unless the
+                             general one was asked for by option), 2 register-resident */
   uint64_t n_clamped_z, n_clamped_gamma, n_reg_draws;
   float ms_full_gradient, ms_recenter, ms_inner_loop; /* mean per halp_epoch over timed_epochs */
   int32_t timed_epochs;   /* halp_epoch calls averaged (the last 32 at most since timing was set) */
@@ -168,8 +170,8 @@ typedef struct {
                                     is only taken when R times the count is at most the number of
                                     CUs, and launches of two handles in that mode should not
                                     overlap.  Results do not depend on it                       */
-#define HALP_OPT_EXCHANGE_SPIN_LIMIT 8 /* polls after which a workgroup of the split minibatch
-                                    loop stops waiting for the others for good (default 2^20,
+#define HALP_OPT_EXCHANGE_SPIN_LIMIT 8 /* polls after which a workgroup of a chain cut across
+                                    workgroups (minibatch loop, wide softmax rows) stops waiting for the others for good (default 2^20,
                                     about a second); -1: never wait.  The launch then ends
                                     normally with counters[3] = 1, status -2 and w~ unchanged:
                                     for tests of that path                                */

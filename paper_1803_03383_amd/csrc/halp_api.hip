@@ -77,6 +77,9 @@ int launch_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
 
 int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t s) {
   if (variant == 3) return launch_inner_svrg(h, epoch, s);
+  // softmax rows past the register kernels, unless the general kernel was asked for
+  if (variant == 1 && h.inner_variant == 0 && inner_softmax_split_supported(h) == HALP_OK)
+    return launch_inner_softmax_split(h, epoch, s);
   return variant == 2 ? launch_reg(h, epoch, s) : launch_inner_generic(h, epoch, TraceBufs{}, s);
 }
 
@@ -167,6 +170,10 @@ int halp_create(halp_handle** out, const halp_params* p) {
   if (p->K == 1 && p->B > 1 && (int64_t)p->R * 2 <= h->num_cus) {
     const size_t slots = (size_t)p->R * 2 * kBatchSlots;
     if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), slots * 64 * sizeof(long long)),
+                 "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
+  }
+  if (const size_t words = inner_softmax_split_words(*p, h->num_cus)) {
+    if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), words * sizeof(long long)),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }
   if (p->algorithm != HALP_ALG_SVRG && inner_generic_supported(*p) == HALP_OK &&

@@ -180,6 +180,34 @@ __device__ __forceinline__ long long wave_fold_i64(long long v) {
   return v;
 }
 
+// ---- folds over a row of 16 lanes in fp64 (softmax: one class per lane) ----------
+
+template <typename F>
+__device__ __forceinline__ double row_fold_f64(double v, F op) {
+  auto step = [&](double x, auto mv) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)mv((int)(uint32_t)u), hi = (uint32_t)mv((int)(u >> 32));
+    return op(x, __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo));
+  };
+  v = step(v, [](int t) { return dpp_quad_swap1(t); });
+  v = step(v, [](int t) { return dpp_quad_swap2(t); });
+  v = step(v, [](int t) { return dpp_half_mirror(t); });
+  v = step(v, [](int t) { return dpp_row_mirror(t); });
+  return v;
+}
+
+// Sum over each row of 16 lanes, left in every lane of the row: lanes are joined in
+// adjacent pairs, the pairs' sums in adjacent pairs, and so on (a + b and b + a round
+// alike, so every lane of a group holds the same bits).
+__device__ __forceinline__ double row_sum_f64(double v) {
+  return row_fold_f64(v, [](double x, double y) { return __dadd_rn(x, y); });
+}
+
+// maximum over each row of 16 lanes, left in every lane of the row
+__device__ __forceinline__ double row_max_f64(double v) {
+  return row_fold_f64(v, [](double x, double y) { return fmax(x, y); });
+}
+
 // ---- exp of the inner loop's scalar path -----------------------------------------
 // l'(phi + x^T z) - l'(phi) is rounded to the integer gamma (Algorithm 4), so the last bit of
 // exp can decide an integer.  The library fixes exp as this sequence of correctly rounded

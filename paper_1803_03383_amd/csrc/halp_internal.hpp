@@ -79,6 +79,9 @@ int inner_reg_supported(const halp_params& p);
 int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
+size_t inner_softmax_split_words(const halp_params& p, int num_cus);  // 64-bit exchange words
+int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
+int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_softmax_batch_supported(const halp_handle& h);  // softmax with a minibatch
 int launch_inner_softmax_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_generic_supported(const halp_params& p);

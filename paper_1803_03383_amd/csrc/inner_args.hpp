@@ -46,4 +46,9 @@ inline InArgs make_inner_args(const halp_handle& h, uint32_t epoch) {
   return a;
 }
 
+// chains cut across workgroups: clears what the launch adds to or waits on; applies w~ <- w~ +
+// delta_m z behind it, for the chains none of whose workgroups gave up a wait
+void launch_split_prepare(long long* xbuf, int nwords, uint64_t* counters, int ncounters, hipStream_t s);
+int launch_split_finish(const InArgs& a, double* scales, int R, int bits, hipStream_t s);
+
 }  // namespace halp

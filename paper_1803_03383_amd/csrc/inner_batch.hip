@@ -681,7 +681,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
       if (ok[k] && (!FS || wv == 0)) {
         const int j = j0 + k;
         zg[j] = (XT)z[k];
-        if (P == 1) {  // several workgroups per chain: batch_split_finish applies the offset
+        if (P == 1) {  // several workgroups per chain: split_finish applies the offset
           const double step = __dmul_rn(delta_m, (double)z[k]);
           wg[j] = lp ? (float)step : (float)__dadd_rn((double)wg[j], step);
         }
@@ -707,7 +707,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
 // for chains none of whose workgroups gave up a wait.  A chain with a wait that ran out keeps
 // its w~ (its z is then not a trajectory of the method) and gets status -2 in scales[7].
 template <int BITS>
-__global__ __launch_bounds__(256) void batch_split_finish(InArgs a, double* scales) {
+__global__ __launch_bounds__(256) void split_finish(InArgs a, double* scales) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
   const int chain = blockIdx.y;
   const int j = (int)(blockIdx.x * 256 + threadIdx.x);
@@ -716,15 +716,16 @@ __global__ __launch_bounds__(256) void batch_split_finish(InArgs a, double* scal
     if (j == 0) sc[7] = -2.0;
     return;
   }
-  if (sc[7] != 0.0 || j >= a.d) return;  // a gradient of zero or not finite: the loop did not run
-  const XT* zg = reinterpret_cast<const XT*>(a.z) + (int64_t)chain * a.d;
-  float* wg = a.w + (int64_t)chain * a.d;
+  const int n = a.K * a.d;
+  if (sc[7] != 0.0 || j >= n) return;  // a gradient of zero or not finite: the loop did not run
+  const XT* zg = reinterpret_cast<const XT*>(a.z) + (int64_t)chain * n;
+  float* wg = a.w + (int64_t)chain * n;
   const double step = __dmul_rn(sc[0], (double)zg[j]);
   wg[j] = a.lp ? (float)step : (float)__dadd_rn((double)wg[j], step);
 }
 
 // clears what the split launch accumulates into or waits on
-__global__ void batch_split_prepare(long long* xbuf, int nwords, uint64_t* counters, int ncounters) {
+__global__ void split_prepare(long long* xbuf, int nwords, uint64_t* counters, int ncounters) {
   const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (k < nwords) xbuf[k] = 0;
   if (k < ncounters) counters[k] = 0;
@@ -761,6 +762,18 @@ BtShape pick_shape(const halp_params& p, int64_t row_bytes) {
 }
 
 }  // namespace
+
+void launch_split_prepare(long long* xbuf, int nwords, uint64_t* counters, int ncounters, hipStream_t s) {
+  const int n = nwords > ncounters ? nwords : ncounters;
+  hipLaunchKernelGGL(split_prepare, dim3((n + 255) / 256), dim3(256), 0, s, xbuf, nwords, counters, ncounters);
+}
+
+int launch_split_finish(const InArgs& a, double* scales, int R, int bits, hipStream_t s) {
+  const dim3 grid((a.K * a.d + 255) / 256, R);
+  if (bits == 8) hipLaunchKernelGGL(split_finish<8>, grid, dim3(256), 0, s, a, scales);
+  else hipLaunchKernelGGL(split_finish<16>, grid, dim3(256), 0, s, a, scales);
+  return hip_ok(hipGetLastError());
+}
 
 // K = 1, 2 <= B <= 64, squared or logistic loss, up to 16 waves of 16-byte fragments
 int inner_batch_supported(const halp_handle& h) {
@@ -853,8 +866,7 @@ int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   const dim3 grid(p.R * P), block(64 * nwaves);
   if (P > 1) {
     const int nwords = p.R * 2 * kBatchSlots * kMaxB, ncnt = p.R * 4;
-    hipLaunchKernelGGL(batch_split_prepare, dim3((nwords + 255) / 256), dim3(256), 0, s, h.batch_xbuf, nwords,
-                       h.buf.counters, ncnt);
+    launch_split_prepare(h.batch_xbuf, nwords, h.buf.counters, ncnt, s);
   }
   // parked Philox blocks: 128 bytes per worker thread at 8 strips per thread (120 KB at most)
   const size_t smem = L.ndw == 4 ? (size_t)64 * nwk * 128 : 0;
@@ -879,10 +891,7 @@ int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
 #undef HALP_BT
   const int lrc = launch_loop();
   if (lrc != HALP_OK || P == 1) return lrc;
-  const dim3 fgrid((p.d + 255) / 256, p.R);
-  if (p.b == 8) hipLaunchKernelGGL(batch_split_finish<8>, fgrid, dim3(256), 0, s, a, h.buf.scales);
-  else hipLaunchKernelGGL(batch_split_finish<16>, fgrid, dim3(256), 0, s, a, h.buf.scales);
-  return hip_ok(hipGetLastError());
+  return launch_split_finish(a, h.buf.scales, p.R, p.b, s);
 }
 
 }  // namespace halp

@@ -1,0 +1,486 @@
+// Inner loop of Algorithm 4 (LM-HALP) for softmax regression (K classes, one sampled row per
+// step) on rows too wide for one workgroup: a chain is cut by columns across P workgroups.
+//
+// Workgroup p holds strips [p S, (p + 1) S) of every row of z ([K][d], strips of 16 rounding
+// bits), S = 64 UPL: K / CPW class waves with UPL strips of CPW rows per lane in registers, and
+// one service wave that evaluates the step's scalars.  z, h~ and the strips' Philox blocks stay
+// in registers for the whole epoch; a class wave loads its fragment of the sampled row itself,
+// eight steps ahead.
+//
+// The only thing the workgroups of a chain share is x_i^T z_c.  A class wave adds its part to
+// the class's 64-bit word in device memory with one device-scope atomic: the part in the low
+// 56 bits, a 1 in the top byte.  The service waves read the K words until every top byte has
+// moved by P since the word's last use (two sets of words, by step parity; words are never
+// reset, both fields are taken as differences modulo 2^64), so arrival, sum and hand-over are
+// one trip out and one trip back.  Integer sums: the order of arrival does not matter.  Every
+// workgroup then evaluates the same K gammas.
+//
+// One step:
+//   class waves   x_i^T z_c over the slice, DPP fold, one atomic add per class; meanwhile
+//                 (the trip takes ~0.7 us) the next window's Philox blocks, one strip at a time
+//   service wave  rounding draws and the softmax of the margins for the next step, then polls,
+//                 softmax after the offset, gamma_c into LDS                             | barrier
+//   class waves   integer update of their rows
+//
+// What bounds it: latency.  Per step ~0.1 us dot and fold, 0.6-0.9 us for the exchange (P = 4
+// .. 32: ~0.01 us per atomic on one word; one word per 256 bytes, since atomics of different
+// waves on one line queue up: 10 waves on one line took 2.6 us at P = 20 instead of 1.0), ~0.35 us
+// for the fp64 softmax and quantizer, the rest barrier and update.
+#include <algorithm>
+
+#include "halp_device.hpp"
+#include "inner_args.hpp"
+
+namespace halp {
+namespace {
+
+constexpr int kWin = 8;          // steps per Philox window
+constexpr int kIdxRing = 64;     // sample indices are drawn 64 steps at a time
+constexpr int kKC = 16;          // classes are padded to one DPP row
+constexpr int kWordStride = 32;  // 64-bit words between two classes' exchange words (256 bytes)
+
+__device__ __forceinline__ int mad24(int a, int b, int c) {
+  int r;
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// workgroup barrier that waits for this wave's LDS traffic only: row fragments and exchange
+// words stay in flight across it
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int BITS, int UPL, int CPW, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs a, int P, int chain0, int nchains,
+                                                                        int same_xcd, unsigned long long* xbuf,
+                                                                        int spin_limit) {
+  using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
+  using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
+  using AccT = typename std::conditional<BITS == 8, int, long long>::type;
+  constexpr int CT = 16 / BITS;     // coordinates per strip
+  constexpr int CPL = UPL * CT;     // coordinates per lane and class
+  constexpr int NDW = UPL / 2;      // dwords of a lane's row fragment
+  constexpr bool PK = BITS == 8;    // 8 bits: the two coordinates of a strip as halves of one register
+  typedef short S2 __attribute__((ext_vector_type(2)));
+  constexpr int QMAX = (1 << (BITS - 1)) - 1, QMIN = -(1 << (BITS - 1));
+  // Consecutive workgroups go to the eight XCDs in turn.  Where a chain's parts fit one XCD they
+  // are placed there (the exchange is 0.15-0.3 us shorter); results do not depend on it.
+  int local, part;
+  if (same_xcd) {
+    local = (int)(blockIdx.x & 7) + 8 * (int)(blockIdx.x / (8 * P));
+    part = (int)(blockIdx.x >> 3) % P;
+  } else {
+    local = (int)blockIdx.x / P;
+    part = (int)blockIdx.x - local * P;
+  }
+  if (local >= nchains) return;
+  const int chain = chain0 + local;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = a.d, K = a.K;
+  const int U = (d + CT - 1) / CT;
+  const int NCW = K / CPW;
+  const uint64_t seed = a.seed + (uint64_t)chain;
+  const int64_t T = epoch_steps(seed, a.epoch, a.T, a.option2);
+  const int64_t row_bytes = a.ldxq * (BITS / 8);
+  const double* sc = a.scales + (int64_t)chain * 8;
+  unsigned long long* cnt_out = reinterpret_cast<unsigned long long*>(a.counters + (int64_t)chain * 4);
+  if (sc[7] != 0.0) return;  // converged or unusable gradient: no-op; the counters were cleared before the launch
+
+  unsigned long long* words = xbuf + (int64_t)local * 2 * kKC * kWordStride;  // [parity][class][kWordStride]
+  __shared__ int s_idx[2][kIdxRing];
+  __shared__ int s_ng[2][kKC];  // -gamma_c
+  __shared__ int s_cl[2];       // c_lambda
+  const bool use_reg = a.lambda > 0;
+  const bool lp = a.lp != 0;
+  const uint32_t N = (uint32_t)a.N;
+  // sample index of step 64 blk + lane: any step number names a valid row
+  auto draw_idx = [&](int64_t blk) {
+    const uint64_t t = (uint64_t)blk * kIdxRing + (uint64_t)lane;
+    const U4 r = stream_block(seed, kIdx, a.epoch, t >> 2);
+    return (int)__umulhi(pick(r, (uint32_t)(t & 3)), N);
+  };
+
+  if (wave == NCW) {
+    // ===================================================================== service wave
+    __builtin_amdgcn_s_setprio(3);
+    const float* __restrict__ phi = a.phi + (int64_t)chain * a.N * K;
+    const double inv_s = sc[5];
+    const double dscale = __dmul_rn(a.delta_d, sc[0]);
+    const double aB = a.hyper[2 * chain];  // alpha / B, B = 1
+    const double al = __dmul_rn(aB, a.lambda);
+    unsigned int n_gclamp = 0, n_reg = 0, n_timeout = spin_limit < 0 ? 1u : 0u;
+    const int lc = min(lane, K - 1);
+    const bool live = lane < K;
+
+    const int i0v = draw_idx(0);
+    s_idx[0][lane] = i0v;
+    float phir[kWin];
+#pragma unroll
+    for (int s = 0; s < kWin; ++s) phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(i0v, s) * K + lc];
+    __syncthreads();
+
+    auto softmax = [&](double v) {  // this lane's class probability
+      const double val = live ? v : -INFINITY;
+      const double mx = row_max_f64(val);
+      const double e = live ? halp_exp(__dadd_rn(val, -mx)) : 0.0;
+      return __ddiv_rn(e, row_sum_f64(e));
+    };
+    // rounding word of gamma_c (lanes 0..15: word t K + c) and of the L2 draw (lane 16: word t) of
+    // a step, one Philox evaluation
+    double rho_n = 0.0;
+    int cl_n = 0;
+    auto draw_scalars = [&](int64_t t) {
+      const bool reg = lane == 16;
+      const uint64_t n = reg ? (uint64_t)t : (uint64_t)t * (uint64_t)K + (uint64_t)lc;
+      const U4 r = stream_block(seed, reg ? kReg : kGamma, a.epoch, n >> 2);
+      const uint32_t w = pick(r, (uint32_t)(n & 3));
+      rho_n = __dmul_rn((double)w, 0x1p-32);
+      cl_n = 0;
+      if (use_reg)
+        cl_n = __builtin_amdgcn_readlane(
+            (int)quantize_real(al, (double)(1 << BITS), w, 0.0, (double)QMAX, nullptr), 16);
+    };
+    double a0_n = (double)phir[0], p0_n = softmax(a0_n);
+    draw_scalars(0);
+    unsigned long long old[2] = {0, 0};
+
+    for (int64_t t0 = 0; t0 < T; t0 += kWin) {
+      if ((t0 & (kIdxRing - 1)) == kIdxRing / 2) {  // the next 64 indices: first read three windows on
+        const int64_t blk = (t0 / kIdxRing) + 1;
+        s_idx[blk & 1][lane] = draw_idx(blk);
+      }
+      const int tn = (int)((t0 + kWin) & (2 * kIdxRing - 1)) + (lane & 7);
+      const int idxn = s_idx[tn >> 6][tn & (kIdxRing - 1)];
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) {
+        const int64_t t = t0 + s;
+        if (t < T) {
+          const double a0 = a0_n, p0 = p0_n, rho = rho_n;
+          const int cl = cl_n;
+          // beside the class waves' dots and the trip of their sums: all that does not need them
+          draw_scalars(t + 1);
+          a0_n = (double)phir[(s + 1) % kWin];
+          p0_n = softmax(a0_n);
+          phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(idxn, s) * K + lc];  // step t + 8
+          unsigned long long* w = words + (s & 1) * kKC * kWordStride + lc * kWordStride;
+          unsigned long long v = old[s & 1];
+          for (int spin = 0; n_timeout == 0; ++spin) {  // after one wait ran out, none is tried again
+            if (live) v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // arrivals so far: a signed part below 2^55 in magnitude may borrow from the top byte
+            const bool missing = live && (uint32_t)((v - old[s & 1] + (1ull << 55)) >> 56) != (uint32_t)P;
+            if (__ballot(missing) == 0) break;
+            if (spin >= spin_limit) n_timeout = 1;  // only if a workgroup of the chain never ran: give up
+          }
+          const long long D = (long long)(v - old[s & 1] - ((unsigned long long)P << 56));
+          old[s & 1] = v;
+          const double moved = __dmul_rn(dscale, (double)D);
+          const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
+          // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
+          const double beta = __dmul_rn(aB, __dadd_rn(p1, -p0));
+          const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
+          const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
+          if (live) s_ng[s & 1][lane] = (int)(-fc);
+          if (lane == 0) s_cl[s & 1] = cl;
+          lds_barrier();  // gamma is out; the class waves update z
+          n_gclamp += (live && f != fc) ? 1u : 0u;
+          n_reg += (lane == 0 && cl != 0) ? 1u : 0u;
+        }
+      }
+    }
+    if (part == 0) {  // the scalars are the same in every part
+      if (n_gclamp) atomicAdd(&cnt_out[1], (unsigned long long)n_gclamp);
+      if (n_reg) atomicAdd(&cnt_out[2], (unsigned long long)n_reg);
+    }
+    if (lane == 0 && n_timeout) atomicMax(&cnt_out[3], 1ull);
+  } else {
+    // ======================================================================= class wave
+    const int cls0 = wave * CPW;
+    const int s0 = (part * 64 + lane) * UPL;  // first strip of this lane in every row
+    const int j0 = s0 * CT;
+    const unsigned char* __restrict__ Xq = reinterpret_cast<const unsigned char*>(a.Xq) +
+                                           (int64_t)chain * a.xq_chain_stride * (BITS / 8);
+    // Rows are padded to whole 8-byte groups.  A lane past the row reads the row's start;
+    // whatever lies past d is masked to zero, so that z stays zero there.
+    const int64_t off0 = s0 < U ? (int64_t)s0 * 2 : 0;
+    const int64_t off1 = UPL == 8 && s0 + 4 < U ? off0 + 8 : off0;
+    uint32_t fm[NDW];
+#pragma unroll
+    for (int q = 0; q < NDW; ++q) {
+      const int nv = d - (j0 + q * (32 / BITS));
+      fm[q] = nv >= 32 / BITS ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << (nv * BITS)) - 1u);
+    }
+    uint32_t fr[kWin][NDW];
+    auto request = [&](int s, int i) {
+      const unsigned char* rp = Xq + (int64_t)i * row_bytes;
+      if constexpr (NDW == 1) {
+        fr[s][0] = *reinterpret_cast<const uint32_t*>(rp + off0);
+      } else {
+        const uint2 v = *reinterpret_cast<const uint2*>(rp + off0);
+        fr[s][0] = v.x; fr[s][1] = v.y;
+        if constexpr (NDW == 4) {
+          const uint2 u = *reinterpret_cast<const uint2*>(rp + off1);
+          fr[s][2] = u.x; fr[s][3] = u.y;
+        }
+      }
+    };
+    // z and h~: 8 bits packed, -h~ = 256 hh + hl with 0 <= hl < 256; 16 bits plain
+    S2 zp[CPW][PK ? UPL : 1], hlp[CPW][PK ? UPL : 1], hhp[CPW][PK ? UPL : 1];
+    int z[CPW][PK ? 1 : CPL], hv[CPW][PK ? 1 : CPL];
+    auto row_of = [&](int cc) { return ((int64_t)chain * K + cls0 + cc) * d; };
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) {
+      const HT* __restrict__ hg = reinterpret_cast<const HT*>(a.h) + row_of(cc);
+      const XT* __restrict__ zg = reinterpret_cast<const XT*>(a.z) + row_of(cc);
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) {
+        const int j = min(j0 + k, d - 1);
+        const int zk = j0 + k < d ? (int)zg[j] : 0, hk = j0 + k < d ? (int)hg[j] : 0;
+        if constexpr (PK) {
+          zp[cc][k / 2][k % 2] = (short)zk;
+          hlp[cc][k / 2][k % 2] = (short)((-hk) & 0xFF);
+          hhp[cc][k / 2][k % 2] = (short)((-hk) >> 8);
+        } else {
+          z[cc][k] = zk;
+          hv[cc][k] = hk;
+        }
+      }
+    }
+    uint32_t zrw[CPW][UPL][4], zrn[CPW][UPL][4];  // this window's rounding words and the next one's
+    auto draw_block = [&](uint32_t (&dst)[4], int cc, int u, uint32_t win) {
+      const U4 r = zround_block(seed, a.epoch, (uint32_t)((cls0 + cc) * U + s0 + u), win);
+      dst[0] = r.x; dst[1] = r.y; dst[2] = r.z; dst[3] = r.w;
+    };
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) draw_block(zrn[cc][u], cc, u, 0u);
+    unsigned long long n_zclamp = 0;
+    __syncthreads();  // the first 64 indices are in LDS
+    {
+      const int iv = s_idx[0][lane & 7];
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) request(s, __builtin_amdgcn_readlane(iv, s));
+    }
+
+    for (int64_t t0 = 0; t0 < T; t0 += kWin) {
+#pragma unroll
+      for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+        for (int u = 0; u < UPL; ++u)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) zrw[cc][u][w] = zrn[cc][u][w];
+      const int tn = (int)((t0 + kWin) & (2 * kIdxRing - 1)) + (lane & 7);
+      const int idxn = s_idx[tn >> 6][tn & (kIdxRing - 1)];  // rows of the next window
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) {
+        if (t0 + s < T) {
+          uint32_t xw[NDW];
+#pragma unroll
+          for (int q = 0; q < NDW; ++q) xw[q] = fr[s][q] & fm[q];
+          S2 xp[PK ? UPL : 1];
+          AccT acc[CPW];
+#pragma unroll
+          for (int cc = 0; cc < CPW; ++cc) acc[cc] = 0;
+          auto x_of = [&](int k) { return (int)(int16_t)(xw[k / 2] >> (16 * (k % 2))); };  // 16 bits
+          if constexpr (PK) {
+#pragma unroll
+            for (int u = 0; u < UPL; ++u) {
+              const uint32_t up = __builtin_amdgcn_perm(0u, xw[u / 2], (u & 1) ? 0x030C020Cu : 0x010C000Cu);
+              xp[u] = __builtin_bit_cast(S2, up) >> (S2)(8);
+#pragma unroll
+              for (int cc = 0; cc < CPW; ++cc)
+                acc[cc] = (AccT)__builtin_amdgcn_sdot2(xp[u], zp[cc][u], (int)acc[cc], false);
+            }
+          } else {  // two products of 16-bit factors fit 32 bits; their sums are added in 64
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+              for (int k = 0; k + 1 < CPL; k += 2)
+                acc[cc] += (AccT)mad24(x_of(k), z[cc][k], mad24(x_of(k + 1), z[cc][k + 1], 0));
+          }
+#pragma unroll
+          for (int cc = 0; cc < CPW; ++cc) {
+            const long long D = BITS == 8 ? (long long)wave_fold_i32((int)acc[cc]) : wave_fold_i64((long long)acc[cc]);
+            if (lane == 63)
+              __hip_atomic_fetch_add(&words[((s & 1) * kKC + cls0 + cc) * kWordStride],
+                                     (1ull << 56) + (unsigned long long)D, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+          }
+          // while the sums travel: blocks of the next window, and what of the update needs no gamma
+#pragma unroll
+          for (int q = 0; q < (CPW * UPL + 7) / 8; ++q) {
+            const int ub = s * ((CPW * UPL + 7) / 8) + q;
+            if (ub < CPW * UPL) draw_block(zrn[ub / UPL][ub % UPL], ub / UPL, ub % UPL, (uint32_t)(t0 >> 3) + 1u);
+          }
+          S2 crp[CPW][PK ? UPL : 1], zh[CPW][PK ? UPL : 1];
+          int hr[CPW][PK ? 1 : CPL];
+#pragma unroll
+          for (int cc = 0; cc < CPW; ++cc) {
+            if constexpr (PK) {
+#pragma unroll
+              for (int u = 0; u < UPL; ++u) {
+                const uint32_t rp = __builtin_amdgcn_perm(0u, zrw[cc][u][s >> 1], (s & 1) ? 0x0C030C02u : 0x0C010C00u);
+                crp[cc][u] = __builtin_bit_cast(S2, rp) + hlp[cc][u];  // rounding bits + hl
+                zh[cc][u] = hhp[cc][u] + zp[cc][u];
+              }
+            } else {
+              // h~ = 2^16 hh + hl, 0 <= hl < 2^16: floor((-gamma x + r - h~) / 2^16) =
+              // floor((-gamma x + r - hl) / 2^16) - hh, and that numerator fits 32 bits
+#pragma unroll
+              for (int k = 0; k < CPL; ++k)
+                hr[cc][k] = (int)((zrw[cc][k][s >> 1] >> (16 * (s & 1))) & 0xFFFFu) - (hv[cc][k] & 0xFFFF);
+            }
+          }
+          lds_barrier();
+          const int cl = use_reg ? __builtin_amdgcn_readfirstlane(s_cl[s & 1]) : 0;
+#pragma unroll
+          for (int cc = 0; cc < CPW; ++cc) {
+            const int ng = s_ng[s & 1][cls0 + cc];
+            if constexpr (PK) {
+              if (cl == 0) {
+                // per half: floor((-gamma x + r + hl) / 256) + hh + z; |gamma x| <= 2^14 and
+                // r + hl < 512, so every intermediate fits 16 bits
+                const S2 ngp = S2{(short)ng, (short)ng};
+                S2 vu[UPL];
+                uint32_t hit = 0;
+#pragma unroll
+                for (int u = 0; u < UPL; ++u) {
+                  const S2 v = ((xp[u] * ngp + crp[cc][u]) >> (S2)(8)) + zh[cc][u];
+                  const S2 zc = __builtin_elementwise_min(__builtin_elementwise_max(v, (S2)(QMIN)), (S2)(QMAX));
+                  hit |= __builtin_bit_cast(uint32_t, v) ^ __builtin_bit_cast(uint32_t, zc);
+                  vu[u] = v;
+                  zp[cc][u] = zc;
+                }
+                if (__ballot(hit != 0) != 0) {
+#pragma unroll
+                  for (int u = 0; u < UPL; ++u) {
+                    const uint32_t df = __builtin_bit_cast(uint32_t, vu[u]) ^ __builtin_bit_cast(uint32_t, zp[cc][u]);
+                    n_zclamp += (unsigned long long)__builtin_popcountll(__ballot((df & 0xFFFFu) != 0)) +
+                                (unsigned long long)__builtin_popcountll(__ballot((df >> 16) != 0));
+                  }
+                }
+              } else {  // a step with an L2 draw: 32-bit arithmetic
+#pragma unroll
+                for (int u = 0; u < UPL; ++u) {
+#pragma unroll
+                  for (int e = 0; e < 2; ++e) {
+                    const S2 xu = xp[u], zu2 = zp[cc][u], cu = crp[cc][u], hu = hhp[cc][u];
+                    const int zk = (int)zu2[e];
+                    const int zu = zk + (int)hu[e] + (mad24(ng, (int)xu[e], mad24(-cl, zk, (int)cu[e])) >> 8);
+                    const int zc = min(max(zu, QMIN), QMAX);
+                    n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
+                    zp[cc][u][e] = (short)zc;
+                  }
+                }
+              }
+            } else {
+#pragma unroll
+              for (int k = 0; k < CPL; ++k) {
+                int num = mad24(ng, x_of(k), hr[cc][k]);
+                if (cl != 0) num = mad24(-cl, z[cc][k], num);
+                const int zu = z[cc][k] + (num >> 16) - (hv[cc][k] >> 16);
+                const int zc = min(max(zu, QMIN), QMAX);
+                n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
+                z[cc][k] = zc;
+              }
+            }
+          }
+          request(s, __builtin_amdgcn_readlane(idxn, s));  // step t + 8
+        }
+        __builtin_amdgcn_sched_barrier(0);  // keep one step's temporaries from overlapping the next's
+      }
+    }
+
+    // ---- hand z out (w~ <- w~ + delta_m z is split_finish's)
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) {
+      XT* __restrict__ zg = reinterpret_cast<XT*>(a.z) + row_of(cc);
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) {
+        int zk;
+        if constexpr (PK) zk = (int)zp[cc][k / 2][k % 2];
+        else zk = z[cc][k];
+        if (j0 + k < d) zg[j0 + k] = (XT)zk;
+      }
+    }
+    if (lane == 0 && n_zclamp) atomicAdd(&cnt_out[0], n_zclamp);  // wave-wide count
+  }
+}
+
+template <int BITS, int UPL, int CPW>
+int launch_waves(const InArgs& a, int P, int chain0, int nchains, int same, unsigned long long* xbuf, int spin_limit,
+                 hipStream_t s) {
+  const dim3 grid(same ? 8 * ((nchains + 7) / 8) * P : nchains * P), block(64 * (a.K / CPW + 1));
+#define HALP_SS(W_)                                                                                              \
+  hipLaunchKernelGGL((inner_softmax_split_kernel<BITS, UPL, CPW, W_>), grid, block, 0, s, a, P, chain0, nchains, \
+                     same, xbuf, spin_limit)
+  const int waves = a.K / CPW + 1;
+  if (waves <= 8) HALP_SS(8);
+  else if (waves <= 12) HALP_SS(12);
+  else if constexpr (UPL * CPW <= 4) HALP_SS(16);
+  else return HALP_ERR_UNSUPPORTED;
+#undef HALP_SS
+  return hip_ok(hipGetLastError());
+}
+
+struct SplitShape {
+  int upl, P, batch;  // strips per lane, workgroups per chain, chains in flight at once
+};
+
+// Four strips per lane; eight where four would need more than 24 workgroups per chain (a longer
+// queue at the exchange words and a longer first arrival cost more than a second helping of
+// strips) and a wave has the registers.  us per step, N = 7500, five chains, 2 / 4 / 8 strips:
+// d = 10000, K = 10: 8 bits 3.9 / 3.5 / 4.1, 16 bits 10 / 4.5 / 3.9; d = 2000, K = 10: 2.0 / 2.0 / 3.0;
+// d = 4001, K = 5: 2.3 / 2.0 / 2.1.
+SplitShape pick_shape(const halp_handle& h) {
+  const halp_params& p = h.p;
+  const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
+  const int upl = p.K < 12 && (U + 255) / 256 > 24 ? 8 : 4;
+  const int P = (U + 64 * upl - 1) / (64 * upl);
+  return SplitShape{upl, P, std::min(p.R, h.num_cus / P)};
+}
+
+}  // namespace
+
+size_t inner_softmax_split_words(const halp_params& p, int num_cus) {
+  return p.loss == HALP_LOSS_SOFTMAX && p.B == 1 ? (size_t)std::min(p.R, num_cus) * 2 * kKC * kWordStride : 0;
+}
+
+int inner_softmax_split_supported(const halp_handle& h) {
+  const halp_params& p = h.p;
+  if (p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return HALP_ERR_UNSUPPORTED;
+  if (p.b == 8 && p.d > 131071) return HALP_ERR_UNSUPPORTED;  // int32 dot products stay exact
+  if (!h.bound || !h.buf.Xq || !h.batch_xbuf) return HALP_ERR_NOT_BOUND;
+  const SplitShape sh = pick_shape(h);
+  // top byte of an exchange word: fewer than 128 workgroups per chain, all of them resident
+  if (sh.P > 127 || sh.batch < 1) return HALP_ERR_UNSUPPORTED;
+  return HALP_OK;
+}
+
+int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s) {
+  const halp_params& p = h.p;
+  const int rc = inner_softmax_split_supported(h);
+  if (rc != HALP_OK) return rc;
+  const InArgs a = make_inner_args(h, epoch);
+  const SplitShape sh = pick_shape(h);
+  unsigned long long* xbuf = reinterpret_cast<unsigned long long*>(h.batch_xbuf);
+  for (int c0 = 0; c0 < p.R; c0 += sh.batch) {
+    const int nc = std::min(sh.batch, p.R - c0);
+    const int same = sh.P * ((nc + 7) / 8) <= h.num_cus / 8 && h.num_cus % 8 == 0;
+    launch_split_prepare(h.batch_xbuf, nc * 2 * kKC * kWordStride, h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
+    int r = HALP_ERR_UNSUPPORTED;
+#define HALP_SU(BITS_, UPL_, CPW_)                                             \
+  if (p.b == BITS_ && sh.upl == UPL_ && (p.K > 15 ? 2 : 1) == CPW_)            \
+    r = launch_waves<BITS_, UPL_, CPW_>(a, sh.P, c0, nc, same, xbuf, h.spin_limit, s);
+    HALP_SU(8, 4, 1) HALP_SU(8, 8, 1) HALP_SU(8, 4, 2)
+    HALP_SU(16, 4, 1) HALP_SU(16, 8, 1) HALP_SU(16, 4, 2)
+#undef HALP_SU
+    if (r != HALP_OK) return r;
+  }
+  return launch_split_finish(a, h.buf.scales, p.R, p.b, s);
+}
+
+}  // namespace halp

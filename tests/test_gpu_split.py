@@ -1,0 +1,71 @@
+"""Chains cut across workgroups (rows too wide for one): bit for bit the oracle, at the edges of the
+slices, of the windows of 8 steps and of the 64-step batches of sample indices."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1803_03383_amd as hp
+from oracle import ref
+from test_gpu_lpsvrg import _lp_case, _problem
+from test_gpu_parity import _inner_case, _run_inner
+
+pytestmark = pytest.mark.gpu
+
+SOFTMAX_CASES = [
+    # N, d, K, b, lam, R, T, mu
+    (60, 1025, 3, 8, 0.0, 1, 130, 0.05),      # one coordinate past the register kernels; two batches of indices
+    (80, 1100, 10, 8, 1e-2, 3, 75, 0.05),     # L2 draws, three chains
+    (40, 2048, 2, 8, 0.0, 2, 64, 500.0),      # slices end with the row; saturating
+    (50, 2049, 15, 8, 1e-2, 1, 33, 0.05),     # a slice of one strip, sixteen waves
+    (40, 1500, 16, 8, 1e-2, 1, 41, 0.05),     # two classes to a wave
+    (60, 1601, 3, 16, 1e-2, 2, 90, 0.05),     # 16 bits, ragged
+    (40, 2047, 12, 16, 0.0, 1, 40, 500.0),    # ... saturating
+    (30, 1300, 16, 16, 1e-2, 1, 30, 0.05),    # ... two classes to a wave
+    (30, 10000, 10, 16, 1e-4, 1, 20, 0.05),   # as many workgroups per chain as the ten-class set takes
+    (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than are in flight at once
+    (30, 1100, 4, 8, 0.0, 1, 1, 0.05),
+    (30, 1100, 4, 8, 0.0, 1, 0, 0.05),
+]
+
+
+@pytest.mark.parametrize("N,d,K,b,lam,R,T,mu", SOFTMAX_CASES)
+def test_softmax_split_bit_exact(N, d, K, b, lam, R, T, mu):
+    loss, seed = hp.LOSS_SOFTMAX, 170 + d + T
+    case = _inner_case(loss, N, d, K, 1, b, lam, R, T, seed, mu=mu)
+    P = _run_inner(case, loss, K, 1, b, lam, R, T, seed, 0, mu=mu)
+    P.h.inner_loop(3)
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in range(R):
+        prob = case["mk"](r)
+        out = ref.inner_loop(prob, case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+    if mu > 100:
+        assert cnt[0, 0] > 0
+
+
+def test_softmax_split_algorithm_2():
+    loss, N, d, K, b, T, seed = hp.LOSS_SOFTMAX, 50, 1200, 5, 8, 60, 9
+    case = _lp_case(loss, N, d, K, 1, b, 1, seed, 0.02, 2.0 ** -7)
+    P = _problem(case, loss, K, 1, b, 1, T, seed, 0.02, 2.0 ** -7)
+    P.put("phi", case["phi"]); P.put("h", case["h"]); P.put("scales", case["scales"]); P.put("z", case["z"])
+    P.h.inner_loop(3)
+    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], case["h"][0], case["scales"][0],
+                         3, T, z0=case["z"][0])
+    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
+    assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
+
+
+def test_softmax_split_gives_up_a_wait_without_touching_the_model():
+    loss, N, d, K, b, T, seed = hp.LOSS_SOFTMAX, 40, 1100, 3, 8, 20, 5
+    case = _inner_case(loss, N, d, K, 1, b, 0.0, 1, T, seed, mu=0.05)
+    P = _run_inner(case, loss, K, 1, b, 0.0, 1, T, seed, 0, mu=0.05)
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, -1)
+    P.h.inner_loop(3)
+    assert np.array_equal(P.get("w"), case["w"].reshape(1, K, d))
+    assert P.get("scales")[0, 7] == -2.0
+    with pytest.raises(hp.HalpError) as e:
+        P.h.get_stats(0)
+    assert e.value.code == hp.ERR_EXCHANGE_TIMEOUT
+    torch.cuda.synchronize()
