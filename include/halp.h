@@ -198,12 +198,10 @@ typedef struct {
                                     depend on it                                              */
 
 #define HALP_OPT_EXCHANGE_POLL_DELAY 11 /* split minibatch loop: sleeps of 256 cycles between a
-                                    workgroup publishing its sums of a step and its first poll
-                                    for the others' (0 .. 64, default 3).  A word needs about
-                                    17 such units to cross device memory, but delays of 4 and
-                                    more were measured to lengthen the step, so the default
-                                    only skips the polls that cannot succeed for free.
-                                    Results do not depend on it                                 */
+                                    workgroup adding its sums of a step and its first poll
+                                    for the total (0 .. 64, default 2: polls that cannot
+                                    succeed only add traffic, longer delays lengthen the
+                                    step).  Results do not depend on it                         */
 #define HALP_OPT_GRADIENT_FP32 12 /* softmax gradient pass on rows of up to 800 coordinates, a
                                     multiple of 4: 0 (default): both matrix products take every
                                     fp32 operand as the sum of two halves (22 of its 24 bits)

@@ -34,9 +34,9 @@ struct halp_handle {
   bool gradient_fp32 = false;    // HALP_OPT_GRADIENT_FP32
   const float* fscale = nullptr; // caller's per-feature data scales [d] (device), or null
   // minibatch inner loop split over several workgroups per chain: partial dots and tags
-  long long* batch_xbuf = nullptr;   // [R][2][kBatchSlots][64] tagged partial dots, margins and labels
+  long long* batch_xbuf = nullptr;   // exchange words of chains cut across workgroups
   int inner_parts = 0;               // workgroups per chain of that kernel, 0 = auto
-  int poll_delay = 3;                // 256-cycle sleeps between publishing a step's sums and the first poll
+  int poll_delay = 2;                // 256-cycle sleeps between publishing a step's sums and the first poll
   int spin_limit = 1 << 20;          // polls before a workgroup stops waiting for the others
   double* hyper = nullptr;       // [R][2] step size and mu of each chain (device)
   int32_t* zh_work = nullptr;    // general inner kernel: z and h~ of models too large for LDS
@@ -49,8 +49,8 @@ struct halp_handle {
 
 namespace halp {
 
-constexpr int kBatchMaxParts = 16;
-constexpr int kBatchSlots = kBatchMaxParts + 2;  // exchange words per row, step parity and chain: the parts' sums, margin, label  // workgroups per chain of the minibatch inner loop at most
+constexpr int kBatchMaxParts = 16;  // workgroups per chain of the minibatch inner loop at most
+constexpr int kBatchSlots = 3;      // exchange words per row, step parity and chain: sum, margin, label
 
 struct TraceBufs {
   int64_t M = 0;
