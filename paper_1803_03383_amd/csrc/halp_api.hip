@@ -59,20 +59,21 @@ int need(const void* p) { return p ? HALP_OK : HALP_ERR_NOT_BOUND; }
 
 int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t s);
 
-// the register-resident family: one kernel for scalar margins, one for softmax
+// the register-resident family: kernels for scalar margins and for softmax, one row or a
+// minibatch per step; minibatches of softmax and scalar ones of more than 64 rows share kernels
+bool batch_family(const halp_params& p) { return p.B > 1 && (p.loss == HALP_LOSS_SOFTMAX || p.B > 64); }
+
 int reg_supported(const halp_handle& h) {
-  if (h.p.loss != HALP_LOSS_SOFTMAX && h.p.B > 64) return inner_softmax_batch_supported(h);
-  if (h.p.loss != HALP_LOSS_SOFTMAX && h.p.B > 1) return inner_batch_supported(h);
-  if (h.p.loss == HALP_LOSS_SOFTMAX && h.p.B > 1) return inner_softmax_batch_supported(h);
+  if (batch_family(h.p)) return h.p.b == 8 ? inner_softmax_mfma_supported(h) : inner_softmax_batch_supported(h);
+  if (h.p.B > 1) return inner_batch_supported(h);
   return h.p.loss == HALP_LOSS_SOFTMAX ? inner_softmax_supported(h) : inner_reg_supported(h.p);
 }
 
 int launch_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
-  if (h.p.loss != HALP_LOSS_SOFTMAX && h.p.B > 64) return launch_inner_softmax_batch(h, epoch, s);
-  if (h.p.loss != HALP_LOSS_SOFTMAX && h.p.B > 1) return launch_inner_batch(h, epoch, s);
-  if (h.p.loss == HALP_LOSS_SOFTMAX && h.p.B > 1) return launch_inner_softmax_batch(h, epoch, s);
-  return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s)
-                                       : launch_inner_reg(h, epoch, s);
+  if (batch_family(h.p))
+    return h.p.b == 8 ? launch_inner_softmax_mfma(h, epoch, s) : launch_inner_softmax_batch(h, epoch, s);
+  if (h.p.B > 1) return launch_inner_batch(h, epoch, s);
+  return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s) : launch_inner_reg(h, epoch, s);
 }
 
 int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t s) {
@@ -176,6 +177,9 @@ int halp_create(halp_handle** out, const halp_params* p) {
     if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), words * sizeof(long long)),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }
+  if (const size_t bytes = inner_softmax_mfma_bytes(*p)) {
+    if (hip_fail(hipMalloc(&h->ahead_ws, bytes), "hipMalloc(ahead_ws)")) { halp_destroy(h); return HALP_ERR_HIP; }
+  }
   if (p->algorithm != HALP_ALG_SVRG && inner_generic_supported(*p) == HALP_OK &&
       inner_generic_needs_workspace(*p) &&
       hip_fail(hipMalloc(reinterpret_cast<void**>(&h->zh_work), inner_generic_workspace_bytes(*p)),
@@ -200,6 +204,7 @@ int halp_destroy(halp_handle* h) {
   if (h->xabsmax) (void)hipFree(h->xabsmax);
   if (h->hyper) (void)hipFree(h->hyper);
   if (h->zh_work) (void)hipFree(h->zh_work);
+  if (h->ahead_ws) (void)hipFree(h->ahead_ws);
   if (h->batch_xbuf) (void)hipFree(h->batch_xbuf);
   for (auto& quad : h->ev)
     for (auto& e : quad)

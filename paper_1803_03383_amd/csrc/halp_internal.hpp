@@ -45,6 +45,7 @@ struct halp_handle {
   static constexpr int kTimedEpochs = 32;
   hipEvent_t ev[kTimedEpochs][4] = {};
   int64_t timed = 0;
+  void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
 };
 
 namespace halp {
@@ -82,6 +83,9 @@ int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t inner_softmax_split_words(const halp_params& p, int num_cus);  // 64-bit exchange words
 int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
+size_t inner_softmax_mfma_bytes(const halp_params& p);  // workspace of the minibatch kernel on the matrix cores
+int inner_softmax_mfma_supported(const halp_handle& h);
+int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_softmax_batch_supported(const halp_handle& h);  // softmax with a minibatch
 int launch_inner_softmax_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_generic_supported(const halp_params& p);

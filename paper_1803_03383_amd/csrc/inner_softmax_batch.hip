@@ -1,11 +1,11 @@
 // Inner loop of Algorithm 4 (LM-HALP) for softmax regression with a minibatch: K classes,
-// B sampled rows per step, register-resident form.  Also takes the scalar margins (K = 1,
-// squared or logistic loss) of minibatches wider than the kernel for that case holds.
+// B sampled rows per step, register-resident form at 16 bits (8 bits: inner_softmax_mfma.hip).
+// Also takes the scalar margins (K = 1, squared or logistic loss) of minibatches wider than the
+// kernel for that case holds.
 //
 // One workgroup per chain: K class waves and (up to 15 classes) one more wave that only takes
 // part in the work that is dealt by thread.  Class wave c owns row c of z ([K][d]): lane l holds the UPL
-// consecutive strips (16 rounding bits each: two coordinates at 8 bits, one at 16) starting at
-// l * UPL, with h~ and the strips' Philox blocks of the current window of 8 steps, in
+// consecutive strips (16 rounding bits, one coordinate) starting at l * UPL, with h~ and the strips' Philox blocks of the current window of 8 steps, in
 // registers for the whole epoch.
 //
 // One step:
@@ -38,13 +38,13 @@ __device__ __forceinline__ double logistic_dl(double a, double y) {
 // WAVES: the most waves a launch of this instance has (K + 1 <= WAVES): fewer waves, more registers each
 // MANY: more rows per step than LDS holds at a time (the loop over chunks then has one pass, and the
 // sums of the update live only inside it)
-template <int BITS, int UPL, int WAVES, bool MANY>
+template <int UPL, int WAVES, bool MANY>
 __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs a, int slot_bytes) {
-  using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
-  using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
-  using AccT = typename std::conditional<BITS == 8, int, long long>::type;
-  constexpr int CT = 16 / BITS;    // coordinates per strip
-  constexpr int CPL = UPL * CT;    // coordinates per lane
+  constexpr int BITS = 16;
+  using XT = int16_t;
+  using HT = int32_t;
+  using AccT = long long;
+  constexpr int CPL = UPL;         // coordinates per lane, one per strip
   constexpr int FQ = UPL / 8;      // 16-byte reads per fragment
   const int chain = blockIdx.x;
   const int tid = threadIdx.x, NT = blockDim.x;
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = a.d, K = a.K, Bt = a.B;  // Bt rows per step, taken kMaxB at a time
   const int n = K * d;
-  const int U = (d + CT - 1) / CT;
+  const int U = d;
   const int64_t N = a.N, ldxq = a.ldxq;
   const int row_dw = (int)(ldxq * (BITS / 8) / 4);
   const int slot_dw = slot_bytes / 4;
@@ -83,12 +83,10 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
   __shared__ double s_es[kMaxB * kKPad * 2];   // exponentials before / after
   __shared__ double s_rowst[kMaxB * 4];        // per row: max0, max1, sum0, sum1
   __shared__ int s_gam[kMaxB * kKPad];
-  __shared__ __attribute__((aligned(4))) int8_t s_gamb[kKPad * kMaxB];  // 8 bits: gamma as bytes [class][row]
   __shared__ unsigned long long s_cnt[3];
   __shared__ int s_clambda;
   if (tid < 3) s_cnt[tid] = 0;
   if (tid == 0) s_clambda = 0;
-  for (int e = tid; e < kKPad * kMaxB / 4; e += NT) reinterpret_cast<int*>(s_gamb)[e] = 0;  // rows past B stay 0
 
   const double delta_m = sc[0], inv_s = sc[5];
   const double dscale = __dmul_rn(a.delta_d, delta_m);
@@ -109,7 +107,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
   const int NACT = (U + UPL - 1) / UPL;        // lanes that hold part of the row
   const bool lane_ok = class_wave && lane < NACT;
   const int s0 = lane_ok ? lane * UPL : 0;     // first strip of this lane
-  const int j0 = s0 * CT;
+  const int j0 = s0;
   const int nvalid = lane_ok ? min(CPL, d - j0) : 0;
   int z[CPL];
   int hv[CPL];
@@ -127,7 +125,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
     const int w = ((k * BITS) % 128) / 32;
     const uint32_t xv = w == 0 ? q.x : (w == 1 ? q.y : (w == 2 ? q.z : q.w));
     const int sh = (k * BITS) % 32;
-    return BITS == 8 ? (int)(int8_t)(xv >> sh) : (int)(int16_t)(xv >> sh);
+    return (int)(int16_t)(xv >> sh);
   };
   __syncthreads();
 
@@ -170,35 +168,15 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
     __syncthreads();
     // integer dot products x_m^T z_c
     if (class_wave) {
-      int zpk[BITS == 8 ? CPL / 4 : 1];  // 8 bits: z as bytes, four to a register
-      if constexpr (BITS == 8) {
-#pragma unroll
-        for (int q = 0; q < CPL / 4; ++q)
-          zpk[q] = (z[4 * q] & 0xff) | ((z[4 * q + 1] & 0xff) << 8) | ((z[4 * q + 2] & 0xff) << 16) |
-                   (int)((uint32_t)z[4 * q + 3] << 24);
-      }
 #pragma unroll 4
       for (int m = 0; m < B; ++m) {  // four rows at a time: their reads and folds overlap
         uint4 f[FQ];
 #pragma unroll
         for (int q = 0; q < FQ; ++q) f[q] = frag[m * (slot_dw / 4) + q];
         AccT acc = 0;
-        if constexpr (BITS == 8) {  // four coordinates per instruction, z as packed bytes
-          int a32 = 0;
 #pragma unroll
-          for (int q = 0; q < CPL / 4; ++q) {
-            const uint4& fq = f[q / 4];
-            const uint32_t xv = q % 4 == 0 ? fq.x : (q % 4 == 1 ? fq.y : (q % 4 == 2 ? fq.z : fq.w));
-            a32 = __builtin_amdgcn_sdot4((int)xv, zpk[q], a32, false);
-          }
-          acc = a32;
-        } else {
-#pragma unroll
-          for (int k = 0; k < CPL; ++k) acc += (AccT)(x_of(f, k) * z[k]);  // |x z| < 2^30; z = 0 past the row
-        }
-        long long tot;
-        if (BITS == 8) tot = (long long)wave_sum_i32((int)acc);
-        else tot = wave_sum_i64((long long)acc);
+        for (int k = 0; k < CPL; ++k) acc += (AccT)(x_of(f, k) * z[k]);  // |x z| < 2^30; z = 0 past the row
+        const long long tot = wave_sum_i64(acc);
         if (lane == 0) s_D[m * K + cls] = tot;
       }
     }
@@ -273,52 +251,20 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
       bool hit = false;
       const int gq = (int)quantize_real(beta, inv_s, r, qmind, qmaxd, &hit);
       s_gam[pr] = gq;
-      if constexpr (BITS == 8) s_gamb[c * kMaxB + m] = (int8_t)gq;
       if (hit) my_gclamp += 1;
-    }
-    if constexpr (BITS == 8) {  // the update takes rows in fours: no gamma for the rows past the chunk
-      if (tid < 4 * K) {
-        const int m = B + (tid & 3);
-        if (m < ((B + 3) & ~3)) s_gamb[(tid >> 2) * kMaxB + m] = 0;
-      }
     }
     __syncthreads();
     // u = z - sum_m gamma_m x_m - h~ (- c_lambda z) in (delta_i, 2b); z = Q_(delta_m, b)(u)
     if (class_wave) {
       cl = s_clambda;
-      if constexpr (BITS == 8) {
-        // four rows at a time: their bytes of a coordinate are brought into one register (a 4 x 4
-        // byte transpose per dword of the fragments) and meet the rows' four gammas in one
-        // 4-way dot product
-        for (int m = 0; m < B; m += 4) {
-          uint4 f[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) f[i] = frag[min(m + i, B - 1) * (slot_dw / 4)];  // gamma is 0 past B
-          const int g4 = reinterpret_cast<const int*>(s_gamb)[(cls * kMaxB + m) >> 2];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            auto dw = [&](const uint4& v) { return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w)); };
-            const uint32_t ra = dw(f[0]), rb = dw(f[1]), rc = dw(f[2]), rd = dw(f[3]);
-            const uint32_t ab_lo = __builtin_amdgcn_perm(rb, ra, 0x05010400u), ab_hi = __builtin_amdgcn_perm(rb, ra, 0x07030602u);
-            const uint32_t cd_lo = __builtin_amdgcn_perm(rd, rc, 0x05010400u), cd_hi = __builtin_amdgcn_perm(rd, rc, 0x07030602u);
-            const uint32_t t0 = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u), t1 = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u);
-            const uint32_t t2 = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u), t3 = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
-            gsum[4 * q + 0] = __builtin_amdgcn_sdot4((int)t0, g4, (int)gsum[4 * q + 0], false);
-            gsum[4 * q + 1] = __builtin_amdgcn_sdot4((int)t1, g4, (int)gsum[4 * q + 1], false);
-            gsum[4 * q + 2] = __builtin_amdgcn_sdot4((int)t2, g4, (int)gsum[4 * q + 2], false);
-            gsum[4 * q + 3] = __builtin_amdgcn_sdot4((int)t3, g4, (int)gsum[4 * q + 3], false);
-          }
-        }
-      } else {
 #pragma unroll 4
-        for (int m = 0; m < B; ++m) {
-          uint4 f[FQ];
+      for (int m = 0; m < B; ++m) {
+        uint4 f[FQ];
 #pragma unroll
-          for (int q = 0; q < FQ; ++q) f[q] = frag[m * (slot_dw / 4) + q];
-          const int g = s_gam[m * K + cls];
+        for (int q = 0; q < FQ; ++q) f[q] = frag[m * (slot_dw / 4) + q];
+        const int g = s_gam[m * K + cls];
 #pragma unroll
-          for (int k = 0; k < CPL; ++k) gsum[k] += (AccT)g * (AccT)x_of(f, k);
-        }
+        for (int k = 0; k < CPL; ++k) gsum[k] += (AccT)g * (AccT)x_of(f, k);
       }
     }
     __syncthreads();  // the rows, indices and gammas of this chunk are done with
@@ -332,18 +278,13 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
 #pragma unroll
       for (int u = 0; u < UPL; ++u) {
         const uint32_t field = zround_field(zblk[u], (uint32_t)t);
-#pragma unroll
-        for (int e = 0; e < CT; ++e) {
-          const int k = u * CT + e;
-          if (k < nvalid) {
-            const long long zk = z[k];
-            const long long v = -(long long)hv[k] - (long long)cl * zk - (long long)gsum[k];
-            const long long rb = (long long)((field >> (e * BITS)) & ((1u << BITS) - 1u));
-            long long zn = zk + ((v + rb) >> BITS);  // arithmetic shift: floor
-            if (zn > QMAX) { zn = QMAX; my_zclamp += 1; }
-            if (zn < QMIN) { zn = QMIN; my_zclamp += 1; }
-            z[k] = (int)zn;
-          }
+        if (u < nvalid) {
+          const long long zk = z[u];
+          const long long v = -(long long)hv[u] - (long long)cl * zk - (long long)gsum[u];
+          long long zn = zk + ((v + (long long)field) >> BITS);  // arithmetic shift: floor
+          if (zn > QMAX) { zn = QMAX; my_zclamp += 1; }
+          if (zn < QMIN) { zn = QMIN; my_zclamp += 1; }
+          z[u] = (int)zn;
         }
       }
     }
@@ -367,26 +308,17 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_batch_kernel(InArgs 
   if (tid < 4) cnt_out[tid] = tid < 3 ? s_cnt[tid] : 0ull;
 }
 
-// strips per lane: 8 up to 512 strips per row, 16 (16 bits only) up to 1024
-int strips_per_lane(const halp_params& p) {
-  const int ct = 16 / p.b;
-  const int U = (p.d + ct - 1) / ct;
-  if (U <= 512) return 8;
-  return (p.b == 16 && U <= 1024) ? 16 : 0;
-}
+// strips per lane: 8 up to 512 coordinates per row, 16 up to 1024
+int strips_per_lane(const halp_params& p) { return p.d <= 512 ? 8 : (p.d <= 1024 ? 16 : 0); }
 
 // bytes of a row's slot in LDS: whole fragments for every lane on the row
-int slot_bytes_of(const halp_params& p, int upl) {
-  const int ct = 16 / p.b;
-  const int U = (p.d + ct - 1) / ct;
-  return (U + upl - 1) / upl * upl * 2;
-}
+int slot_bytes_of(const halp_params& p, int upl) { return (p.d + upl - 1) / upl * upl * 2; }
 
-template <int BITS, int UPL, int WAVES>
+template <int UPL, int WAVES>
 int launch_waves(const InArgs& a, int R, int slot_bytes, hipStream_t s) {
   const size_t smem = (size_t)std::min(a.B, kMaxB) * slot_bytes;
-  auto kern = a.B > kMaxB ? inner_softmax_batch_kernel<BITS, UPL, WAVES, true>
-                          : inner_softmax_batch_kernel<BITS, UPL, WAVES, false>;
+  auto kern = a.B > kMaxB ? inner_softmax_batch_kernel<UPL, WAVES, true>
+                          : inner_softmax_batch_kernel<UPL, WAVES, false>;
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)smem) != hipSuccess)
     return HALP_ERR_HIP;
@@ -394,18 +326,18 @@ int launch_waves(const InArgs& a, int R, int slot_bytes, hipStream_t s) {
   return hip_ok(hipGetLastError());
 }
 
-template <int BITS, int UPL>
+template <int UPL>
 int launch_one(const InArgs& a, int R, int slot_bytes, hipStream_t s) {
-  if (a.K + 1 <= 8) return launch_waves<BITS, UPL, 8>(a, R, slot_bytes, s);
-  if (a.K + 1 <= 12) return launch_waves<BITS, UPL, 12>(a, R, slot_bytes, s);
-  return launch_waves<BITS, UPL, 16>(a, R, slot_bytes, s);
+  if (a.K + 1 <= 8) return launch_waves<UPL, 8>(a, R, slot_bytes, s);
+  if (a.K + 1 <= 12) return launch_waves<UPL, 12>(a, R, slot_bytes, s);
+  return launch_waves<UPL, 16>(a, R, slot_bytes, s);
 }
 
 }  // namespace
 
 int inner_softmax_batch_supported(const halp_handle& h) {
   const halp_params& p = h.p;
-  if (p.B < 2 || p.B > 512 || p.K > kMaxK) return HALP_ERR_UNSUPPORTED;
+  if (p.b != 16 || p.B < 2 || p.B > 512 || p.K > kMaxK) return HALP_ERR_UNSUPPORTED;
   // softmax; or a scalar margin with more rows per step than the kernel for that case takes
   if (p.loss == HALP_LOSS_SOFTMAX ? p.K < 2 : (p.K != 1 || p.B <= 64)) return HALP_ERR_UNSUPPORTED;
   const int upl = strips_per_lane(p);
@@ -423,8 +355,7 @@ int launch_inner_softmax_batch(const halp_handle& h, uint32_t epoch, hipStream_t
   const InArgs a = make_inner_args(h, epoch);
   const int upl = strips_per_lane(p);
   const int slot = slot_bytes_of(p, upl);
-  if (p.b == 8) return launch_one<8, 8>(a, p.R, slot, s);
-  return upl == 8 ? launch_one<16, 8>(a, p.R, slot, s) : launch_one<16, 16>(a, p.R, slot, s);
+  return upl == 8 ? launch_one<8>(a, p.R, slot, s) : launch_one<16>(a, p.R, slot, s);
 }
 
 }  // namespace halp

@@ -1,0 +1,39 @@
+// What the softmax inner loops (and the scalar margins of wide minibatches) need at every step
+// and what does not depend on z, made ahead of the loop by the whole chip: sample indices,
+// margins and softmax of the sampled rows before the offset, rounding words of gamma, L2 draws
+// and the rounding bits of z.  A chain's loop is one workgroup's dependent chain; with these
+// made elsewhere it keeps only what follows from z.  An epoch is cut into segments whose
+// records fit the workspace: records of a segment, then its steps, then the next segment.
+#pragma once
+
+#include "inner_args.hpp"
+
+namespace halp {
+
+struct AheadRec {  // one (row, class) of a step, 16 bytes
+  double p0;       // softmax of the margins (K = 1: l'(phi_i), logistic only)
+  float phi;       // margin (class 1 of a row with K = 1: the label)
+  uint32_t rho;    // rounding word of gamma
+};
+constexpr int kAheadK = 16;  // classes are padded to one DPP row
+
+struct Ahead {
+  AheadRec* rec;    // [chain][step][row][16]
+  int32_t* idx;     // [chain][step][rows]
+  int32_t* cl;      // [chain][step] c_lambda
+  uint16_t* zbits;  // [chain][step][class][UP] rounding bits of the strips, or null
+  int64_t S;        // steps per segment, a multiple of 8 (buffer dimension)
+  int UP;           // strips per class, padded
+  int64_t t0;       // first step of the segment
+  int64_t t1;       // one past its last step
+};
+
+// bytes of workspace for S steps
+size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP);
+// steps per segment that fit `bytes`: a multiple of 8, 0 if not even 8 fit
+int64_t ahead_steps(const halp_params& p, int chains, int UP, size_t bytes);
+Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws);
+// fills the segment [t0, t1) of chains chain0 .. chain0 + chains - 1 (zbits only where UP > 0)
+int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chains, hipStream_t stream);
+
+}  // namespace halp

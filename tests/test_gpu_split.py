@@ -69,3 +69,29 @@ def test_softmax_split_gives_up_a_wait_without_touching_the_model():
         P.h.get_stats(0)
     assert e.value.code == hp.ERR_EXCHANGE_TIMEOUT
     torch.cuda.synchronize()
+
+
+MATRIX_CASES = [
+    # N, d, K, B, lam, R, T, mu: the 8-bit minibatch kernel on the matrix cores
+    (200, 1024, 16, 64, 1e-3, 1, 9, 0.05),    # every block, 64 rows do not fit LDS: two chunks
+    (200, 961, 10, 48, 0.0, 1, 9, 0.05),      # sixteen blocks, one ragged; one chunk of 48 rows
+    (150, 513, 3, 17, 1e-2, 2, 21, 0.05),     # a second block for the first owner only
+    (150, 64, 2, 33, 0.0, 1, 17, 500.0),      # one block; saturating
+    (100, 65, 9, 16, 1e-2, 1, 30, 0.05),
+    (90, 40, 16, 512, 1e-2, 8, 150, 0.05),    # several segments of records, sixteen chunks
+]
+
+
+@pytest.mark.parametrize("N,d,K,B,lam,R,T,mu", MATRIX_CASES)
+def test_softmax_minibatch_on_the_matrix_cores_bit_exact(N, d, K, B, lam, R, T, mu):
+    loss, b, seed = hp.LOSS_SOFTMAX, 8, 270 + d + T
+    case = _inner_case(loss, N, d, K, B, b, lam, R, T, seed, mu=mu)
+    P = _run_inner(case, loss, K, B, b, lam, R, T, seed, 2, mu=mu)
+    P.h.inner_loop(3)
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in range(R):
+        prob = case["mk"](r)
+        out = ref.inner_loop(prob, case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
