@@ -78,6 +78,7 @@ int launch_full_gradient_static(const halp_params& p, const halp_buffers& buf, h
 int launch_recenter(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_reg_supported(const halp_params& p);
 int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s);
+size_t inner_softmax_bytes(const halp_params& p);  // workspace of the softmax kernel's records
 int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t inner_softmax_split_words(const halp_params& p, int num_cus);  // 64-bit exchange words

@@ -528,27 +528,6 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
 
 int mfma_up(const halp_params& p) { return 32 * ((p.d + 63) / 64); }  // strips per class in the records
 
-// Workspace of the records: 64 MB, more for many chains (1 MB each) up to 256 MB.
-size_t mfma_budget(const halp_params& p) {
-  const size_t mb = (size_t)1 << 20;
-  return std::min((size_t)256 * mb, std::max((size_t)64 * mb, (size_t)p.R * mb));
-}
-
-// chains per launch and steps per segment
-struct Segments {
-  int chains;
-  int64_t S;
-};
-Segments mfma_segments(const halp_params& p) {
-  int chains = std::min(p.R, 256);
-  int64_t S = 0;
-  for (; chains >= 1; chains = (chains + 1) / 2) {
-    S = ahead_steps(p, chains, mfma_up(p), mfma_budget(p));
-    if (S >= 8 || chains == 1) break;
-  }
-  return Segments{chains, S};
-}
-
 // LDS of an iteration of `rows` rows: two buffers of them, and the owners' parts of D
 size_t mfma_lds(int d, int rows) {
   const int nblk = (d + 63) / 64;
@@ -578,7 +557,7 @@ int launch_one(const InArgs& a, const Ahead& s, int c0, int chains, int last, hi
 size_t inner_softmax_mfma_bytes(const halp_params& p) {
   if (p.algorithm == HALP_ALG_SVRG || p.b != 8 || p.d > 1024 || p.K > 16 || p.B < 2 || p.B > 512) return 0;
   if (p.loss == HALP_LOSS_SOFTMAX ? p.K < 2 : p.B <= 64) return 0;
-  const Segments g = mfma_segments(p);
+  const AheadSegments g = ahead_segments(p, mfma_up(p));
   return ahead_bytes(p, g.chains, g.S, mfma_up(p));
 }
 
@@ -593,32 +572,16 @@ int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t 
   const int rc = inner_softmax_mfma_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const Segments g = mfma_segments(p);
   const bool many = p.B > mfma_rows(p.d, p.B), soft = p.loss == HALP_LOSS_SOFTMAX;
   const bool al16 = h.buf.ldxq % 16 == 0 && reinterpret_cast<uintptr_t>(h.buf.Xq) % 16 == 0;
-  for (int c0 = 0; c0 < p.R; c0 += g.chains) {
-    const int nc = std::min(g.chains, p.R - c0);
-    Ahead s = ahead_layout(p, g.chains, g.S, mfma_up(p), h.ahead_ws);
-    int64_t t = 0;
-    do {
-      s.t0 = t;
-      s.t1 = std::min(t + g.S, p.T);
-      const int last = s.t1 == p.T;
-      if (s.t1 > s.t0) {
-        const int r = launch_ahead(a, s, 8, c0, nc, st);
-        if (r != HALP_OK) return r;
-      }
-      int r = HALP_ERR_UNSUPPORTED;
+  return for_segments(a, p, mfma_up(p), h.ahead_ws, st, [&](const Ahead& s, int c0, int chains, int last) -> int {
 #define HALP_MF(MANY_, AL_, SOFT_) \
-  if (many == MANY_ && al16 == AL_ && soft == SOFT_) r = launch_one<MANY_, AL_, SOFT_>(a, s, c0, nc, last, st);
-      HALP_MF(false, true, true) HALP_MF(false, false, true) HALP_MF(true, true, true) HALP_MF(true, false, true)
-      HALP_MF(true, true, false) HALP_MF(true, false, false)  // one class: more than 64 rows only
+  if (many == MANY_ && al16 == AL_ && soft == SOFT_) return launch_one<MANY_, AL_, SOFT_>(a, s, c0, chains, last, st);
+    HALP_MF(false, true, true) HALP_MF(false, false, true) HALP_MF(true, true, true) HALP_MF(true, false, true)
+    HALP_MF(true, true, false) HALP_MF(true, false, false)  // one class: more than 64 rows only
 #undef HALP_MF
-      if (r != HALP_OK) return r;
-      t = s.t1;
-    } while (t < p.T);
-  }
-  return HALP_OK;
+    return HALP_ERR_UNSUPPORTED;
+  });
 }
 
 }  // namespace halp

@@ -56,19 +56,18 @@ __global__ __launch_bounds__(256) void ahead_scalars(InArgs a, Ahead s, int chai
 }
 
 // Two strips of a class and one window of 8 steps per thread: two Philox blocks, eight dwords, a
-// wave's stores 256 contiguous bytes each.
+// wave's stores 256 contiguous bytes each.  Strips past the row are left as they are: whatever
+// bits stand there, a coordinate with z = h~ = x = 0 stays 0.
 __global__ __launch_bounds__(256) void ahead_zbits(InArgs a, Ahead s, int bits, int chain0) {
   const int local = blockIdx.z;
   const uint64_t seed = a.seed + (uint64_t)(chain0 + local);
-  const int per = s.UP / 2;
+  const int ct = 16 / bits, U = (a.d + ct - 1) / ct, per = (U + 1) / 2;
   const int v = (int)(blockIdx.x * 256 + threadIdx.x);
   if (v >= a.K * per) return;
   const int c = v / per, u = 2 * (v - c * per);
-  const int ct = 16 / bits, U = (a.d + ct - 1) / ct;
   const int64_t tw = s.t0 + 8 * (int64_t)blockIdx.y;
-  U4 r0{0, 0, 0, 0}, r1{0, 0, 0, 0};
-  if (u < U) r0 = zround_block(seed, a.epoch, (uint32_t)(c * U + u), (uint32_t)(tw >> 3));
-  if (u + 1 < U) r1 = zround_block(seed, a.epoch, (uint32_t)(c * U + u + 1), (uint32_t)(tw >> 3));
+  const U4 r0 = zround_block(seed, a.epoch, (uint32_t)(c * U + u), (uint32_t)(tw >> 3));
+  const U4 r1 = zround_block(seed, a.epoch, (uint32_t)(c * U + u + 1), (uint32_t)(tw >> 3));
   uint32_t* out = reinterpret_cast<uint32_t*>(s.zbits + (((int64_t)local * s.S + (tw - s.t0)) * a.K + c) * s.UP + u);
   const int64_t stride = (int64_t)a.K * s.UP / 2;  // dwords per step
 #pragma unroll
@@ -90,6 +89,16 @@ int64_t ahead_steps(const halp_params& p, int chains, int UP, size_t bytes) {
   int64_t S = (int64_t)(bytes / per8) * 8;  // each part is rounded up once per call, so this is on the safe side
   const int64_t most = (p.T + 7) / 8 * 8;
   return S < most ? S : (most > 8 ? most : 8);
+}
+
+AheadSegments ahead_segments(const halp_params& p, int UP) {
+  const size_t mb = (size_t)1 << 20;
+  const size_t budget = std::min((size_t)1024 * mb, std::max((size_t)64 * mb, (size_t)p.R * 4 * mb));
+  int chains = std::min(p.R, 256);
+  for (;; chains = (chains + 1) / 2) {
+    const int64_t S = ahead_steps(p, chains, UP, budget);
+    if (S >= 8 || chains == 1) return AheadSegments{chains, S >= 8 ? S : 8};
+  }
 }
 
 Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws) {
@@ -115,7 +124,8 @@ int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chai
   if (bits == 8) hipLaunchKernelGGL(ahead_scalars<8>, g1, dim3(256), 0, stream, a, s, chain0);
   else hipLaunchKernelGGL(ahead_scalars<16>, g1, dim3(256), 0, stream, a, s, chain0);
   if (s.UP > 0) {
-    const dim3 g2((unsigned)((a.K * (s.UP / 2) + 255) / 256), (unsigned)((steps + 7) / 8), chains);
+    const int U = (a.d + 16 / bits - 1) / (16 / bits);
+    const dim3 g2((unsigned)((a.K * ((U + 1) / 2) + 255) / 256), (unsigned)((steps + 7) / 8), chains);
     hipLaunchKernelGGL(ahead_zbits, g2, dim3(256), 0, stream, a, s, bits, chain0);
   }
   return hip_ok(hipGetLastError());

@@ -33,7 +33,37 @@ size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP);
 // steps per segment that fit `bytes`: a multiple of 8, 0 if not even 8 fit
 int64_t ahead_steps(const halp_params& p, int chains, int UP, size_t bytes);
 Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws);
+// how an epoch is cut: chains per launch (at most 256) and steps per segment, from a workspace of
+// 64 MB, more for many chains (4 MB each) up to 1 GB: a segment costs its three launches and the
+// loop's way in and out, ~30 us, which 256 chains at 125 steps a segment paid with 10 %
+struct AheadSegments {
+  int chains;
+  int64_t S;
+};
+AheadSegments ahead_segments(const halp_params& p, int UP);
 // fills the segment [t0, t1) of chains chain0 .. chain0 + chains - 1 (zbits only where UP > 0)
 int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chains, hipStream_t stream);
+
+// The epoch's launches: for every group of chains, segment after segment, the records and then
+// loop(segment, first chain, chains, last segment?).  An epoch without steps is one empty segment.
+template <typename F>
+int for_segments(const InArgs& a, const halp_params& p, int UP, void* ws, hipStream_t st, F loop) {
+  const AheadSegments g = ahead_segments(p, UP);
+  for (int c0 = 0; c0 < p.R; c0 += g.chains) {
+    const int nc = g.chains < p.R - c0 ? g.chains : p.R - c0;
+    Ahead s = ahead_layout(p, g.chains, g.S, UP, ws);
+    do {
+      s.t0 = s.t1;
+      s.t1 = s.t0 + g.S < p.T ? s.t0 + g.S : p.T;
+      if (s.t1 > s.t0) {
+        const int r = launch_ahead(a, s, p.b, c0, nc, st);
+        if (r != HALP_OK) return r;
+      }
+      const int r = loop(s, c0, nc, s.t1 == p.T ? 1 : 0);
+      if (r != HALP_OK) return r;
+    } while (s.t1 < p.T);
+  }
+  return HALP_OK;
+}
 
 }  // namespace halp

@@ -95,3 +95,31 @@ def test_softmax_minibatch_on_the_matrix_cores_bit_exact(N, d, K, B, lam, R, T, 
         assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
         assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
         assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+
+ROW_CASES = [
+    # N, d, K, b, lam, R, T, mu: one row per step, a class (or two) to a wave
+    (60, 1024, 15, 8, 1e-2, 1, 4500, 0.05),   # sixteen waves, full strips; two segments of records
+    (60, 1023, 16, 8, 1e-2, 1, 30, 500.0),    # two classes to a wave; saturating
+    (60, 1001, 14, 16, 1e-2, 1, 40, 0.05),    # 16 bits, the update all after the barrier
+    (60, 1023, 5, 16, 1e-2, 2, 40, 500.0),    # ... saturating
+    (60, 511, 16, 16, 0.0, 1, 30, 0.05),
+    (40, 63, 2, 16, 1e-2, 1, 40, 500.0),      # a coordinate to a lane; the service wave last
+    (40, 2, 3, 8, 1e-2, 1, 33, 0.05),
+    (40, 1, 8, 16, 1e-2, 300, 9, 0.05),       # more chains than one launch takes
+]
+
+
+@pytest.mark.parametrize("N,d,K,b,lam,R,T,mu", ROW_CASES)
+def test_softmax_rows_in_registers_bit_exact(N, d, K, b, lam, R, T, mu):
+    loss, seed = hp.LOSS_SOFTMAX, 370 + d + T
+    case = _inner_case(loss, N, d, K, 1, b, lam, R, T, seed, mu=mu)
+    P = _run_inner(case, loss, K, 1, b, lam, R, T, seed, 2, mu=mu)
+    P.h.inner_loop(3)
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in {0, R // 2, R - 1}:
+        prob = case["mk"](r)
+        out = ref.inner_loop(prob, case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
