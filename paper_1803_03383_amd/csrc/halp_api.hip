@@ -4,7 +4,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
+#include <unordered_map>
 #include <vector>
 
 #include "halp_internal.hpp"
@@ -76,11 +78,37 @@ int launch_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s) : launch_inner_reg(h, epoch, s);
 }
 
+// The workgroups of a chain cut by columns wait for one another, with a limit.  Two such launches
+// on one device at a time, of two handles on two streams, could each hold half of the CUs while
+// their chains wait for parts that find none until the limit has run out.  So they run one
+// after the other, whatever their streams: each waits for the event behind the one before it.
+// Not under capture, where an event of another stream cannot be waited for.
+int launch_softmax_split_in_order(const halp_handle& h, uint32_t epoch, hipStream_t s) {
+  static std::mutex lock;
+  static std::unordered_map<int, hipEvent_t> last;  // by device
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return launch_inner_softmax_split(h, epoch, s);
+  int dev = 0;
+  if (hip_fail(hipGetDevice(&dev), "hipGetDevice")) return HALP_ERR_HIP;
+  const std::lock_guard<std::mutex> guard(lock);
+  hipEvent_t& ev = last[dev];
+  if (ev) {
+    if (hip_fail(hipStreamWaitEvent(s, ev, 0), "hipStreamWaitEvent")) return HALP_ERR_HIP;
+  } else if (hip_fail(hipEventCreateWithFlags(&ev, hipEventDisableTiming), "hipEventCreate")) {
+    ev = nullptr;
+    return HALP_ERR_HIP;
+  }
+  const int r = launch_inner_softmax_split(h, epoch, s);
+  if (hip_fail(hipEventRecord(ev, s), "hipEventRecord")) return HALP_ERR_HIP;
+  return r;
+}
+
 int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t s) {
   if (variant == 3) return launch_inner_svrg(h, epoch, s);
   // softmax rows past the register kernels, unless the general kernel was asked for
   if (variant == 1 && h.inner_variant == 0 && inner_softmax_split_supported(h) == HALP_OK)
-    return launch_inner_softmax_split(h, epoch, s);
+    return launch_softmax_split_in_order(h, epoch, s);
   return variant == 2 ? launch_reg(h, epoch, s) : launch_inner_generic(h, epoch, TraceBufs{}, s);
 }
 

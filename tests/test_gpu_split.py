@@ -71,6 +71,27 @@ def test_softmax_split_gives_up_a_wait_without_touching_the_model():
     torch.cuda.synchronize()
 
 
+def test_softmax_split_on_two_streams():
+    """The second launch finds four CUs of every 32 free and needs seven, with a wait limit far below the first
+    one's run time: it has to start when the first has ended and give the bits it gives alone."""
+    loss, N, d, K, b, T, seed = hp.LOSS_SOFTMAX, 30, 3584, 14, 8, 40, 11
+    args = (loss, N, d, K, 1, b, 0.0)
+    one, two = _inner_case(*args, 32, T, seed, mu=0.05), _inner_case(*args, 8, T, seed, mu=0.05)
+    first = _run_inner(one, loss, K, 1, b, 0.0, 32, 20000, seed, 0, mu=0.05)
+    second = _run_inner(two, loss, K, 1, b, 0.0, 8, T, seed, 0, mu=0.05)
+    second.h.inner_loop(3)
+    alone = second.get("z").copy()
+    assert np.any(alone)
+    second.put("z", np.zeros_like(alone))
+    second.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 4000)
+    streams = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    first.h.inner_loop(3, stream=streams[0].cuda_stream)
+    second.h.inner_loop(3, stream=streams[1].cuda_stream)
+    assert np.array_equal(second.get("z"), alone)
+    assert not np.any(second.get("scales")[:, 7])
+
+
 MATRIX_CASES = [
     # N, d, K, B, lam, R, T, mu: the 8-bit minibatch kernel on the matrix cores
     (200, 1024, 16, 64, 1e-3, 1, 9, 0.05),    # every block, 64 rows do not fit LDS: two chunks
