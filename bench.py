@@ -272,7 +272,7 @@ def side_inner_loop(hp, inp, torch, which, T, poll_delay=-1):
         Xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
         cases = [dict(b=8, B=1, loss=hp.LOSS_SOFTMAX, lam=1e-4, alpha=1e-2, mu=2.5),
                  dict(b=16, B=1, loss=hp.LOSS_SOFTMAX, lam=1e-4, alpha=1e-2, mu=2.5)]
-        if which == "c3batch":  # the same data with 64 rows per step: class-wave kernel, general kernel
+        if which == "c3batch":  # the same data with 64 rows per step: minibatch kernels, general kernel
             cases = [dict(b=8, B=64, loss=hp.LOSS_SOFTMAX, lam=1e-4, alpha=1e-2, mu=2.5, variant=0),
                      dict(b=16, B=64, loss=hp.LOSS_SOFTMAX, lam=1e-4, alpha=1e-2, mu=2.5, variant=0),
                      dict(b=8, B=64, loss=hp.LOSS_SOFTMAX, lam=1e-4, alpha=1e-2, mu=2.5, variant=1)]

@@ -6,7 +6,6 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <unordered_map>
 #include <vector>
 
 #include "halp_internal.hpp"
@@ -71,44 +70,67 @@ int reg_supported(const halp_handle& h) {
   return h.p.loss == HALP_LOSS_SOFTMAX ? inner_softmax_supported(h) : inner_reg_supported(h.p);
 }
 
+// The workgroups of a chain cut across CUs wait for one another, with a limit.  Two launches of
+// such chains on one device at a time, of two handles on two streams, could each hold CUs that
+// the other's chains need until the limit has run out.  So a launch of softmax chains runs
+// after every earlier launch of cut chains and before every later one, whatever their streams,
+// by waiting for the events behind them.  Cut minibatch chains overlap one another as the caller
+// has them.  Not under capture, where an event of another stream cannot be waited for.
+std::mutex cut_lock;
+const halp_handle* cut_handles = nullptr;  // handles that have launched such chains
+
+void forget_cut_launches(const halp_handle& h) {
+  const std::lock_guard<std::mutex> guard(cut_lock);
+  for (const halp_handle** at = &cut_handles; *at; at = &(*at)->cut_next)
+    if (*at == &h) {
+      *at = h.cut_next;
+      break;
+    }
+  if (h.cut_event) (void)hipEventDestroy(h.cut_event);
+}
+
+template <typename F>
+int launch_cut_in_order(const halp_handle& h, hipStream_t s, F&& launch) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return launch();
+  int dev = 0;
+  if (hip_fail(hipGetDevice(&dev), "hipGetDevice")) return HALP_ERR_HIP;
+  const bool softmax = h.p.loss == HALP_LOSS_SOFTMAX;
+  const std::lock_guard<std::mutex> guard(cut_lock);
+  for (const halp_handle* o = cut_handles; o; o = o->cut_next)
+    if (o->cut_device == dev && (softmax || o->p.loss == HALP_LOSS_SOFTMAX) &&
+        hip_fail(hipStreamWaitEvent(s, o->cut_event, 0), "hipStreamWaitEvent"))
+      return HALP_ERR_HIP;
+  if (!h.cut_event) {
+    if (hip_fail(hipEventCreateWithFlags(&h.cut_event, hipEventDisableTiming), "hipEventCreate")) {
+      h.cut_event = nullptr;
+      return HALP_ERR_HIP;
+    }
+    h.cut_device = dev;
+    h.cut_next = cut_handles;
+    cut_handles = &h;
+  }
+  const int r = launch();
+  if (hip_fail(hipEventRecord(h.cut_event, s), "hipEventRecord")) return HALP_ERR_HIP;
+  return r;
+}
+
 int launch_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   if (batch_family(h.p))
     return h.p.b == 8 ? launch_inner_softmax_mfma(h, epoch, s) : launch_inner_softmax_batch(h, epoch, s);
-  if (h.p.B > 1) return launch_inner_batch(h, epoch, s);
-  return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s) : launch_inner_reg(h, epoch, s);
-}
-
-// The workgroups of a chain cut by columns wait for one another, with a limit.  Two such launches
-// on one device at a time, of two handles on two streams, could each hold half of the CUs while
-// their chains wait for parts that find none until the limit has run out.  So they run one
-// after the other, whatever their streams: each waits for the event behind the one before it.
-// Not under capture, where an event of another stream cannot be waited for.
-int launch_softmax_split_in_order(const halp_handle& h, uint32_t epoch, hipStream_t s) {
-  static std::mutex lock;
-  static std::unordered_map<int, hipEvent_t> last;  // by device
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-  if (capture != hipStreamCaptureStatusNone) return launch_inner_softmax_split(h, epoch, s);
-  int dev = 0;
-  if (hip_fail(hipGetDevice(&dev), "hipGetDevice")) return HALP_ERR_HIP;
-  const std::lock_guard<std::mutex> guard(lock);
-  hipEvent_t& ev = last[dev];
-  if (ev) {
-    if (hip_fail(hipStreamWaitEvent(s, ev, 0), "hipStreamWaitEvent")) return HALP_ERR_HIP;
-  } else if (hip_fail(hipEventCreateWithFlags(&ev, hipEventDisableTiming), "hipEventCreate")) {
-    ev = nullptr;
-    return HALP_ERR_HIP;
+  if (h.p.B > 1) {
+    if (inner_batch_parts(h) == 1) return launch_inner_batch(h, epoch, s);
+    return launch_cut_in_order(h, s, [&] { return launch_inner_batch(h, epoch, s); });
   }
-  const int r = launch_inner_softmax_split(h, epoch, s);
-  if (hip_fail(hipEventRecord(ev, s), "hipEventRecord")) return HALP_ERR_HIP;
-  return r;
+  return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s) : launch_inner_reg(h, epoch, s);
 }
 
 int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t s) {
   if (variant == 3) return launch_inner_svrg(h, epoch, s);
   // softmax rows past the register kernels, unless the general kernel was asked for
   if (variant == 1 && h.inner_variant == 0 && inner_softmax_split_supported(h) == HALP_OK)
-    return launch_softmax_split_in_order(h, epoch, s);
+    return launch_cut_in_order(h, s, [&] { return launch_inner_softmax_split(h, epoch, s); });
   return variant == 2 ? launch_reg(h, epoch, s) : launch_inner_generic(h, epoch, TraceBufs{}, s);
 }
 
@@ -237,6 +259,7 @@ int halp_destroy(halp_handle* h) {
   for (auto& quad : h->ev)
     for (auto& e : quad)
       if (e) (void)hipEventDestroy(e);
+  forget_cut_launches(*h);  // the frees above have waited for its launches
   delete h;
   return HALP_OK;
 }

@@ -46,6 +46,10 @@ struct halp_handle {
   hipEvent_t ev[kTimedEpochs][4] = {};
   int64_t timed = 0;
   void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
+  // launches of chains cut across workgroups, listed under a lock (halp_api.hip)
+  mutable hipEvent_t cut_event = nullptr;             // behind the last one
+  mutable int cut_device = 0;
+  mutable const halp_handle* cut_next = nullptr;
 };
 
 namespace halp {
@@ -94,6 +98,7 @@ bool inner_generic_needs_workspace(const halp_params& p);
 size_t inner_generic_workspace_bytes(const halp_params& p);
 int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s);
 int inner_batch_supported(const halp_handle& h);
+int inner_batch_parts(const halp_handle& h);  // workgroups per chain, where supported
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_svrg_supported(const halp_handle& h);
 int launch_inner_svrg(const halp_handle& h, uint32_t epoch, hipStream_t s);

@@ -811,6 +811,8 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
   return BtLaunch{false, sh.ndw, (sh.nwk + P - 1) / P, P};
 }
 
+int inner_batch_parts(const halp_handle& h) { return pick_launch(h, h.buf.ldxq * (h.p.b / 8)).P; }
+
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   const halp_params& p = h.p;
   const int rc = inner_batch_supported(h);

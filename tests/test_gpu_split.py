@@ -92,6 +92,31 @@ def test_softmax_split_on_two_streams():
     assert not np.any(second.get("scales")[:, 7])
 
 
+def test_softmax_and_minibatch_chains_cut_on_two_streams():
+    """Softmax chains in 224 workgroups, minibatch chains cut into 128 behind them,
+    softmax chains again, with wait limits far below a launch's run time: each waits for the one before it."""
+    N, T, seed = 64, 40, 13
+    soft = _inner_case(hp.LOSS_SOFTMAX, N, 3584, 14, 1, 8, 0.0, 32, T, seed, mu=0.05)
+    first = _run_inner(soft, hp.LOSS_SOFTMAX, 14, 1, 8, 0.0, 32, 20000, seed, 0, mu=0.05)
+    third = _run_inner(soft, hp.LOSS_SOFTMAX, 14, 1, 8, 0.0, 32, T, seed, 0, mu=0.05)
+    mini = _inner_case(hp.LOSS_SQUARED, N, 2048, 1, 64, 16, 0.0, 16, T, seed, mu=0.05)
+    second = _run_inner(mini, hp.LOSS_SQUARED, 1, 64, 16, 0.0, 16, T, seed, 2, mu=0.05)
+    alone = []
+    for P in (second, third):
+        P.h.inner_loop(3)
+        alone.append(P.get("z").copy())
+        assert np.any(alone[-1])
+        P.put("z", np.zeros_like(alone[-1]))
+        P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 4000)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    for P, s in zip((first, second, third), streams):
+        P.h.inner_loop(3, stream=s.cuda_stream)
+    for P, z in zip((second, third), alone):
+        assert np.array_equal(P.get("z"), z)
+        assert not np.any(P.get("scales")[:, 7])
+
+
 MATRIX_CASES = [
     # N, d, K, B, lam, R, T, mu: the 8-bit minibatch kernel on the matrix cores
     (200, 1024, 16, 64, 1e-3, 1, 9, 0.05),    # every block, 64 rows do not fit LDS: two chunks
