@@ -26,8 +26,10 @@ __global__ __launch_bounds__(256) void ahead_scalars(InArgs a, Ahead s, int chai
   const int64_t i = (int64_t)__umulhi(ri, (uint32_t)a.N);
   const float* phi = a.phi + (int64_t)chain * a.N * K;
   const bool live = c < K;
+  // Algorithm 4 with squared loss needs no margins, and a caller need not have bound any
+  const bool need_phi = a.loss != HALP_LOSS_SQUARED || a.lp;
   AheadRec r;
-  r.phi = live ? phi[i * K + c] : 0.f;
+  r.phi = live && need_phi ? phi[i * K + c] : 0.f;
   r.p0 = 0.0;
   if (a.loss == HALP_LOSS_SOFTMAX) {
     const double v = live ? (double)r.phi : -INFINITY;

@@ -169,3 +169,19 @@ def test_softmax_rows_in_registers_bit_exact(N, d, K, b, lam, R, T, mu):
         assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
         assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
         assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+
+@pytest.mark.parametrize("N,d,B,b", [(200, 200, 65, 8), (150, 1000, 130, 8), (200, 200, 65, 16)])
+def test_squared_loss_in_wide_minibatches_without_margins_bound(N, d, B, b):
+    """Algorithm 4 with squared loss reads no margins: phi need not be bound."""
+    loss, T, seed = hp.LOSS_SQUARED, 12, 470 + d
+    case = _inner_case(loss, N, d, 1, B, b, 1e-2, 2, T, seed, mu=0.05)
+    P = _run_inner(case, loss, 1, B, b, 1e-2, 2, T, seed, 2, mu=0.05)
+    P.h.bind(X=P.X, Xq=P.Xq, y=P.y, **{k: v for k, v in P.st.items() if k != "phi"})
+    P.h.inner_loop(3)
+    z, cnt = P.get("z"), P.get("counters")
+    for r in range(2):
+        out = ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r],
+                             case["scales"][r], 3, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
