@@ -104,7 +104,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
   // waves alone fill whole rounds: then it comes last.
   const int ncw = K / CPW, svc = ncw % 4 == 0 ? ncw : min(3, ncw);
   const int64_t T = epoch_steps(a.seed + (uint64_t)chain, a.epoch, a.T, a.option2);
-  const int steps = (int)(min(ah.t1, T) - ah.t0);  // a segment's records fit the workspace: far below 2^31
+  const int steps = segment_steps(ah.t0, ah.t1, T);
   const int64_t row_bytes = a.ldxq * (BITS / 8);
   const double* sc = a.scales + (int64_t)chain * 8;
   unsigned long long* cnt_out = reinterpret_cast<unsigned long long*>(a.counters + (int64_t)chain * 4);

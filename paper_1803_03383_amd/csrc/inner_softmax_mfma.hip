@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
     return;
   }
   const int64_t T = epoch_steps(a.seed + (uint64_t)chain, a.epoch, a.T, a.option2);
-  const int steps = (int)(min(ah.t1, T) - ah.t0);  // a segment's records fit the workspace: far below 2^31
+  const int steps = segment_steps(ah.t0, ah.t1, T);
   const int nblk = (d + 63) / 64;
   const int stride = 64 * nblk + 16;   // bytes between rows in LDS: 4 mod 16 dwords, 16 rows in distinct banks
   const int nchunk = MANY ? (B + rows - 1) / rows : 1;

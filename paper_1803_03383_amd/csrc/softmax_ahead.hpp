@@ -7,6 +7,7 @@
 #pragma once
 
 #include "inner_args.hpp"
+#include "segments.hpp"
 
 namespace halp {
 

@@ -185,3 +185,32 @@ def test_squared_loss_in_wide_minibatches_without_margins_bound(N, d, B, b):
                              case["scales"][r], 3, T)
         assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
         assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+
+OPTION_II_CASES = [
+    # loss, N, d, K, B, b, lam, R, T, variant, segment: steps of a segment of records, or a few fewer (0: no records)
+    (hp.LOSS_SOFTMAX, 60, 1024, 15, 1, 8, 1e-2, 3, 3000, 2, 1400),   # a class to a wave
+    (hp.LOSS_SOFTMAX, 60, 40, 10, 64, 8, 1e-2, 3, 2700, 2, 1280),    # minibatch on the matrix cores, one chunk
+    (hp.LOSS_SOFTMAX, 90, 40, 16, 512, 8, 1e-2, 4, 300, 2, 110),     # ... sixteen chunks
+    (hp.LOSS_SOFTMAX, 60, 1100, 4, 1, 8, 1e-2, 3, 90, 0, 0),         # a chain cut across workgroups
+    (hp.LOSS_SOFTMAX, 60, 1100, 4, 1, 16, 0.0, 3, 90, 0, 0),
+]
+
+
+@pytest.mark.parametrize("loss,N,d,K,B,b,lam,R,T,variant,segment", OPTION_II_CASES)
+def test_softmax_option_2_bit_exact(loss, N, d, K, B, b, lam, R, T, variant, segment):
+    """Chains that end in different segments: z is handed on through the segments behind the end, w~ gets it once."""
+    seed = next(s for s in range(570, 700)
+                if (lambda e: not segment or (min(e) < segment < max(e)))([ref.option2_steps(1000 + s + r, 3, T) for r in range(R)]))
+    case = _inner_case(loss, N, d, K, B, b, lam, R, T, seed, mu=0.05)
+    P = _run_inner(case, loss, K, B, b, lam, R, T, seed, variant, mu=0.05)
+    P.h.set_option(hp.OPT_OPTION_II, 1)
+    P.h.inner_loop(3)
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in range(R):
+        prob = case["mk"](r)
+        t = ref.option2_steps(prob.seed, 3, T)
+        out = ref.inner_loop(prob, case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, t)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}, t={t}"
+        assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
