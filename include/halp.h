@@ -171,10 +171,14 @@ typedef struct {
                                     CUs, and launches of two handles in that mode should not
                                     overlap.  Results do not depend on it                       */
 #define HALP_OPT_EXCHANGE_SPIN_LIMIT 8 /* polls after which a workgroup of a chain cut across
-                                    workgroups (minibatch loop, wide softmax rows) stops waiting for the others for good (default 2^20,
-                                    about a second); -1: never wait.  The launch then ends
-                                    normally with counters[3] = 1, status -2 and w~ unchanged:
-                                    for tests of that path                                */
+                                    workgroups (minibatch loop, softmax rows past the
+                                    register-resident kernels) stops waiting for the others for
+                                    good (default 2^20, about a second).  A minibatch chain then
+                                    ends with counters[3] = 1, status -2 and w~ unchanged; a
+                                    softmax chain is run again by the general kernel, in the
+                                    same launch sequence, and only takes longer.  -1: never
+                                    wait, and chains of either kind end with status -2: for
+                                    tests of that path                                     */
 
 #define HALP_OPT_INNER_PACKED 9  /* register-resident inner loop at 8 bits with one wave per chain:
                                     the form that updates the two coordinates of a strip as packed

@@ -34,7 +34,7 @@ struct halp_handle {
   bool gradient_fp32 = false;    // HALP_OPT_GRADIENT_FP32
   const float* fscale = nullptr; // caller's per-feature data scales [d] (device), or null
   // minibatch inner loop split over several workgroups per chain: partial dots and tags
-  long long* batch_xbuf = nullptr;   // exchange words of chains cut across workgroups
+  long long* batch_xbuf = nullptr;   // chains cut across workgroups: exchange words, softmax: then their z
   int inner_parts = 0;               // workgroups per chain of that kernel, 0 = auto
   int poll_delay = 2;                // 256-cycle sleeps between publishing a step's sums and the first poll
   int spin_limit = 1 << 20;          // polls before a workgroup stops waiting for the others
@@ -85,7 +85,7 @@ int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t inner_softmax_bytes(const halp_params& p);  // workspace of the softmax kernel's records
 int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
-size_t inner_softmax_split_words(const halp_params& p, int num_cus);  // 64-bit exchange words
+size_t inner_softmax_split_bytes(const halp_params& p, int num_cus);  // workspace: exchange words and z
 int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t inner_softmax_mfma_bytes(const halp_params& p);  // workspace of the minibatch kernel on the matrix cores
@@ -96,7 +96,8 @@ int launch_inner_softmax_batch(const halp_handle& h, uint32_t epoch, hipStream_t
 int inner_generic_supported(const halp_params& p);
 bool inner_generic_needs_workspace(const halp_params& p);
 size_t inner_generic_workspace_bytes(const halp_params& p);
-int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s);
+// redo: only the chains whose counters[3] is set, from the z they came with
+int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s, bool redo = false);
 int inner_batch_supported(const halp_handle& h);
 int inner_batch_parts(const halp_handle& h);  // workgroups per chain, where supported
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);

@@ -23,6 +23,7 @@ struct InArgs {
   int d, K, B, loss;
   int option2;  // 1: the epoch ends at a uniformly drawn earlier iterate (option II)
   int lp;  // 1: LP-SVRG (Algorithm 2): z is the model itself, the margin is x^T z alone
+  int redo;  // general kernel, 1: takes only the chains whose counters[3] is set (a wait that ran out)
   double lambda, delta_d;
   uint64_t seed;
   uint32_t epoch;
@@ -41,14 +42,17 @@ inline InArgs make_inner_args(const halp_handle& h, uint32_t epoch) {
   a.d = p.d; a.K = p.K; a.B = p.B; a.loss = p.loss;
   a.lp = p.algorithm == HALP_ALG_LPSVRG;
   a.option2 = h.option2 ? 1 : 0;
+  a.redo = 0;
   a.lambda = p.lambda; a.delta_d = p.delta_d;
   a.seed = p.seed; a.epoch = epoch;
   return a;
 }
 
 // chains cut across workgroups: clears what the launch adds to or waits on; applies w~ <- w~ +
-// delta_m z behind it, for the chains none of whose workgroups gave up a wait
+// delta_m z behind it, for the chains none of whose workgroups gave up a wait.  zs: z of the
+// chains from chain0 on, copied to a.z unless it is that; report: the others get status -2
 void launch_split_prepare(long long* xbuf, int nwords, uint64_t* counters, int ncounters, hipStream_t s);
-int launch_split_finish(const InArgs& a, double* scales, int R, int bits, hipStream_t s);
+int launch_split_finish(const InArgs& a, double* scales, const void* zs, int chain0, int chains, bool report, int bits,
+                        hipStream_t s);
 
 }  // namespace halp

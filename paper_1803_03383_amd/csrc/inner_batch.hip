@@ -661,22 +661,23 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
 
 // Several workgroups per chain: w~ <- w~ + delta_m z is applied here, after the launch, and only
 // for chains none of whose workgroups gave up a wait.  A chain with a wait that ran out keeps
-// its w~ (its z is then not a trajectory of the method) and gets status -2 in scales[7].
+// its w~ (its z is then not a trajectory of the method) and, with report, gets status -2 in scales[7].
 template <int BITS>
-__global__ __launch_bounds__(256) void split_finish(InArgs a, double* scales) {
+__global__ __launch_bounds__(256) void split_finish(InArgs a, double* scales, const void* zs, int chain0, int report) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
-  const int chain = blockIdx.y;
+  const int chain = chain0 + (int)blockIdx.y;
   const int j = (int)(blockIdx.x * 256 + threadIdx.x);
   double* sc = scales + (int64_t)chain * 8;
   if (a.counters[(int64_t)chain * 4 + 3] != 0) {
-    if (j == 0) sc[7] = -2.0;
+    if (report && j == 0) sc[7] = -2.0;
     return;
   }
   const int n = a.K * a.d;
   if (sc[7] != 0.0 || j >= n) return;  // a gradient of zero or not finite: the loop did not run
-  const XT* zg = reinterpret_cast<const XT*>(a.z) + (int64_t)chain * n;
+  const XT zk = reinterpret_cast<const XT*>(zs)[(int64_t)blockIdx.y * n + j];
+  if (zs != a.z) reinterpret_cast<XT*>(a.z)[(int64_t)chain * n + j] = zk;
   float* wg = a.w + (int64_t)chain * n;
-  const double step = __dmul_rn(sc[0], (double)zg[j]);
+  const double step = __dmul_rn(sc[0], (double)zk);
   wg[j] = a.lp ? (float)step : (float)__dadd_rn((double)wg[j], step);
 }
 
@@ -724,10 +725,11 @@ void launch_split_prepare(long long* xbuf, int nwords, uint64_t* counters, int n
   hipLaunchKernelGGL(split_prepare, dim3((n + 255) / 256), dim3(256), 0, s, xbuf, nwords, counters, ncounters);
 }
 
-int launch_split_finish(const InArgs& a, double* scales, int R, int bits, hipStream_t s) {
-  const dim3 grid((a.K * a.d + 255) / 256, R);
-  if (bits == 8) hipLaunchKernelGGL(split_finish<8>, grid, dim3(256), 0, s, a, scales);
-  else hipLaunchKernelGGL(split_finish<16>, grid, dim3(256), 0, s, a, scales);
+int launch_split_finish(const InArgs& a, double* scales, const void* zs, int chain0, int chains, bool report, int bits,
+                        hipStream_t s) {
+  const dim3 grid((a.K * a.d + 255) / 256, chains);
+  if (bits == 8) hipLaunchKernelGGL(split_finish<8>, grid, dim3(256), 0, s, a, scales, zs, chain0, report ? 1 : 0);
+  else hipLaunchKernelGGL(split_finish<16>, grid, dim3(256), 0, s, a, scales, zs, chain0, report ? 1 : 0);
   return hip_ok(hipGetLastError());
 }
 
@@ -849,7 +851,7 @@ int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
 #undef HALP_BT
   const int lrc = launch_loop();
   if (lrc != HALP_OK || P == 1) return lrc;
-  return launch_split_finish(a, h.buf.scales, p.R, p.b, s);
+  return launch_split_finish(a, h.buf.scales, a.z, 0, p.R, true, p.b, s);
 }
 
 }  // namespace halp

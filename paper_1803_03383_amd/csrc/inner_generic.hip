@@ -40,6 +40,7 @@ __global__ __launch_bounds__(512) void inner_generic_kernel(InArgs a) {
   uint64_t* cnt_out = a.counters + (int64_t)chain * 4;
   const uint64_t seed = a.seed + (uint64_t)chain;
 
+  if (a.redo && cnt_out[3] == 0) return;
   if (sc[7] != 0.0) {  // converged or unusable gradient: the epoch is a no-op
     if (tid < 4) cnt_out[tid] = 0;
     return;
@@ -327,10 +328,11 @@ int inner_generic_supported(const halp_params& p) {
   return (generic_step_smem(p) > kGenericSmemCap || p.B > 512) ? HALP_ERR_UNSUPPORTED : HALP_OK;
 }
 
-int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s) {
+int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s, bool redo) {
   const halp_params& p = h.p;
   InArgs a = make_inner_args(h, epoch);
   a.tr = tr;
+  a.redo = redo ? 1 : 0;
   if (inner_generic_supported(p) != HALP_OK) return HALP_ERR_UNSUPPORTED;
   const bool outside = inner_generic_needs_workspace(p);
   if (outside && !h.zh_work) return HALP_ERR_UNSUPPORTED;

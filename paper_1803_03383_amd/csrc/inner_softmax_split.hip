@@ -15,6 +15,11 @@
 // one trip out and one trip back.  Integer sums: the order of arrival does not matter.  Every
 // workgroup then evaluates the same K gammas.
 //
+// A wait has a limit: on a device whose CUs other work holds, some of a chain's workgroups may not
+// get to run while the others wait.  z therefore goes to a workspace, and only a chain none of
+// whose waits ran out hands it on; the others are run by the general kernel behind the launch,
+// from the z they came with (one launch of workgroups that read a flag where there are none).
+//
 // One step:
 //   class waves   x_i^T z_c over the slice, DPP fold, one atomic add per class; meanwhile
 //                 (the trip takes ~0.7 us) the next window's Philox blocks, one strip at a time
@@ -54,7 +59,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int BITS, int UPL, int CPW, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs a, int P, int chain0, int nchains,
                                                                         int same_xcd, unsigned long long* xbuf,
-                                                                        int spin_limit) {
+                                                                        void* zs, int spin_limit) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
   using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
   using AccT = typename std::conditional<BITS == 8, int, long long>::type;
@@ -394,10 +399,10 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       }
     }
 
-    // ---- hand z out (w~ <- w~ + delta_m z is split_finish's)
+    // ---- hand z out (on to a.z, and w~ <- w~ + delta_m z: split_finish)
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
-      XT* __restrict__ zg = reinterpret_cast<XT*>(a.z) + row_of(cc);
+      XT* __restrict__ zg = reinterpret_cast<XT*>(zs) + ((int64_t)local * K + cls0 + cc) * d;
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
         int zk;
@@ -411,12 +416,12 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
 }
 
 template <int BITS, int UPL, int CPW>
-int launch_waves(const InArgs& a, int P, int chain0, int nchains, int same, unsigned long long* xbuf, int spin_limit,
-                 hipStream_t s) {
+int launch_waves(const InArgs& a, int P, int chain0, int nchains, int same, unsigned long long* xbuf, void* zs,
+                 int spin_limit, hipStream_t s) {
   const dim3 grid(same ? 8 * ((nchains + 7) / 8) * P : nchains * P), block(64 * (a.K / CPW + 1));
 #define HALP_SS(W_)                                                                                              \
   hipLaunchKernelGGL((inner_softmax_split_kernel<BITS, UPL, CPW, W_>), grid, block, 0, s, a, P, chain0, nchains, \
-                     same, xbuf, spin_limit)
+                     same, xbuf, zs, spin_limit)
   const int waves = a.K / CPW + 1;
   if (waves <= 8) HALP_SS(8);
   else if (waves <= 12) HALP_SS(12);
@@ -435,29 +440,35 @@ struct SplitShape {
 // strips) and a wave has the registers.  us per step, N = 7500, five chains, 2 / 4 / 8 strips:
 // d = 10000, K = 10: 8 bits 3.9 / 3.5 / 4.1, 16 bits 10 / 4.5 / 3.9; d = 2000, K = 10: 2.0 / 2.0 / 3.0;
 // d = 4001, K = 5: 2.3 / 2.0 / 2.1.
-SplitShape pick_shape(const halp_handle& h) {
-  const halp_params& p = h.p;
+SplitShape pick_shape(const halp_params& p, int num_cus) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
   const int upl = p.K < 12 && (U + 255) / 256 > 24 ? 8 : 4;
   const int P = (U + 64 * upl - 1) / (64 * upl);
-  return SplitShape{upl, P, std::min(p.R, h.num_cus / P)};
+  return SplitShape{upl, P, std::min(p.R, num_cus / P)};
 }
+
+// top byte of an exchange word: fewer than 128 workgroups per chain, all of them resident
+bool split_shape(const halp_params& p, int num_cus) {
+  if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return false;
+  if (p.b == 8 && p.d > 131071) return false;  // int32 dot products stay exact
+  const SplitShape sh = pick_shape(p, num_cus);
+  return sh.P <= 127 && sh.batch >= 1;
+}
+
+size_t split_words(int chains) { return (size_t)chains * 2 * kKC * kWordStride; }
 
 }  // namespace
 
-size_t inner_softmax_split_words(const halp_params& p, int num_cus) {
-  return p.loss == HALP_LOSS_SOFTMAX && p.B == 1 ? (size_t)std::min(p.R, num_cus) * 2 * kKC * kWordStride : 0;
+size_t inner_softmax_split_bytes(const halp_params& p, int num_cus) {
+  if (!split_shape(p, num_cus) || inner_softmax_bytes(p) != 0) return 0;  // the register kernel takes the shape
+  const int batch = pick_shape(p, num_cus).batch;
+  return split_words(batch) * sizeof(long long) + (size_t)batch * p.K * p.d * (p.b / 8);
 }
 
 int inner_softmax_split_supported(const halp_handle& h) {
   const halp_params& p = h.p;
-  if (p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return HALP_ERR_UNSUPPORTED;
-  if (p.b == 8 && p.d > 131071) return HALP_ERR_UNSUPPORTED;  // int32 dot products stay exact
-  if (!h.bound || !h.buf.Xq || !h.batch_xbuf) return HALP_ERR_NOT_BOUND;
-  const SplitShape sh = pick_shape(h);
-  // top byte of an exchange word: fewer than 128 workgroups per chain, all of them resident
-  if (sh.P > 127 || sh.batch < 1) return HALP_ERR_UNSUPPORTED;
-  return HALP_OK;
+  if (inner_softmax_split_bytes(p, h.num_cus) == 0) return HALP_ERR_UNSUPPORTED;
+  return !h.bound || !h.buf.Xq || !h.batch_xbuf ? HALP_ERR_NOT_BOUND : HALP_OK;
 }
 
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s) {
@@ -465,22 +476,25 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   const int rc = inner_softmax_split_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const SplitShape sh = pick_shape(h);
+  const SplitShape sh = pick_shape(p, h.num_cus);
   unsigned long long* xbuf = reinterpret_cast<unsigned long long*>(h.batch_xbuf);
+  void* zs = h.batch_xbuf + split_words(sh.batch);
+  const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for
   for (int c0 = 0; c0 < p.R; c0 += sh.batch) {
     const int nc = std::min(sh.batch, p.R - c0);
     const int same = sh.P * ((nc + 7) / 8) <= h.num_cus / 8 && h.num_cus % 8 == 0;
-    launch_split_prepare(h.batch_xbuf, nc * 2 * kKC * kWordStride, h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
+    launch_split_prepare(h.batch_xbuf, (int)split_words(nc), h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
     int r = HALP_ERR_UNSUPPORTED;
 #define HALP_SU(BITS_, UPL_, CPW_)                                             \
   if (p.b == BITS_ && sh.upl == UPL_ && (p.K > 15 ? 2 : 1) == CPW_)            \
-    r = launch_waves<BITS_, UPL_, CPW_>(a, sh.P, c0, nc, same, xbuf, h.spin_limit, s);
+    r = launch_waves<BITS_, UPL_, CPW_>(a, sh.P, c0, nc, same, xbuf, zs, h.spin_limit, s);
     HALP_SU(8, 4, 1) HALP_SU(8, 8, 1) HALP_SU(8, 4, 2)
     HALP_SU(16, 4, 1) HALP_SU(16, 8, 1) HALP_SU(16, 4, 2)
 #undef HALP_SU
+    if (r == HALP_OK) r = launch_split_finish(a, h.buf.scales, zs, c0, nc, report, p.b, s);
     if (r != HALP_OK) return r;
   }
-  return launch_split_finish(a, h.buf.scales, p.R, p.b, s);
+  return report ? HALP_OK : launch_inner_generic(h, epoch, TraceBufs{}, s, true);
 }
 
 }  // namespace halp

@@ -214,3 +214,47 @@ def test_softmax_option_2_bit_exact(loss, N, d, K, B, b, lam, R, T, variant, seg
         assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}, t={t}"
         assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
         assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+
+REDO_CASES = [
+    # N, d, K, b, lam, R, T
+    (60, 1100, 3, 8, 1e-2, 3, 40),
+    (40, 2500, 10, 8, 0.0, 2, 20),     # the general kernel's z and h~ in device memory
+    (60, 1601, 3, 16, 1e-2, 70, 12),   # more chains than are in flight at once
+]
+
+
+@pytest.mark.parametrize("N,d,K,b,lam,R,T", REDO_CASES)
+def test_softmax_split_chains_whose_waits_run_out_are_run_again(N, d, K, b, lam, R, T):
+    """A limit of no polls: a wait ends at the first look that finds a part missing.  Every chain still ends with the
+    oracle's z, w~ and counters, from a z that is not zero, and so does every replay of a captured launch."""
+    loss, seed = hp.LOSS_SOFTMAX, 670 + d
+    case = _inner_case(loss, N, d, K, 1, b, lam, R, T, seed, mu=0.05)
+    P = _run_inner(case, loss, K, 1, b, lam, R, T, seed, 0, mu=0.05)
+    z0 = np.random.default_rng(3).integers(-20, 21, size=(R, K, d))
+    outs = [(r, ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r],
+                               case["scales"][r], 3, T, z0=z0[r])) for r in sorted({0, R // 2, R - 1})]
+
+    def check():
+        z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+        assert not np.any(P.get("scales")[:, 7]) and not np.any(cnt[:, 3])
+        for r, out in outs:
+            assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+            assert np.array_equal(w[r], ref.apply_offset(case["mk"](r), case["scales"][r], out["z"], case["w"][r]))
+            assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+    for limit in (0, 1 << 20):
+        P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, limit)
+        P.put("z", z0); P.put("w", case["w"])
+        P.h.inner_loop(3)
+        check()
+        P.h.get_stats(0)
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            P.h.inner_loop(3, stream=torch.cuda.current_stream().cuda_stream)
+        for _ in range(3):
+            P.put("z", z0); P.put("w", case["w"])
+            torch.cuda.synchronize()
+            graph.replay()
+            check()
