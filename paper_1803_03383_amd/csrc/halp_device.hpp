@@ -182,7 +182,8 @@ __device__ __forceinline__ long long wave_fold_i64(long long v) {
 
 // ---- folds over a row of 16 lanes in fp64 (softmax: one class per lane) ----------
 
-template <typename F>
+// over each group of W = 2, 4, 8 or 16 adjacent lanes
+template <int W, typename F>
 __device__ __forceinline__ double row_fold_f64(double v, F op) {
   auto step = [&](double x, auto mv) {
     const uint64_t u = __builtin_bit_cast(uint64_t, x);
@@ -190,22 +191,24 @@ __device__ __forceinline__ double row_fold_f64(double v, F op) {
     return op(x, __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo));
   };
   v = step(v, [](int t) { return dpp_quad_swap1(t); });
-  v = step(v, [](int t) { return dpp_quad_swap2(t); });
-  v = step(v, [](int t) { return dpp_half_mirror(t); });
-  v = step(v, [](int t) { return dpp_row_mirror(t); });
+  if constexpr (W > 2) v = step(v, [](int t) { return dpp_quad_swap2(t); });
+  if constexpr (W > 4) v = step(v, [](int t) { return dpp_half_mirror(t); });
+  if constexpr (W > 8) v = step(v, [](int t) { return dpp_row_mirror(t); });
   return v;
 }
 
-// Sum over each row of 16 lanes, left in every lane of the row: lanes are joined in
-// adjacent pairs, the pairs' sums in adjacent pairs, and so on (a + b and b + a round
-// alike, so every lane of a group holds the same bits).
+// Sum over each group of W lanes, left in every lane of it: lanes are joined in adjacent pairs,
+// the pairs' sums in adjacent pairs, and so on (a + b and b + a round alike, so every lane of a
+// group holds the same bits; lanes of +0 beyond the group would change none).
+template <int W = 16>
 __device__ __forceinline__ double row_sum_f64(double v) {
-  return row_fold_f64(v, [](double x, double y) { return __dadd_rn(x, y); });
+  return row_fold_f64<W>(v, [](double x, double y) { return __dadd_rn(x, y); });
 }
 
-// maximum over each row of 16 lanes, left in every lane of the row
+// maximum over each group of W lanes, left in every lane of it
+template <int W = 16>
 __device__ __forceinline__ double row_max_f64(double v) {
-  return row_fold_f64(v, [](double x, double y) { return fmax(x, y); });
+  return row_fold_f64<W>(v, [](double x, double y) { return fmax(x, y); });
 }
 
 // ---- exp of the inner loop's scalar path -----------------------------------------

@@ -46,6 +46,8 @@ struct halp_handle {
   hipEvent_t ev[kTimedEpochs][4] = {};
   int64_t timed = 0;
   void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
+  int ahead_chains = 0;          // chains per launch of those loops
+  int64_t ahead_steps = 0;       // steps per segment
   // launches of chains cut across workgroups, listed under a lock (halp_api.hip)
   mutable hipEvent_t cut_event = nullptr;             // behind the last one
   mutable int cut_device = 0;
@@ -82,13 +84,15 @@ int launch_full_gradient_static(const halp_params& p, const halp_buffers& buf, h
 int launch_recenter(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_reg_supported(const halp_params& p);
 int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s);
-size_t inner_softmax_bytes(const halp_params& p);  // workspace of the softmax kernel's records
+bool inner_softmax_takes(const halp_params& p);
+// sets how an epoch is cut (ahead_chains, ahead_steps); bytes of workspace, 0 for other kernels' shapes
+size_t plan_inner_softmax(halp_handle& h);
 int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t inner_softmax_split_bytes(const halp_params& p, int num_cus);  // workspace: exchange words and z
 int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
-size_t inner_softmax_mfma_bytes(const halp_params& p);  // workspace of the minibatch kernel on the matrix cores
+size_t plan_inner_softmax_mfma(halp_handle& h);  // as plan_inner_softmax, the minibatch kernel on the matrix cores
 int inner_softmax_mfma_supported(const halp_handle& h);
 int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_softmax_batch_supported(const halp_handle& h);  // softmax with a minibatch

@@ -534,41 +534,40 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
   }
 }
 
+using Kernel = void (*)(InArgs, Ahead, int, int);
+
+// one row of z per class wave up to 15 classes; 16 classes: two rows per wave, 8 + 1 waves
+int classes_per_wave(int K) { return K > 15 ? 2 : 1; }
+int block_threads(int K) { return 64 * (K / classes_per_wave(K) + 1); }
+
 template <int BITS, int UPL>
-int launch_kt(const InArgs& a, const Ahead& ah, int c0, int chains, int last, hipStream_t s) {
-  // one row of z per class wave up to 15 classes; 16 classes: two rows per wave, 8 + 1 waves
-  const int cpw = a.K > 15 ? 2 : 1;
-  const dim3 grid(chains), block(64 * (a.K / cpw + 1));
-#define HALP_SM(KT_, CPW_) \
-  hipLaunchKernelGGL((inner_softmax_kernel<BITS, UPL, KT_, CPW_>), grid, block, 0, s, a, ah, c0, last)
-  if (cpw == 2) {
-    if constexpr (UPL <= 8) HALP_SM(12, 2);
-    else return HALP_ERR_UNSUPPORTED;
+Kernel kernel_for(int K) {
+  if (classes_per_wave(K) == 2) {
+    if constexpr (UPL <= 8) return inner_softmax_kernel<BITS, UPL, 12, 2>;
+    else return nullptr;
   } else if constexpr (UPL <= 4) {
-    HALP_SM(16, 1);
+    return inner_softmax_kernel<BITS, UPL, 16, 1>;
   } else {  // fewer waves, more registers each
-    if (a.K + 1 <= 8) HALP_SM(8, 1);
-    else if (a.K + 1 <= 12) HALP_SM(12, 1);
-    else HALP_SM(16, 1);
+    if (K + 1 <= 8) return inner_softmax_kernel<BITS, UPL, 8, 1>;
+    if (K + 1 <= 12) return inner_softmax_kernel<BITS, UPL, 12, 1>;
+    return inner_softmax_kernel<BITS, UPL, 16, 1>;
   }
-#undef HALP_SM
-  return hip_ok(hipGetLastError());
 }
 
 template <int BITS>
-int launch_upl(const InArgs& a, int upl, const Ahead& ah, int c0, int chains, int last, hipStream_t s) {
+Kernel kernel_for(int K, int upl) {
   switch (upl) {
-    case 1: return launch_kt<BITS, 1>(a, ah, c0, chains, last, s);
-    case 2: return launch_kt<BITS, 2>(a, ah, c0, chains, last, s);
-    case 4: return launch_kt<BITS, 4>(a, ah, c0, chains, last, s);
-    case 8: return launch_kt<BITS, 8>(a, ah, c0, chains, last, s);
+    case 1: return kernel_for<BITS, 1>(K);
+    case 2: return kernel_for<BITS, 2>(K);
+    case 4: return kernel_for<BITS, 4>(K);
+    case 8: return kernel_for<BITS, 8>(K);
     default: break;
   }
   // 16 strips per lane exist at 16 bits only (16 coordinates per lane; at 8 bits they would be 32)
   if constexpr (BITS == 16) {
-    if (upl == 16) return launch_kt<16, 16>(a, ah, c0, chains, last, s);
+    if (upl == 16) return kernel_for<16, 16>(K);
   }
-  return HALP_ERR_UNSUPPORTED;
+  return nullptr;
 }
 
 int strips_per_lane(const halp_params& p) {
@@ -586,24 +585,36 @@ int softmax_up(const halp_params& p) {
   return ((p.d + ct - 1) / ct + m - 1) / m * m;
 }
 
-bool softmax_shape(const halp_params& p) {
-  if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return false;
-  return strips_per_lane(p) <= (p.b == 16 && p.K <= 15 ? 16 : 8);
+Kernel kernel_for(const halp_params& p) {
+  return p.b == 8 ? kernel_for<8>(p.K, strips_per_lane(p)) : kernel_for<16>(p.K, strips_per_lane(p));
 }
 
 }  // namespace
 
-size_t inner_softmax_bytes(const halp_params& p) {
-  if (!softmax_shape(p)) return 0;
-  const AheadSegments g = ahead_segments(p, softmax_up(p));
-  return ahead_bytes(p, g.chains, g.S, softmax_up(p));
+bool inner_softmax_takes(const halp_params& p) {
+  if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return false;
+  return strips_per_lane(p) <= (p.b == 16 && p.K <= 15 ? 16 : 8);
+}
+
+// A launch takes as many chains as the device holds at once: a chain's step is mostly waiting, so
+// several of them to a CU take little longer than one, and launches run one after the other.  us per
+// step of all chains at 8 bits, 256 chains per launch and as many as fit: 64 x 2, 512 chains 1.13 and
+// 0.75, 1024 chains 2.24 and 0.87; 64 x 10, 512 chains 1.52 and 0.89; 300 x 5, 1024 chains 3.54 and 2.21
+// (two launches of 512: even shares, 768 and 256 took 2.97); 784 x 5, 1024 chains 4.0 either way.
+size_t plan_inner_softmax(halp_handle& h) {
+  if (!inner_softmax_takes(h.p)) return 0;
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(h.p)),
+                                                   block_threads(h.p.K), 0) != hipSuccess)
+    (void)hipGetLastError();
+  return plan_ahead(h, softmax_up(h.p), std::max(per_cu, 1) * h.num_cus);
 }
 
 // softmax, one row per step, up to 15 classes one wave each plus the service wave, 16 classes
 // two to a wave (8 strips per lane at most then, for the registers of two rows of z), a
 // class's row of z within one wave (8 strips per lane at most at 8 bits, 16 at 16 bits)
 int inner_softmax_supported(const halp_handle& h) {
-  if (!softmax_shape(h.p)) return HALP_ERR_UNSUPPORTED;
+  if (!inner_softmax_takes(h.p)) return HALP_ERR_UNSUPPORTED;
   return (!h.bound || !h.buf.Xq || !h.ahead_ws) ? HALP_ERR_NOT_BOUND : HALP_OK;
 }
 
@@ -612,9 +623,10 @@ int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t st) {
   const int rc = inner_softmax_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const int upl = strips_per_lane(p), up = softmax_up(p);
-  return for_segments(a, p, up, h.ahead_ws, st, [&](const Ahead& s, int c0, int chains, int last) {
-    return p.b == 8 ? launch_upl<8>(a, upl, s, c0, chains, last, st) : launch_upl<16>(a, upl, s, c0, chains, last, st);
+  const Kernel kernel = kernel_for(p);
+  return for_segments(a, h, softmax_up(p), st, [&](const Ahead& s, int c0, int chains, int last) {
+    hipLaunchKernelGGL(kernel, dim3(chains), dim3(block_threads(p.K)), 0, st, a, s, c0, last);
+    return hip_ok(hipGetLastError());
   });
 }
 

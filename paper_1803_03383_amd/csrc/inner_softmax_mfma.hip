@@ -540,6 +540,12 @@ int mfma_rows(int d, int B) {
   return rows <= kRows && mfma_lds(d, rows) <= kLdsCap ? rows : kManyRows;
 }
 
+// 8 bits, rows up to 1024 coordinates (16 blocks of 64 over eight waves, two buffers of 64 rows in LDS)
+bool mfma_shape(const halp_params& p) {
+  if (p.algorithm == HALP_ALG_SVRG || p.b != 8 || p.d > 1024 || p.K > 16 || p.B < 2 || p.B > 512) return false;
+  return p.loss == HALP_LOSS_SOFTMAX ? p.K >= 2 : p.B > 64;
+}
+
 template <bool MANY, bool AL16, bool SOFT>
 int launch_one(const InArgs& a, const Ahead& s, int c0, int chains, int last, hipStream_t st) {
   const int rows = mfma_rows(a.d, a.B);
@@ -554,16 +560,13 @@ int launch_one(const InArgs& a, const Ahead& s, int c0, int chains, int last, hi
 
 }  // namespace
 
-size_t inner_softmax_mfma_bytes(const halp_params& p) {
-  if (p.algorithm == HALP_ALG_SVRG || p.b != 8 || p.d > 1024 || p.K > 16 || p.B < 2 || p.B > 512) return 0;
-  if (p.loss == HALP_LOSS_SOFTMAX ? p.K < 2 : p.B <= 64) return 0;
-  const AheadSegments g = ahead_segments(p, mfma_up(p));
-  return ahead_bytes(p, g.chains, g.S, mfma_up(p));
+// one workgroup per CU: twelve waves with the registers of three per SIMD
+size_t plan_inner_softmax_mfma(halp_handle& h) {
+  return mfma_shape(h.p) ? plan_ahead(h, mfma_up(h.p), h.num_cus) : 0;
 }
 
-// 8 bits, rows up to 1024 coordinates (16 blocks of 64 over eight waves, two buffers of 64 rows in LDS)
 int inner_softmax_mfma_supported(const halp_handle& h) {
-  if (inner_softmax_mfma_bytes(h.p) == 0) return HALP_ERR_UNSUPPORTED;
+  if (!mfma_shape(h.p)) return HALP_ERR_UNSUPPORTED;
   return (!h.bound || !h.buf.Xq || !h.ahead_ws) ? HALP_ERR_NOT_BOUND : HALP_OK;
 }
 
@@ -574,7 +577,7 @@ int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t 
   const InArgs a = make_inner_args(h, epoch);
   const bool many = p.B > mfma_rows(p.d, p.B), soft = p.loss == HALP_LOSS_SOFTMAX;
   const bool al16 = h.buf.ldxq % 16 == 0 && reinterpret_cast<uintptr_t>(h.buf.Xq) % 16 == 0;
-  return for_segments(a, p, mfma_up(p), h.ahead_ws, st, [&](const Ahead& s, int c0, int chains, int last) -> int {
+  return for_segments(a, h, mfma_up(p), st, [&](const Ahead& s, int c0, int chains, int last) -> int {
 #define HALP_MF(MANY_, AL_, SOFT_) \
   if (many == MANY_ && al16 == AL_ && soft == SOFT_) return launch_one<MANY_, AL_, SOFT_>(a, s, c0, chains, last, st);
     HALP_MF(false, true, true) HALP_MF(false, false, true) HALP_MF(true, true, true) HALP_MF(true, false, true)

@@ -460,7 +460,7 @@ size_t split_words(int chains) { return (size_t)chains * 2 * kKC * kWordStride; 
 }  // namespace
 
 size_t inner_softmax_split_bytes(const halp_params& p, int num_cus) {
-  if (!split_shape(p, num_cus) || inner_softmax_bytes(p) != 0) return 0;  // the register kernel takes the shape
+  if (!split_shape(p, num_cus) || inner_softmax_takes(p)) return 0;  // the register kernel takes the shape
   const int batch = pick_shape(p, num_cus).batch;
   return split_words(batch) * sizeof(long long) + (size_t)batch * p.K * p.d * (p.b / 8);
 }

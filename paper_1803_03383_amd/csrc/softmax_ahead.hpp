@@ -16,7 +16,7 @@ struct AheadRec {  // one (row, class) of a step, 16 bytes
   float phi;       // margin (class 1 of a row with K = 1: the label)
   uint32_t rho;    // rounding word of gamma
 };
-constexpr int kAheadK = 16;  // classes are padded to one DPP row
+constexpr int kAheadK = 16;  // records of a row (those past its classes may hold anything)
 
 struct Ahead {
   AheadRec* rec;    // [chain][step][row][16]
@@ -34,28 +34,26 @@ size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP);
 // steps per segment that fit `bytes`: a multiple of 8, 0 if not even 8 fit
 int64_t ahead_steps(const halp_params& p, int chains, int UP, size_t bytes);
 Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws);
-// how an epoch is cut: chains per launch (at most 256) and steps per segment, from a workspace of
-// 64 MB, more for many chains (4 MB each) up to 1 GB: a segment costs its three launches and the
-// loop's way in and out, ~30 us, which 256 chains at 125 steps a segment paid with 10 %
-struct AheadSegments {
-  int chains;
-  int64_t S;
-};
-AheadSegments ahead_segments(const halp_params& p, int UP);
+// Sets how an epoch is cut and returns the bytes of workspace.  Chains per launch: even shares of at
+// most `resident`, those the device holds at once, since launches run one after the other.  Steps per
+// segment: from a workspace of 64 MB, more for many chains (4 MB each) up to 1 GB: a segment costs its
+// three launches and the loop's way in and out, ~30 us, which 256 chains at 125 steps a segment paid
+// with 10 % (2 GB instead of 1: no faster at 512 and 1024 chains).
+size_t plan_ahead(halp_handle& h, int UP, int resident);
 // fills the segment [t0, t1) of chains chain0 .. chain0 + chains - 1 (zbits only where UP > 0)
 int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chains, hipStream_t stream);
 
 // The epoch's launches: for every group of chains, segment after segment, the records and then
 // loop(segment, first chain, chains, last segment?).  An epoch without steps is one empty segment.
 template <typename F>
-int for_segments(const InArgs& a, const halp_params& p, int UP, void* ws, hipStream_t st, F loop) {
-  const AheadSegments g = ahead_segments(p, UP);
-  for (int c0 = 0; c0 < p.R; c0 += g.chains) {
-    const int nc = g.chains < p.R - c0 ? g.chains : p.R - c0;
-    Ahead s = ahead_layout(p, g.chains, g.S, UP, ws);
+int for_segments(const InArgs& a, const halp_handle& h, int UP, hipStream_t st, F loop) {
+  const halp_params& p = h.p;
+  for (int c0 = 0; c0 < p.R; c0 += h.ahead_chains) {
+    const int nc = h.ahead_chains < p.R - c0 ? h.ahead_chains : p.R - c0;
+    Ahead s = ahead_layout(p, h.ahead_chains, h.ahead_steps, UP, h.ahead_ws);
     do {
       s.t0 = s.t1;
-      s.t1 = s.t0 + g.S < p.T ? s.t0 + g.S : p.T;
+      s.t1 = s.t0 + s.S < p.T ? s.t0 + s.S : p.T;
       if (s.t1 > s.t0) {
         const int r = launch_ahead(a, s, p.b, c0, nc, st);
         if (r != HALP_OK) return r;

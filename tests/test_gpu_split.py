@@ -152,7 +152,10 @@ ROW_CASES = [
     (60, 511, 16, 16, 0.0, 1, 30, 0.05),
     (40, 63, 2, 16, 1e-2, 1, 40, 500.0),      # a coordinate to a lane; the service wave last
     (40, 2, 3, 8, 1e-2, 1, 33, 0.05),
-    (40, 1, 8, 16, 1e-2, 300, 9, 0.05),       # more chains than one launch takes
+    (40, 1, 8, 16, 1e-2, 300, 9, 0.05),       # more chains than CUs
+    (30, 600, 12, 8, 1e-2, 300, 9, 0.05),     # more chains than one launch takes: two of 150
+    (40, 100, 4, 8, 1e-2, 1100, 9, 0.05),     # several chains to a CU, four lanes to a row of the records
+    (40, 30, 2, 16, 1e-2, 700, 17, 0.05),     # ... two lanes
 ]
 
 
@@ -258,3 +261,35 @@ def test_softmax_split_chains_whose_waits_run_out_are_run_again(N, d, K, b, lam,
             torch.cuda.synchronize()
             graph.replay()
             check()
+
+
+MANY_CHAINS = [
+    # d, K, few, many: one chain to a CU at most, then four times as many
+    (64, 2, 256, 1024),    # rows in registers
+]
+
+
+@pytest.mark.parametrize("d,K,few,many", MANY_CHAINS)
+def test_many_softmax_chains_run_side_by_side(d, K, few, many):
+    """A chain is mostly waiting, so several to a CU cost little: 1.5 - 1.7 times the time where launches one after
+    the other take 4 times."""
+    N, T = 200, 2000
+    rng = np.random.default_rng(5)
+    X = torch.from_numpy(rng.uniform(0, 1, (1, N, d)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.integers(0, K, (1, N)).astype(np.int32)).cuda()
+    Xq = torch.zeros((1, N, (d + 7) // 8 * 8), dtype=torch.int8, device="cuda")
+
+    def best(R):
+        h = hp.Halp(N, d, K=K, R=R, loss=hp.LOSS_SOFTMAX, T=T, alpha=0.01, mu=1.0, delta_d=1.0 / 127, share_data=True)
+        st = hp.alloc_state(N, d, K=K, R=R)
+        h.bind(X=X, Xq=Xq, y=y, **st)
+        h.quantize_data()
+        ms = []
+        for _ in range(4):
+            st["w"].zero_()
+            h.set_option(hp.OPT_TIMING, 1)
+            h.epoch(0)
+            ms.append(h.get_stats(0).ms_inner_loop)
+        return min(ms)
+
+    assert best(many) < 2.7 * best(few)
