@@ -223,7 +223,7 @@ int halp_create(halp_handle** out, const halp_params* p) {
     if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), slots * 64 * sizeof(long long)),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }
-  if (const size_t bytes = inner_softmax_split_bytes(*p, h->num_cus)) {
+  if (const size_t bytes = plan_inner_softmax_split(*h)) {
     if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), bytes),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }

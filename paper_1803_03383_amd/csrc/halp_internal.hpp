@@ -48,6 +48,8 @@ struct halp_handle {
   void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
   int ahead_chains = 0;          // chains per launch of those loops
   int64_t ahead_steps = 0;       // steps per segment
+  int split_chains = 0;          // softmax chains cut across workgroups: chains per launch, 0: not that kernel's shape
+  int split_workgroups = 0;      // ... and workgroups the device holds at once
   // launches of chains cut across workgroups, listed under a lock (halp_api.hip)
   mutable hipEvent_t cut_event = nullptr;             // behind the last one
   mutable int cut_device = 0;
@@ -89,7 +91,8 @@ bool inner_softmax_takes(const halp_params& p);
 size_t plan_inner_softmax(halp_handle& h);
 int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
-size_t inner_softmax_split_bytes(const halp_params& p, int num_cus);  // workspace: exchange words and z
+// sets how many chains a launch takes; bytes of workspace (exchange words and z), 0 for other kernels' shapes
+size_t plan_inner_softmax_split(halp_handle& h);
 int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t plan_inner_softmax_mfma(halp_handle& h);  // as plan_inner_softmax, the minibatch kernel on the matrix cores

@@ -59,7 +59,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int BITS, int UPL, int CPW, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs a, int P, int chain0, int nchains,
                                                                         int same_xcd, unsigned long long* xbuf,
-                                                                        void* zs, int spin_limit) {
+                                                                        int spin_limit) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
   using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
   using AccT = typename std::conditional<BITS == 8, int, long long>::type;
@@ -402,7 +402,8 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     // ---- hand z out (on to a.z, and w~ <- w~ + delta_m z: split_finish)
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
-      XT* __restrict__ zg = reinterpret_cast<XT*>(zs) + ((int64_t)local * K + cls0 + cc) * d;
+      XT* __restrict__ zg =
+          reinterpret_cast<XT*>(xbuf + (int64_t)nchains * 2 * kKC * kWordStride) + ((int64_t)local * K + cls0 + cc) * d;
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
         int zk;
@@ -415,24 +416,28 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
   }
 }
 
+using Kernel = void (*)(InArgs, int, int, int, int, unsigned long long*, int);
+
+int classes_per_wave(int K) { return K > 15 ? 2 : 1; }
+int block_threads(int K) { return 64 * (K / classes_per_wave(K) + 1); }
+
 template <int BITS, int UPL, int CPW>
-int launch_waves(const InArgs& a, int P, int chain0, int nchains, int same, unsigned long long* xbuf, void* zs,
-                 int spin_limit, hipStream_t s) {
-  const dim3 grid(same ? 8 * ((nchains + 7) / 8) * P : nchains * P), block(64 * (a.K / CPW + 1));
-#define HALP_SS(W_)                                                                                              \
-  hipLaunchKernelGGL((inner_softmax_split_kernel<BITS, UPL, CPW, W_>), grid, block, 0, s, a, P, chain0, nchains, \
-                     same, xbuf, zs, spin_limit)
-  const int waves = a.K / CPW + 1;
-  if (waves <= 8) HALP_SS(8);
-  else if (waves <= 12) HALP_SS(12);
-  else if constexpr (UPL * CPW <= 4) HALP_SS(16);
-  else return HALP_ERR_UNSUPPORTED;
-#undef HALP_SS
-  return hip_ok(hipGetLastError());
+Kernel kernel_for(int waves) {
+  if (waves <= 8) return inner_softmax_split_kernel<BITS, UPL, CPW, 8>;
+  if (waves <= 12) return inner_softmax_split_kernel<BITS, UPL, CPW, 12>;
+  if constexpr (UPL * CPW <= 4) return inner_softmax_split_kernel<BITS, UPL, CPW, 16>;
+  else return nullptr;
+}
+
+template <int BITS>
+Kernel kernel_for(int K, int upl) {
+  const int cpw = classes_per_wave(K), waves = block_threads(K) / 64;
+  if (upl == 4) return cpw == 1 ? kernel_for<BITS, 4, 1>(waves) : kernel_for<BITS, 4, 2>(waves);
+  return cpw == 1 ? kernel_for<BITS, 8, 1>(waves) : nullptr;
 }
 
 struct SplitShape {
-  int upl, P, batch;  // strips per lane, workgroups per chain, chains in flight at once
+  int upl, P;  // strips per lane, workgroups per chain
 };
 
 // Four strips per lane; eight where four would need more than 24 workgroups per chain (a longer
@@ -440,34 +445,45 @@ struct SplitShape {
 // strips) and a wave has the registers.  us per step, N = 7500, five chains, 2 / 4 / 8 strips:
 // d = 10000, K = 10: 8 bits 3.9 / 3.5 / 4.1, 16 bits 10 / 4.5 / 3.9; d = 2000, K = 10: 2.0 / 2.0 / 3.0;
 // d = 4001, K = 5: 2.3 / 2.0 / 2.1.
-SplitShape pick_shape(const halp_params& p, int num_cus) {
+SplitShape pick_shape(const halp_params& p) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
   const int upl = p.K < 12 && (U + 255) / 256 > 24 ? 8 : 4;
   const int P = (U + 64 * upl - 1) / (64 * upl);
-  return SplitShape{upl, P, std::min(p.R, num_cus / P)};
+  return SplitShape{upl, P};
 }
 
-// top byte of an exchange word: fewer than 128 workgroups per chain, all of them resident
-bool split_shape(const halp_params& p, int num_cus) {
-  if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return false;
-  if (p.b == 8 && p.d > 131071) return false;  // int32 dot products stay exact
-  const SplitShape sh = pick_shape(p, num_cus);
-  return sh.P <= 127 && sh.batch >= 1;
+Kernel kernel_for(const halp_params& p) {
+  const int upl = pick_shape(p).upl;
+  return p.b == 8 ? kernel_for<8>(p.K, upl) : kernel_for<16>(p.K, upl);
 }
 
 size_t split_words(int chains) { return (size_t)chains * 2 * kKC * kWordStride; }
 
 }  // namespace
 
-size_t inner_softmax_split_bytes(const halp_params& p, int num_cus) {
-  if (!split_shape(p, num_cus) || inner_softmax_takes(p)) return 0;  // the register kernel takes the shape
-  const int batch = pick_shape(p, num_cus).batch;
-  return split_words(batch) * sizeof(long long) + (size_t)batch * p.K * p.d * (p.b / 8);
+// A launch takes as many chains as the device holds workgroups for (a wait that other work makes run
+// out all the same only costs time).  us per step of all chains, one workgroup to a CU and as many as
+// fit (the general kernel): 1100 x 2 at 8 bits, 256 chains 5.55 and 2.04 (8.0), 1024 chains 18.4 and 6.9 (31.7);
+// 1100 x 5, 256 chains 7.0 and 4.2 (9.7); 1100 x 2 at 16 bits, 256 chains 8.9 and 3.0 (7.6).  Where one fits:
+// 1100 x 10, 256 chains 8.1 (18.5); 60000 x 15, 256 chains, two to a launch, 795 (2143).
+size_t plan_inner_softmax_split(halp_handle& h) {
+  const halp_params& p = h.p;
+  if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return 0;
+  if (inner_softmax_takes(p)) return 0;          // the register kernel has the shape
+  if (p.b == 8 && p.d > 131071) return 0;        // int32 dot products stay exact
+  const int P = pick_shape(p).P;
+  if (P > 127 || P > h.num_cus) return 0;  // top byte of an exchange word; all workgroups of a chain resident
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(p)),
+                                                   block_threads(p.K), 0) != hipSuccess)
+    (void)hipGetLastError();
+  h.split_workgroups = std::max(per_cu, 1) * h.num_cus;
+  h.split_chains = std::min(p.R, h.split_workgroups / P);
+  return split_words(h.split_chains) * sizeof(long long) + (size_t)h.split_chains * p.K * p.d * (p.b / 8);
 }
 
 int inner_softmax_split_supported(const halp_handle& h) {
-  const halp_params& p = h.p;
-  if (inner_softmax_split_bytes(p, h.num_cus) == 0) return HALP_ERR_UNSUPPORTED;
+  if (h.split_chains == 0) return HALP_ERR_UNSUPPORTED;
   return !h.bound || !h.buf.Xq || !h.batch_xbuf ? HALP_ERR_NOT_BOUND : HALP_OK;
 }
 
@@ -476,22 +492,18 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   const int rc = inner_softmax_split_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const SplitShape sh = pick_shape(p, h.num_cus);
+  const int P = pick_shape(p).P;
+  const Kernel kernel = kernel_for(p);
   unsigned long long* xbuf = reinterpret_cast<unsigned long long*>(h.batch_xbuf);
-  void* zs = h.batch_xbuf + split_words(sh.batch);
   const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for
-  for (int c0 = 0; c0 < p.R; c0 += sh.batch) {
-    const int nc = std::min(sh.batch, p.R - c0);
-    const int same = sh.P * ((nc + 7) / 8) <= h.num_cus / 8 && h.num_cus % 8 == 0;
+  for (int c0 = 0; c0 < p.R; c0 += h.split_chains) {
+    const int nc = std::min(h.split_chains, p.R - c0);
+    const int same = P * ((nc + 7) / 8) <= h.split_workgroups / 8 && h.num_cus % 8 == 0;
     launch_split_prepare(h.batch_xbuf, (int)split_words(nc), h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
-    int r = HALP_ERR_UNSUPPORTED;
-#define HALP_SU(BITS_, UPL_, CPW_)                                             \
-  if (p.b == BITS_ && sh.upl == UPL_ && (p.K > 15 ? 2 : 1) == CPW_)            \
-    r = launch_waves<BITS_, UPL_, CPW_>(a, sh.P, c0, nc, same, xbuf, zs, h.spin_limit, s);
-    HALP_SU(8, 4, 1) HALP_SU(8, 8, 1) HALP_SU(8, 4, 2)
-    HALP_SU(16, 4, 1) HALP_SU(16, 8, 1) HALP_SU(16, 4, 2)
-#undef HALP_SU
-    if (r == HALP_OK) r = launch_split_finish(a, h.buf.scales, zs, c0, nc, report, p.b, s);
+    hipLaunchKernelGGL(kernel, dim3(same ? 8 * ((nc + 7) / 8) * P : nc * P), dim3(block_threads(p.K)), 0, s, a, P, c0,
+                       nc, same, xbuf, h.spin_limit);
+    int r = hip_ok(hipGetLastError());
+    if (r == HALP_OK) r = launch_split_finish(a, h.buf.scales, xbuf + split_words(nc), c0, nc, report, p.b, s);
     if (r != HALP_OK) return r;
   }
   return report ? HALP_OK : launch_inner_generic(h, epoch, TraceBufs{}, s, true);

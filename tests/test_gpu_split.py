@@ -22,7 +22,8 @@ SOFTMAX_CASES = [
     (40, 2047, 12, 16, 0.0, 1, 40, 500.0),    # ... saturating
     (30, 1300, 16, 16, 1e-2, 1, 30, 0.05),    # ... two classes to a wave
     (30, 10000, 10, 16, 1e-4, 1, 20, 0.05),   # as many workgroups per chain as the ten-class set takes
-    (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than are in flight at once
+    (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than one workgroup to a CU holds
+    (30, 2500, 12, 8, 1e-2, 70, 9, 0.05),     # more chains than are in flight at once
     (30, 1100, 4, 8, 0.0, 1, 1, 0.05),
     (30, 1100, 4, 8, 0.0, 1, 0, 0.05),
 ]
@@ -266,6 +267,7 @@ def test_softmax_split_chains_whose_waits_run_out_are_run_again(N, d, K, b, lam,
 MANY_CHAINS = [
     # d, K, few, many: one chain to a CU at most, then four times as many
     (64, 2, 256, 1024),    # rows in registers
+    (1100, 2, 64, 256),    # a chain cut across workgroups
 ]
 
 
