@@ -459,6 +459,17 @@ Kernel kernel_for(const halp_params& p) {
 
 size_t split_words(int chains) { return (size_t)chains * 2 * kKC * kWordStride; }
 
+// The words begin at an odd multiple of 4096 bytes, so that a chain's two sets, 4096 bytes each, lie in
+// different aligned blocks of 8192.  us per step with the words at an even multiple and at an odd one:
+// d = 4000, K = 10, 8 bits, 5 chains 2.44 and 2.17, 32 chains 2.69 and 2.32; d = 10000, K = 10, 5 chains 3.0-3.2 and 2.8;
+// d = 2500, K = 10, 16 bits, 25 chains 2.55 and 2.21; d = 1100, K = 5, 5 chains 1.74 and 1.57 (medians; the rest of the
+// address changes little).  What an allocation gives by itself goes by its size: from 2 MB on always even.
+constexpr size_t kPage = 4096;
+unsigned long long* words_at(void* ws) {
+  const uintptr_t page = (reinterpret_cast<uintptr_t>(ws) + kPage - 1) / kPage;
+  return reinterpret_cast<unsigned long long*>((page | 1) * kPage);
+}
+
 }  // namespace
 
 // A launch takes as many chains as the device holds workgroups for (a wait that other work makes run
@@ -479,7 +490,7 @@ size_t plan_inner_softmax_split(halp_handle& h) {
     (void)hipGetLastError();
   h.split_workgroups = std::max(per_cu, 1) * h.num_cus;
   h.split_chains = std::min(p.R, h.split_workgroups / P);
-  return split_words(h.split_chains) * sizeof(long long) + (size_t)h.split_chains * p.K * p.d * (p.b / 8);
+  return 2 * kPage + split_words(h.split_chains) * sizeof(long long) + (size_t)h.split_chains * p.K * p.d * (p.b / 8);
 }
 
 int inner_softmax_split_supported(const halp_handle& h) {
@@ -494,12 +505,12 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   const InArgs a = make_inner_args(h, epoch);
   const int P = pick_shape(p).P;
   const Kernel kernel = kernel_for(p);
-  unsigned long long* xbuf = reinterpret_cast<unsigned long long*>(h.batch_xbuf);
+  unsigned long long* xbuf = words_at(h.batch_xbuf);
   const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for
   for (int c0 = 0; c0 < p.R; c0 += h.split_chains) {
     const int nc = std::min(h.split_chains, p.R - c0);
     const int same = P * ((nc + 7) / 8) <= h.split_workgroups / 8 && h.num_cus % 8 == 0;
-    launch_split_prepare(h.batch_xbuf, (int)split_words(nc), h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
+    launch_split_prepare(reinterpret_cast<long long*>(xbuf), (int)split_words(nc), h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
     hipLaunchKernelGGL(kernel, dim3(same ? 8 * ((nc + 7) / 8) * P : nc * P), dim3(block_threads(p.K)), 0, s, a, P, c0,
                        nc, same, xbuf, h.spin_limit);
     int r = hip_ok(hipGetLastError());
