@@ -88,6 +88,8 @@ LP_CASES = [
     (hp.LOSS_SOFTMAX, 120, 600, 3, 16, 16, 1, 40, (2, 1)),   # ... 16 strips per lane at 16 bits
     (hp.LOSS_SQUARED, 300, 64, 1, 100, 8, 1, 30, (2, 1)),    # a scalar margin, more than 64 rows per step
     (hp.LOSS_LOGISTIC, 200, 300, 1, 70, 16, 1, 25, (2, 1)),
+    (hp.LOSS_LOGISTIC, 200, 300, 1, 70, 8, 2, 25, (2, 1)),
+    (hp.LOSS_LOGISTIC, 150, 1000, 1, 300, 8, 1, 12, (2, 1)),
 ]
 
 

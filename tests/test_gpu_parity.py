@@ -762,6 +762,9 @@ WIDE_BATCH_CASES = [
     (hp.LOSS_LOGISTIC, 500, 256, 512, 16, 1e-5, 1, 8, 0.05),   # the widest minibatch
     (hp.LOSS_LOGISTIC, 200, 1024, 130, 16, 0.0, 1, 12, 0.05),  # 16 strips per lane
     (hp.LOSS_SQUARED, 64, 64, 200, 8, 0.0, 1, 60, 500.0),      # box far too small: z saturates
+    (hp.LOSS_LOGISTIC, 300, 500, 65, 8, 1e-2, 2, 25, 0.05),    # logistic at 8 bits, row stride 8 mod 16 bytes
+    (hp.LOSS_LOGISTIC, 200, 1009, 512, 8, 1e-2, 2, 9, 0.05),   # ... the widest minibatch, stride 0 mod 16
+    (hp.LOSS_LOGISTIC, 100, 30, 130, 8, 0.0, 1, 40, 500.0),    # ... saturating
 ]
 
 
