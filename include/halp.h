@@ -25,8 +25,15 @@
  *     launched when an error is returned.  Conditions only the device can see
  *     (a zero or non-finite gradient) are reported through scales[7] and
  *     halp_get_stats, and turn the rest of that epoch into a no-op.
- *   - A handle is not thread-safe; distinct handles are independent.  There is
- *     no global state.
+ *   - A handle is not thread-safe; distinct handles may be used from different
+ *     threads and streams at once and give the results they give alone.  They
+ *     are ordered against each other in one case: softmax chains cut across
+ *     workgroups (rows past the register-resident kernels) need many CUs at
+ *     once, so such a launch waits for earlier launches of cut chains on the
+ *     device, of any handle and stream, and later ones wait for it (the library
+ *     keeps a locked list of these handles for it).  Launches captured into a
+ *     graph are not ordered: replays at once on two streams give the same
+ *     results but may take much longer (HALP_OPT_EXCHANGE_SPIN_LIMIT).
  *   - All randomness is counter-based (Philox4x32-10): each draw is a pure
  *     function of (seed + chain, epoch, step, purpose, position), so a run can
  *     be resumed from (w~, epoch, seed) alone and replayed on a CPU.
@@ -48,9 +55,10 @@ extern "C" {
 #define HALP_ERR_HIP (-5)         /* a HIP runtime call failed                          */
 #define HALP_ERR_ALIGN (-6)       /* pointer or stride alignment requirement not met    */
 #define HALP_ERR_TOO_LARGE (-7)   /* beyond the fixed scratch of halp_full_gradient_static */
-#define HALP_ERR_EXCHANGE_TIMEOUT (-8) /* halp_get_stats: a cross-workgroup wait of the split
-                                     minibatch inner loop ran out; that chain's w~ was left as
-                                     it was before the loop (status -2)                    */
+#define HALP_ERR_EXCHANGE_TIMEOUT (-8) /* halp_get_stats: a cross-workgroup wait of a minibatch
+                                     chain cut across workgroups ran out; that chain's w~ was
+                                     left as it was before the loop (status -2).  Softmax chains
+                                     are run again instead, see HALP_OPT_EXCHANGE_SPIN_LIMIT */
 
 /* scalar loss l_i of the linear model (Sec. 4); labels y as noted */
 #define HALP_LOSS_SQUARED 0  /* l(a) = (a - y)^2 / 2,        y: float               */
@@ -111,11 +119,11 @@ typedef struct {
   void* h;            /* out  [R][K][d] int16 / int32 h~ in (delta_i, 2b)               */
   double* scales;     /* out  [R][8]: delta_m, delta_i, delta_s, ||g~||, 1/delta_i, 1/delta_s,
                          f(w~), status (0 ok, 1 gradient exactly zero, -1 not finite, -2 a wait
-                         between the workgroups of the split minibatch loop ran out: w~ was not
+                         between the workgroups of a minibatch chain ran out: w~ was not
                          updated)                                                       */
   uint64_t* counters; /* out  [R][4]: coordinates of z clamped by the last inner loop, gammas
                          clamped, steps with a non-zero L2 draw, 1 if a cross-workgroup wait
-                         of the split minibatch loop ran out (z is then invalid, w~ is left
+                         of a minibatch chain ran out (z is then invalid, w~ is left
                          unchanged and the status becomes -2)                              */
 } halp_buffers;
 
@@ -129,26 +137,28 @@ typedef struct {
   uint64_t n_clamped_z, n_clamped_gamma, n_reg_draws;
   float ms_full_gradient, ms_recenter, ms_inner_loop; /* mean per halp_epoch over timed_epochs */
   int32_t timed_epochs;   /* halp_epoch calls averaged (the last 32 at most since timing was set) */
-  uint64_t n_exchange_timeouts; /* 1 if a cross-workgroup wait of the last split minibatch loop
-                             ran out (counters[3]); halp_get_stats then returns
+  uint64_t n_exchange_timeouts; /* 1 if a cross-workgroup wait of the last inner loop left the
+                             chain without a result (counters[3]); halp_get_stats then returns
                              HALP_ERR_EXCHANGE_TIMEOUT with every field filled in           */
 } halp_stats;
 
 #define HALP_OPT_INNER_VARIANT 1 /* 0 auto (default), 1 general, 2 register-resident.
                                     Register-resident kernels exist for B = 1 with K = 1 (squared,
                                     logistic; d up to 8 strips of 16 rounding bits per lane and
-                                    16 waves), for K = 1 with 2 <= B <= 64 (same limit on d), and
-                                    for softmax with B = 1 (a class's row of z within 8
-                                    strips per lane of one wave at 8 bits, 16 at 16 bits -- 8
-                                    at either width for 16 classes, which share waves in
-                                    pairs -- and the staged rows within the LDS of a CU), and
-                                    for softmax with 2 <= B <= 512 (a class's
-                                    row of z within 8 strips per lane at 8 bits, 16 at 16
-                                    bits, 64 rows of a step within 128 KB of LDS; the same kernel
-                                    takes K = 1 with 64 < B <= 512 on such rows); auto takes
-                                    them when the shape fits, 2 fails with HALP_ERR_UNSUPPORTED
-                                    when it does not.  HALP_ALG_SVRG has one fp32 kernel and
-                                    ignores this option                                      */
+                                    16 waves), for K = 1 with 2 <= B <= 64 (same limit on d), for
+                                    softmax with B = 1 (a class's row of z within 8 strips per
+                                    lane of one wave at 8 bits, 16 at 16 bits -- 8 at either width
+                                    for 16 classes, which share waves in pairs: rows up to 1024
+                                    coordinates, 512 for 16 classes at 16 bits), and for softmax
+                                    with 2 <= B <= 512 and K = 1 with 64 < B <= 512 (at 8 bits rows
+                                    up to 1024 coordinates; at 16 bits a class's row of z within
+                                    16 strips per lane and 64 rows of a step within 128 KB of
+                                    LDS).  auto takes them when the shape fits, and for wider
+                                    softmax rows with B = 1 a form of the general kernel cut
+                                    across workgroups; 1 takes the general kernel itself; 2 fails
+                                    with HALP_ERR_UNSUPPORTED where no register-resident kernel
+                                    fits.  HALP_ALG_SVRG has one fp32 kernel and ignores this
+                                    option                                                   */
 #define HALP_OPT_TIMING 2        /* 1: halp_epoch brackets its phases with events on its stream;
                                     setting it restarts the averages of halp_get_stats     */
 #define HALP_OPT_FULLGRAD_BLOCKS 4 /* workgroups per chain of the gradient pass, 0 = auto  */
@@ -214,7 +224,11 @@ typedef struct {
                                     1e-5; the first is the faster one                          */
 
 /* Validates p (HALP_ERR_INVALID / HALP_ERR_UNSUPPORTED) and allocates the
- * library's own device workspace on the current device.                               */
+ * library's own device workspace on the current device, held until halp_destroy: partial sums of
+ * the gradient pass; for softmax with B = 1 on rows up to 1024 coordinates, and for 8-bit minibatches
+ * of softmax or of more than 64 rows, records made ahead of the steps (64 MB, 4 MB a chain where
+ * that is more, at most 1 GB, less where T is small); for wider softmax rows with B = 1 a second z
+ * of the chains in flight.                                                             */
 int halp_create(halp_handle** out, const halp_params* p);
 int halp_destroy(halp_handle* h);
 

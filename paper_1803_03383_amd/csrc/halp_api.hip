@@ -568,7 +568,7 @@ const char* halp_strerror(int code) {
     case HALP_ERR_HIP: return "a HIP runtime call failed";
     case HALP_ERR_ALIGN: return "pointer or stride alignment requirement not met";
     case HALP_ERR_EXCHANGE_TIMEOUT:
-      return "a wait between the workgroups of the split minibatch loop ran out; w~ was not updated";
+      return "a wait between the workgroups of a chain ran out; w~ was not updated";
     case HALP_ERR_TOO_LARGE:
       return "the problem does not fit the fixed scratch of the allocation-free entry point";
     default: return "unknown error code";
