@@ -784,18 +784,18 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
       const int cpt = ndw * epd;
       P = (p.d + 64 * cpt - 1) / (64 * cpt);
       if (P > most_any) return false;
-      // several workgroups pay ~2 us per step for their exchange.  Measured: worth it down to
-      // steps of 16 KB of rows (3.3 - 4.6 us split against 3.9 - 5.2 on one workgroup; at 64 - 128 KB
-      // 3.9 - 4.9 against 9.6 - 11.3)
+      // several workgroups pay for an exchange per step.  us per step, cut and on one workgroup: steps of
+      // 16 KB of rows 3.1 - 4.2 and 3.2 - 4.2 (five shapes, none slower cut), 32 KB 3.7 and 3.9, 64 KB 3.0 - 4.3 and
+      // 5.0 - 9.7
       if (P > 1 && (int64_t)p.B * row_bytes < 16 * 1024) return false;
       return (int64_t)((p.d + cpt - 1) / cpt) * ndw * 4 <= row_bytes;  // fragments inside the row
     };
     int rg = (p.B + 7) / 8;
     if (rg > 4) rg = 4;
     // A chain cut across workgroups: the narrowest fragment of at least four coordinates whose
-    // slices are few enough -- more, narrower slices shorten both passes over the rows of a step
-    // (measured: 4096 x 16 bits 6.6 us with 8 slices, 6.2 with 16; 2048 x 16 bits 5.8 / 4.9 with
-    // 4 / 8; 4096 x 8 bits 5.4 / 5.2 with 8 / 16; two coordinates per thread lose again).
+    // slices are few enough -- more, narrower slices shorten both passes over the rows of a step.  us per
+    // step, B = 64: 4096 x 16 bits 5.7 with 8 slices, 4.2 with 16; 2048 x 16 bits 5.6 / 4.4 with 4 / 8; 1024 x 16
+    // bits 5.0 / 4.3 with 2 / 4; 4096 x 8 bits 4.5 / 3.6 with 8 / 16.
     for (int ndw = p.b == 16 ? 2 : 1; ndw <= ndw_max; ndw *= 2) {
       int P;
       if (fits(ndw, P) && P > 1) return BtLaunch{true, ndw, rg, P};

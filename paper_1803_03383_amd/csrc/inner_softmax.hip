@@ -35,7 +35,7 @@
 // 784 x 10 at 8 bits 1.43 -> 0.89, at 16 bits 2.73 -> 1.45; 1024 x 15 at 8 bits 2.42 -> 1.02;
 // 784 x 16 at 8 bits 3.92 -> 1.13; 1000 x 15 at 16 bits 29.8 -> 3.1; 300 x 4 at 8 bits
 // 0.91 -> 0.57; 64 x 2 at 16 bits 0.75 -> 0.56.  With 256 chains, where making the records
-// takes the whole chip's issue slots too: 784 x 10 at 8 bits 1.43 -> 1.42, at 16 bits 3.22 -> 2.28.
+// takes the whole chip's issue slots too: 784 x 10 at 8 bits 1.38 -> 1.45, at 16 bits 3.2 -> 2.35.
 #include <algorithm>
 
 #include "halp_device.hpp"
