@@ -445,7 +445,7 @@ struct SplitShape {
 // strips) and a wave has the registers.  us per step, N = 7500, five chains, K = 10, 4 / 8 strips:
 // 16 bits, d = 2000 2.2 / 2.3, 6500 3.2 / 2.8, 10000 4.3 / 3.1; 8 bits, where eight
 // strips spill 26 registers, 2000 1.9 / 2.6, 10000 3.0 / 3.4, 15000 3.5 / 3.8; K = 5, d = 4001 1.9 / 1.9.  Two strips
-// were the slower ones throughout.
+// were nowhere the faster ones.
 SplitShape pick_shape(const halp_params& p) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
   const int upl = p.K < 12 && (U + 255) / 256 > 24 ? 8 : 4;
