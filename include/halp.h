@@ -203,12 +203,11 @@ typedef struct {
                                     0 (default): taken while a CU holds at most five chains
                                     (four chain waves up to two chains per CU, two beyond);
                                     1: wherever that shape is launched; 2: never; 3: the 8-bit
-                                    form with ONE chain wave that holds all of z (two
-                                    coordinates per register, packed 16-bit arithmetic) and
-                                    helper waves on the other SIMDs of the CU, for rows up to
+                                    form with ONE chain wave that holds all of z and helper
+                                    waves on the other SIMDs of the CU, for rows up to
                                     1024 coordinates (HALP_ERR_UNSUPPORTED elsewhere); 0 takes
-                                    it for rows of 129 .. 512 coordinates at up to two chains
-                                    per CU and for wider rows at up to one.  Results do not
+                                    it up to one chain per CU for any of these rows, two for up
+                                    to 512 coordinates, three to six for up to 256.  Results do not
                                     depend on it                                              */
 
 #define HALP_OPT_EXCHANGE_POLL_DELAY 11 /* split minibatch loop: sleeps of 256 cycles between a

@@ -9,7 +9,7 @@ int launch_inner_reg_b8(const InArgs& a, int nw, int upl, int R, bool packed, hi
 int launch_inner_reg_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_helped_b8(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_helped_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
-int launch_inner_reg_lone_b8(const InArgs& a, int upl, int R, bool pair, hipStream_t s);
+int launch_inner_reg_lone_b8(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
 
 namespace {
 
@@ -54,32 +54,33 @@ bool helped_shape(Shape sh) { return (sh.nw == 2 || sh.nw == 4) && sh.upl <= 2; 
 // 6.0 at 1280 against 4.8 and 7.6 -- beyond that one wave per chain and no helpers)
 constexpr int kHelpedChainsPerCu4 = 2, kHelpedChainsPerCu2 = 5;
 
-// Strips per lane of the form with one chain wave and its helpers on the other SIMDs (8 bits,
-// rows up to 1024 coordinates), or 0 if the shape does not fit it.  A helper reads fragments
-// of one or two strips: every fragment that starts inside the row must end inside it.
-int lone_strips(const halp_handle& h) {
+// Strips per lane and lanes of the form with one chain wave and its helpers on the other SIMDs (8
+// bits, rows up to 1024 coordinates); upl 0 if the shape does not fit it.
+struct Lone {
+  int upl, lanes;
+};
+Lone lone_shape(const halp_handle& h) {
   const halp_params& p = h.p;
-  if (p.b != 8 || p.B != 1 || p.K != 1) return 0;
+  if (p.b != 8 || p.B != 1 || p.K != 1) return Lone{0, 0};
   const int U = (p.d + 1) / 2;
-  const int upl = U <= 128 ? 2 : (U <= 256 ? 4 : (U <= 512 ? 8 : 0));
-  if (upl == 0) return 0;
-  const int sph = upl == 8 ? 2 : 1;  // strips of the widest fragment a helper reads
-  if ((int64_t)((U + sph - 1) / sph) * sph * 2 > h.buf.ldxq) return 0;
-  return upl;
+  if (U <= 32) return Lone{2, 16};
+  return Lone{U <= 128 ? 2 : (U <= 256 ? 4 : (U <= 512 ? 8 : 0)), 64};
 }
 
-// Where the library takes that form by itself: rows of 129 .. 512 coordinates (two or four strips
-// per lane) up to two chains per CU, wider rows up to one.  Measured per epoch of 16384 steps at d = 512 (ms):
-// 128 chains 2.57 against 2.91 for four chain waves with helpers, 256: 2.66 / 3.00, 384: 3.19 /
-// 3.67, 512: 3.26 / 3.69; 768: 5.95 against 4.27 for the library's choice there, 1024: 6.43 / 5.15.
-// d = 256 at 256 chains: 2.10 against 2.91.  d = 1024: 3.97 against 3.79 (the single wave issues
-// ~9 instructions per strip and step); up to 128 coordinates one wave without helpers is faster.
-// Rows of 513 .. 1024 coordinates (eight strips per lane) gain little -- 3.76 against 3.80 ms at 256
-// chains, 22.4 against 22.8 ms for the single chain of 100000 steps, logistic 5.56 against 5.80 -- and only
-// with a CU per chain.
-bool lone_pays(const halp_handle& h, int upl) {
-  if (h.p.d <= 128) return false;
-  const int64_t per_cu = upl <= 4 ? 2 : 1;
+// Where the library takes that form by itself, in chains per CU.  Measured in ns per step of all chains
+// (shared data, squared loss), this form against what runs without it:
+//   d = 64    256 chains 81 / 143, 1024: 114 / 152, 1536: 170 / 210, 2048: 221 / 236
+//   d = 128   512: 96 / 146, 768: 125 / 148, 900: 147 / 147
+//   d = 256   512: 93 / 135, 1024: 148 / 214, 1536: 214 / 277
+//   d = 512   512: 147 / 177 (two workgroups fit a CU; 600 chains would take two turns)
+//   d = 1024  256: 159 / 237, 300 would take two turns
+// and logistic: d = 64 1024: 216 / 255, 1200: 364 / 396; d = 256 1024: 410 / 442; d = 512 512: 246 / 340;
+// d = 1024 256: 277 / 350.
+bool lone_pays(const halp_handle& h, Lone sh) {
+  const bool logistic = h.p.loss == HALP_LOSS_LOGISTIC;
+  int64_t per_cu = 1;
+  if (sh.upl == 2) per_cu = h.p.d > 64 && h.p.d <= 128 ? 3 : (logistic ? 4 : 6);
+  else if (sh.upl == 4) per_cu = 2;
   return (int64_t)h.p.R <= per_cu * h.num_cus;
 }
 
@@ -119,10 +120,10 @@ int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   int rc = inner_reg_supported(p);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  // 8 bits, at most one chain per CU: one chain wave with all of z, helpers on the other SIMDs
-  const int lone_upl = lone_strips(h);
-  if (lone_upl > 0 && (h.inner_helpers == 3 || (h.inner_helpers == 0 && h.inner_waves == 0 && lone_pays(h, lone_upl))))
-    return launch_inner_reg_lone_b8(a, lone_upl, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);  // more chains than CUs: the build that fits twice
+  // 8 bits, few chains per CU: one chain wave with all of z, helpers on the other SIMDs
+  const Lone lone = lone_shape(h);
+  if (lone.upl > 0 && (h.inner_helpers == 3 || (h.inner_helpers == 0 && h.inner_waves == 0 && lone_pays(h, lone))))
+    return launch_inner_reg_lone_b8(a, lone.upl, lone.lanes, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);  // more chains than CUs: the build with at most 128 registers
   if (h.inner_helpers == 3) return HALP_ERR_UNSUPPORTED;
   Shape sh = pick_shape(p, auto_waves(h));
   const int ct = 16 / p.b;

@@ -1,36 +1,44 @@
-// Inner loop of Algorithm 4 (LM-HALP), register-resident form for one chain per CU at
-// 8 bits: one sampled row per step (B = 1), one class, ONE "chain" wave that carries
-// the whole of z, and helper waves on the other SIMDs of the CU.
+// Inner loop of Algorithm 4 (LM-HALP), register-resident form for few chains per CU: one sampled
+// row per step (B = 1), one class, ONE "chain" wave that carries the whole of z, and helper waves
+// on the other SIMDs of the CU.
 //
-// With a chain to itself a CU is bound by the step's dependent chain.  Several waves per
-// chain shorten the update but pay an LDS word and a barrier per step to add their dot
-// products up; one wave with all the coordinates pays nothing across waves, and at 8 bits
-// its arithmetic packs two coordinates into a register:
-//   dot     one packed 16-bit dot per strip (two coordinates), DPP fold, sum read from lane 63
-//   scalar  beta and gamma = Q_(delta_s,b)(beta) in fp64, wave-uniform
-//   update  per strip: floor((-gamma x + r + hl) / 256) + hh + z on packed halves, clamp
-//           (-h~ = 256 hh + hl, 0 <= hl < 256; |gamma x| <= 2^14 and r + hl < 512, so
-//           every intermediate fits 16 bits)
-// Whatever does not depend on z is made by the helpers, a window of 8 steps ahead, and
-// handed over through LDS as one record per lane and step: per strip the sign-extended
-// pair of row values and the pair of rounding bytes with hl added.  A helper serves one or
-// two of the strips of every lane: it draws their Philox blocks, requests the row fragments
-// three windows ahead and writes its dwords of the records.  Where -h~ / 256 is small in
-// every coordinate the records carry r - h~ whole (it fits 16 bits beside -gamma x) and the
-// chain wave adds no hh.  A service wave refills the 256-step batches of step-indexed draws
+// With a chain to itself a CU is bound by the step's dependent chain; a dependent vector
+// instruction of a lone wave takes 8 cycles, an LDS round trip 66, so the chain wave is written
+// for the fewest dependent instructions:
+//   dot     one packed dot per strip (8 bits: two coordinates), DPP fold over 16 lanes.  Rows that
+//           16 lanes hold (LANES = 16: the four rows of a wave do the same work) are done there;
+//           wider rows are added up across the four rows of 16 lanes by one fp64 4x4x4 matrix
+//           instruction (28 cycles; two row broadcasts and a lane read take 45), which multiplies
+//           by the step's scale and adds the rounding draw in the same breath
+//   scalar  gamma = floor(t), t = beta / delta_s + rho, out of ONE fused multiply-add: the draw
+//           comes as C = 1.5 2^20 + 1 - rho, so that the high word of C - t' is a constant plus -gamma
+//           and the low word is the fraction in units of 2^-32 (no floor, no conversion).  The method
+//           fixes the order of roundings on the way to t, which differs from the fused form by
+//           less than 2^-28 there: a step whose fraction lies within 2^-24 of an integer makes its
+//           window (8 steps) be run again in that order from the z it began with.  Everything
+//           else is the same integer in both, so results are those of the other kernels bit for bit
+//   update  z is kept as 2^b z: n = -gamma x + r - h~, z <- saturating (z + n) with the low b bits
+//           cleared -- the saturation of the 16-bit (b = 8) or 32-bit add is the box.  Three
+//           instructions per strip
+// Whatever does not depend on z is made by the helpers, up to two windows of 8 steps ahead, and
+// handed over through LDS as one record per lane and step: per strip the sign-extended row
+// values and r - h~.  A helper serves one or two of the strips of every lane: it draws their Philox
+// blocks, requests the row fragments kSets - 1 windows ahead and writes its dwords of the records.
+// Where -h~ / 2^b is not small in every coordinate, n leaves its word: the records then carry only
+// the low b bits of -h~ and the chain wave adds the rest behind the shift (FOLD = false; five
+// instructions per strip).  A service wave refills the 256-step batches of step-indexed draws
 // (sample indices, rounding draws of gamma and of the L2 term, margins and labels of the
-// sampled rows) and counts the clamped coordinates: the chain wave stores the unclamped strips
-// of a step in LDS instead of comparing them with the clamped ones, and the service wave
-// counts the halves outside [-128, 127] a window later.  One barrier per window orders every
-// hand-over: in period w the chain wave consumes window w from one half of the record ring
-// and fills one half of the log, while the helpers fill the other half of the ring with
-// window w + 1 and the service wave reads the other half of the log (window w - 1).
+// sampled rows) and counts the clamped coordinates: the chain wave stores the n of a step in LDS
+// and the service wave, which holds a z of its own, adds them up a window later with and without
+// saturation.  One barrier per window orders every hand-over: in period w the chain wave consumes
+// window w out of a ring of three and fills one half of the log, while the helpers make window
+// w + 2 and the service wave reads the other half of the log (window w - 1).  The third slot lets
+// the chain wave request the first record of a window before the barrier.
 //
 // The chain wave is wave 0; the helpers and the service wave are placed on the other three
 // SIMDs (waves w and w + 4 of a workgroup share a SIMD: wave 4 only keeps the barriers).
 //
-// Results are those of inner_reg_kernel bit for bit; this header holds the kernel template,
-// inner_reg_lone_b8.hip instantiates it.
+// This header holds the kernel template, inner_reg_lone_b8.hip instantiates it.
 #pragma once
 
 #include "inner_reg_impl.hpp"
@@ -46,52 +54,116 @@ using innerreg::mad24;
 using innerreg::short2r;
 
 typedef int int4r __attribute__((ext_vector_type(4)));
+typedef int int2r __attribute__((ext_vector_type(2)));
+typedef unsigned short ushort2r __attribute__((ext_vector_type(2)));
 
 template <int LOSS>
 constexpr bool logistic_c = LOSS == HALP_LOSS_LOGISTIC;
 
 // waves of a workgroup: chain, helpers, the service wave, and wave 4 kept idle when there is one
-constexpr int waves_of(int upl) { return upl == 2 ? 4 : (upl == 4 ? 7 : 8); }
+constexpr int waves_of(int upl, int lanes) { return lanes == 16 ? 3 : (upl == 2 ? 4 : 7); }
 
-// PAIR: built for two workgroups per CU (more chains than CUs): their 14 waves need four wave
-// slots on two of the SIMDs, i.e. at most 128 registers per lane, which costs the single
-// workgroup of a CU a few spills (2.59 against 2.50 ms per 16384 steps at 4 strips per lane).
-template <int LOSS, int UPL, bool PAIR>
-__global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lone_kernel(InArgs a) {
-  static_assert(UPL == 2 || UPL == 4 || UPL == 8, "two, four or eight strips per lane");
-  constexpr int BITS = 8;
-  constexpr int NQ = UPL / 2;           // 16-byte quads of a record: UPL value pairs, then UPL rounding pairs
-  constexpr int QMAX = 127, QMIN = -128;
+constexpr int kSlots = 4;  // windows of records in the ring
+constexpr int kSets = 4;   // windows of row fragments a helper has in flight
+constexpr int kHis = 3;    // windows of gammas that the chain wave leaves for the service wave
+
+// C = kMagic + 1 - rho + kNear / 2^32: at this magnitude a double's last place is 2^-32 and its high
+// word counts whole numbers.  Fractions within kNear / 2^32 of an integer are told by a low word of at most 2 kNear.
+constexpr double kMagic = 0x1.8p20;
+constexpr int kMagicHi = 0x41380000;
+constexpr uint32_t kNear = 256;
+constexpr double kDraw = kMagic + 1.0 + kNear * 0x1p-32;  // C + rho
+
+// strip u of a lane; the strips a helper reads as one fragment are adjacent, those of its lanes too
+template <int UPL, int LANES>
+__device__ __forceinline__ int strip_of(int u, int lane) {
+  if (LANES == 16) return 16 * u + (lane & 15);
+  if (UPL == 8) return 128 * (u / 2) + 2 * lane + (u & 1);
+  return 64 * u + lane;
+}
+
+// What a strip is: two coordinates as the halves of a word (8 bits) or one (16 bits), values times 2^b.
+template <int BITS>
+struct Strip;
+template <>
+struct Strip<8> {
+  static constexpr int CT = 2;
+  static constexpr int kMask = (int)0xFF00FF00;
+  // n = -gamma x + c; g: the low half is -gamma
+  static __device__ __forceinline__ int mad(int x, int g, int c) {
+    const short2r gp = short2r{(short)g, (short)g};
+    return __builtin_bit_cast(int, __builtin_bit_cast(short2r, x) * gp + __builtin_bit_cast(short2r, c));
+  }
+  static __device__ __forceinline__ int add_sat(int z, int n) {
+    return __builtin_bit_cast(int, __builtin_elementwise_add_sat(__builtin_bit_cast(short2r, z), __builtin_bit_cast(short2r, n)));
+  }
+  static __device__ __forceinline__ int add(int z, int n) {
+    return __builtin_bit_cast(int, __builtin_bit_cast(short2r, z) + __builtin_bit_cast(short2r, n));
+  }
+  // (n >> b) + k, before the clamp
+  static __device__ __forceinline__ int shifted(int n, int k) {
+    return __builtin_bit_cast(int, (__builtin_bit_cast(short2r, n) >> (short2r)(8)) + __builtin_bit_cast(short2r, k));
+  }
+  static __device__ __forceinline__ int high(int z) { return __builtin_bit_cast(int, __builtin_bit_cast(short2r, z) >> (short2r)(8)); }
+  static __device__ __forceinline__ int clamp_up(int v) {  // clamped to the box, times 2^b
+    const short2r c = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(short2r, v), (short2r)(-128)), (short2r)(127));
+    return __builtin_bit_cast(int, c << (short2r)(8));
+  }
+  // coordinates of v outside the box
+  static __device__ __forceinline__ int outside(int v) {
+    const ushort2r t = __builtin_bit_cast(ushort2r, __builtin_bit_cast(short2r, v) + short2r{128, 128}) >> (ushort2r)(8);
+    return __builtin_bit_cast(int, __builtin_elementwise_min(t, (ushort2r)(1)));
+  }
+  // coordinates in which the sum of z and n leaves its word: its sign there is not that of the saturated sum
+  static __device__ __forceinline__ int clamped(int sat, int wrapped) {
+    return __builtin_bit_cast(int, __builtin_bit_cast(ushort2r, sat ^ wrapped) >> (ushort2r)(15));
+  }
+  static __device__ __forceinline__ unsigned int counted(int acc) { return (unsigned int)(acc & 0xFFFF) + ((unsigned int)acc >> 16); }
+  // x^T z of a strip, times 2^b, added to acc
+  static __device__ __forceinline__ int dot(int x, int z, int acc) {
+    return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2r, x), __builtin_bit_cast(short2r, z), acc, false);
+  }
+  static __device__ __forceinline__ int dot(int x, int z) {  // as an instruction: the compiler's form wants a zeroed register
+    int r;
+    asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "v"(z));
+    return r;
+  }
+  static __device__ __forceinline__ int value(int v, int e) { return e ? v >> 16 : (int)(short)v; }
+  static __device__ __forceinline__ int join(int a, int b) { return (a & 0xFFFF) | (b << 16); }
+};
+
+// LANES: lanes that share a row of z, 64 or 16 (four copies of the same work in a wave).
+// PAIR: built for several workgroups per CU (more chains than CUs), at most 128 registers per lane.
+template <int BITS, int LOSS, int UPL, int LANES, bool PAIR>
+__global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner_reg_lone_kernel(InArgs a) {
+  static_assert(BITS == 8, "8 bits");
+  static_assert(UPL == 2 || (LANES == 64 && (UPL == 4 || UPL == 8)), "two, four or eight strips per lane");
+  using S = Strip<BITS>;
+  constexpr int CT = S::CT;
+  constexpr int NQ = UPL / 2;           // 16-byte quads of a record: UPL row values, then UPL of r - h~
+  constexpr int QMAX = (1 << (BITS - 1)) - 1, QMIN = -(1 << (BITS - 1));
   constexpr int kMask = 2 * kBatch - 1;
   const int chain = blockIdx.x;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // Roles by wave.  Waves w and w + 4 share a SIMD and wave 0 is the chain wave, so wave 4 only
-  // keeps the barriers.  2 strips per lane: waves 1, 2 serve one strip each, wave 3 is the
-  // service wave.  4: waves 1, 2, 3, 5 one strip each, service wave 6.  8: waves 1, 2, 3 two
-  // strips each, waves 5, 6 one each (three strips on two SIMDs, two and the service wave 7 on
-  // the third).
-  int first_strip = -1, strips_here = 0;
-  bool is_service = false;
-  if (UPL == 2) {
-    if (wave == 1 || wave == 2) { first_strip = wave - 1; strips_here = 1; }
-    is_service = wave == 3;
-  } else if (UPL == 4) {
-    if (wave >= 1 && wave <= 3) { first_strip = wave - 1; strips_here = 1; }
-    if (wave == 5) { first_strip = 3; strips_here = 1; }
-    is_service = wave == 6;
-  } else {
-    if (wave >= 1 && wave <= 3) { first_strip = 2 * (wave - 1); strips_here = 2; }
-    if (wave == 5 || wave == 6) { first_strip = wave + 1; strips_here = 1; }
-    is_service = wave == 7;
-  }
+  // keeps the barriers.  The service wave has a SIMD to itself where the row is wide (counting
+  // the clamps of a strip takes about as long as serving it): 16 lanes: wave 1 serves every strip,
+  // wave 2 is the service wave.  2 strips per lane: waves 1, 2 one strip each, service wave 3.  4 and 8: waves
+  // 1, 2, 5, 6 one or two strips each, service wave 3.
+  constexpr int kStripsHere = UPL == 8 ? 2 : 1;  // of a lane, served by a helper
+  int first_strip = -1;
+  if (LANES == 16) first_strip = wave == 1 ? 0 : -1;
+  else if (wave == 1 || wave == 2) first_strip = kStripsHere * (wave - 1);
+  else if (UPL >= 4 && (wave == 5 || wave == 6)) first_strip = kStripsHere * (wave - 3);
+  const bool is_service = wave == (LANES == 16 ? 2 : 3);
   const int d = a.d;
-  const int U = (d + 1) / 2;  // strips in a row
+  const int U = (d + CT - 1) / CT;  // strips in a row
   const uint32_t N = (uint32_t)a.N;
-  const int64_t row_bytes = a.ldxq;
+  const int64_t row_bytes = a.ldxq * (BITS / 8);
   const unsigned char* __restrict__ Xq =
-      reinterpret_cast<const unsigned char*>(a.Xq) + (int64_t)chain * a.xq_chain_stride;
+      reinterpret_cast<const unsigned char*>(a.Xq) + (int64_t)chain * a.xq_chain_stride * (BITS / 8);
   const float* __restrict__ phi = a.phi + (int64_t)chain * a.N;
   const float* __restrict__ y =
       reinterpret_cast<const float*>(a.y) + (int64_t)chain * a.y_chain_stride;
@@ -110,21 +182,28 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
   }
 
   __shared__ __attribute__((aligned(16))) int s_idx[2 * kBatch];
-  __shared__ __attribute__((aligned(16))) double s_rho[2 * kBatch];
-  __shared__ __attribute__((aligned(16))) int s_creg[2 * kBatch];
-  __shared__ __attribute__((aligned(16))) float s_phi[2 * kBatch];
-  __shared__ __attribute__((aligned(16))) float s_y[2 * kBatch];
+  __shared__ __attribute__((aligned(16))) double s_c[2 * kBatch];  // kDraw - rho
+  __shared__ __attribute__((aligned(16))) short s_creg[2 * kBatch];
+  constexpr bool kMargins = LOSS != HALP_LOSS_SQUARED;
+  __shared__ __attribute__((aligned(16))) float s_phi[kMargins ? 2 * kBatch : 4];
+  __shared__ __attribute__((aligned(16))) float s_y[logistic_c<LOSS> ? 2 * kBatch : 4];
   // logistic loss: l'(phi_i) of the sampled rows, which no step has to evaluate itself
   __shared__ __attribute__((aligned(16))) double s_dl0[logistic_c<LOSS> ? 2 * kBatch : 2];
+  __shared__ __attribute__((aligned(16))) int s_hi[kHis][kWin];  // kMagicHi - gamma of the steps, before the clamp
   __shared__ unsigned long long s_cnt[4];
   __shared__ int s_fold;  // 1: the whole of -h~ rides in the records (set by the chain wave before the first barrier)
-  // records: [half of the ring][step of the window][quad][lane], 16 bytes each
+  // records: [slot of the ring][step of the window][quad][lane], 16 bytes each
   extern __shared__ __attribute__((aligned(16))) int4r s_rec[];
-  auto rec_at = [&](int half, int s, int q) -> int4r* { return s_rec + ((half * kWin + s) * NQ + q) * 64 + lane; };
-  // behind it, what the chain wave hands back: the unclamped strips of every step, [half][step][quad][lane]
-  constexpr int NQV = UPL >= 4 ? UPL / 4 : 1;
-  int4r* const s_vlog = s_rec + 2 * kWin * NQ * 64;
-  auto vlog_at = [&](int half, int s, int q) -> int4r* { return s_vlog + ((half * kWin + s) * NQV + q) * 64 + lane; };
+  auto rec_at = [&](int slot, int s, int q) -> const int4r* {
+    return s_rec + ((slot * kWin + s) * NQ + q) * LANES + (lane & (LANES - 1));
+  };
+  auto split_record = [&](const int4r (&r)[NQ], int (&x)[UPL], int (&cr)[UPL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < UPL; ++u) {
+      x[u] = r[u / 4][u % 4];
+      cr[u] = r[(UPL + u) / 4][(UPL + u) % 4];
+    }
+  };
 
   const double delta_m = sc[0], inv_s = sc[5];
   const double dscale = __dmul_rn(a.delta_d, delta_m);
@@ -135,13 +214,56 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
   const bool lp = a.lp != 0;
   const double al = __dmul_rn(aB, a.lambda);
 
-  const int s0 = lane * UPL;  // first strip of the lane
-  const int j0 = s0 * 2;      // first coordinate
-
   if (tid < 4) s_cnt[tid] = 0;
+
+  // z of a lane's strips times 2^b, the coordinates that exist, and the high part of -h~; true where every
+  // high part is small.  With -h~ = 2^b hh + hl, 0 <= hl < 2^b, and every hh in [-64, 62] (8 bits),
+  // n = -gamma x + r - h~ fits its word (|gamma x| <= 2^14, 0 <= r < 256).
+  auto load_z = [&](int (&zp)[UPL], int (&mask)[UPL], int (&hh)[UPL]) -> bool {
+    bool small = true;
+#pragma unroll
+    for (int u = 0; u < UPL; ++u) {
+      int zv[2], mv[2], hv[2];
+#pragma unroll
+      for (int e = 0; e < CT; ++e) {
+        const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
+        const bool ok = j < d;
+        zv[e] = ok ? (int)zg[ok ? j : 0] << BITS : 0;
+        mv[e] = ok ? S::kMask : 0;
+        hv[e] = ok ? (-(int)hg[ok ? j : 0]) >> BITS : 0;
+        small = small && hv[e] >= -64 && hv[e] <= 62;
+      }
+      zp[u] = S::join(zv[0], zv[1]);
+      mask[u] = S::join(mv[0], mv[1]);
+      hh[u] = S::join(hv[0], hv[1]);
+    }
+    return small;
+  };
+  // z <- Q(z - gamma x - h~) of a strip; g: -gamma.  fold: c holds r - h~, else r + hl
+  auto step_strip = [&](int z, int x, int g, int c, int hh, int mask, auto fold_tag) __attribute__((always_inline)) -> int {
+    const int n = S::mad(x, g, c);
+    if constexpr (decltype(fold_tag)::value) return S::add_sat(z, n) & mask;
+    else return S::clamp_up(S::shifted(n, S::add(hh, S::high(z)))) & mask;
+  };
+  // the same of a step with an L2 draw (rare), in wide arithmetic on the coordinates
+  auto step_strip_reg = [&](int z, int x, int g, int cl, int c, int hh, int mask, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
+    int zn[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < CT; ++e) {
+      const int zk = S::value(z, e) >> BITS, xk = S::value(x, e);
+      const int hr = (decltype(fold_tag)::value ? 0 : S::value(hh, e) << BITS) + S::value(c, e);
+      const int zuk = zk + (mad24(-cl, zk, mad24(g, xk, hr)) >> BITS);
+      const int zc = min(max(zuk, QMIN), QMAX);
+      if (clamped) *clamped += (S::value(mask, e) != 0 && zuk != zc) ? 1 : 0;
+      zn[e] = zc << BITS;
+    }
+    return S::join(zn[0], zn[1]) & mask;
+  };
 
   if (is_service) {
     // ============================ service wave ============================
+    int zs[UPL], mask[UPL], hh[UPL];
+    (void)load_z(zs, mask, hh);
     // draws that depend on the step number only, 256 steps per batch
     auto fill_batch = [&](int64_t bb) {
       const int half = (int)(bb & 1) * kBatch;
@@ -152,93 +274,124 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
       iv.x = (int)__umulhi(ri.x, N); iv.y = (int)__umulhi(ri.y, N);
       iv.z = (int)__umulhi(ri.z, N); iv.w = (int)__umulhi(ri.w, N);
       *reinterpret_cast<int4*>(&s_idx[half + 4 * lane]) = iv;
-      if (need_phi) {
+      if constexpr (need_phi) {
         float4 pv;
         pv.x = phi[iv.x]; pv.y = phi[iv.y]; pv.z = phi[iv.z]; pv.w = phi[iv.w];
         *reinterpret_cast<float4*>(&s_phi[half + 4 * lane]) = pv;
+        if constexpr (logistic) {
+          float4 yv;
+          yv.x = y[iv.x]; yv.y = y[iv.y]; yv.z = y[iv.z]; yv.w = y[iv.w];
+          *reinterpret_cast<float4*>(&s_y[half + 4 * lane]) = yv;
+          s_dl0[half + 4 * lane + 0] = logistic_dl((double)pv.x, (double)yv.x);
+          s_dl0[half + 4 * lane + 1] = logistic_dl((double)pv.y, (double)yv.y);
+          s_dl0[half + 4 * lane + 2] = logistic_dl((double)pv.z, (double)yv.z);
+          s_dl0[half + 4 * lane + 3] = logistic_dl((double)pv.w, (double)yv.w);
+        }
       }
-      if (logistic) {
-        float4 yv;
-        yv.x = y[iv.x]; yv.y = y[iv.y]; yv.z = y[iv.z]; yv.w = y[iv.w];
-        *reinterpret_cast<float4*>(&s_y[half + 4 * lane]) = yv;
-        const float4 pv = *reinterpret_cast<const float4*>(&s_phi[half + 4 * lane]);
-        s_dl0[half + 4 * lane + 0] = logistic_dl((double)pv.x, (double)yv.x);
-        s_dl0[half + 4 * lane + 1] = logistic_dl((double)pv.y, (double)yv.y);
-        s_dl0[half + 4 * lane + 2] = logistic_dl((double)pv.z, (double)yv.z);
-        s_dl0[half + 4 * lane + 3] = logistic_dl((double)pv.w, (double)yv.w);
-      }
-      s_rho[half + 4 * lane + 0] = __dmul_rn((double)rg.x, 0x1p-32);
-      s_rho[half + 4 * lane + 1] = __dmul_rn((double)rg.y, 0x1p-32);
-      s_rho[half + 4 * lane + 2] = __dmul_rn((double)rg.z, 0x1p-32);
-      s_rho[half + 4 * lane + 3] = __dmul_rn((double)rg.w, 0x1p-32);
+      auto magic = [](uint32_t r) { return __dadd_rn(kDraw, -__dmul_rn((double)r, 0x1p-32)); };  // exact
+      s_c[half + 4 * lane + 0] = magic(rg.x);
+      s_c[half + 4 * lane + 1] = magic(rg.y);
+      s_c[half + 4 * lane + 2] = magic(rg.z);
+      s_c[half + 4 * lane + 3] = magic(rg.w);
       if (use_reg) {
         const U4 rr = stream_block(seed, kReg, a.epoch, blk);
         const double two_b = (double)(1 << BITS);
-        int4 cv;
-        cv.x = (int)quantize_real(al, two_b, rr.x, 0.0, (double)QMAX, nullptr);
-        cv.y = (int)quantize_real(al, two_b, rr.y, 0.0, (double)QMAX, nullptr);
-        cv.z = (int)quantize_real(al, two_b, rr.z, 0.0, (double)QMAX, nullptr);
-        cv.w = (int)quantize_real(al, two_b, rr.w, 0.0, (double)QMAX, nullptr);
-        *reinterpret_cast<int4*>(&s_creg[half + 4 * lane]) = cv;
+        short4 cv;
+        cv.x = (short)quantize_real(al, two_b, rr.x, 0.0, (double)QMAX, nullptr);
+        cv.y = (short)quantize_real(al, two_b, rr.y, 0.0, (double)QMAX, nullptr);
+        cv.z = (short)quantize_real(al, two_b, rr.z, 0.0, (double)QMAX, nullptr);
+        cv.w = (short)quantize_real(al, two_b, rr.w, 0.0, (double)QMAX, nullptr);
+        *reinterpret_cast<short4*>(&s_creg[half + 4 * lane]) = cv;
       }
     };
-    // Clamped coordinates: the chain wave stores the unclamped strips of a step (one LDS store)
-    // instead of comparing them with the clamped ones; they are counted here, a window later.
-    // A half outside [-128, 127] has a bit set above its low byte once 128 is added.
-    unsigned int n_lane = 0;  // this lane's count
-    auto count_window = [&](int64_t w) {
-      const int half = (int)(w & 1);
-      const int64_t left = T - w * kWin;
-      const short2r k128 = short2r{128, 128};
-      short2r acc = short2r{0, 0};  // at most 8 UPL per half and window
+    // Clamped coordinates: this wave holds a z of its own and takes it through the steps once more, with
+    // the gammas that the chain wave leaves in s_hi; a coordinate was clamped where the sums with and
+    // without saturation differ.  The records of window w are taken out of the ring in period w + 1
+    // and gone through in period w + 2, when the chain wave's stores have landed for certain.
+    unsigned int n_lane = 0;    // this lane's count of clamped coordinates
+    unsigned int n_gclamp = 0;  // clamped gammas
+    int4r r[kWin][NQ];
+    auto take = [&](int64_t w) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < kWin; ++s)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) r[s][q] = *rec_at((int)(w & (kSlots - 1)), s, q);
+    };
+    int part = 0;  // of s_hi, the next to be counted
+    auto count_steps = [&](int64_t w, int steps, auto full_tag, auto fold_tag) __attribute__((always_inline)) {
+      constexpr bool FULL = decltype(full_tag)::value;  // eight steps, none of them with an L2 draw
+      const int4r h0 = *reinterpret_cast<const int4r*>(&s_hi[part][0]), h1 = *reinterpret_cast<const int4r*>(&s_hi[part][4]);
+      const int hi[kWin] = {h0[0], h0[1], h0[2], h0[3], h1[0], h1[1], h1[2], h1[3]};
+      int acc = 0;  // at most 8 UPL per half and window
+      int wide = 0;
 #pragma unroll
       for (int s = 0; s < kWin; ++s) {
-        if (s < left) {
+        if (FULL || s < steps) {
+          const int cl = !FULL && use_reg ? __builtin_amdgcn_readfirstlane((int)s_creg[(int)((w * kWin + s) & kMask)]) : 0;
+          const int g = min(max(hi[s], kMagicHi - QMAX), kMagicHi - QMIN);
+          int x[UPL], cr[UPL];
+          split_record(r[s], x, cr);
 #pragma unroll
-          for (int q = 0; q < NQV; ++q) {
-            const int4r v4 = *vlog_at(half, s, q);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              if (4 * q + k < UPL) {
-                const int vk = v4[k];
-                typedef unsigned short ushort2r __attribute__((ext_vector_type(2)));
-                const ushort2r t = __builtin_bit_cast(ushort2r, __builtin_bit_cast(short2r, vk) + k128) >> (ushort2r)(8);
-                acc += __builtin_bit_cast(short2r, __builtin_elementwise_min(t, (ushort2r)(1)));
-              }
+          for (int u = 0; u < UPL; ++u) {
+            if (!FULL && cl != 0) {
+              zs[u] = step_strip_reg(zs[u], x[u], g - kMagicHi, cl, cr[u], hh[u], mask[u], fold_tag, &wide);
+            } else if constexpr (decltype(fold_tag)::value) {
+              const int n = S::mad(x[u], g, cr[u]);
+              const int sat = S::add_sat(zs[u], n);
+              acc = S::add(acc, S::clamped(sat, S::add(zs[u], n)));
+              zs[u] = sat & mask[u];
+            } else {
+              const int v = S::shifted(S::mad(x[u], g, cr[u]), S::add(hh[u], S::high(zs[u])));
+              acc = S::add(acc, S::outside(v));  // (none where no coordinate is: |v| <= 67 there)
+              zs[u] = S::clamp_up(v) & mask[u];
             }
           }
         }
       }
-      n_lane += (unsigned int)(unsigned short)acc[0] + (unsigned int)(unsigned short)acc[1];
+      n_lane += S::counted(acc) + (unsigned int)wide;
+    };
+    auto count_window = [&](int64_t w, auto fold_tag) __attribute__((always_inline)) {
+      const int64_t left = T - w * kWin;
+      const int steps = (int)(left < kWin ? left : kWin);
+      if (left >= kWin && !use_reg) count_steps(w, kWin, std::true_type{}, fold_tag);
+      else count_steps(w, steps, std::false_type{}, fold_tag);
+      const int hi = s_hi[part][lane & (kWin - 1)];
+      n_gclamp += (unsigned int)__builtin_popcountll(__ballot(lane < steps && (hi < kMagicHi - QMAX || hi > kMagicHi - QMIN)));
+      part = part == kHis - 1 ? 0 : part + 1;
     };
     fill_batch(0);
     fill_batch(1);
     __syncthreads();  // P0: the first two batches are in place
-    __syncthreads();  // P1: the records of window 0 are in place
-    for (int64_t w = 0; w < nwin; ++w) {
-      // window w = 32 m: every reader has left batch m - 1, whose half takes batch m + 1
-      if ((w & (kBatch / kWin - 1)) == 0 && w > 0) fill_batch(w / (kBatch / kWin) + 1);
-      if (w > 0) count_window(w - 1);
-      __syncthreads();
+    __syncthreads();  // P1: the records of windows 0 and 1 are in place
+    auto run = [&](auto fold_tag) __attribute__((always_inline)) {
+      for (int64_t w = 0; w < nwin + 2; ++w) {
+        if (w >= 2) count_window(w - 2, fold_tag);
+        if (w >= 1 && w <= nwin) take(w - 1);
+        // window w = 32 m + 1: every reader has left batch m - 1, whose half takes batch m + 1
+        if ((w & (kBatch / kWin - 1)) == 1 && w > 1 && w < nwin) fill_batch(w / (kBatch / kWin) + 1);
+        if (w <= nwin) __syncthreads();  // w = nwin: P2, the last gammas are in place
+      }
+    };
+    if (s_fold) run(std::true_type{});
+    else run(std::false_type{});
+    const unsigned int total = (unsigned int)wave_sum_i32(lane < LANES ? (int)n_lane : 0);
+    if (lane == 0) {
+      s_cnt[0] = total;
+      s_cnt[1] = n_gclamp;
     }
-    if (nwin > 0) count_window(nwin - 1);
-    const unsigned int total = (unsigned int)wave_sum_i32((int)n_lane);
-    if (lane == 0) s_cnt[0] = total;
     __syncthreads();  // the counters
     return;
   }
 
   if (first_strip >= 0) {
     // ============================ helper wave =============================
-    auto helper_body = [&](auto sph_c) {
-      constexpr int SPH = decltype(sph_c)::value;  // strips of a lane this wave serves
-      const int u0 = first_strip;               // the first of them
-      const int g0 = s0 + u0;                   // ... in the row
-      const bool frag_ok = g0 < U;              // the fragment starts inside the row
-      const uint32_t frag_off = frag_ok ? (uint32_t)(2 * g0) : 0u;  // lanes past the row re-read its first bytes
+      constexpr int SPH = kStripsHere;
+      // 16 lanes: lane h of the helper serves strip h mod 16 UPL, i.e. strip h / 16 of lane h mod 16
+      const int g0 = LANES == 16 ? lane & (16 * UPL - 1) : 64 * first_strip + SPH * lane;  // the first of them in the row
+      const int owner = LANES == 16 ? g0 & 15 : lane;
+      const int u0 = LANES == 16 ? g0 >> 4 : first_strip;
       short2r hlp[SPH];                         // what a record adds to the rounding bytes: the low byte of
       short2r hfp[SPH];                         // -h~, or the whole of it where every -h~ / 256 is small
-      uint32_t xmask = 0;                       // bytes of the fragment that are coordinates < d
 #pragma unroll
       for (int i = 0; i < SPH; ++i) {
         int hl[2], hf[2];
@@ -249,14 +402,14 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
           const int hneg = ok ? -(int)hg[ok ? j : 0] : 0;
           hl[e] = hneg & 0xFF;
           hf[e] = hneg;
-          if (ok) xmask |= 0xFFu << (16 * i + 8 * e);
         }
         hlp[i] = short2r{(short)hl[0], (short)hl[1]};
         hfp[i] = short2r{(short)hf[0], (short)hf[1]};
       }
-      // The rows of a window: its eight sample indices in two LDS reads (every entry of the
-      // index ring is a valid row at any time, so windows past the end of the epoch fetch
-      // rows that are never used), then one load per step.
+      // The rows of a window: its eight sample indices in two LDS reads (every entry of the index ring is
+      // a valid row at any time, so windows past the end of the epoch fetch rows that are never used),
+      // then one multiply-add for the address and one load per step.
+      const unsigned char* const frag = Xq + (g0 < U ? 2 * g0 : 0);  // lanes past the row re-read its first bytes
       auto request = [&](uint32_t (&dst)[kWin], int64_t win) {
         const int base = (int)((win * kWin) & kMask);
         const int4 i0 = *reinterpret_cast<const int4*>(&s_idx[base]);
@@ -264,34 +417,37 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
         const int iv[kWin] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
-          const int i = __builtin_amdgcn_readfirstlane(iv[s]);
-          const unsigned char* rowp = Xq + (int64_t)i * row_bytes;  // uniform
-          if (SPH == 1) dst[s] = (uint32_t) * reinterpret_cast<const uint16_t*>(rowp + frag_off);
-          else dst[s] = *reinterpret_cast<const uint32_t*>(rowp + frag_off);
+          const unsigned char* const at = frag + (uint64_t)(uint32_t)iv[s] * (uint32_t)row_bytes;
+          if (SPH == 1) dst[s] = (uint32_t) * reinterpret_cast<const uint16_t*>(at);
+          else dst[s] = *reinterpret_cast<const uint32_t*>(at);
         }
       };
-      uint32_t f0[kWin], f1[kWin], f2[kWin];  // row fragments in flight: window v in set v % 3
-      U4 zr[SPH], zn[SPH];  // rounding blocks of window 0, and of the window whose records are made next
-      auto blocks = [&](U4 (&dst)[SPH], int64_t win) {
+      uint32_t f[kSets][kWin];  // row fragments in flight: window v in set v % kSets
+      U4 zn[SPH];  // rounding blocks of the window whose records are made next
+      auto blocks = [&](int64_t win) {
 #pragma unroll
-        for (int i = 0; i < SPH; ++i) dst[i] = zround_block(seed, a.epoch, (uint32_t)(g0 + i), (uint32_t)win);
+        for (int i = 0; i < SPH; ++i) zn[i] = zround_block(seed, a.epoch, (uint32_t)(g0 + i), (uint32_t)win);
       };
-      // the records of a window into a half of the ring
-      auto make_window = [&](const uint32_t (&fr)[kWin], const U4 (&zb)[SPH], int half) {
+      int* const rec = reinterpret_cast<int*>(s_rec) + 4 * owner;
+      // the records of a window into a slot of the ring
+      auto make_window = [&](const uint32_t (&fr)[kWin], int slot) {
+        int* const at = rec + slot * (kWin * NQ * LANES * 4);
+        int* const xw = at + (u0 / 4) * (4 * LANES) + u0 % 4;
+        int* const cw = at + ((UPL + u0) / 4) * (4 * LANES) + (UPL + u0) % 4;
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
-          const uint32_t fv = fr[s] & xmask;
+          const uint32_t fv = fr[s];
 #pragma unroll
           for (int i = 0; i < SPH; ++i) {
-            // the strip's two bytes go to the high bytes of the halves and come back down with their signs
+            // the strip's two bytes go to the high bytes of the halves and come back down with their
+            // signs (bytes past the row's end are kept out of z by the chain wave)
             const uint32_t up = __builtin_amdgcn_perm(0u, fv, i ? 0x030C020Cu : 0x010C000Cu);
             const short2r xp = __builtin_bit_cast(short2r, up) >> (short2r)(8);
-            const uint32_t word = pick(zb[i], (uint32_t)(s >> 1));
+            const uint32_t word = pick(zn[i], (uint32_t)(s >> 1));
             const uint32_t rp = __builtin_amdgcn_perm(0u, word, (s & 1) ? 0x0C030C02u : 0x0C010C00u);
             const short2r crp = __builtin_bit_cast(short2r, rp) + hlp[i];
-            const int u = u0 + i;
-            reinterpret_cast<int*>(rec_at(half, s, u / 4))[u % 4] = __builtin_bit_cast(int, xp);
-            reinterpret_cast<int*>(rec_at(half, s, (UPL + u) / 4))[(UPL + u) % 4] = __builtin_bit_cast(int, crp);
+            xw[s * (NQ * LANES * 4) + i] = __builtin_bit_cast(int, xp);
+            cw[s * (NQ * LANES * 4) + i] = __builtin_bit_cast(int, crp);
           }
         }
       };
@@ -300,39 +456,41 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
 #pragma unroll
         for (int i = 0; i < SPH; ++i) hlp[i] = hfp[i];
       }
-      request(f0, 0);
-      request(f1, 1);
-      request(f2, 2);
-      blocks(zr, 0);
-      make_window(f0, zr, 0);
-      blocks(zn, 1);
-      __syncthreads();  // P1: the records of window 0 are in place
-      // Period w: the rows of window w + 3 are requested into the set window w left, the records
-      // of window w + 1 are made, then the blocks of window w + 2.  Three periods per trip, so that
-      // the fragment sets rotate by name.
+#pragma unroll
+      for (int v = 0; v < kSets; ++v) request(f[v], v);
+      blocks(0);
+      make_window(f[0], 0);
+      request(f[0], kSets);
+      blocks(1);
+      make_window(f[1], 1);
+      blocks(2);
+      __syncthreads();  // P1: the records of windows 0 and 1 are in place
+      // Period w: the rows of window w + 1 + kSets are requested into the set window w + 1 left, the
+      // records of window w + 2 are made, then the blocks of window w + 3.  kSets periods per
+      // trip, so that the fragment sets rotate by name.
       // (nothing may be scheduled across the borders of a period: left to itself the compiler
-      // masks the fragments of all three sets at the top of the loop, i.e. waits for every load)
+      // masks the fragments of all sets at the top of the loop, i.e. waits for every load)
+      int slot = 2;
       auto period = [&](int64_t w, uint32_t (&freq)[kWin], const uint32_t (&fuse)[kWin]) {
         __builtin_amdgcn_sched_barrier(0);
-        request(freq, w + 3);
+        request(freq, w + 1 + kSets);
         __builtin_amdgcn_sched_barrier(0);
-        make_window(fuse, zn, (int)((w + 1) & 1));
-        blocks(zn, w + 2);
+        make_window(fuse, slot);
+        slot = (slot + 1) & (kSlots - 1);
+        blocks(w + 3);
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
       };
       int64_t w = 0;
-      for (; w + 3 <= nwin; w += 3) {
-        period(w, f0, f1);
-        period(w + 1, f1, f2);
-        period(w + 2, f2, f0);
+      for (; w + kSets <= nwin; w += kSets) {
+#pragma unroll
+        for (int k = 0; k < kSets; ++k) period(w + k, f[(k + 1) % kSets], f[(k + 2) % kSets]);
       }
-      if (w < nwin) period(w, f0, f1);
-      if (w + 1 < nwin) period(w + 1, f1, f2);
-      __syncthreads();  // the chain wave's counters
-    };
-    if (strips_here == 2) helper_body(std::integral_constant<int, 2>{});
-    else helper_body(std::integral_constant<int, 1>{});
+#pragma unroll
+      for (int k = 0; k < kSets - 1; ++k)
+        if (w + k < nwin) period(w + k, f[(k + 1) % kSets], f[(k + 2) % kSets]);
+      __syncthreads();  // P2
+      __syncthreads();  // the counters
     return;
   }
 
@@ -342,214 +500,216 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
     __syncthreads();
     for (int64_t w = 0; w < nwin; ++w) __syncthreads();
     __syncthreads();
+    __syncthreads();
     return;
   }
 
   // ============================== chain wave ==============================
-  short2r zp[UPL], hhp[UPL];  // z, and the high part of -h~, two coordinates per register
-#pragma unroll
-  for (int u = 0; u < UPL; ++u) {
-    int zv[2], hh[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int j = j0 + 2 * u + e;
-      const bool ok = j < d;
-      zv[e] = ok ? (int)zg[ok ? j : 0] : 0;
-      hh[e] = ok ? (-(int)hg[ok ? j : 0]) >> 8 : 0;
-    }
-    zp[u] = short2r{(short)zv[0], (short)zv[1]};
-    hhp[u] = short2r{(short)hh[0], (short)hh[1]};
-  }
-  // With -h~ = 256 hh + hl the update adds hh behind the shift.  Where every hh lies in
-  // [-64, 62], -gamma x + r - h~ itself fits 16 bits (|gamma x| <= 2^14, 0 <= r < 256): the
-  // records then carry r - h~ whole and the chain wave saves the addition of hh, one
-  // instruction per strip and step.
-  bool hh_small = true;
-#pragma unroll
-  for (int u = 0; u < UPL; ++u)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) hh_small = hh_small && (int)hhp[u][e] >= -64 && (int)hhp[u][e] <= 62;
+  int zp[UPL], mask[UPL], hh[UPL];
+  const bool hh_small = load_z(zp, mask, hh);
   const bool fold = __ballot(!hh_small) == 0;  // uniform
   if (lane == 0) s_fold = fold ? 1 : 0;
-  unsigned int n_zclamp = 0, n_reg = 0;  // uniform over the wave
-  unsigned int n_gclamp_v = 0;          // per lane, the same in every lane
+  // The fused form stands for the fixed order of roundings while nothing underflows on the way and
+  // no partial sum of the matrix instruction is so large that its last place matters (|t| <= 2^22).
+  const double k2 = __dmul_rn(aB, inv_s), k1 = __dmul_rn(dscale, k2);
+  auto normal = [](double v) { return v > 1e-200 && v < 1e200; };
+  const bool fused_ok = normal(dscale) && normal(aB) && normal(__dmul_rn(dscale, aB)) && normal(inv_s) && normal(k2) && normal(k1) &&
+                        (LANES == 16 || k1 * (double)d * (double)(1 << (2 * BITS - 2)) < 0x1p22);
+  const double scale_one = 1.0 / (double)(1 << BITS);         // the dot is with 2^b z
+  const double scale_t = -k1 * scale_one;
+  unsigned int n_reg = 0;  // steps with an L2 draw
   __syncthreads();  // P0
-  __syncthreads();  // P1: the records of window 0 are in place
+  __syncthreads();  // P1: the records of windows 0 and 1 are in place
   __builtin_amdgcn_s_setprio(3);
 
-  // step-indexed draws of a window (rounding draws of gamma, margins and labels of its rows),
-  // read from the batch ring one window before they are used
-  double rho_n[kWin], dl0_n[kWin];
-  float phi_n[kWin], y_n[kWin];
+  // what a step needs from LDS, requested kAhead steps ahead: its record and its step-indexed draws
+  struct Step {
+    int4r rec[NQ];
+    double c, dl0;
+    float phi, y;
+  };
+  auto load_step = [&](Step& st, int slot, int base, int s) __attribute__((always_inline)) {
 #pragma unroll
-  for (int s = 0; s < kWin; ++s) {
-    phi_n[s] = y_n[s] = 0.f;
-    dl0_n[s] = 0.0;
-  }
-  auto load_draws = [&](int64_t tt) {
-    const int base = (int)(tt & kMask);
-    if (need_phi) {
-      const float4 p0 = *reinterpret_cast<const float4*>(&s_phi[base]);
-      const float4 p1 = *reinterpret_cast<const float4*>(&s_phi[base + 4]);
-      phi_n[0] = p0.x; phi_n[1] = p0.y; phi_n[2] = p0.z; phi_n[3] = p0.w;
-      phi_n[4] = p1.x; phi_n[5] = p1.y; phi_n[6] = p1.z; phi_n[7] = p1.w;
-    }
-    if (logistic) {
-      const float4 y0 = *reinterpret_cast<const float4*>(&s_y[base]);
-      const float4 y1 = *reinterpret_cast<const float4*>(&s_y[base + 4]);
-      y_n[0] = y0.x; y_n[1] = y0.y; y_n[2] = y0.z; y_n[3] = y0.w;
-      y_n[4] = y1.x; y_n[5] = y1.y; y_n[6] = y1.z; y_n[7] = y1.w;
-#pragma unroll
-      for (int s = 0; s < kWin; s += 2) {
-        const double2 d2 = *reinterpret_cast<const double2*>(&s_dl0[base + s]);
-        dl0_n[s] = d2.x;
-        dl0_n[s + 1] = d2.y;
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < kWin; s += 2) {
-      const double2 r2 = *reinterpret_cast<const double2*>(&s_rho[base + s]);
-      rho_n[s] = r2.x;
-      rho_n[s + 1] = r2.y;
+    for (int q = 0; q < NQ; ++q) st.rec[q] = *rec_at(slot, s, q);
+    st.c = s_c[base + s];
+    if constexpr (need_phi) st.phi = s_phi[base + s];
+    if constexpr (logistic) {
+      st.y = s_y[base + s];
+      st.dl0 = s_dl0[base + s];
     }
   };
-  load_draws(0);
+  constexpr int kAhead = logistic ? 1 : 2;  // (a step with exp in it is long enough for one, and needs the registers)
+  Step ahead[kAhead];
 
-  auto window = [&](int64_t t0, auto full_tag, auto reg_tag, auto fold_tag) __attribute__((always_inline)) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    constexpr bool REGW = decltype(reg_tag)::value;  // some step of the window may have c_lambda != 0
-    constexpr bool FOLD = decltype(fold_tag)::value;  // the records carry the whole of -h~
+  // x^T z of a step's row: the sum over the 16 lanes of a row of lanes, times 2^b
+  auto row_dot = [&](const int (&x)[UPL]) __attribute__((always_inline)) -> int {
+    int v;
+    if constexpr (UPL == 2) {
+      v = S::dot(x[1], zp[1], S::dot(x[0], zp[0]));
+    } else {
+      int p0 = S::dot(x[0], zp[0]), p1 = S::dot(x[1], zp[1]);
+#pragma unroll
+      for (int u = 2; u < UPL; u += 2) {
+        p0 = S::dot(x[u], zp[u], p0);
+        p1 = S::dot(x[u + 1], zp[u + 1], p1);
+      }
+      v = p0 + p1;
+    }
+    v += dpp_quad_swap1(v);
+    v += dpp_quad_swap2(v);
+    v += dpp_half_mirror(v);
+    v += dpp_row_mirror(v);
+    return v;
+  };
+  // scale * (the whole x^T z times 2^b) + add
+  auto whole_dot = [&](int row, double scale, double add) -> double {
+    if (LANES == 16) return __fma_rn((double)row, scale, add);
+    return __builtin_amdgcn_mfma_f64_4x4x4f64((double)row, scale, add, 0, 0, 0);
+  };
+  // l'(phi_i + x^T z) - l'(phi_i), in the fixed order
+  auto moved = [&](double D, float phi_s, float y_s, double dl0_s) -> double {
+    const double delta = __dmul_rn(dscale, D);
+    if constexpr (logistic) {
+      const double a1 = lp ? delta : __dadd_rn((double)phi_s, delta);
+      return __dadd_rn(logistic_dl(a1, (double)y_s), -dl0_s);  // l'(phi_i) comes with the draws
+    } else if constexpr (need_phi) {
+      return __dadd_rn(delta, -(double)phi_s);
+    } else {
+      return delta;
+    }
+  };
+  // A window in the fixed order of roundings, whatever it holds: `steps` of them, L2 draws among
+  // them or not.  For windows in which a fused step came too close to an integer, the last, partial
+  // window, and epochs whose scales the fused form does not cover.
+  auto window_fixed = [&](int64_t t0, int slot, int part, int steps, auto fold_tag) __attribute__((always_inline)) {
     const int base = (int)(t0 & kMask);
-    const int half = (int)((t0 >> 3) & 1);
-    double rho[kWin], dl08[kWin];
-    float phi8[kWin], y8[kWin];
-    int creg[kWin];
+#pragma unroll 1
+    for (int s = 0; s < steps; ++s) {
+      int4r r[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) r[q] = *rec_at(slot, s, q);
+      int x[UPL], cr[UPL];
+      split_record(r, x, cr);
+      const double D = whole_dot(row_dot(x), scale_one, 0.0);
+      const int k = base + s;
+      const double diff = moved(D, kMargins ? s_phi[kMargins ? k : 0] : 0.f, logistic ? s_y[logistic ? k : 0] : 0.f,
+                                logistic ? s_dl0[logistic ? k : 0] : 0.0);
+      const double beta = __dmul_rn(aB, diff);
+      const double rho = __dadd_rn(kDraw, -s_c[k]);  // exact
+      const double fl = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
+      int nf;
+      asm("v_cvt_i32_f64 %0, -%1" : "=v"(nf) : "v"(fl));  // saturates
+      const int ng = min(max(nf, -QMAX), -QMIN);
+      s_hi[part][s] = kMagicHi + min(max(nf, -(1 << 20)), 1 << 20);
+      const int cl = use_reg ? __builtin_amdgcn_readfirstlane(s_creg[k]) : 0;
+      n_reg += cl != 0 ? 1u : 0u;
+#pragma unroll
+      for (int u = 0; u < UPL; ++u)
+        zp[u] = cl == 0 ? step_strip(zp[u], x[u], ng, cr[u], hh[u], mask[u], fold_tag)
+                        : step_strip_reg(zp[u], x[u], ng, cl, cr[u], hh[u], mask[u], fold_tag, nullptr);
+    }
+  };
+
+  // A whole window of fused steps; false (and z as it was) where one of them came too close to an integer.
+  auto window = [&](int64_t t0, int slot, int part, auto reg_tag, auto fold_tag) __attribute__((always_inline)) -> bool {
+    constexpr bool REGW = decltype(reg_tag)::value;  // some step of the window may have c_lambda != 0
+    const int base = (int)(t0 & kMask);
+    const int next_base = (base + kWin) & kMask;  // (any window has its place in the ring, also past the end of the epoch)
+    int zsave[UPL];
+#pragma unroll
+    for (int u = 0; u < UPL; ++u) zsave[u] = zp[u];
+    unsigned int nr = 0;
+    uint32_t nearest = 0xFFFFFFFFu;  // the least of the window's low words
+    int hi_even = 0;
+    const int next_slot = (slot + 1) & (kSlots - 1);
 #pragma unroll
     for (int s = 0; s < kWin; ++s) {
-      dl08[s] = dl0_n[s];
-      rho[s] = rho_n[s];
-      phi8[s] = phi_n[s];
-      y8[s] = y_n[s];
-      creg[s] = 0;
-    }
-    if (REGW) {
-      const int4 c0 = *reinterpret_cast<const int4*>(&s_creg[base]);
-      const int4 c1 = *reinterpret_cast<const int4*>(&s_creg[base + 4]);
-      creg[0] = c0.x; creg[1] = c0.y; creg[2] = c0.z; creg[3] = c0.w;
-      creg[4] = c1.x; creg[5] = c1.y; creg[6] = c1.z; creg[7] = c1.w;
-    }
-    int4r rq[NQ];
+      const Step st = ahead[s % kAhead];
+      int x[UPL], cr[UPL];
+      split_record(st.rec, x, cr);
+      double t = need_phi ? whole_dot(row_dot(x), scale_one, 0.0) : whole_dot(row_dot(x), scale_t, st.c);
+      // (held in place: the scheduler would sink the reads to where their latency is not covered)
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + kAhead < kWin) load_step(ahead[s % kAhead], slot, base, s + kAhead);
+      else load_step(ahead[s % kAhead], next_slot, next_base, s + kAhead - kWin);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (need_phi) t = __fma_rn(moved(t, st.phi, st.y, st.dl0), -k2, st.c);
+      const uint64_t bits = __builtin_bit_cast(uint64_t, t);
+      const int hi = (int)(bits >> 32);
+      const uint32_t fr = (uint32_t)bits;
+      nearest = fr < nearest ? fr : nearest;
+      // monotone in t over the whole range of doubles, so the clamp of the word is the clamp of gamma
+      const int g = min(max(hi, kMagicHi - QMAX), kMagicHi - QMIN);
+      if (s & 1) *reinterpret_cast<int2r*>(&s_hi[part][s - 1]) = int2r{hi_even, hi};
+      else hi_even = hi;
+      int cl = 0;
+      if (REGW) {
+        cl = __builtin_amdgcn_readfirstlane((int)s_creg[base + s]);
+        nr += cl != 0 ? 1u : 0u;
+      }
+      if (!REGW || cl == 0) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) rq[q] = *rec_at(half, 0, q);
-    load_draws(t0 + kWin);  // (any window has its place in the ring, also past the end of the epoch)
+        for (int u = 0; u < UPL; ++u) zp[u] = step_strip(zp[u], x[u], g, cr[u], hh[u], mask[u], fold_tag);
+      } else {
 #pragma unroll
-    for (int s = 0; s < kWin; ++s) {
-      if (FULL || t0 + s < T) {
-        short2r xp[UPL], crp[UPL];
-#pragma unroll
-        for (int u = 0; u < UPL; ++u) {
-          // (element by value first: a bit cast applied to a vector's element reads element 0)
-          const int xv = rq[u / 4][u % 4], cv = rq[(UPL + u) / 4][(UPL + u) % 4];
-          xp[u] = __builtin_bit_cast(short2r, xv);
-          crp[u] = __builtin_bit_cast(short2r, cv);
-        }
-        if (s + 1 < kWin) {  // the next step's record, one step ahead
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) rq[q] = *rec_at(half, s + 1, q);
-        }
-        // low-precision dot product x_i^T z: one packed dot per strip, two accumulators
-        int p0 = 0, p1 = 0;
-#pragma unroll
-        for (int u = 0; u < UPL; u += 2) {
-          p0 = __builtin_amdgcn_sdot2(xp[u], zp[u], p0, false);
-          p1 = __builtin_amdgcn_sdot2(xp[u + 1], zp[u + 1], p1, false);
-        }
-        const int D = wave_sum_i32(p0 + p1);
-        // beta = alpha (l'(phi_i + x_i^T z) - l'(phi_i)), gamma = Q_(delta_s, b)(beta)
-        const double delta = __dmul_rn(dscale, (double)D);
-        double diff = delta;
-        if (logistic) {
-          const double a0 = (double)phi8[s], yi = (double)y8[s];
-          const double a1 = lp ? delta : __dadd_rn(a0, delta);
-          diff = __dadd_rn(logistic_dl(a1, yi), -dl08[s]);  // l'(phi_i) comes with the draws
-        } else if (need_phi) {
-          diff = __dadd_rn(delta, -(double)phi8[s]);
-        }
-        const double beta = __dmul_rn(aB, diff);
-        const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho[s]));
-        int nfv;
-        asm("v_cvt_i32_f64 %0, -%1" : "=v"(nfv) : "v"(f));
-        const int ng = min(max(nfv, -QMAX), -QMIN);
-        n_gclamp_v += (nfv != ng) ? 1u : 0u;  // the same in every lane
-        int cl = 0;
-        if (REGW) {
-          cl = __builtin_amdgcn_readfirstlane(creg[s]);
-          n_reg += cl != 0 ? 1u : 0u;
-        }
-        // u = z - gamma x - h~ (- c_lambda z), z = Q_(delta_m, b)(u)
-        if (!REGW || cl == 0) {
-          // Clamped coordinates are not looked for here (comparing the strips before and after the
-          // clamp costs 70 of 410 cycles per step at 4 strips per lane): the unclamped strips go to
-          // LDS in one store and the service wave counts a window later.
-          const short2r ngp = short2r{(short)ng, (short)ng};
-          int4r vq[NQV];
-#pragma unroll
-          for (int q = 0; q < NQV; ++q) vq[q] = int4r{0, 0, 0, 0};
-#pragma unroll
-          for (int u = 0; u < UPL; ++u) {
-            short2r v = xp[u] * ngp + crp[u];
-            if (FOLD) v = (v >> (short2r)(8)) + zp[u];
-            else v = (v >> (short2r)(8)) + (hhp[u] + zp[u]);  // the sum in brackets does not wait for gamma
-            vq[u / 4][u % 4] = __builtin_bit_cast(int, v);
-            zp[u] = __builtin_elementwise_min(__builtin_elementwise_max(v, (short2r)(QMIN)), (short2r)(QMAX));
-          }
-#pragma unroll
-          for (int q = 0; q < NQV; ++q) *vlog_at(half, s, q) = vq[q];
-        } else {
-          // a step with an L2 draw (rare): 32-bit arithmetic on the unpacked halves,
-          // -h~ + r = 256 hh + (hl + r); its clamps are counted here and its log entry is empty
-#pragma unroll
-          for (int q = 0; q < NQV; ++q) *vlog_at(half, s, q) = int4r{0, 0, 0, 0};
-#pragma unroll
-          for (int u = 0; u < UPL; ++u) {
-            int zn2[2];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const int zk = (int)zp[u][e], xk = (int)xp[u][e];
-              const int hr = FOLD ? (int)crp[u][e] : ((int)hhp[u][e] << 8) + (int)crp[u][e];
-              const int v = mad24(-cl, zk, mad24(ng, xk, hr));
-              const int zuk = zk + (v >> 8);
-              const int zc = min(max(zuk, QMIN), QMAX);
-              n_zclamp += (unsigned int)__builtin_popcountll(__ballot(zuk != zc));
-              zn2[e] = zc;
-            }
-            zp[u] = short2r{(short)zn2[0], (short)zn2[1]};
-          }
-        }
+        for (int u = 0; u < UPL; ++u)
+          zp[u] = step_strip_reg(zp[u], x[u], g - kMagicHi, cl, cr[u], hh[u], mask[u], fold_tag, nullptr);
       }
     }
+    if (__builtin_expect(__ballot(nearest <= 2 * kNear) != 0, 0)) {
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) zp[u] = zsave[u];
+      return false;
+    }
+    n_reg += nr;
+    return true;
   };
   // true if some step of the window at tt has an L2 draw (rare: alpha lambda 2^b is tiny)
   auto any_creg = [&](int64_t tt) -> bool {
     if (!use_reg) return false;
     const int base = (int)(tt & kMask);
-    const int4 c0 = *reinterpret_cast<const int4*>(&s_creg[base]);
-    const int4 c1 = *reinterpret_cast<const int4*>(&s_creg[base + 4]);
-    const int any = c0.x | c0.y | c0.z | c0.w | c1.x | c1.y | c1.z | c1.w;
+    const int4 c = *reinterpret_cast<const int4*>(&s_creg[base]);
+    const int any = c.x | c.y | c.z | c.w;
     return __builtin_amdgcn_readfirstlane(any) != 0;
   };
-  int64_t t0 = 0;
   auto run = [&](auto fold_tag) __attribute__((always_inline)) {
-    for (; t0 + kWin <= T; t0 += kWin) {
-      if (any_creg(t0)) window(t0, std::true_type{}, std::true_type{}, fold_tag);
-      else window(t0, std::true_type{}, std::false_type{}, fold_tag);
-      __syncthreads();  // window t0 / 8 is consumed, the records of the next one are in place
+    int slot = 0, part = 0;
+    int64_t t0 = 0;
+    auto next_window = [&]() {
+      // window t0 / 8 is consumed, the records of the one after the next are in place; nothing of this wave
+      // is waited for (what the service wave reads of it was stored a window ago: LDS answers in order, and
+      // reads behind those stores have been used by now)
+      asm volatile("s_barrier" ::: "memory");
+      slot = (slot + 1) & (kSlots - 1);
+      part = part == kHis - 1 ? 0 : part + 1;
+      t0 += kWin;
+    };
+    while (t0 < T) {
+      // Windows of fused steps without an L2 draw, in a loop of their own: the registers that the steps'
+      // records arrive in are carried round it, and a copy anywhere would wait for them
+      bool again = false;
+      if (fused_ok) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
+        while (t0 + kWin <= T && !any_creg(t0)) {
+          if (__builtin_expect(!window(t0, slot, part, std::false_type{}, fold_tag), 0)) {
+            again = true;
+            break;
+          }
+          next_window();
+        }
+      }
+      if (t0 >= T) break;
+      bool done = false;
+      if (fused_ok && !again && t0 + kWin <= T) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
+        done = window(t0, slot, part, std::true_type{}, fold_tag);
+      }
+      if (!done) window_fixed(t0, slot, part, (int)(T - t0 < kWin ? T - t0 : kWin), fold_tag);
+      next_window();
     }
-    if (t0 < T) {
-      if (use_reg) window(t0, std::false_type{}, std::true_type{}, fold_tag);
-      else window(t0, std::false_type{}, std::false_type{}, fold_tag);
-      __syncthreads();
-    }
+    __syncthreads();  // P2: the last gammas are in place
   };
   if (fold) run(std::true_type{});
   else run(std::false_type{});
@@ -558,37 +718,30 @@ __global__ __launch_bounds__(64 * waves_of(UPL), PAIR ? 4 : 2) void inner_reg_lo
 #pragma unroll
   for (int u = 0; u < UPL; ++u)
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int j = j0 + 2 * u + e;
-      if (j < d) {
-        const int zk = (int)zp[u][e];
+    for (int e = 0; e < CT; ++e) {
+      const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
+      if (lane < LANES && j < d) {
+        const int zk = S::value(zp[u], e) >> BITS;
         zg[j] = (int8_t)zk;
         const double step = __dmul_rn(delta_m, (double)zk);
         wg[j] = lp ? (float)step : (float)__dadd_rn((double)wg[j], step);  // Alg. 2: w~ = delta w
       }
     }
-  if (lane == 0) {
-    s_cnt[3] = n_zclamp;  // clamps of the steps with an L2 draw; the service wave puts the others into s_cnt[0]
-    s_cnt[1] = n_gclamp_v;
-    s_cnt[2] = n_reg;
-  }
+  if (lane == 0) s_cnt[2] = n_reg;  // the service wave has the other two
   __syncthreads();
-  if (tid < 4) cnt_out[tid] = tid == 0 ? s_cnt[0] + s_cnt[3] : (tid < 3 ? s_cnt[tid] : 0ull);
+  if (tid < 4) cnt_out[tid] = tid < 3 ? s_cnt[tid] : 0ull;
 }
 
-// the record ring (two windows of 8 steps, 8 UPL bytes per lane and step) and the log of
-// unclamped strips behind it (4 UPL bytes, 16 at least)
-constexpr size_t ring_bytes(int upl) {
-  return (size_t)2 * kWin * (upl / 2) * 64 * 16 + (size_t)2 * kWin * (upl >= 4 ? upl / 4 : 1) * 64 * 16;
-}
+// the record ring: windows of 8 steps, 8 UPL bytes per lane and step
+constexpr size_t ring_bytes(int upl, int lanes) { return (size_t)kSlots * kWin * upl * 8 * lanes; }
 
-template <int UPL, bool PAIR>
+template <int BITS, int UPL, int LANES, bool PAIR>
 int launch_one(const InArgs& a, int R, hipStream_t s) {
-  const dim3 grid(R), block(64 * waves_of(UPL));
-  const size_t smem = ring_bytes(UPL);
+  const dim3 grid(R), block(64 * waves_of(UPL, LANES));
 #define HALP_LONE(LOSS_)                                                                          \
   do {                                                                                            \
-    auto kern = inner_reg_lone_kernel<LOSS_, UPL, PAIR>;                                          \
+    auto kern = inner_reg_lone_kernel<BITS, LOSS_, UPL, LANES, PAIR>;                             \
+    const size_t smem = ring_bytes(UPL, LANES);                                     \
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                  \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) \
       return HALP_ERR_HIP;                                                                        \
