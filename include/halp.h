@@ -206,8 +206,9 @@ typedef struct {
                                     form with ONE chain wave that holds all of z and helper
                                     waves on the other SIMDs of the CU, for rows up to
                                     1024 coordinates (HALP_ERR_UNSUPPORTED elsewhere); 0 takes
-                                    it up to one chain per CU for any of these rows, two for up
-                                    to 512 coordinates, three to six for up to 256.  Results do not
+                                    it, and its 16-bit twin for rows up to 512 coordinates, up
+                                    to one chain per CU, two for up to 256 strips of 16 rounding
+                                    bits, three to six for up to 128.  Results do not
                                     depend on it                                              */
 
 #define HALP_OPT_EXCHANGE_POLL_DELAY 11 /* split minibatch loop: sleeps of 256 cycles between a

@@ -10,6 +10,7 @@ int launch_inner_reg_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s)
 int launch_inner_reg_helped_b8(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_helped_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_lone_b8(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
+int launch_inner_reg_lone_b16(const InArgs& a, int upl, int R, bool pair, hipStream_t s);
 
 namespace {
 
@@ -54,16 +55,19 @@ bool helped_shape(Shape sh) { return (sh.nw == 2 || sh.nw == 4) && sh.upl <= 2; 
 // 6.0 at 1280 against 4.8 and 7.6 -- beyond that one wave per chain and no helpers)
 constexpr int kHelpedChainsPerCu4 = 2, kHelpedChainsPerCu2 = 5;
 
-// Strips per lane and lanes of the form with one chain wave and its helpers on the other SIMDs (8
-// bits, rows up to 1024 coordinates); upl 0 if the shape does not fit it.
+// Strips per lane and lanes of the form with one chain wave and its helpers on the other SIMDs (rows
+// of up to 512 strips: 1024 coordinates at 8 bits, 512 at 16); upl 0 if the shape does not fit it.
+// 16 lanes at 8 bits and up to 32 strips: 71 ns per step with two strips per lane; with four, for up to 64
+// strips, 93 against the 78 of two strips on 64 lanes.
 struct Lone {
   int upl, lanes;
 };
 Lone lone_shape(const halp_handle& h) {
   const halp_params& p = h.p;
-  if (p.b != 8 || p.B != 1 || p.K != 1) return Lone{0, 0};
-  const int U = (p.d + 1) / 2;
-  if (U <= 32) return Lone{2, 16};
+  if (p.B != 1 || p.K != 1) return Lone{0, 0};
+  const int U = p.b == 8 ? (p.d + 1) / 2 : p.d;
+  if (p.b == 8 && U <= 32) return Lone{2, 16};
+  if (p.b == 16 && U <= 64) return Lone{1, 64};
   return Lone{U <= 128 ? 2 : (U <= 256 ? 4 : (U <= 512 ? 8 : 0)), 64};
 }
 
@@ -76,10 +80,12 @@ Lone lone_shape(const halp_handle& h) {
 //   d = 1024  256: 159 / 237, 300 would take two turns
 // and logistic: d = 64 1024: 216 / 255, 1200: 364 / 396; d = 256 1024: 410 / 442; d = 512 512: 246 / 340;
 // d = 1024 256: 277 / 350.
+// 16 bits: d = 64 512: 90 / 162, 1024: 98 / 160, 1536: 171 / 224; d = 128 768: 122 / 213, 1536: 210 / 267; d = 256
+// 512: 143 / 259; d = 512 256: 207 / 240; logistic d = 64 1024: 218 / 258, d = 128 1024: 425 / 481, d = 512 256: 312 / 347.
 bool lone_pays(const halp_handle& h, Lone sh) {
   const bool logistic = h.p.loss == HALP_LOSS_LOGISTIC;
   int64_t per_cu = 1;
-  if (sh.upl == 2) per_cu = h.p.d > 64 && h.p.d <= 128 ? 3 : (logistic ? 4 : 6);
+  if (sh.upl <= 2) per_cu = h.p.b == 8 && h.p.d > 64 && h.p.d <= 128 ? 3 : (logistic ? 4 : 6);
   else if (sh.upl == 4) per_cu = 2;
   return (int64_t)h.p.R <= per_cu * h.num_cus;
 }
@@ -120,10 +126,13 @@ int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   int rc = inner_reg_supported(p);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  // 8 bits, few chains per CU: one chain wave with all of z, helpers on the other SIMDs
+  // few chains per CU: one chain wave with all of z, helpers on the other SIMDs
   const Lone lone = lone_shape(h);
-  if (lone.upl > 0 && (h.inner_helpers == 3 || (h.inner_helpers == 0 && h.inner_waves == 0 && lone_pays(h, lone))))
+  const bool lone_forced = h.inner_helpers == 3 && p.b == 8;
+  if (lone.upl > 0 && (lone_forced || (h.inner_helpers == 0 && h.inner_waves == 0 && lone_pays(h, lone)))) {
+    if (p.b == 16) return launch_inner_reg_lone_b16(a, lone.upl, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);
     return launch_inner_reg_lone_b8(a, lone.upl, lone.lanes, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);  // more chains than CUs: the build with at most 128 registers
+  }
   if (h.inner_helpers == 3) return HALP_ERR_UNSUPPORTED;
   Shape sh = pick_shape(p, auto_waves(h));
   const int ct = 16 / p.b;

@@ -5,7 +5,8 @@
 // With a chain to itself a CU is bound by the step's dependent chain; a dependent vector
 // instruction of a lone wave takes 8 cycles, an LDS round trip 66, so the chain wave is written
 // for the fewest dependent instructions:
-//   dot     one packed dot per strip (8 bits: two coordinates), DPP fold over 16 lanes.  Rows that
+//   dot     one packed dot per strip (8 bits: two coordinates; at 16 bits one, multiplied and cut into
+//           low 16 bits and the rest), DPP fold over 16 lanes.  Rows that
 //           16 lanes hold (LANES = 16: the four rows of a wave do the same work) are done there;
 //           wider rows are added up across the four rows of 16 lanes by one fp64 4x4x4 matrix
 //           instruction (28 cycles; two row broadcasts and a lane read take 45), which multiplies
@@ -38,7 +39,7 @@
 // The chain wave is wave 0; the helpers and the service wave are placed on the other three
 // SIMDs (waves w and w + 4 of a workgroup share a SIMD: wave 4 only keeps the barriers).
 //
-// This header holds the kernel template, inner_reg_lone_b8.hip instantiates it.
+// This header holds the kernel template, inner_reg_lone_b8.hip and inner_reg_lone_b16.hip instantiate it.
 #pragma once
 
 #include "inner_reg_impl.hpp"
@@ -61,7 +62,7 @@ template <int LOSS>
 constexpr bool logistic_c = LOSS == HALP_LOSS_LOGISTIC;
 
 // waves of a workgroup: chain, helpers, the service wave, and wave 4 kept idle when there is one
-constexpr int waves_of(int upl, int lanes) { return lanes == 16 ? 3 : (upl == 2 ? 4 : 7); }
+constexpr int waves_of(int upl, int lanes) { return lanes == 16 || upl == 1 ? 3 : (upl == 2 ? 4 : 7); }
 
 constexpr int kSlots = 4;  // windows of records in the ring
 constexpr int kSets = 4;   // windows of row fragments a helper has in flight
@@ -88,8 +89,11 @@ struct Strip;
 template <>
 struct Strip<8> {
   static constexpr int CT = 2;
+  using Z = int8_t;
+  using H = int16_t;
   static constexpr int kMask = (int)0xFF00FF00;
-  // n = -gamma x + c; g: the low half is -gamma
+  static constexpr int kSmallLow = -64, kSmallHigh = 62;  // high parts of -h~ that may ride in the records
+  // n = -gamma x + c; g: kMagicHi - gamma, whose low half is -gamma
   static __device__ __forceinline__ int mad(int x, int g, int c) {
     const short2r gp = short2r{(short)g, (short)g};
     return __builtin_bit_cast(int, __builtin_bit_cast(short2r, x) * gp + __builtin_bit_cast(short2r, c));
@@ -128,19 +132,60 @@ struct Strip<8> {
     asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "v"(z));
     return r;
   }
+  // the row value and the addend of a record from the strip's two bytes (at `at` bytes into a fragment) and
+  // the 16 rounding bits of step s; add: what the record adds to them
+  static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t word, int s, int add, int* x, int* c) {
+    // the bytes go to the high bytes of the halves and come back down with their signs
+    const uint32_t up = __builtin_amdgcn_perm(0u, frag, at ? 0x030C020Cu : 0x010C000Cu);
+    const uint32_t rp = __builtin_amdgcn_perm(0u, word, (s & 1) ? 0x0C030C02u : 0x0C010C00u);
+    *x = __builtin_bit_cast(int, __builtin_bit_cast(short2r, up) >> (short2r)(8));
+    *c = __builtin_bit_cast(int, __builtin_bit_cast(short2r, rp) + __builtin_bit_cast(short2r, add));
+  }
+  static __device__ __forceinline__ int addend(int c, int /*x*/) { return c; }  // r - h~ (r + hl) of a record
   static __device__ __forceinline__ int value(int v, int e) { return e ? v >> 16 : (int)(short)v; }
   static __device__ __forceinline__ int join(int a, int b) { return (a & 0xFFFF) | (b << 16); }
+};
+
+template <>
+struct Strip<16> {
+  static constexpr int CT = 1;
+  using Z = int16_t;
+  using H = int32_t;
+  static constexpr int kMask = (int)0xFFFF0000;
+  static constexpr int kSmallLow = -16000, kSmallHigh = 16000;
+  // The 24-bit multiplier takes g = kMagicHi - gamma as it is, i.e. kOffset - gamma; the records carry
+  // c - kOffset x, and everything is exact modulo 2^32, where n lies.
+  static constexpr int kOffset = kMagicHi & 0xFFFFFF;
+  static __device__ __forceinline__ int mad(int x, int g, int c) { return mad24(g, x, c); }
+  static __device__ __forceinline__ int add_sat(int z, int n) { return __builtin_elementwise_add_sat(z, n); }
+  static __device__ __forceinline__ int add(int z, int n) { return (int)((uint32_t)z + (uint32_t)n); }
+  static __device__ __forceinline__ int shifted(int n, int k) { return (n >> 16) + k; }
+  static __device__ __forceinline__ int high(int z) { return z >> 16; }
+  static __device__ __forceinline__ int clamp_up(int v) { return min(max(v, -32768), 32767) << 16; }
+  static __device__ __forceinline__ int outside(int v) { return (uint32_t)(v + 32768) > 65535u ? 1 : 0; }
+  static __device__ __forceinline__ int clamped(int sat, int wrapped) { return (int)((uint32_t)(sat ^ wrapped) >> 31); }
+  static __device__ __forceinline__ unsigned int counted(int acc) { return (unsigned int)acc; }
+  static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t word, int s, int add, int* x, int* c) {
+    *x = at ? (int)frag >> 16 : (int)(short)frag;
+    *c = mad24(*x, -kOffset, (int)((s & 1) ? word >> 16 : word & 0xFFFFu) + add);
+  }
+  static __device__ __forceinline__ int addend(int c, int x) { return mad24(x, kOffset, c); }
+  static __device__ __forceinline__ int value(int v, int) { return v; }
+  static __device__ __forceinline__ int join(int a, int) { return a; }
 };
 
 // LANES: lanes that share a row of z, 64 or 16 (four copies of the same work in a wave).
 // PAIR: built for several workgroups per CU (more chains than CUs), at most 128 registers per lane.
 template <int BITS, int LOSS, int UPL, int LANES, bool PAIR>
 __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner_reg_lone_kernel(InArgs a) {
-  static_assert(BITS == 8, "8 bits");
-  static_assert(UPL == 2 || (LANES == 64 && (UPL == 4 || UPL == 8)), "two, four or eight strips per lane");
+  static_assert((UPL == 2 && (LANES == 64 || BITS == 8)) || (LANES == 64 && (UPL == 4 || UPL == 8 || (UPL == 1 && BITS == 16))), "the forms that are launched");
   using S = Strip<BITS>;
   constexpr int CT = S::CT;
-  constexpr int NQ = UPL / 2;           // 16-byte quads of a record: UPL row values, then UPL of r - h~
+  constexpr int NQ = UPL > 1 ? UPL / 2 : 1;  // vectors of a record: UPL row values, then UPL of r - h~
+  constexpr int QW = UPL > 1 ? 4 : 2;        // dwords of one
+  using RecV = typename std::conditional<UPL == 1, int2r, int4r>::type;
+  using ZT = typename S::Z;
+  using HT = typename S::H;
   constexpr int QMAX = (1 << (BITS - 1)) - 1, QMIN = -(1 << (BITS - 1));
   constexpr int kMask = 2 * kBatch - 1;
   const int chain = blockIdx.x;
@@ -150,14 +195,14 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   // Roles by wave.  Waves w and w + 4 share a SIMD and wave 0 is the chain wave, so wave 4 only
   // keeps the barriers.  The service wave has a SIMD to itself where the row is wide (counting
   // the clamps of a strip takes about as long as serving it): 16 lanes: wave 1 serves every strip,
-  // wave 2 is the service wave.  2 strips per lane: waves 1, 2 one strip each, service wave 3.  4 and 8: waves
+  // wave 2 is the service wave, and so with one strip per lane.  2: waves 1, 2 one strip each, service wave 3.  4 and 8: waves
   // 1, 2, 5, 6 one or two strips each, service wave 3.
   constexpr int kStripsHere = UPL == 8 ? 2 : 1;  // of a lane, served by a helper
   int first_strip = -1;
-  if (LANES == 16) first_strip = wave == 1 ? 0 : -1;
+  if (LANES == 16 || UPL == 1) first_strip = wave == 1 ? 0 : -1;
   else if (wave == 1 || wave == 2) first_strip = kStripsHere * (wave - 1);
   else if (UPL >= 4 && (wave == 5 || wave == 6)) first_strip = kStripsHere * (wave - 3);
-  const bool is_service = wave == (LANES == 16 ? 2 : 3);
+  const bool is_service = wave == (LANES == 16 || UPL == 1 ? 2 : 3);
   const int d = a.d;
   const int U = (d + CT - 1) / CT;  // strips in a row
   const uint32_t N = (uint32_t)a.N;
@@ -167,8 +212,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   const float* __restrict__ phi = a.phi + (int64_t)chain * a.N;
   const float* __restrict__ y =
       reinterpret_cast<const float*>(a.y) + (int64_t)chain * a.y_chain_stride;
-  const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + (int64_t)chain * d;
-  int8_t* __restrict__ zg = reinterpret_cast<int8_t*>(a.z) + (int64_t)chain * d;
+  const HT* __restrict__ hg = reinterpret_cast<const HT*>(a.h) + (int64_t)chain * d;
+  ZT* __restrict__ zg = reinterpret_cast<ZT*>(a.z) + (int64_t)chain * d;
   float* __restrict__ wg = a.w + (int64_t)chain * d;
   const double* sc = a.scales + (int64_t)chain * 8;
   uint64_t* cnt_out = a.counters + (int64_t)chain * 4;
@@ -192,16 +237,16 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   __shared__ __attribute__((aligned(16))) int s_hi[kHis][kWin];  // kMagicHi - gamma of the steps, before the clamp
   __shared__ unsigned long long s_cnt[4];
   __shared__ int s_fold;  // 1: the whole of -h~ rides in the records (set by the chain wave before the first barrier)
-  // records: [slot of the ring][step of the window][quad][lane], 16 bytes each
-  extern __shared__ __attribute__((aligned(16))) int4r s_rec[];
-  auto rec_at = [&](int slot, int s, int q) -> const int4r* {
-    return s_rec + ((slot * kWin + s) * NQ + q) * LANES + (lane & (LANES - 1));
+  // records: [slot of the ring][step of the window][vector][lane]
+  extern __shared__ __attribute__((aligned(16))) int s_rec[];
+  auto rec_at = [&](int slot, int s, int q) -> const RecV* {
+    return reinterpret_cast<const RecV*>(s_rec) + ((slot * kWin + s) * NQ + q) * LANES + (lane & (LANES - 1));
   };
-  auto split_record = [&](const int4r (&r)[NQ], int (&x)[UPL], int (&cr)[UPL]) __attribute__((always_inline)) {
+  auto split_record = [&](const RecV (&r)[NQ], int (&x)[UPL], int (&cr)[UPL]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      x[u] = r[u / 4][u % 4];
-      cr[u] = r[(UPL + u) / 4][(UPL + u) % 4];
+      x[u] = r[u / QW][u % QW];
+      cr[u] = r[(UPL + u) / QW][(UPL + u) % QW];
     }
   };
 
@@ -217,21 +262,21 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   if (tid < 4) s_cnt[tid] = 0;
 
   // z of a lane's strips times 2^b, the coordinates that exist, and the high part of -h~; true where every
-  // high part is small.  With -h~ = 2^b hh + hl, 0 <= hl < 2^b, and every hh in [-64, 62] (8 bits),
-  // n = -gamma x + r - h~ fits its word (|gamma x| <= 2^14, 0 <= r < 256).
+  // high part is small.  With -h~ = 2^b hh + hl, 0 <= hl < 2^b, and every hh in [-64, 62] (16 bits: [-16000, 16000]),
+  // n = -gamma x + r - h~ fits its word of 2 b bits (|gamma x| <= 2^(2b-2), 0 <= r < 2^b).
   auto load_z = [&](int (&zp)[UPL], int (&mask)[UPL], int (&hh)[UPL]) -> bool {
     bool small = true;
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      int zv[2], mv[2], hv[2];
+      int zv[2] = {0, 0}, mv[2] = {0, 0}, hv[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < CT; ++e) {
         const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
         const bool ok = j < d;
         zv[e] = ok ? (int)zg[ok ? j : 0] << BITS : 0;
         mv[e] = ok ? S::kMask : 0;
-        hv[e] = ok ? (-(int)hg[ok ? j : 0]) >> BITS : 0;
-        small = small && hv[e] >= -64 && hv[e] <= 62;
+        hv[e] = ok ? (int)((-(int64_t)hg[ok ? j : 0]) >> BITS) : 0;
+        small = small && hv[e] >= S::kSmallLow && hv[e] <= S::kSmallHigh;
       }
       zp[u] = S::join(zv[0], zv[1]);
       mask[u] = S::join(mv[0], mv[1]);
@@ -239,23 +284,24 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     }
     return small;
   };
-  // z <- Q(z - gamma x - h~) of a strip; g: -gamma.  fold: c holds r - h~, else r + hl
+  // z <- Q(z - gamma x - h~) of a strip; g: kMagicHi - gamma.  fold: c holds r - h~, else r + hl
   auto step_strip = [&](int z, int x, int g, int c, int hh, int mask, auto fold_tag) __attribute__((always_inline)) -> int {
     const int n = S::mad(x, g, c);
     if constexpr (decltype(fold_tag)::value) return S::add_sat(z, n) & mask;
     else return S::clamp_up(S::shifted(n, S::add(hh, S::high(z)))) & mask;
   };
-  // the same of a step with an L2 draw (rare), in wide arithmetic on the coordinates
+  // the same of a step with an L2 draw (rare), in wide arithmetic on the coordinates; g here is -gamma itself
   auto step_strip_reg = [&](int z, int x, int g, int cl, int c, int hh, int mask, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
     int zn[2] = {0, 0};
+    const int cc = S::addend(c, x);
 #pragma unroll
     for (int e = 0; e < CT; ++e) {
-      const int zk = S::value(z, e) >> BITS, xk = S::value(x, e);
-      const int hr = (decltype(fold_tag)::value ? 0 : S::value(hh, e) << BITS) + S::value(c, e);
-      const int zuk = zk + (mad24(-cl, zk, mad24(g, xk, hr)) >> BITS);
-      const int zc = min(max(zuk, QMIN), QMAX);
+      const int64_t zk = S::value(z, e) >> BITS, xk = S::value(x, e);
+      const int64_t hr = (decltype(fold_tag)::value ? 0 : (int64_t)S::value(hh, e) << BITS) + S::value(cc, e);
+      const int64_t zuk = zk + ((g * xk - cl * zk + hr) >> BITS);
+      const int64_t zc = zuk < QMIN ? QMIN : (zuk > QMAX ? QMAX : zuk);
       if (clamped) *clamped += (S::value(mask, e) != 0 && zuk != zc) ? 1 : 0;
-      zn[e] = zc << BITS;
+      zn[e] = (int)zc << BITS;
     }
     return S::join(zn[0], zn[1]) & mask;
   };
@@ -310,7 +356,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     // and gone through in period w + 2, when the chain wave's stores have landed for certain.
     unsigned int n_lane = 0;    // this lane's count of clamped coordinates
     unsigned int n_gclamp = 0;  // clamped gammas
-    int4r r[kWin][NQ];
+    RecV r[kWin][NQ];
     auto take = [&](int64_t w) __attribute__((always_inline)) {
 #pragma unroll
       for (int s = 0; s < kWin; ++s)
@@ -390,21 +436,21 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const int g0 = LANES == 16 ? lane & (16 * UPL - 1) : 64 * first_strip + SPH * lane;  // the first of them in the row
       const int owner = LANES == 16 ? g0 & 15 : lane;
       const int u0 = LANES == 16 ? g0 >> 4 : first_strip;
-      short2r hlp[SPH];                         // what a record adds to the rounding bytes: the low byte of
-      short2r hfp[SPH];                         // -h~, or the whole of it where every -h~ / 256 is small
+      int hlp[SPH];  // what a record adds to the rounding bits: the low b bits of -h~, or the whole of it
+      int hfp[SPH];  // where every -h~ / 2^b is small
 #pragma unroll
       for (int i = 0; i < SPH; ++i) {
-        int hl[2], hf[2];
+        int hl[2] = {0, 0}, hf[2] = {0, 0};
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int j = 2 * (g0 + i) + e;
+        for (int e = 0; e < CT; ++e) {
+          const int j = CT * (g0 + i) + e;
           const bool ok = j < d;
-          const int hneg = ok ? -(int)hg[ok ? j : 0] : 0;
-          hl[e] = hneg & 0xFF;
-          hf[e] = hneg;
+          const int64_t hneg = ok ? -(int64_t)hg[ok ? j : 0] : 0;
+          hl[e] = (int)(hneg & ((1 << BITS) - 1));
+          hf[e] = (int)hneg;
         }
-        hlp[i] = short2r{(short)hl[0], (short)hl[1]};
-        hfp[i] = short2r{(short)hf[0], (short)hf[1]};
+        hlp[i] = S::join(hl[0], hl[1]);
+        hfp[i] = S::join(hf[0], hf[1]);
       }
       // The rows of a window: its eight sample indices in two LDS reads (every entry of the index ring is
       // a valid row at any time, so windows past the end of the epoch fetch rows that are never used),
@@ -428,27 +474,18 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 #pragma unroll
         for (int i = 0; i < SPH; ++i) zn[i] = zround_block(seed, a.epoch, (uint32_t)(g0 + i), (uint32_t)win);
       };
-      int* const rec = reinterpret_cast<int*>(s_rec) + 4 * owner;
+      int* const rec = s_rec + QW * owner;
+      constexpr int kStep = NQ * LANES * QW;  // dwords of a step's records
       // the records of a window into a slot of the ring
       auto make_window = [&](const uint32_t (&fr)[kWin], int slot) {
-        int* const at = rec + slot * (kWin * NQ * LANES * 4);
-        int* const xw = at + (u0 / 4) * (4 * LANES) + u0 % 4;
-        int* const cw = at + ((UPL + u0) / 4) * (4 * LANES) + (UPL + u0) % 4;
+        int* const at = rec + slot * (kWin * kStep);
+        int* const xw = at + (u0 / QW) * (QW * LANES) + u0 % QW;
+        int* const cw = at + ((UPL + u0) / QW) * (QW * LANES) + (UPL + u0) % QW;
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
-          const uint32_t fv = fr[s];
 #pragma unroll
-          for (int i = 0; i < SPH; ++i) {
-            // the strip's two bytes go to the high bytes of the halves and come back down with their
-            // signs (bytes past the row's end are kept out of z by the chain wave)
-            const uint32_t up = __builtin_amdgcn_perm(0u, fv, i ? 0x030C020Cu : 0x010C000Cu);
-            const short2r xp = __builtin_bit_cast(short2r, up) >> (short2r)(8);
-            const uint32_t word = pick(zn[i], (uint32_t)(s >> 1));
-            const uint32_t rp = __builtin_amdgcn_perm(0u, word, (s & 1) ? 0x0C030C02u : 0x0C010C00u);
-            const short2r crp = __builtin_bit_cast(short2r, rp) + hlp[i];
-            xw[s * (NQ * LANES * 4) + i] = __builtin_bit_cast(int, xp);
-            cw[s * (NQ * LANES * 4) + i] = __builtin_bit_cast(int, crp);
-          }
+          for (int i = 0; i < SPH; ++i)  // (what lies past the row's end is kept out of z by the chain wave)
+            S::record(fr[s], i, pick(zn[i], (uint32_t)(s >> 1)), s, hlp[i], &xw[s * kStep + i], &cw[s * kStep + i]);
         }
       };
       __syncthreads();  // P0: the first two batches are in place
@@ -509,13 +546,14 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   const bool hh_small = load_z(zp, mask, hh);
   const bool fold = __ballot(!hh_small) == 0;  // uniform
   if (lane == 0) s_fold = fold ? 1 : 0;
-  // The fused form stands for the fixed order of roundings while nothing underflows on the way and
-  // no partial sum of the matrix instruction is so large that its last place matters (|t| <= 2^22).
+  // The fused form stands for the fixed order of roundings while nothing underflows on the way.  `direct`: and
+  // no partial sum of the matrix instruction is so large that its last place matters (|t| <= 2^22), so that it
+  // may do the multiply-add too; else it adds up the whole number x^T z, and the multiply-add follows.
   const double k2 = __dmul_rn(aB, inv_s), k1 = __dmul_rn(dscale, k2);
   auto normal = [](double v) { return v > 1e-200 && v < 1e200; };
-  const bool fused_ok = normal(dscale) && normal(aB) && normal(__dmul_rn(dscale, aB)) && normal(inv_s) && normal(k2) && normal(k1) &&
-                        (LANES == 16 || k1 * (double)d * (double)(1 << (2 * BITS - 2)) < 0x1p22);
-  const double scale_one = 1.0 / (double)(1 << BITS);         // the dot is with 2^b z
+  const bool fused_ok = normal(dscale) && normal(aB) && normal(__dmul_rn(dscale, aB)) && normal(inv_s) && normal(k2) && normal(k1);
+  const bool direct = LANES == 16 || k1 * (double)d * (double)(1 << (2 * BITS - 2)) < 0x1p22;
+  const double scale_one = BITS == 8 ? 0x1p-8 : 1.0;  // at 8 bits the dot is with 2^8 z
   const double scale_t = -k1 * scale_one;
   unsigned int n_reg = 0;  // steps with an L2 draw
   __syncthreads();  // P0
@@ -524,7 +562,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 
   // what a step needs from LDS, requested kAhead steps ahead: its record and its step-indexed draws
   struct Step {
-    int4r rec[NQ];
+    RecV rec[NQ];
     double c, dl0;
     float phi, y;
   };
@@ -541,30 +579,55 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   constexpr int kAhead = logistic ? 1 : 2;  // (a step with exp in it is long enough for one, and needs the registers)
   Step ahead[kAhead];
 
-  // x^T z of a step's row: the sum over the 16 lanes of a row of lanes, times 2^b
-  auto row_dot = [&](const int (&x)[UPL]) __attribute__((always_inline)) -> int {
-    int v;
-    if constexpr (UPL == 2) {
-      v = S::dot(x[1], zp[1], S::dot(x[0], zp[0]));
-    } else {
-      int p0 = S::dot(x[0], zp[0]), p1 = S::dot(x[1], zp[1]);
-#pragma unroll
-      for (int u = 2; u < UPL; u += 2) {
-        p0 = S::dot(x[u], zp[u], p0);
-        p1 = S::dot(x[u + 1], zp[u + 1], p1);
-      }
-      v = p0 + p1;
-    }
+  // x^T z of a step's row: the sum over the 16 lanes of a row of lanes, divided by scale_one
+  auto fold16 = [](int v) {
     v += dpp_quad_swap1(v);
     v += dpp_quad_swap2(v);
     v += dpp_half_mirror(v);
     v += dpp_row_mirror(v);
     return v;
   };
+  auto row_dot = [&](const int (&x)[UPL]) __attribute__((always_inline)) -> double {
+    if constexpr (BITS == 8) {
+      int v;
+      if constexpr (UPL == 2) {
+        v = S::dot(x[1], zp[1], S::dot(x[0], zp[0]));
+      } else {
+        int p0 = S::dot(x[0], zp[0]), p1 = S::dot(x[1], zp[1]);
+#pragma unroll
+        for (int u = 2; u < UPL; u += 2) {
+          p0 = S::dot(x[u], zp[u], p0);
+          p1 = S::dot(x[u + 1], zp[u + 1], p1);
+        }
+        v = p0 + p1;
+      }
+      return (double)fold16(v);
+    } else {
+      // products, or sums of two less 2^16, fit 32 bits; each is cut into its low 16 bits and the rest, and the
+      // two kinds are folded apart (the instructions of one fill the wait states of the other)
+      int lo = 0, hi = 0;
+      if constexpr (UPL == 1) {
+        const int p = mad24(x[0], zp[0] >> 16, 0);
+        lo = p & 0xFFFF;
+        hi = p >> 16;
+      } else {
+        hi = UPL / 2;
+#pragma unroll
+        for (int u = 0; u < UPL; u += 2) {
+          const int p = mad24(x[u], zp[u] >> 16, mad24(x[u + 1], zp[u + 1] >> 16, -65536));
+          lo += p & 0xFFFF;
+          hi += p >> 16;
+        }
+      }
+      lo = fold16(lo);
+      hi = fold16(hi);
+      return __fma_rn((double)hi, 65536.0, (double)lo);
+    }
+  };
   // scale * (the whole x^T z times 2^b) + add
-  auto whole_dot = [&](int row, double scale, double add) -> double {
-    if (LANES == 16) return __fma_rn((double)row, scale, add);
-    return __builtin_amdgcn_mfma_f64_4x4x4f64((double)row, scale, add, 0, 0, 0);
+  auto whole_dot = [&](double row, double scale, double add) -> double {
+    if (LANES == 16) return __fma_rn(row, scale, add);
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(row, scale, add, 0, 0, 0);
   };
   // l'(phi_i + x^T z) - l'(phi_i), in the fixed order
   auto moved = [&](double D, float phi_s, float y_s, double dl0_s) -> double {
@@ -585,7 +648,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     const int base = (int)(t0 & kMask);
 #pragma unroll 1
     for (int s = 0; s < steps; ++s) {
-      int4r r[NQ];
+      RecV r[NQ];
 #pragma unroll
       for (int q = 0; q < NQ; ++q) r[q] = *rec_at(slot, s, q);
       int x[UPL], cr[UPL];
@@ -605,13 +668,13 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       n_reg += cl != 0 ? 1u : 0u;
 #pragma unroll
       for (int u = 0; u < UPL; ++u)
-        zp[u] = cl == 0 ? step_strip(zp[u], x[u], ng, cr[u], hh[u], mask[u], fold_tag)
+        zp[u] = cl == 0 ? step_strip(zp[u], x[u], kMagicHi + ng, cr[u], hh[u], mask[u], fold_tag)
                         : step_strip_reg(zp[u], x[u], ng, cl, cr[u], hh[u], mask[u], fold_tag, nullptr);
     }
   };
 
   // A whole window of fused steps; false (and z as it was) where one of them came too close to an integer.
-  auto window = [&](int64_t t0, int slot, int part, auto reg_tag, auto fold_tag) __attribute__((always_inline)) -> bool {
+  auto window = [&](int64_t t0, int slot, int part, auto reg_tag, auto fold_tag, auto direct_tag) __attribute__((always_inline)) -> bool {
     constexpr bool REGW = decltype(reg_tag)::value;  // some step of the window may have c_lambda != 0
     const int base = (int)(t0 & kMask);
     const int next_base = (base + kWin) & kMask;  // (any window has its place in the ring, also past the end of the epoch)
@@ -627,13 +690,15 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const Step st = ahead[s % kAhead];
       int x[UPL], cr[UPL];
       split_record(st.rec, x, cr);
-      double t = need_phi ? whole_dot(row_dot(x), scale_one, 0.0) : whole_dot(row_dot(x), scale_t, st.c);
+      constexpr bool DIRECT = decltype(direct_tag)::value && !need_phi;
+      double t = DIRECT ? whole_dot(row_dot(x), scale_t, st.c) : whole_dot(row_dot(x), scale_one, 0.0);
       // (held in place: the scheduler would sink the reads to where their latency is not covered)
       __builtin_amdgcn_sched_barrier(0);
       if (s + kAhead < kWin) load_step(ahead[s % kAhead], slot, base, s + kAhead);
       else load_step(ahead[s % kAhead], next_slot, next_base, s + kAhead - kWin);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (need_phi) t = __fma_rn(moved(t, st.phi, st.y, st.dl0), -k2, st.c);
+      else if constexpr (!DIRECT) t = __fma_rn(t, -k1, st.c);
       const uint64_t bits = __builtin_bit_cast(uint64_t, t);
       const int hi = (int)(bits >> 32);
       const uint32_t fr = (uint32_t)bits;
@@ -672,7 +737,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     const int any = c.x | c.y | c.z | c.w;
     return __builtin_amdgcn_readfirstlane(any) != 0;
   };
-  auto run = [&](auto fold_tag) __attribute__((always_inline)) {
+  auto run = [&](auto fold_tag, auto direct_tag) __attribute__((always_inline)) {
     int slot = 0, part = 0;
     int64_t t0 = 0;
     auto next_window = [&]() {
@@ -692,7 +757,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
         while (t0 + kWin <= T && !any_creg(t0)) {
-          if (__builtin_expect(!window(t0, slot, part, std::false_type{}, fold_tag), 0)) {
+          if (__builtin_expect(!window(t0, slot, part, std::false_type{}, fold_tag, direct_tag), 0)) {
             again = true;
             break;
           }
@@ -704,15 +769,16 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       if (fused_ok && !again && t0 + kWin <= T) {
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
-        done = window(t0, slot, part, std::true_type{}, fold_tag);
+        done = window(t0, slot, part, std::true_type{}, fold_tag, std::false_type{});
       }
       if (!done) window_fixed(t0, slot, part, (int)(T - t0 < kWin ? T - t0 : kWin), fold_tag);
       next_window();
     }
     __syncthreads();  // P2: the last gammas are in place
   };
-  if (fold) run(std::true_type{});
-  else run(std::false_type{});
+  if (!fold) run(std::false_type{}, std::false_type{});
+  else if (direct && !need_phi) run(std::true_type{}, std::bool_constant<!need_phi>{});
+  else run(std::true_type{}, std::false_type{});
 
   // ---- w~ <- w~ + delta_m z (option I); hand z out
 #pragma unroll
@@ -722,7 +788,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
       if (lane < LANES && j < d) {
         const int zk = S::value(zp[u], e) >> BITS;
-        zg[j] = (int8_t)zk;
+        zg[j] = (ZT)zk;
         const double step = __dmul_rn(delta_m, (double)zk);
         wg[j] = lp ? (float)step : (float)__dadd_rn((double)wg[j], step);  // Alg. 2: w~ = delta w
       }

@@ -14,35 +14,62 @@ pytestmark = pytest.mark.gpu
 NEAR = {22397602: 0xFFFFFF64, 41644664: 0x5C, 44213804: 0x49, 59438199: 0xFFFFFFE1}
 
 
-def _check(case, loss, d, b, lam, T, seed, alpha, mu, helpers):
-    P = _run_inner(case, loss, 1, 1, b, lam, 1, T, seed, 2, alpha=alpha, mu=mu)
-    P.h.set_option(hp.OPT_INNER_HELPERS, helpers)
+def _check(case, loss, d, b, lam, R, T, seed, alpha, mu):
+    P = _run_inner(case, loss, 1, 1, b, lam, R, T, seed, 2, alpha=alpha, mu=mu)
+    if b == 8:
+        P.h.set_option(hp.OPT_INNER_HELPERS, 3)  # (at 16 bits the library takes the form for few chains)
     P.h.inner_loop(3)
-    out = _oracle_inner(case, 0, T)
-    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
-    assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in range(R):
+        out = _oracle_inner(case, r, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"])
+        assert np.array_equal(w[r], ref.apply_offset(case["mk"](r), case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
     return out
 
 
 @pytest.mark.parametrize("seed", sorted(NEAR))
-@pytest.mark.parametrize("loss,d,lam", [(hp.LOSS_SQUARED, 40, 0.0), (hp.LOSS_SQUARED, 200, 0.0),
-                                        (hp.LOSS_LOGISTIC, 500, 0.0), (hp.LOSS_SQUARED, 1000, 5e-2)])
-def test_a_fraction_next_to_an_integer_is_settled_in_the_fixed_order(loss, d, lam, seed):
-    assert ref.stream_word(seed, 1, 3, 0) == NEAR[seed]
-    case = _inner_case(loss, 60, d, 1, 1, 8, lam, 1, 29, seed - 1000, mu=0.2)
-    _check(case, loss, d, 8, lam, 29, seed - 1000, 0.02, 0.2, 3)
-
-
-@pytest.mark.parametrize("loss,d,alpha,mu", [
-    (hp.LOSS_SQUARED, 60, 50.0, 0.01),     # gammas far outside their range
-    (hp.LOSS_SQUARED, 512, 500.0, 0.01),   # scales too large for the matrix instruction's sum: no step is fused
-    (hp.LOSS_SQUARED, 1000, 500.0, 1e-4),
-    (hp.LOSS_LOGISTIC, 130, 500.0, 0.01),
-    (hp.LOSS_SQUARED, 130, 0.9, 2.0),      # -h~ / 2^b too large to ride in the records
-    (hp.LOSS_SQUARED, 1000, 0.9, 8.0),
+@pytest.mark.parametrize("loss,d,b,lam", [
+    (hp.LOSS_SQUARED, 40, 8, 0.0), (hp.LOSS_SQUARED, 200, 8, 0.0), (hp.LOSS_LOGISTIC, 500, 8, 0.0),
+    (hp.LOSS_SQUARED, 1000, 8, 5e-2), (hp.LOSS_SQUARED, 64, 16, 0.0), (hp.LOSS_SQUARED, 300, 16, 1e-3),
 ])
-def test_steps_that_the_fused_form_does_not_cover(loss, d, alpha, mu):
-    case = _inner_case(loss, 60, d, 1, 1, 8, 0.0, 1, 67, 7, alpha=alpha, mu=mu)
-    out = _check(case, loss, d, 8, 0.0, 67, 7, alpha, mu, 3)
+def test_a_fraction_next_to_an_integer_is_settled_in_the_fixed_order(loss, d, b, lam, seed):
+    assert ref.stream_word(seed, 1, 3, 0) == NEAR[seed]
+    case = _inner_case(loss, 60, d, 1, 1, b, lam, 1, 29, seed - 1000, mu=0.2)
+    _check(case, loss, d, b, lam, 1, 29, seed - 1000, 0.02, 0.2)
+
+
+@pytest.mark.parametrize("loss,d,b,alpha,mu", [
+    (hp.LOSS_SQUARED, 60, 8, 50.0, 0.01),      # gammas far outside their range
+    (hp.LOSS_SQUARED, 512, 8, 500.0, 0.01),    # too large for the matrix instruction to do the multiply-add
+    (hp.LOSS_SQUARED, 1000, 8, 500.0, 1e-4),
+    (hp.LOSS_LOGISTIC, 130, 8, 500.0, 0.01),
+    (hp.LOSS_SQUARED, 130, 8, 0.9, 2.0),       # -h~ / 2^b too large to ride in the records
+    (hp.LOSS_SQUARED, 1000, 8, 0.9, 8.0),
+    (hp.LOSS_SQUARED, 60, 16, 500.0, 0.01),
+    (hp.LOSS_SQUARED, 500, 16, 500.0, 0.01),
+    (hp.LOSS_LOGISTIC, 100, 16, 500.0, 0.01),
+    (hp.LOSS_SQUARED, 64, 16, 0.9, 2.0),
+    (hp.LOSS_SQUARED, 512, 16, 0.9, 8.0),
+    (hp.LOSS_SQUARED, 130, 16, 1e-230, 1e-230),  # scales next to underflow: no step is fused
+    (hp.LOSS_SQUARED, 130, 8, 1e-230, 1e-230),
+])
+def test_scales_at_the_ends_of_the_fused_form(loss, d, b, alpha, mu):
+    case = _inner_case(loss, 60, d, 1, 1, b, 0.0, 1, 67, 7, alpha=alpha, mu=mu)
+    out = _check(case, loss, d, b, 0.0, 1, 67, 7, alpha, mu)
     if alpha >= 50 and loss == hp.LOSS_SQUARED:
         assert out["counters"][1] > 0
+
+
+@pytest.mark.parametrize("loss,d,lam,T", [
+    (hp.LOSS_SQUARED, 1, 0.0, 40), (hp.LOSS_SQUARED, 63, 0.0, 8), (hp.LOSS_LOGISTIC, 64, 1e-3, 513),
+    (hp.LOSS_SQUARED, 65, 0.0, 17), (hp.LOSS_SQUARED, 128, 1e-3, 264), (hp.LOSS_LOGISTIC, 129, 0.0, 16),
+    (hp.LOSS_SQUARED, 256, 0.0, 257), (hp.LOSS_SQUARED, 257, 1e-3, 24), (hp.LOSS_SQUARED, 511, 0.0, 300),
+    (hp.LOSS_LOGISTIC, 512, 0.0, 33), (hp.LOSS_SQUARED, 512, 0.0, 7), (hp.LOSS_SQUARED, 300, 0.0, 0),
+])
+@pytest.mark.parametrize("mu", [0.2, 300.0])
+def test_sixteen_bits_one_to_eight_strips_per_lane(loss, d, lam, T, mu):
+    """1, 2, 4 and 8 strips per lane, whole and ragged rows, L2 draws, epochs around windows and batches; the
+    box far too small, so that z saturates and -h~ does not ride in the records."""
+    case = _inner_case(loss, 90, d, 1, 1, 16, lam, 2, T, 5 + d + T, mu=mu)
+    _check(case, loss, d, 16, lam, 2, T, 5 + d + T, 0.02, mu)
