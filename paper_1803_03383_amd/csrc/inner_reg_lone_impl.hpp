@@ -463,7 +463,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         const int iv[kWin] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
-          const unsigned char* const at = frag + (uint64_t)(uint32_t)iv[s] * (uint32_t)row_bytes;
+          const unsigned char* at = frag + (uint64_t)(uint32_t)iv[s] * (uint32_t)row_bytes;
+          if (row_bytes >> 32) at += (uint64_t)(uint32_t)iv[s] * (uint32_t)(row_bytes >> 32) << 32;  // uniform
           if (SPH == 1) dst[s] = (uint32_t) * reinterpret_cast<const uint16_t*>(at);
           else dst[s] = *reinterpret_cast<const uint32_t*>(at);
         }

@@ -4,12 +4,14 @@
 //
 //   w <- w - alpha ( (l'(x_i^T w) - l'(phi_i)) x_i + lambda (w - w~) + g~ ),   phi_i = x_i^T w~
 //
-// One workgroup per chain.  A thread owns CPL consecutive coordinates of w (fp32 registers)
+// One workgroup per chain.  inner_svrg_kernel: a thread owns CPL consecutive coordinates of w (fp32 registers)
 // together with alpha g~ and w~; rows of the fp32 data are gathered in windows of 8 steps, the
 // next window's fragments being requested at the top of the current one.  Vector work is
 // fp32 (fused multiply-adds), the scalar l' difference fp64, the wave sums DPP folds, the
 // cross-wave sum one LDS word per wave added in wave order.  Sample indices (and the margins
 // and labels of the sampled rows) are produced 256 steps at a time into LDS.
+#include <type_traits>
+
 #include "halp_device.hpp"
 #include "halp_internal.hpp"
 
@@ -208,6 +210,272 @@ __global__ __launch_bounds__(64 * NWT) void inner_svrg_kernel(SvArgs a) {
     if (j0 + k < d) wg[j0 + k] = w[k];
 }
 
+// The form for few chains per CU: ONE chain wave that holds all of w, helper waves on the other SIMDs.
+//
+// Such a chain is bound by its step's dependent instructions (8 cycles each on a lone wave) and, in the form
+// above, by the LDS exchange and the barrier between its waves in every step.  Here the chain wave adds up x^T w
+// alone: DPP over 16 lanes in fp32, then one fp64 4x4x4 matrix instruction across the four rows of lanes, which for
+// squared loss also takes the step size and the margin along (-alpha x^T w + alpha phi_i).  w - alpha g~ (and the L2
+// term) is taken while the dot is under way, so that one multiply-add per coordinate follows it.  Helper wave v
+// fetches the float4s 4 (lane + 64 v) of the sampled rows, kSets - 1 windows of 8 steps ahead, clears what lies
+// past d and puts them into a ring of three windows in LDS; the service wave refills the 256-step batches of
+// indices, margins, labels.  One barrier per window: in period w the chain wave consumes window w while the helpers
+// store window w + 2.
+constexpr int kSvSlots = 3;
+constexpr int sv_waves(int nv) { return nv == 1 ? 3 : (nv == 2 ? 4 : 7); }
+
+typedef float float4r __attribute__((ext_vector_type(4)));
+
+// NV: float4s of w per lane.  PAIR: built for two workgroups per CU, at most 128 registers.
+template <int NV, int LOSS, bool PAIR>
+__global__ __launch_bounds__(64 * sv_waves(NV), PAIR ? 4 : 2) void inner_svrg_lone_kernel(SvArgs a) {
+  constexpr bool logistic = LOSS == HALP_LOSS_LOGISTIC;
+  constexpr int kMask = 2 * kBatch - 1;
+  constexpr int kSets = PAIR ? 3 : 4;  // windows of rows a helper has in flight
+  const int chain = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int d = a.d;
+  const uint32_t N = (uint32_t)a.N;
+  const uint64_t seed = a.seed + (uint64_t)chain;
+  const int64_t T = epoch_steps(seed, a.epoch, a.T, a.option2);
+  const int64_t nwin = (T + kWin - 1) / kWin;
+  const double alpha = a.hyper[2 * chain];
+
+  __shared__ __attribute__((aligned(16))) int s_idx[2 * kBatch];
+  // squared loss: alpha phi_i; logistic: l'(phi_i) and the label
+  __shared__ __attribute__((aligned(16))) double s_at[2 * kBatch];
+  __shared__ __attribute__((aligned(16))) float s_y[logistic ? 2 * kBatch : 4];
+  extern __shared__ __attribute__((aligned(16))) float4r s_row[];  // [slot][step][v][lane]
+
+  // waves w and w + 4 share a SIMD, wave 4 only keeps the barriers
+  const int helper = wave == 1 || wave == 2 ? wave - 1 : (NV == 4 && (wave == 5 || wave == 6) ? wave - 3 : -1);
+  if (wave == (NV == 1 ? 2 : 3)) {
+    // ============================ service wave ============================
+    const float* __restrict__ phi = a.phi + (int64_t)chain * a.N;
+    const float* __restrict__ y = a.y + (int64_t)chain * a.y_chain_stride;
+    auto fill_batch = [&](int64_t bb) {
+      const int at = (int)(bb & 1) * kBatch + 4 * lane;
+      const U4 ri = stream_block(seed, kIdx, a.epoch, (uint64_t)bb * 64 + (uint64_t)lane);
+      int4 iv;
+      iv.x = (int)__umulhi(ri.x, N); iv.y = (int)__umulhi(ri.y, N);
+      iv.z = (int)__umulhi(ri.z, N); iv.w = (int)__umulhi(ri.w, N);
+      *reinterpret_cast<int4*>(&s_idx[at]) = iv;
+      const float pv[4] = {phi[iv.x], phi[iv.y], phi[iv.z], phi[iv.w]};
+      if constexpr (logistic) {
+        const float yv[4] = {y[iv.x], y[iv.y], y[iv.z], y[iv.w]};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          s_y[at + k] = yv[k];
+          s_at[at + k] = logistic_dl((double)pv[k], (double)yv[k]);
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s_at[at + k] = __dmul_rn(alpha, (double)pv[k]);
+      }
+    };
+    fill_batch(0);
+    fill_batch(1);
+    __syncthreads();  // P0: the first two batches are in place
+    __syncthreads();  // P1: windows 0 and 1 are in the ring
+    for (int64_t w = 0; w < nwin; ++w) {
+      // window w = 32 m: every reader has left batch m - 1, whose half takes batch m + 1
+      if ((w & (kBatch / kWin - 1)) == 0 && w > 0) fill_batch(w / (kBatch / kWin) + 1);
+      __syncthreads();
+    }
+    return;
+  }
+
+  if (helper >= 0 && helper < NV) {
+    // ============================ helper wave =============================
+    const int c0 = 4 * (lane + 64 * helper);  // first coordinate
+    const uint64_t row_bytes = (uint64_t)a.ldx * 4;
+    // rows are padded to a multiple of 4 floats: a float4 that starts inside the row ends inside it; lanes
+    // past the row re-read its start
+    const unsigned char* const frag = reinterpret_cast<const unsigned char*>(a.X + (int64_t)chain * a.x_chain_stride + (c0 < d ? c0 : 0));
+    const bool whole = __ballot(c0 + 3 >= d) == 0;  // every coordinate of this wave exists
+    auto request = [&](float4r (&dst)[kWin], int64_t win) {
+      const int base = (int)((win * kWin) & kMask);
+      const int4 i0 = *reinterpret_cast<const int4*>(&s_idx[base]);
+      const int4 i1 = *reinterpret_cast<const int4*>(&s_idx[base + 4]);
+      const int iv[kWin] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) {
+        const unsigned char* at = frag + (uint64_t)(uint32_t)iv[s] * (uint32_t)row_bytes;
+        if (row_bytes >> 32) at += (uint64_t)(uint32_t)iv[s] * (uint32_t)(row_bytes >> 32) << 32;  // uniform
+        dst[s] = *reinterpret_cast<const float4r*>(at);
+      }
+    };
+    auto store = [&](const float4r (&src)[kWin], int slot) {
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) {
+        float4r v = src[s];
+        if (!whole) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = c0 + k < d ? v[k] : 0.f;
+        }
+        s_row[((slot * kWin + s) * NV + helper) * 64 + lane] = v;
+      }
+    };
+    float4r f[kSets][kWin];  // window v in set v % kSets
+    __syncthreads();  // P0
+#pragma unroll
+    for (int v = 0; v < kSets; ++v) request(f[v], v);
+    store(f[0], 0);
+    request(f[0], kSets);
+    store(f[1], 1);
+    __syncthreads();  // P1
+    int slot = 2;
+    // period w: the rows of window w + 1 + kSets go into the set window w + 1 left, window w + 2 into the ring
+    // (nothing may be scheduled across the borders of a period: the loads of all sets would be waited for)
+    auto period = [&](int64_t w, float4r (&freq)[kWin], const float4r (&fuse)[kWin]) {
+      __builtin_amdgcn_sched_barrier(0);
+      request(freq, w + 1 + kSets);
+      __builtin_amdgcn_sched_barrier(0);
+      store(fuse, slot);
+      slot = slot == kSvSlots - 1 ? 0 : slot + 1;
+      // LDS only: the rows in flight are not waited for
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int64_t w = 0;
+    for (; w + kSets <= nwin; w += kSets) {
+#pragma unroll
+      for (int k = 0; k < kSets; ++k) period(w + k, f[(k + 1) % kSets], f[(k + 2) % kSets]);
+    }
+#pragma unroll
+    for (int k = 0; k < kSets - 1; ++k)
+      if (w + k < nwin) period(w + k, f[(k + 1) % kSets], f[(k + 2) % kSets]);
+    return;
+  }
+
+  if (wave != 0) {
+    // ============================== idle wave ==============================
+    __syncthreads();
+    __syncthreads();
+    for (int64_t w = 0; w < nwin; ++w) __syncthreads();
+    return;
+  }
+
+  // ============================== chain wave ==============================
+  const float* __restrict__ g = a.g + (int64_t)chain * d;
+  float* __restrict__ wg = a.w + (int64_t)chain * d;
+  float wv[4 * NV], ag[4 * NV], wt[4 * NV];  // coordinates past d hold zeros and never change
+#pragma unroll
+  for (int k = 0; k < 4 * NV; ++k) {
+    const int j = 4 * (lane + 64 * (k / 4)) + k % 4;
+    wv[k] = wt[k] = j < d ? wg[j] : 0.f;
+    ag[k] = j < d ? (float)__dmul_rn(alpha, (double)g[j]) : 0.f;
+  }
+  const float al = (float)__dmul_rn(alpha, a.lambda);
+  __syncthreads();  // P0
+  __syncthreads();  // P1
+  __builtin_amdgcn_s_setprio(3);
+
+  struct Step {  // what a step needs from LDS, requested two steps ahead (logistic: one)
+    float4r x[NV];
+    double at;
+    float y;
+  };
+  constexpr int kAhead = logistic ? 1 : 2;
+  auto load_step = [&](Step& st, int slot, int base, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) st.x[v] = s_row[((slot * kWin + s) * NV + v) * 64 + lane];
+    st.at = s_at[base + s];
+    if constexpr (logistic) st.y = s_y[base + s];
+  };
+  auto step = [&](const Step& st, auto reg_tag, auto&& prefetch) __attribute__((always_inline)) {
+    constexpr int NA = 4;  // partial sums of a lane
+    float p[NA];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) p[k] = st.x[0][k] * wv[k];
+#pragma unroll
+    for (int k = NA; k < 4 * NV; ++k) p[k % NA] = __builtin_fmaf(st.x[k / 4][k % 4], wv[k], p[k % NA]);
+    float v = (p[0] + p[1]) + (p[2] + p[3]);
+    v += dpp_quad_swap1(v);
+    v += dpp_quad_swap2(v);
+    v += dpp_half_mirror(v);
+    v += dpp_row_mirror(v);
+    // -alpha (l'(x_i^T w) - l'(phi_i))
+    const double row = (double)v;
+    double t = logistic ? __builtin_amdgcn_mfma_f64_4x4x4f64(row, 1.0, 0.0, 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f64_4x4x4f64(row, -alpha, st.at, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    prefetch();
+#pragma unroll
+    for (int k = 0; k < 4 * NV; ++k) {
+      const float moved = wv[k] - ag[k];
+      if constexpr (decltype(reg_tag)::value) wv[k] = __builtin_fmaf(-al, wv[k] - wt[k], moved);
+      else wv[k] = moved;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (logistic) t = __dmul_rn(-alpha, __dadd_rn(logistic_dl(t, (double)st.y), -st.at));
+    const float c = (float)t;
+#pragma unroll
+    for (int k = 0; k < 4 * NV; ++k) wv[k] = __builtin_fmaf(c, st.x[k / 4][k % 4], wv[k]);
+  };
+  auto run = [&](auto reg_tag) __attribute__((always_inline)) {
+    int slot = 0;
+    int64_t t0 = 0;
+    Step ahead[kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load_step(ahead[k], 0, 0, k);
+    for (; t0 + kWin <= T; t0 += kWin) {
+      const int base = (int)(t0 & kMask), next_base = (base + kWin) & kMask;  // (any window has its place in the ring)
+      const int next_slot = slot == kSvSlots - 1 ? 0 : slot + 1;
+#pragma unroll
+      for (int s = 0; s < kWin; ++s) {
+        const Step st = ahead[s % kAhead];
+        step(st, reg_tag, [&]() __attribute__((always_inline)) {
+          if (s + kAhead < kWin) load_step(ahead[s % kAhead], slot, base, s + kAhead);
+          else load_step(ahead[s % kAhead], next_slot, next_base, s + kAhead - kWin);
+        });
+      }
+      // the window is consumed, the one after the next is in place; nothing of this wave is waited for
+      asm volatile("s_barrier" ::: "memory");
+      slot = next_slot;
+    }
+    if (t0 < T) {
+      const int base = (int)(t0 & kMask);
+#pragma unroll 1
+      for (int s = 0; t0 + s < T; ++s) {
+        Step st;
+        load_step(st, slot, base, s);
+        step(st, reg_tag, []() {});
+      }
+      asm volatile("s_barrier" ::: "memory");
+    }
+  };
+  if (a.lambda > 0) run(std::true_type{});
+  else run(std::false_type{});
+
+  // ---- w~ <- w_T (option I)
+#pragma unroll
+  for (int k = 0; k < 4 * NV; ++k) {
+    const int j = 4 * (lane + 64 * (k / 4)) + k % 4;
+    if (j < d) wg[j] = wv[k];
+  }
+}
+
+template <int NV, bool PAIR>
+int launch_lone(const SvArgs& a, int R, hipStream_t s) {
+  const dim3 grid(R), block(64 * sv_waves(NV));
+  const size_t smem = (size_t)kSvSlots * kWin * NV * 64 * sizeof(float4r);
+#define HALP_SVL(LOSS_)                                                                                   \
+  do {                                                                                                    \
+    auto kern = inner_svrg_lone_kernel<NV, LOSS_, PAIR>;                                                  \
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, \
+                            (int)smem) != hipSuccess)                                                     \
+      return HALP_ERR_HIP;                                                                                \
+    hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                                    \
+  } while (0)
+  if (a.loss == HALP_LOSS_LOGISTIC) HALP_SVL(HALP_LOSS_LOGISTIC);
+  else HALP_SVL(HALP_LOSS_SQUARED);
+#undef HALP_SVL
+  return hip_ok(hipGetLastError());
+}
+
 template <int CPL, int NWT>
 int launch_loss(const SvArgs& a, int R, hipStream_t s) {
   const dim3 grid(R), block(64 * NWT);
@@ -236,6 +504,17 @@ SvShape pick_shape(const halp_handle& h) {
   return SvShape{cpl, nw};
 }
 
+// Where the form with one chain wave is taken, in chains per CU.  ns per step of all chains (shared data, squared
+// loss), with it / without: d = 64 512 chains 81 / 121, 1280 112 / 143, 1536 170 / 143; d = 200 1 chain 70 / 235, 512 80 / 234,
+// 1280 112 / 201, 2048 198 / 211; d = 512 1 chain 92 / 249, 512 107 / 265 (two workgroups fit a CU; 600 chains would take two
+// turns: 267 / 268); d = 1000 256 157 / 294.  Logistic: d = 60 1280 443 / 471, d = 200 1280 445 / 534, d = 512 512 205 / 601.
+bool lone_pays(const halp_handle& h) {
+  const int d = h.p.d;
+  if (h.inner_waves > 0 || d > 1024) return false;
+  const int per_cu = d <= 64 ? 5 : (d <= 256 ? 8 : (d <= 512 ? 2 : 1));
+  return (int64_t)h.p.R <= (int64_t)h.num_cus * per_cu;
+}
+
 }  // namespace
 
 // squared or logistic loss, one row per step, d <= 4096 (16 waves of 64 threads of 4 coordinates)
@@ -262,6 +541,12 @@ int launch_inner_svrg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   a.y_chain_stride = p.share_data ? 0 : p.N;
   a.d = p.d; a.loss = p.loss; a.hyper = h.hyper; a.lambda = p.lambda; a.option2 = h.option2 ? 1 : 0;
   a.seed = p.seed; a.epoch = epoch;
+  if (lone_pays(h)) {
+    const bool pair = p.R > h.num_cus;
+    if (p.d <= 256) return pair ? launch_lone<1, true>(a, p.R, s) : launch_lone<1, false>(a, p.R, s);
+    if (p.d <= 512) return pair ? launch_lone<2, true>(a, p.R, s) : launch_lone<2, false>(a, p.R, s);
+    return launch_lone<4, false>(a, p.R, s);
+  }
   const SvShape sh = pick_shape(h);
 #define HALP_SV(C_, W_) \
   if (sh.cpl == C_ && sh.nw == W_) return launch_loss<C_, W_>(a, p.R, s);

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import paper_1803_03383_amd as hp
+import test_gpu_svrg
 from oracle import ref
 from test_gpu_parity import _inner_case, _oracle_inner, _run_inner
 
@@ -73,3 +74,14 @@ def test_sixteen_bits_one_to_eight_strips_per_lane(loss, d, lam, T, mu):
     box far too small, so that z saturates and -h~ does not ride in the records."""
     case = _inner_case(loss, 90, d, 1, 1, 16, lam, 2, T, 5 + d + T, mu=mu)
     _check(case, loss, d, 16, lam, 2, T, 5 + d + T, 0.02, mu)
+
+
+@pytest.mark.parametrize("loss,d,lam,R,T", [
+    (hp.LOSS_SQUARED, 3, 0.0, 1, 9), (hp.LOSS_SQUARED, 255, 1e-3, 2, 264), (hp.LOSS_LOGISTIC, 256, 0.0, 1, 16),
+    (hp.LOSS_SQUARED, 257, 0.0, 1, 513), (hp.LOSS_LOGISTIC, 511, 1e-3, 2, 31), (hp.LOSS_SQUARED, 512, 1e-2, 1, 257),
+    (hp.LOSS_SQUARED, 513, 0.0, 2, 24), (hp.LOSS_LOGISTIC, 1000, 0.0, 1, 40), (hp.LOSS_SQUARED, 1024, 1e-3, 1, 25),
+    (hp.LOSS_SQUARED, 30, 0.0, 300, 70), (hp.LOSS_LOGISTIC, 300, 1e-3, 260, 20),  # more chains than CUs
+])
+def test_full_precision_chain_wave(loss, d, lam, R, T):
+    """One, two and four float4s per lane, whole and ragged rows, the L2 term, epochs around windows and batches."""
+    test_gpu_svrg.test_inner_loop_matches_the_oracle(loss, 120, d, lam, R, T, 0)
