@@ -40,6 +40,7 @@
 
 #include "halp_device.hpp"
 #include "softmax_ahead.hpp"
+#include "softmax_fused.hpp"
 
 namespace halp {
 namespace {
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
   __shared__ AccT s_dumpD[64];  // partial folds of lanes 0..62 of every class wave (never read)
   __shared__ unsigned long long s_cnt[3];
   if (tid < 3) s_cnt[tid] = 0;
+  if (tid < 2 * kKC) (&s_D[0][0])[tid] = 0;  // classes past K stay 0
   const bool use_reg = a.lambda > 0;
   const int32_t* __restrict__ clv = ah.cl + (int64_t)local * ah.S;
   const int tlast = steps > 0 ? steps - 1 : 0;  // requests past the segment's end repeat its last step
@@ -137,41 +139,73 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
       const double aB = a.hyper[2 * chain];  // alpha / B, B = 1
       unsigned int n_gclamp = 0, n_reg = 0;
       const int lc = lane & 15;
-      const bool live = lc < K;
-      AheadRec rr[kDep];
+      // gammas of a step in the fixed order of roundings, one class per lane of a row of 16
+      auto step_fixed = [&](int par, const AheadRec& r) __attribute__((always_inline)) {
+        const bool live = lc < K;
+        // Algorithm 4 moves the margins by x^T z; in Algorithm 2 (LP-SVRG) x^T w is the margin
+        const double moved = __dmul_rn(dscale, (double)s_D[par][lc]);
+        const double val = live ? (lp ? moved : __dadd_rn((double)r.phi, moved)) : -INFINITY;
+        const double mx = row_max_f64(val);
+        const double e = live ? halp_exp(__dadd_rn(val, -mx)) : 0.0;
+        // normaliser: pairwise over adjacent classes, the order the DPP fold gives
+        const double p = __ddiv_rn(e, row_sum_f64(e));
+        // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
+        const double beta = __dmul_rn(aB, __dadd_rn(p, -r.p0));
+        const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), __dmul_rn((double)r.rho, 0x1p-32)));
+        const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
+        if (lane < K) s_ng[par][lane] = BITS == 8 ? (int)(-fc) : (int)fc;
+        n_gclamp += (lane < K && f != fc) ? 1u : 0u;
+      };
+      auto run = [&](auto fused_tag) __attribute__((always_inline)) {
+        constexpr bool FUSED = decltype(fused_tag)::value;
+        const int rc = FUSED ? soft_class(lane) : lc;  // class of the lane's records
+        const bool live = rc < K;
+        const double k2 = __dmul_rn(aB, inv_s);
+        AheadRec rr[kDep];
 #pragma unroll
-      for (int s = 0; s < kDep; ++s) rr[s] = rec[(int64_t)min(s, tlast) * kAheadK + lc];
-      int cln = use_reg ? clv[min(lane & 7, tlast)] : 0;
-      double a0 = (double)rr[0].phi, rho = __dmul_rn((double)rr[0].rho, 0x1p-32);
-      for (int t0 = 0; t0 < steps; t0 += kWin) {
-        if (use_reg) {
-          n_reg += (lane < kWin && t0 + lane < steps && cln != 0) ? 1u : 0u;
-          cln = clv[min(t0 + kWin + (lane & 7), tlast)];
-        }
+        for (int s = 0; s < kDep; ++s) rr[s] = rec[(int64_t)min(s, tlast) * kAheadK + rc];
+        int cln = use_reg ? clv[min(lane & 7, tlast)] : 0;
+        SoftDraw dr{};
+        double from = 0.0;  // what the new margins are measured from: phi in Algorithm 2
+        auto draw = [&](const AheadRec& r) __attribute__((always_inline)) {
+          if constexpr (FUSED) {
+            dr = soft_draw<BITS == 8>(live, r.p0, r.phi, r.rho, k2);
+            from = lp && live ? (double)r.phi : 0.0;
+          }
+        };
+        draw(rr[0]);
+        for (int t0 = 0; t0 < steps; t0 += kWin) {
+          if (use_reg) {
+            n_reg += (lane < kWin && t0 + lane < steps && cln != 0) ? 1u : 0u;
+            cln = clv[min(t0 + kWin + (lane & 7), tlast)];
+          }
 #pragma unroll
-        for (int s = 0; s < kWin; ++s) {
-          if (t0 + s < steps) {
-            lds_barrier();  // the dot products of this step are in LDS
-            // Algorithm 4 moves the margins by x^T z; in Algorithm 2 (LP-SVRG) x^T w is the margin
-            const double moved = __dmul_rn(dscale, (double)s_D[s & 1][lc]);
-            const double val = live ? (lp ? moved : __dadd_rn(a0, moved)) : -INFINITY;
-            const double mx = row_max_f64(val);
-            const double e = live ? halp_exp(__dadd_rn(val, -mx)) : 0.0;
-            // normaliser: pairwise over adjacent classes, the order the DPP fold gives
-            const double p = __ddiv_rn(e, row_sum_f64(e));
-            // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
-            const double beta = __dmul_rn(aB, __dadd_rn(p, -rr[s % kDep].p0));
-            const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
-            const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
-            if (lane < K) s_ng[s & 1][lane] = BITS == 8 ? (int)(-fc) : (int)fc;
-            lds_barrier();  // gamma is out; the class waves update z
-            n_gclamp += (lane < K && f != fc) ? 1u : 0u;
-            rr[s % kDep] = rec[(int64_t)min(t0 + s + kDep, tlast) * kAheadK + lc];
-            a0 = (double)rr[(s + 1) % kDep].phi;
-            rho = __dmul_rn((double)rr[(s + 1) % kDep].rho, 0x1p-32);
+          for (int s = 0; s < kWin; ++s) {
+            if (t0 + s < steps) {
+              lds_barrier();  // the dot products of this step are in LDS
+              if constexpr (FUSED) {
+                int hi;
+                if (__builtin_expect_with_probability(
+                        soft_gamma<BITS == 8>(dr, live, __fma_rn(dscale, (double)s_D[s & 1][rc], -from), &hi), 1, 1.0)) {
+                  const int lo = BITS == 8 ? -QMAX : QMIN, up = BITS == 8 ? -QMIN : QMAX;
+                  const int g = min(max(hi, kSoftMagicHi + lo), kSoftMagicHi + up);
+                  s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
+                  n_gclamp += (live && soft_first_copy(lane) && g != hi) ? 1u : 0u;
+                } else {
+                  step_fixed(s & 1, rec[(int64_t)(t0 + s) * kAheadK + lc]);
+                }
+              } else {
+                step_fixed(s & 1, rr[s % kDep]);
+              }
+              lds_barrier();  // gamma is out; the class waves update z
+              rr[s % kDep] = rec[(int64_t)min(t0 + s + kDep, tlast) * kAheadK + rc];
+              draw(rr[(s + 1) % kDep]);
+            }
           }
         }
-      }
+      };
+      if (soft_covers(dscale, aB, inv_s)) run(std::true_type{});
+      else run(std::false_type{});
       if (n_gclamp) atomicAdd(&s_cnt[1], (unsigned long long)n_gclamp);
       if (n_reg) atomicAdd(&s_cnt[2], (unsigned long long)n_reg);
     }
