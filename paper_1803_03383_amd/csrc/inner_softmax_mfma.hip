@@ -42,6 +42,7 @@
 
 #include "halp_device.hpp"
 #include "softmax_ahead.hpp"
+#include "softmax_fused.hpp"
 
 namespace halp {
 namespace {
@@ -168,6 +169,23 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
       const int m0 = 16 * tile + 4 * q + (lc & 3), c0 = lc & 12;
       AheadRec rn[SOFT ? 4 : 1];
       float yn = 0.f;
+      // softmax: the short chain to the gammas (softmax_fused.hpp) where the chain's scales allow it.  Four classes
+      // per lane here, so that it saves instructions as much as latency: one reciprocal per row for four divisions
+      // per lane, no maximum
+      const bool fused = SOFT && soft_covers(dscale, aB, inv_s);
+      const double k2 = __dmul_rn(aB, inv_s);
+      SoftDraw sd[SOFT ? 4 : 1];
+      double from[SOFT ? 4 : 1];
+      auto draw = [&]() {
+        if (fused) {
+#pragma unroll
+          for (int e = 0; e < (SOFT ? 4 : 1); ++e) {
+            const bool live = c0 + e < K;
+            sd[e] = soft_draw<false>(live, rn[e].p0, rn[e].phi, rn[e].rho, k2);
+            from[e] = lp && live ? (double)rn[e].phi : 0.0;
+          }
+        }
+      };
       auto fetch_rec = [&](int it) {
         it = min(it, niter - 1);  // past the segment's end its last rows are repeated
         const int tl = MANY ? it / nchunk : it;
@@ -178,6 +196,7 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
         if (!SOFT && a.loss == HALP_LOSS_LOGISTIC) yn = rec[o + 1].phi;
       };
       fetch_rec(0);
+      draw();
       __syncthreads();
       int ch = 0;
       for (int it = 0; it < niter; ++it) {
@@ -198,49 +217,86 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
           quad_transpose(D, lane);
           // ---- gamma of row m0, classes c0 .. c0 + 3.  Algorithm 4 moves the margins by x^T z; in
           // Algorithm 2 (LP-SVRG) x^T w is the margin
-          double diff[4];
+          int8_t* gp = s_gam + c0 * kGamStride + (m0 & 3) * 16 + (m0 >> 2);
+          bool done = false;
           if constexpr (SOFT) {
-            double v[4], ex[4];
+            if (fused) {
+              double delta[4], ex[4], sum = 0.0;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const double moved = __dmul_rn(dscale, (double)D[e]);
-              v[e] = c0 + e < K ? (lp ? moved : __dadd_rn((double)rn[e].phi, moved)) : -INFINITY;
-            }
-            double mx = fmax(fmax(v[0], v[1]), fmax(v[2], v[3]));
-            mx = fmax(mx, bank_swap_f64(mx));
-            mx = fmax(mx, half_swap_f64(mx));
+              for (int e = 0; e < 4; ++e) delta[e] = __fma_rn(dscale, (double)D[e], -from[e]);  // 0 past the classes
 #pragma unroll
-            for (int e = 0; e < 4; ++e) ex[e] = c0 + e < K ? halp_exp(__dadd_rn(v[e], -mx)) : 0.0;
-            // normaliser: pairwise over adjacent classes
-            double sum = __dadd_rn(__dadd_rn(ex[0], ex[1]), __dadd_rn(ex[2], ex[3]));
-            sum = __dadd_rn(sum, bank_swap_f64(sum));
-            sum = __dadd_rn(sum, half_swap_f64(sum));
+              for (int e = 0; e < 4; ++e) ex[e] = exp_short(delta[e]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) diff[e] = __dadd_rn(__ddiv_rn(ex[e], sum), -rn[e].p0);
-          } else {
-            const double a0 = (double)rn[0].phi, moved = __dmul_rn(dscale, (double)D[0]);
-            if (a.loss == HALP_LOSS_SQUARED) {
-              // Algorithm 4: (phi + Delta - y) - (phi - y) = Delta; Algorithm 2: (x^T w - y) - (phi - y)
-              diff[0] = lp ? __dadd_rn(moved, -a0) : moved;
-            } else {
-              const double y = (double)yn, a1 = lp ? moved : __dadd_rn(a0, moved);
-              diff[0] = __dadd_rn(__ddiv_rn(-y, __dadd_rn(1.0, halp_exp(__dmul_rn(y, a1)))), -rn[0].p0);
+              for (int e = 0; e < 4; ++e) sum = __fma_rn(sd[e].p0, ex[e], sum);
+              sum += bank_swap_f64(sum);
+              sum += half_swap_f64(sum);
+              double y = __builtin_amdgcn_rcp(sum);
+              y = __fma_rn(__fma_rn(-sum, y, 1.0), y, y);
+              bool bad = !(sum > 0x1p-4);
+              int hi[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const uint64_t bits = __builtin_bit_cast(uint64_t, __fma_rn(sd[e].kp * ex[e], y, sd[e].c));
+                hi[e] = (int)(bits >> 32);
+                bad = bad || sd[e].wide || !(__builtin_fabs(delta[e]) <= 64.0) || (c0 + e < K && (uint32_t)bits <= 2 * kSoftNear);
+              }
+              done = __ballot(bad) == 0;
+              if (__builtin_expect_with_probability(done, 1, 1.0)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const bool in = m0 < nrow && c0 + e < K;
+                  const int g = min(max(hi[e], kSoftMagicHi + QMIN), kSoftMagicHi + QMAX);
+                  n_gclamp += (in && g != hi[e]) ? 1u : 0u;
+                  gp[e * kGamStride] = in ? (int8_t)(g & 0xFF) : (int8_t)0;
+                }
+              }
             }
           }
-          int8_t* gp = s_gam + c0 * kGamStride + (m0 & 3) * 16 + (m0 >> 2);
+          if (!done) {  // in the fixed order of roundings
+            double diff[4];
+            if constexpr (SOFT) {
+              double v[4], ex[4];
 #pragma unroll
-          for (int e = 0; e < (SOFT ? 4 : 1); ++e) {
-            const double beta = __dmul_rn(aB, diff[e]);
-            const double rho = __dmul_rn((double)rn[e].rho, 0x1p-32);
-            const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
-            const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
-            const bool in = m0 < nrow && c0 + e < K;
-            n_gclamp += (in && f != fc) ? 1u : 0u;
-            gp[e * kGamStride] = in ? (int8_t)(int)fc : (int8_t)0;
+              for (int e = 0; e < 4; ++e) {
+                const double moved = __dmul_rn(dscale, (double)D[e]);
+                v[e] = c0 + e < K ? (lp ? moved : __dadd_rn((double)rn[e].phi, moved)) : -INFINITY;
+              }
+              double mx = fmax(fmax(v[0], v[1]), fmax(v[2], v[3]));
+              mx = fmax(mx, bank_swap_f64(mx));
+              mx = fmax(mx, half_swap_f64(mx));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) ex[e] = c0 + e < K ? halp_exp(__dadd_rn(v[e], -mx)) : 0.0;
+              // normaliser: pairwise over adjacent classes
+              double sum = __dadd_rn(__dadd_rn(ex[0], ex[1]), __dadd_rn(ex[2], ex[3]));
+              sum = __dadd_rn(sum, bank_swap_f64(sum));
+              sum = __dadd_rn(sum, half_swap_f64(sum));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) diff[e] = __dadd_rn(__ddiv_rn(ex[e], sum), -rn[e].p0);
+            } else {
+              const double a0 = (double)rn[0].phi, moved = __dmul_rn(dscale, (double)D[0]);
+              if (a.loss == HALP_LOSS_SQUARED) {
+                // Algorithm 4: (phi + Delta - y) - (phi - y) = Delta; Algorithm 2: (x^T w - y) - (phi - y)
+                diff[0] = lp ? __dadd_rn(moved, -a0) : moved;
+              } else {
+                const double y = (double)yn, a1 = lp ? moved : __dadd_rn(a0, moved);
+                diff[0] = __dadd_rn(__ddiv_rn(-y, __dadd_rn(1.0, halp_exp(__dmul_rn(y, a1)))), -rn[0].p0);
+              }
+            }
+#pragma unroll
+            for (int e = 0; e < (SOFT ? 4 : 1); ++e) {
+              const double beta = __dmul_rn(aB, diff[e]);
+              const double rho = __dmul_rn((double)rn[e].rho, 0x1p-32);
+              const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
+              const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
+              const bool in = m0 < nrow && c0 + e < K;
+              n_gclamp += (in && f != fc) ? 1u : 0u;
+              gp[e * kGamStride] = in ? (int8_t)(int)fc : (int8_t)0;
+            }
           }
         }
         lds_barrier();  // gamma is out
         fetch_rec(it + 1);
+        draw();
         if (MANY) ch = ch + 1 == nchunk ? 0 : ch + 1;
       }
     }

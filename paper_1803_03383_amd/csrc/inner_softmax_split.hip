@@ -35,6 +35,7 @@
 
 #include "halp_device.hpp"
 #include "inner_args.hpp"
+#include "softmax_fused.hpp"
 
 namespace halp {
 namespace {
@@ -133,9 +134,21 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       const double e = live ? halp_exp(__dadd_rn(val, -mx)) : 0.0;
       return __ddiv_rn(e, row_sum_f64(e));
     };
+    // The step's gammas come from the short chain of softmax_fused.hpp, which has its classes in other lanes:
+    // what is made one class per lane of the first sixteen goes there through LDS's lane exchange, beside the
+    // trip of the sums.
+    const int rc = soft_class(lane);
+    const bool live_f = rc < K;
+    const bool fused = soft_covers(dscale, aB, inv_s);
+    const double k2 = __dmul_rn(aB, inv_s);
+    auto to_lane = [&](int src, int v) { return __builtin_amdgcn_ds_bpermute(src << 2, v); };
+    auto to_lane64 = [&](int src, uint64_t v) {
+      return (uint64_t)(uint32_t)to_lane(src, (int)(uint32_t)v) | ((uint64_t)(uint32_t)to_lane(src, (int)(v >> 32)) << 32);
+    };
     // rounding word of gamma_c (lanes 0..15: word t K + c) and of the L2 draw (lane 16: word t) of
     // a step, one Philox evaluation
     double rho_n = 0.0;
+    uint32_t word_n = 0;
     int cl_n = 0;
     auto draw_scalars = [&](int64_t t) {
       const bool reg = lane == 16;
@@ -143,6 +156,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       const U4 r = stream_block(seed, reg ? kReg : kGamma, a.epoch, n >> 2);
       const uint32_t w = pick(r, (uint32_t)(n & 3));
       rho_n = __dmul_rn((double)w, 0x1p-32);
+      word_n = w;
       cl_n = 0;
       if (use_reg)
         cl_n = __builtin_amdgcn_readlane(
@@ -150,6 +164,15 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     };
     double a0_n = (double)phir[0], p0_n = softmax(a0_n);
     draw_scalars(0);
+    SoftDraw dr_n{};
+    double from_n = 0.0;
+    auto draw_fused = [&]() {
+      const float ph = __builtin_bit_cast(float, to_lane(rc, __builtin_bit_cast(int, (float)a0_n)));
+      const double p = __builtin_bit_cast(double, to_lane64(rc, __builtin_bit_cast(uint64_t, p0_n)));
+      dr_n = soft_draw<true>(live_f, p, ph, (uint32_t)to_lane(rc, (int)word_n), k2);
+      from_n = lp && live_f ? (double)ph : 0.0;  // Algorithm 2: x^T w is the whole margin
+    };
+    draw_fused();
     unsigned long long old[2] = {0, 0};
 
     for (int64_t t0 = 0; t0 < T; t0 += kWin) {
@@ -163,34 +186,45 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       for (int s = 0; s < kWin; ++s) {
         const int64_t t = t0 + s;
         if (t < T) {
-          const double a0 = a0_n, p0 = p0_n, rho = rho_n;
+          const double a0 = a0_n, p0 = p0_n, rho = rho_n, from = from_n;
+          const SoftDraw dr = dr_n;
           const int cl = cl_n;
           // beside the class waves' dots and the trip of their sums: all that does not need them
           draw_scalars(t + 1);
           a0_n = (double)phir[(s + 1) % kWin];
           p0_n = softmax(a0_n);
+          draw_fused();
           phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(idxn, s) * K + lc];  // step t + 8
-          unsigned long long* w = words + (s & 1) * kKC * kWordStride + lc * kWordStride;
+          unsigned long long* w = words + (s & 1) * kKC * kWordStride + (live_f ? rc : 0) * kWordStride;
           unsigned long long v = old[s & 1];
           for (int spin = 0; n_timeout == 0; ++spin) {  // after one wait ran out, none is tried again
-            if (live) v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (live_f) v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // arrivals so far: a signed part below 2^55 in magnitude may borrow from the top byte
-            const bool missing = live && (uint32_t)((v - old[s & 1] + (1ull << 55)) >> 56) != (uint32_t)P;
+            const bool missing = live_f && (uint32_t)((v - old[s & 1] + (1ull << 55)) >> 56) != (uint32_t)P;
             if (__ballot(missing) == 0) break;
             if (spin >= spin_limit) n_timeout = 1;  // only if a workgroup of the chain never ran: give up
           }
           const long long D = (long long)(v - old[s & 1] - ((unsigned long long)P << 56));
           old[s & 1] = v;
-          const double moved = __dmul_rn(dscale, (double)D);
-          const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
-          // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
-          const double beta = __dmul_rn(aB, __dadd_rn(p1, -p0));
-          const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
-          const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
-          if (live) s_ng[s & 1][lane] = (int)(-fc);
+          int hi = 0;
+          if (__builtin_expect_with_probability(
+                  fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
+            const int g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
+            s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
+            n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
+          } else {  // in the fixed order of roundings, classes in the first lanes
+            const long long Dc = (long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D);
+            const double moved = __dmul_rn(dscale, (double)Dc);
+            const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
+            // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
+            const double beta = __dmul_rn(aB, __dadd_rn(p1, -p0));
+            const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
+            const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
+            if (live) s_ng[s & 1][lane] = (int)(-fc);
+            n_gclamp += (live && f != fc) ? 1u : 0u;
+          }
           if (lane == 0) s_cl[s & 1] = cl;
           lds_barrier();  // gamma is out; the class waves update z
-          n_gclamp += (live && f != fc) ? 1u : 0u;
           n_reg += (lane == 0 && cl != 0) ? 1u : 0u;
         }
       }

@@ -1,5 +1,5 @@
-// gamma_c = floor(beta_c / delta_s + rho) of a softmax step by a short chain of operations, for a wave with
-// one class per lane.
+// gamma_c = floor(beta_c / delta_s + rho) of a softmax step by a short chain of operations; soft_gamma for a wave
+// with one class per lane.
 //
 // The inner loop fixes the order of roundings from x^T z to gamma: the margins' maximum, exp, the pairwise
 // normaliser, a division -- ~90 dependent fp64 instructions, 700 cycles of a lone wave.  With p0, the softmax
@@ -10,8 +10,8 @@
 //   t = -k2 p0_c e_c / sum + C',   C' = kSoftDraw - rho + k2 p0_c,   k2 = (alpha / B) / delta_s
 // whose high word is a constant minus gamma (plus: with the signs turned) and whose low word is the fraction.
 // It differs from the fixed order by less than k2 2^-40 (|delta| <= 64, |phi| <= 1024, sum > 1/16; the fixed
-// order's own roundings of the exponent, |phi| 2^-52, are most of that), i.e. 2^-17 for k2 < 2^23.  A step with a fraction within
-// 2^-14 of an integer, or outside those bounds, is done in the fixed order: one of a few hundred.
+// order's own roundings of the exponent, |phi| 2^-52, are most of that), i.e. 2^-19 for k2 < 2^21.  A step with a fraction within
+// 2^-16 of an integer, or outside those bounds, is done in the fixed order: one gamma of 32768.
 #pragma once
 
 #include "halp_device.hpp"
@@ -20,8 +20,8 @@ namespace halp {
 
 constexpr double kSoftMagic = 0x1.8p20;  // a double's last place is 2^-32 here, its high word counts whole numbers
 constexpr int kSoftMagicHi = 0x41380000;
-constexpr uint32_t kSoftNear = 1u << 18;  // 2^-14
-constexpr double kSoftMaxK2 = 0x1p23;
+constexpr uint32_t kSoftNear = 1u << 16;  // 2^-16
+constexpr double kSoftMaxK2 = 0x1p21;
 
 // class of a lane: its four copies are lanes apart by 4
 __device__ __forceinline__ int soft_class(int lane) { return (lane & 3) + 4 * (lane >> 4); }
