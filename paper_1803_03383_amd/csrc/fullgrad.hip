@@ -11,6 +11,7 @@
 // wave computes.  Waves of a workgroup fold their partial gradients through
 // LDS; a second small kernel adds the per-workgroup partials in a fixed order
 // (fp64), so the result does not depend on scheduling.
+#include <algorithm>
 #include <mutex>
 
 #include "halp_device.hpp"
@@ -192,7 +193,11 @@ __global__ __launch_bounds__(256) void fullgrad_k1(FgArgs a) {
 // A row of up to 4 G floats is held by G lanes (G = 4, 8, 16, 32), so a wave works on 64 / G
 // consecutive rows at once -- one coalesced load of 1 KB at d = 4 G -- instead of leaving most
 // of its lanes idle.  The margin is folded inside the G lanes only.  RB such row groups make
-// a batch; batches are double-buffered as above.
+// a batch; several batches are in flight.  A residual with its loss is evaluated once, by one lane of its
+// row, with a label that came with the rows.  What bounds it is the latency of a wave's rows.  us per pass, before (every
+// lane every residual, labels read when a margin waited for one) and now: 10^6 x 64 125 -> 86 (3.0 TB/s), 256 chains
+// of 16000 x 64 508 -> 327, 504 of 1000 x 64 63 -> 45, logistic 76 -> 49.  (Four row groups to a batch and twice the
+// workgroups: 56, 232, 30 and 34, but another order of sums, and with it other whole numbers behind the gradient.)
 template <typename T>
 __device__ __forceinline__ T group_sum(T v, int G) {
   v += dpp_quad_swap1(v);
@@ -203,10 +208,17 @@ __device__ __forceinline__ T group_sum(T v, int G) {
   return v;
 }
 
-template <int G, int RB, int LOSS>
-__global__ __launch_bounds__(256) void fullgrad_k1_narrow(FgArgs a) {
+// ALONE: one workgroup of up to sixteen waves does a chain's whole pass and writes its gradient and loss, without
+// partials and the launch that adds them up (small passes: a launch takes as long as they do).  It goes through
+// what the waves of the `parts` workgroups would have done, one such wave after the other, and adds up in their
+// order, so that the gradient is the same bits either way.
+constexpr int kAloneParts = 16;
+template <int G, int RB, int LOSS, bool ALONE>
+__global__ __launch_bounds__(ALONE ? 1024 : 256) void fullgrad_k1_narrow(FgArgs a) {
   constexpr int RW = 64 / G;       // rows per wave and group
   constexpr int BR = RB * RW;      // rows per batch
+  constexpr int QR = (RB + G - 1) / G;  // rows of a batch whose residual a lane evaluates
+  const int NW = ALONE ? (int)blockDim.x / 64 : 4;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane % G, rsel = lane / G;
@@ -229,80 +241,143 @@ __global__ __launch_bounds__(256) void fullgrad_k1_narrow(FgArgs a) {
 
   const int64_t nblk = (N + BR - 1) / BR;
   const int64_t stride = (int64_t)a.parts * 4;
-  int64_t bi = (int64_t)blockIdx.x * 4 + wave;
 
-  F4 xa[RB], xb[RB];
-  auto load_batch = [&](F4(&xv)[RB], int64_t blk) {
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      const int64_t row = blk * BR + r * RW + rsel;
-      xv[r] = make_f4(0.f, 0.f, 0.f, 0.f);
-      if (row < N) xv[r] = load_chunk<false>(X + row * ldx, col, d);
-    }
+  struct Batch {
+    F4 x[RB];
+    float y[QR];  // labels of the lane's rows
   };
-  auto reduce_batch = [&](F4(&xv)[RB], int64_t blk) {
+  // row q of the batch whose residual and loss this lane evaluates
+  auto row_of = [&](int64_t blk, int q) { return blk * BR + (sub + q * G) * RW + rsel; };
+  auto mine = [&](int64_t blk, int q) { return sub + q * G < RB && row_of(blk, q) < N; };
+  auto load_batch = [&](Batch& b, int64_t blk) {
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      const float m = group_sum(dot4(xv[r], wv, 0.f), G);  // phi_i, in all G lanes of the row
       const int64_t row = blk * BR + r * RW + rsel;
-      const bool ok = row < N;
-      const float yi = ok ? y[row] : 0.f;
+      b.x[r] = make_f4(0.f, 0.f, 0.f, 0.f);
+      if (row < N) b.x[r] = load_chunk<false>(X + row * ldx, col, d);
+    }
+#pragma unroll
+    for (int q = 0; q < QR; ++q) b.y[q] = y[mine(blk, q) ? row_of(blk, q) : 0];
+  };
+  auto reduce_batch = [&](Batch& b, int64_t blk) {
+    float m[QR];
+#pragma unroll
+    for (int q = 0; q < QR; ++q) m[q] = 0.f;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const float mr = group_sum(dot4(b.x[r], wv, 0.f), G);  // phi_i, in all G lanes of the row
+      m[r / G] = sub == r % G ? mr : m[r / G];
+    }
+    float res[QR];
+#pragma unroll
+    for (int q = 0; q < QR; ++q) {
+      const bool ok = mine(blk, q);
+      const float yi = b.y[q];
       float rr, li;
       if (LOSS == HALP_LOSS_SQUARED) {
-        rr = m - yi;
+        rr = m[q] - yi;
         li = 0.5f * rr * rr;
       } else {
-        rr = -yi / (1.0f + expf(yi * m));
-        const float sgn = -yi * m;
+        rr = -yi / (1.0f + expf(yi * m[q]));
+        const float sgn = -yi * m[q];
         li = fmaxf(sgn, 0.f) + log1pf(expf(-fabsf(sgn)));
       }
-      if (ok && sub == 0) {
-        phi[row] = m;
+      if (ok) {
+        phi[row_of(blk, q)] = m[q];
         loss_acc += (double)li;
       }
-      axpy4(ok ? rr : 0.f, xv[r], gv);
+      res[q] = ok ? rr : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) axpy4(__shfl(res[r / G], (lane & ~(G - 1)) + r % G), b.x[r], gv);
+  };
+  // the batches bi, bi + stride, ..: kept apart by name, so that a wait is for the oldest only
+  auto all_batches = [&](int64_t bi) {
+    Batch xa, xb;
+    if (bi < nblk) load_batch(xa, bi);
+    while (bi < nblk) {
+      const int64_t b1 = bi + stride;
+      if (b1 < nblk) load_batch(xb, b1);
+      reduce_batch(xa, bi);
+      if (b1 >= nblk) break;
+      const int64_t b2 = b1 + stride;
+      if (b2 < nblk) load_batch(xa, b2);
+      reduce_batch(xb, b1);
+      bi = b2;
+    }
+    // the wave's row groups hold partial gradients of the same columns: add them, group 0 ends
+    // up with the wave's sum (a fixed order)
+#pragma unroll
+    for (int off = 32; off >= G; off >>= 1) {
+      gv.x += __shfl_xor(gv.x, off); gv.y += __shfl_xor(gv.y, off);
+      gv.z += __shfl_xor(gv.z, off); gv.w += __shfl_xor(gv.w, off);
     }
   };
-
-  if (bi < nblk) load_batch(xa, bi);
-  while (bi < nblk) {
-    const int64_t b1 = bi + stride;
-    if (b1 < nblk) load_batch(xb, b1);
-    reduce_batch(xa, bi);
-    if (b1 >= nblk) break;
-    const int64_t b2 = b1 + stride;
-    if (b2 < nblk) load_batch(xa, b2);
-    reduce_batch(xb, b1);
-    bi = b2;
-  }
-
-  // the wave's row groups hold partial gradients of the same columns: add them, group 0 ends
-  // up with the wave's sum (a fixed order), likewise the loss
+  __shared__ F4 fold[ALONE ? 4 * kAloneParts : 4][G];
+  __shared__ double fold_loss[16];
+  auto wave_loss = [&]() {
 #pragma unroll
-  for (int off = 32; off >= G; off >>= 1) {
-    gv.x += __shfl_xor(gv.x, off); gv.y += __shfl_xor(gv.y, off);
-    gv.z += __shfl_xor(gv.z, off); gv.w += __shfl_xor(gv.w, off);
-    loss_acc += __shfl_xor(loss_acc, off);
-  }
-  __shared__ F4 fold[4][G];
-  __shared__ double fold_loss[4];
-  if (lane < G) fold[wave][lane] = gv;
-  if (lane == 0) fold_loss[wave] = loss_acc;
-  __syncthreads();
-  if (wave == 0 && lane < G) {
-#pragma unroll
-    for (int sw = 1; sw < 4; ++sw) {
-      const F4 o = fold[sw][lane];
-      gv.x += o.x; gv.y += o.y; gv.z += o.z; gv.w += o.w;
+    for (int off = 32; off > 0; off >>= 1) loss_acc += __shfl_xor(loss_acc, off);
+    if (lane == 0) fold_loss[wave] = loss_acc;
+  };
+
+  if constexpr (ALONE) {
+    for (int v = wave; v < 4 * a.parts; v += NW) {  // wave v % 4 of workgroup v / 4
+      gv = make_f4(0.f, 0.f, 0.f, 0.f);
+      all_batches(v);
+      if (lane < G) fold[v][lane] = gv;
     }
-    float* pg = a.partial_g + ((int64_t)chain * a.parts + blockIdx.x) * (int64_t)d;
-    if (col < d) pg[col] = gv.x;
-    if (col + 1 < d) pg[col + 1] = gv.y;
-    if (col + 2 < d) pg[col + 2] = gv.z;
-    if (col + 3 < d) pg[col + 3] = gv.w;
-    if (lane == 0)
-      a.partial_loss[(int64_t)chain * max(a.parts, a.loss_parts) + blockIdx.x] =
-          ((fold_loss[0] + fold_loss[1]) + fold_loss[2]) + fold_loss[3];
+    wave_loss();
+    __syncthreads();
+    const int k = threadIdx.x;
+    if (k < d) {
+      double part[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // in the order of fullgrad_reduce<8>
+      for (int p = 0; p < a.parts; ++p) {
+        float f = fold[4 * p][k / 4][k % 4];
+#pragma unroll
+        for (int sw = 1; sw < 4; ++sw) f += fold[4 * p + sw][k / 4][k % 4];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          if (p % 8 == q) part[q] += (double)f;
+      }
+      double t = part[0];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) t += part[q];
+      double gk = t / (double)N + a.lambda * (double)w[k];
+      if (a.fscale) gk = gk / (double)a.fscale[k];
+      a.g[(int64_t)chain * d + k] = (float)gk;
+    }
+    if (wave == NW - 1) {  // f(w~): data term plus lambda/2 ||w~||^2
+      double l = lane < NW ? fold_loss[lane] : 0.0, w2 = 0.0;
+      if (a.lambda != 0.0)
+        for (int j = lane; j < d; j += 64) w2 += (double)w[j] * (double)w[j];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        l += __shfl_xor(l, off);
+        w2 += __shfl_xor(w2, off);
+      }
+      if (lane == 0) a.scales[(int64_t)chain * 8 + 6] = l / (double)N + 0.5 * a.lambda * w2;
+    }
+  } else {
+    all_batches((int64_t)blockIdx.x * 4 + wave);
+    if (lane < G) fold[wave][lane] = gv;
+    wave_loss();
+    __syncthreads();
+    if (wave == 0 && lane < G) {
+#pragma unroll
+      for (int sw = 1; sw < 4; ++sw) {
+        const F4 o = fold[sw][lane];
+        gv.x += o.x; gv.y += o.y; gv.z += o.z; gv.w += o.w;
+      }
+      float* pg = a.partial_g + ((int64_t)chain * a.parts + blockIdx.x) * (int64_t)d;
+      if (col < d) pg[col] = gv.x;
+      if (col + 1 < d) pg[col + 1] = gv.y;
+      if (col + 2 < d) pg[col + 2] = gv.z;
+      if (col + 3 < d) pg[col + 3] = gv.w;
+      if (lane == 0)
+        a.partial_loss[(int64_t)chain * max(a.parts, a.loss_parts) + blockIdx.x] =
+            ((fold_loss[0] + fold_loss[1]) + fold_loss[2]) + fold_loss[3];
+    }
   }
 }
 
@@ -416,12 +491,24 @@ static int rows_per_batch(int d) {
   return nv >= 16 ? 1 : 16 / nv;
 }
 
+// One workgroup of sixteen waves per chain where that is as fast as several and their second launch.  us per pass,
+// one / several: 500 x 32 6.4 / 9.1, 1000 x 64 7.7 / 9.1, 2000 x 48 13.5 / 8.7; 64 chains of 4000 x 64 45 / 28; with a chain per
+// CU or more it has as many waves as the others.
+static bool narrow_alone(const halp_params& p, int parts, int num_cus) {
+  const int64_t n = p.N * (int64_t)p.d, few = p.loss == HALP_LOSS_LOGISTIC ? 32 : 64;
+  return p.K == 1 && p.d <= 128 && parts <= kAloneParts && (p.R >= num_cus || n <= (p.R >= 64 ? 96 : few) * 1024);
+}
+
 template <int G>
-int launch_narrow(const FgArgs& a, int loss, dim3 grid, hipStream_t s) {
-  if (loss == HALP_LOSS_SQUARED)
-    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_SQUARED>), grid, dim3(256), 0, s, a);
+int launch_narrow(const FgArgs& a, int loss, bool alone, dim3 grid, hipStream_t s) {
+  if (alone && loss == HALP_LOSS_SQUARED)
+    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_SQUARED, true>), dim3(1, grid.y), dim3(64 * std::min(16, 4 * a.parts)), 0, s, a);
+  else if (alone)
+    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_LOGISTIC, true>), dim3(1, grid.y), dim3(64 * std::min(16, 4 * a.parts)), 0, s, a);
+  else if (loss == HALP_LOSS_SQUARED)
+    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_SQUARED, false>), grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_LOGISTIC>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((fullgrad_k1_narrow<G, kNarrowGroups, HALP_LOSS_LOGISTIC, false>), grid, dim3(256), 0, s, a);
   return hip_ok(hipGetLastError());
 }
 
@@ -486,6 +573,8 @@ struct FgPlan {
   int loss_parts;  // entries per chain of partial_loss in use (its rows are max(parts, loss_parts) long)
   float* resid;    // [R][N][16] for the two-pass softmax form, else unused
   const uint32_t* xabsmax = nullptr;  // softmax: bits of the largest |X|, or null (fp32 products)
+  bool parts_set = false;             // parts is the caller's choice
+  int num_cus = 256;
 };
 
 static int launch_full_gradient_plan(const FgPlan& f, hipStream_t s) {
@@ -501,6 +590,9 @@ static int launch_full_gradient_plan(const FgPlan& f, hipStream_t s) {
   a.y_chain_stride = p.share_data ? 0 : p.N;
   a.d = p.d; a.K = p.K; a.parts = f.parts; a.fscale = f.fscale;
   a.loss_parts = f.loss_parts; a.resid = f.resid; a.xabsmax = f.xabsmax;
+  // (a count of workgroups that the caller has set stands)
+  const bool alone = !f.parts_set && narrow_alone(p, f.parts, f.num_cus);
+  if (alone) { a.g = buf.g; a.scales = buf.scales; a.lambda = p.lambda; }
   const dim3 grid(f.parts, p.R);
   const int nv = nv_for(p.d);
   if (p.loss == HALP_LOSS_SOFTMAX) {
@@ -509,10 +601,10 @@ static int launch_full_gradient_plan(const FgPlan& f, hipStream_t s) {
     rc = launch_fullgrad_k1_wide(a, p.loss, p.R, s);
   } else if (const int g = narrow_lanes(p.d)) {
     switch (g) {
-      case 4: rc = launch_narrow<4>(a, p.loss, grid, s); break;
-      case 8: rc = launch_narrow<8>(a, p.loss, grid, s); break;
-      case 16: rc = launch_narrow<16>(a, p.loss, grid, s); break;
-      default: rc = launch_narrow<32>(a, p.loss, grid, s); break;
+      case 4: rc = launch_narrow<4>(a, p.loss, alone, grid, s); break;
+      case 8: rc = launch_narrow<8>(a, p.loss, alone, grid, s); break;
+      case 16: rc = launch_narrow<16>(a, p.loss, alone, grid, s); break;
+      default: rc = launch_narrow<32>(a, p.loss, alone, grid, s); break;
     }
   } else {
     const bool exact = p.d == 256 * nv;
@@ -524,7 +616,7 @@ static int launch_full_gradient_plan(const FgPlan& f, hipStream_t s) {
       default: rc = launch_k1<16, 1>(a, p.loss, exact, grid, s); break;
     }
   }
-  if (rc != HALP_OK) return rc;
+  if (rc != HALP_OK || alone) return rc;
   RedArgs r;
   r.partial_g = f.partial_g; r.partial_loss = f.partial_loss; r.w = buf.w; r.g = buf.g;
   r.scales = buf.scales; r.N = p.N; r.n = p.K * p.d; r.parts = f.parts; r.lambda = p.lambda;
@@ -540,7 +632,7 @@ static int launch_full_gradient_plan(const FgPlan& f, hipStream_t s) {
 int launch_full_gradient(const halp_handle& h, hipStream_t s) {
   const bool halves = h.xabsmax && h.xabsmax_fresh && !h.gradient_fp32;
   const FgPlan f{&h.p, &h.buf, h.fscale, h.partial_g, h.partial_loss, h.parts, h.loss_parts, h.resid,
-                 halves ? h.xabsmax : nullptr};
+                 halves ? h.xabsmax : nullptr, h.fullgrad_blocks > 0, h.num_cus};
   return launch_full_gradient_plan(f, s);
 }
 
@@ -614,7 +706,7 @@ int launch_full_gradient_static(const halp_params& p, const halp_buffers& buf, h
   const size_t g_bytes = ((size_t)p.R * (size_t)parts * n * sizeof(float) + 255) / 256 * 256;
   float* partial_g = reinterpret_cast<float*>(ds.ptr);
   double* partial_loss = reinterpret_cast<double*>(ds.ptr + g_bytes);
-  const FgPlan f{&p, &buf, nullptr, partial_g, partial_loss, (int)parts, (int)parts, nullptr};
+  const FgPlan f{&p, &buf, nullptr, partial_g, partial_loss, (int)parts, (int)parts, nullptr, nullptr, false, ds.cus};
   return launch_full_gradient_plan(f, s);
 }
 

@@ -23,6 +23,10 @@ struct FgArgs {
   // softmax: bits of the largest |X| over the data (one word, device), or null if not known:
   // with it both products of the pass take their operands as pairs of halves
   const uint32_t* xabsmax = nullptr;
+  // where one workgroup does a chain's whole pass
+  float* g = nullptr;
+  double* scales = nullptr;
+  double lambda = 0.0;
 };
 
 // softmax: margins and gradient as two matrix products on the matrix cores
