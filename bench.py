@@ -150,7 +150,7 @@ def step_latency_floor(hp, torch, T, inner_ms, waves=4, steps=65536):
     per CU, and the share of it the measured inner loop reaches.  waves = 4: the several-wave form
     (multiply-adds, DPP fold, one LDS word per wave and a barrier, the fp64 path of gamma, the
     update).  waves = 1: the form with one chain wave (a row of 512 coordinates in four strips per
-    lane: packed dots, DPP fold, fp64 path, packed update, one LDS store; records from an LDS
+    lane: packed dots, DPP fold, one fp64 matrix instruction, packed update; records from an LDS
     ring, one barrier per 8 steps)."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     out = torch.empty(cus * waves * 64, dtype=torch.int32, device="cuda")
@@ -168,8 +168,8 @@ def step_latency_floor(hp, torch, T, inner_ms, waves=4, steps=65536):
     ns = best * 1e6 / steps
     what = ("critical path of a step (dot, DPP fold, LDS word + barrier, fp64 scalar path, update) "
             "measured alone" if waves > 1 else
-            "the chain wave's step (packed dots, DPP fold, fp64 scalar path, packed update, LDS store of "
-            "the unclamped strips; records from an LDS ring) measured alone")
+            "the chain wave's step (packed dots, DPP fold, fp64 matrix instruction, packed update; "
+            "records from an LDS ring) measured alone")
     return dict(kernel="step_latency_kernel" if waves > 1 else "step_latency_lone_kernel",
                 waves_per_chain=waves, chain_ns_per_step=ns,
                 bound_ms=ns * T * 1e-6, achieved_ms=inner_ms, frac=ns * T * 1e-6 / inner_ms,

@@ -339,9 +339,9 @@ int halp_debug_read_bandwidth(const void* p, int64_t bytes, uint32_t* out, void*
  * multiple of 8, >= 8) on lane constants; out (DEVICE) receives blocks * waves * 64 uint32.
  * Its time per step is the latency floor of the several-wave register kernels when a CU holds
  * one chain.  `waves` = 1: the chain of the form with one chain wave instead (a row of 512
- * coordinates, four strips per lane on packed 16-bit halves: packed dots, DPP fold, fp64 path,
- * packed update, one LDS store of the unclamped strips; records read from an LDS ring, one
- * barrier per 8 steps): the floor of that form.                                           */
+ * coordinates, four strips per lane on packed 16-bit halves: packed dots, DPP fold, one fp64
+ * matrix instruction, packed update; records read from an LDS ring, one barrier per 8 steps):
+ * the floor of that form.                                                                 */
 int halp_debug_step_latency(int32_t waves, int64_t steps, int32_t blocks, uint32_t* out,
                             void* stream);
 

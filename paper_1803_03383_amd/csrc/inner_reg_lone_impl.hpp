@@ -29,12 +29,12 @@
 // the low b bits of -h~ and the chain wave adds the rest behind the shift (FOLD = false; five
 // instructions per strip).  A service wave refills the 256-step batches of step-indexed draws
 // (sample indices, rounding draws of gamma and of the L2 term, margins and labels of the
-// sampled rows) and counts the clamped coordinates: the chain wave stores the n of a step in LDS
-// and the service wave, which holds a z of its own, adds them up a window later with and without
-// saturation.  One barrier per window orders every hand-over: in period w the chain wave consumes
-// window w out of a ring of three and fills one half of the log, while the helpers make window
-// w + 2 and the service wave reads the other half of the log (window w - 1).  The third slot lets
-// the chain wave request the first record of a window before the barrier.
+// sampled rows) and counts the clamped coordinates: the chain wave stores the gammas of a window in
+// LDS and the service wave, which holds a z of its own, takes it through the same steps with and
+// without saturation.  One barrier per window orders every hand-over: in period w the chain wave
+// consumes window w out of a ring of four and requests the first records of window w + 1 before the
+// barrier, the helpers make window w + 2, and the service wave takes the records of window w - 1 out
+// of the ring and goes through window w - 2.
 //
 // The chain wave is wave 0; the helpers and the service wave are placed on the other three
 // SIMDs (waves w and w + 4 of a workgroup share a SIMD: wave 4 only keeps the barriers).

@@ -9,6 +9,7 @@
 // (`waves` = 2 or 4; `waves` = 1 runs the chain of the one-chain-wave form, further down).
 #include "halp_device.hpp"
 #include "halp_internal.hpp"
+#include "inner_reg_lone_impl.hpp"
 
 namespace halp {
 namespace {
@@ -75,79 +76,89 @@ __global__ __launch_bounds__(64 * NW) void step_latency_kernel(int64_t steps, do
   out[blockIdx.x * 64 * NW + tid] = (uint32_t)(z0 * 131 + z1);
 }
 
-// The same for the form with ONE chain wave that holds a row of 512 coordinates (four strips
-// per lane, two coordinates per register): per step one packed dot per strip, the DPP fold, the
-// sum read from lane 63, the fp64 path of gamma, the update on packed 16-bit halves and one LDS
-// store of the unclamped strips; the step's record (row values and rounding terms) comes from
-// an LDS ring that nobody refills, read one step ahead; one barrier per window of 8 steps.
+// The same for the form with ONE chain wave, at a row of 512 coordinates (four strips per lane, two
+// coordinates per register): per step one packed dot per strip, the DPP fold over 16 lanes, the fp64
+// matrix instruction that adds up the rows of lanes and does the multiply-add of gamma, the clamp of
+// its high word and three instructions per strip for the update; gammas go to LDS two at a time and a window of
+// 8 steps ends with the look at its fractions and a barrier.  A step's record (row values and
+// rounding terms) and its rounding draw come from an LDS ring that nobody refills, two steps ahead.
 __global__ __launch_bounds__(64) void step_latency_lone_kernel(int64_t steps, double dscale, double aB,
                                                               double inv_s, uint32_t* out) {
+  using S = innerlone::Strip<8>;
+  using innerlone::int2r;
+  using innerlone::int4r;
   constexpr int UPL = 4;
-  typedef short S2 __attribute__((ext_vector_type(2)));
-  typedef int I4 __attribute__((ext_vector_type(4)));
   const int lane = threadIdx.x & 63;
-  __shared__ __attribute__((aligned(16))) I4 s_rec[8][2][64];  // [step][values | rounding terms][lane]
-  __shared__ __attribute__((aligned(16))) I4 s_log[8][64];
+  __shared__ __attribute__((aligned(16))) int4r s_rec[8][2][64];  // [step][values | rounding terms][lane]
+  __shared__ double s_c[8];
+  __shared__ __attribute__((aligned(16))) int s_hi[8];
   for (int s = 0; s < 8; ++s) {
-    I4 xv, cv;
+    int4r xv, cv;
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
       const int a = ((lane * 13 + s * 5 + u) % 11) - 5, b = ((lane * 17 + s * 3 + u) % 13) - 6;
-      xv[u] = (a & 0xFFFF) | (b << 16);
-      cv[u] = ((lane * 29 + s * 37 + u) & 511) | (((lane * 31 + s * 11 + u) & 511) << 16);
+      xv[u] = S::join(a, b);
+      cv[u] = S::join((lane * 29 + s * 37 + u) & 511, (lane * 31 + s * 11 + u) & 511);
     }
     s_rec[s][0][lane] = xv;
     s_rec[s][1][lane] = cv;
   }
-  S2 zp[UPL];
+  if (lane < 8) s_c[lane] = innerlone::kDraw - 0.37;
+  int zp[UPL];
 #pragma unroll
-  for (int u = 0; u < UPL; ++u) zp[u] = S2{(short)((lane * 7 + u) & 7), (short)(-((lane * 3 + u) & 3))};
-  const double rho = 0.37;
+  for (int u = 0; u < UPL; ++u) zp[u] = S::join(((lane * 7 + u) & 7) << 8, -((lane * 3 + u) & 3) * 256);
+  const double scale_t = -dscale * aB * inv_s * 0x1p-8;
+  struct Step {
+    int4r x, r;
+    double c;
+  };
+  Step ahead[2];
   __syncthreads();
+  auto load_step = [&](Step& st, int s) __attribute__((always_inline)) {
+    st.x = s_rec[s][0][lane];
+    st.r = s_rec[s][1][lane];
+    st.c = s_c[s];
+  };
+  load_step(ahead[0], 0);
+  load_step(ahead[1], 1);
   for (int64_t t = 0; t < steps; t += 8) {
-    I4 rx = s_rec[0][0][lane], rc = s_rec[0][1][lane];
+    int zsave[UPL];
+#pragma unroll
+    for (int u = 0; u < UPL; ++u) zsave[u] = zp[u];
+    uint32_t nearest = 0xFFFFFFFFu;
+    int hi_even = 0;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      S2 xp[UPL], crp[UPL];
+      const Step st = ahead[s % 2];
+      int p0 = S::dot(st.x[0], zp[0]), p1 = S::dot(st.x[1], zp[1]);
+      p0 = S::dot(st.x[2], zp[2], p0);
+      p1 = S::dot(st.x[3], zp[3], p1);
+      int v = p0 + p1;
+      v += dpp_quad_swap1(v);
+      v += dpp_quad_swap2(v);
+      v += dpp_half_mirror(v);
+      v += dpp_row_mirror(v);
+      const uint64_t bits = __builtin_bit_cast(uint64_t, __builtin_amdgcn_mfma_f64_4x4x4f64((double)v, scale_t, st.c, 0, 0, 0));
+      __builtin_amdgcn_sched_barrier(0);
+      load_step(ahead[s % 2], (s + 2) % 8);
+      __builtin_amdgcn_sched_barrier(0);
+      const int hi = (int)(bits >> 32);
+      nearest = (uint32_t)bits < nearest ? (uint32_t)bits : nearest;
+      const int g = min(max(hi, innerlone::kMagicHi - 127), innerlone::kMagicHi + 128);
+      if (s & 1) *reinterpret_cast<int2r*>(&s_hi[s - 1]) = int2r{hi_even, hi};
+      else hi_even = hi;
 #pragma unroll
-      for (int u = 0; u < UPL; ++u) {
-        const int xe = rx[u], ce = rc[u];
-        xp[u] = __builtin_bit_cast(S2, xe);
-        crp[u] = __builtin_bit_cast(S2, ce);
-      }
-      if (s + 1 < 8) {
-        rx = s_rec[s + 1][0][lane];
-        rc = s_rec[s + 1][1][lane];
-      }
-      int p0 = 0, p1 = 0;
-#pragma unroll
-      for (int u = 0; u < UPL; u += 2) {
-        p0 = __builtin_amdgcn_sdot2(xp[u], zp[u], p0, false);
-        p1 = __builtin_amdgcn_sdot2(xp[u + 1], zp[u + 1], p1, false);
-      }
-      const int D = wave_sum_i32(p0 + p1);
-      const double delta = __dmul_rn(dscale, (double)D);
-      const double beta = __dmul_rn(aB, delta);
-      const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
-      int nf;
-      asm("v_cvt_i32_f64 %0, -%1" : "=v"(nf) : "v"(f));
-      const int ng = min(max(nf, -127), 128);
-      const S2 ngp = S2{(short)ng, (short)ng};
-      I4 vq;
-#pragma unroll
-      for (int u = 0; u < UPL; ++u) {
-        S2 v = xp[u] * ngp + crp[u];
-        v = (v >> (S2)(8)) + zp[u];  // the rounding term of the record carries the whole of -h~
-        vq[u] = __builtin_bit_cast(int, v);
-        zp[u] = __builtin_elementwise_min(__builtin_elementwise_max(v, (S2)(-128)), (S2)(127));
-      }
-      s_log[s][lane] = vq;
+      for (int u = 0; u < UPL; ++u) zp[u] = S::add_sat(zp[u], S::mad(st.x[u], g, st.r[u])) & S::kMask;
     }
-    __syncthreads();
-  }
-  uint32_t acc = (uint32_t)s_log[7][lane][0];
+    if (__builtin_expect(__ballot(nearest <= 2 * innerlone::kNear) != 0, 0)) {
 #pragma unroll
-  for (int u = 0; u < UPL; ++u) acc = acc * 131u + __builtin_bit_cast(uint32_t, zp[u]);
+      for (int u = 0; u < UPL; ++u) zp[u] = zsave[u];
+    }
+    asm volatile("s_barrier" ::: "memory");
+  }
+  uint32_t acc = (uint32_t)s_hi[7];
+#pragma unroll
+  for (int u = 0; u < UPL; ++u) acc = acc * 131u + (uint32_t)zp[u];
   out[blockIdx.x * 64 + threadIdx.x] = acc;
 }
 
