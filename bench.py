@@ -559,16 +559,17 @@ def main():
     inner_ms, fg_ms = stats.ms_inner_loop, stats.ms_full_gradient
     # fp32 SVRG: one FMA for the dot, one FMA and one subtraction for the update per coordinate
     laneops = 3.0 if args.algorithm == "svrg" else LANEOPS_PER_UPDATE_B8
-    # at the headline shape (few chains, four waves each) the register kernel with helper waves runs
-    # the library's launch rule at 8 bits, restated: one chain wave + helpers on the other SIMDs for
-    # rows of 129 .. 512 coordinates up to two chains per CU (.. 1024 up to one); chain waves with a helper beside each
-    # up to five chains per CU; one wave per chain beyond
+    # the library's launch rule at 8 bits and squared loss, restated: one chain wave + helpers on the other
+    # SIMDs for rows of up to 1024 coordinates as far as its chains per CU go; chain waves with a helper
+    # beside each up to five chains per CU; one wave per chain beyond
+    per_cu = 1 if d > 512 else (2 if d > 256 else (3 if 64 < d <= 128 else 6))
     lone = (args.algorithm != "svrg" and d <= 1024 and
-            (args.inner_helpers == 3 or (args.inner_helpers == 0 and args.inner_waves == 0 and 128 < d
-                                         and R <= (2 if d <= 512 else 1) * 256)))
+            (args.inner_helpers == 3 or
+             (args.inner_helpers == 0 and args.inner_waves == 0 and R <= per_cu * 256)))
     helped = (not lone and args.algorithm != "svrg" and args.inner_helpers in (0, 1)
               and args.inner_waves in (0, 2, 4) and d <= 1024 and (R <= 5 * 256 or args.inner_helpers == 1))
-    inner_kernel = "inner_svrg_kernel" if args.algorithm == "svrg" else (
+    svrg_lone = args.inner_waves == 0 and R <= (1 if d > 512 else (2 if d > 256 else (8 if d > 64 else 5))) * 256
+    inner_kernel = ("inner_svrg_lone_kernel" if svrg_lone else "inner_svrg_kernel") if args.algorithm == "svrg" else (
         "inner_reg_lone_kernel" if lone else ("inner_reg_helped_kernel" if helped else "inner_reg_kernel"))
     alu_achieved = updates * laneops / (inner_ms * 1e-3)
     fg_bytes = (1 if cfg.get("share_data") else R) * N * (4 * d + 4 + 4) + \
