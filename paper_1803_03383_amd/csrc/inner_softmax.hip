@@ -24,9 +24,10 @@
 //                 fragment unpacked, the next requests                                 | barrier
 //   class waves   integer update of row c of z
 //
-// What bounds it: the dependent chain dot, fold, LDS, softmax (~70 dependent fp64 operations,
-// 700 cycles), LDS, update, with the issue slots of the SIMD that has most class waves next to
-// it: three waves of 784 coordinates take 920 cycles for update and dot where one takes 630.
+// What bounds it: the dependent chain dot, fold, LDS, softmax (the short chain of softmax_fused.hpp,
+// ~350 cycles), LDS, update, with the issue slots of the SIMD that has most class waves next to
+// it: three waves of 784 coordinates take 920 cycles for update and dot where one takes 630, and
+// at ten classes of that width these slots are the longer part.
 // So the class waves' instructions are kept few: coordinates in pairs (packed 16-bit update at
 // 8 bits, z biased so that one test of the wave finds a clamp), requests with a scalar base, the
 // rare paths (a clamp, an L2 draw) behind one branch each.
@@ -36,6 +37,8 @@
 // 784 x 16 at 8 bits 3.92 -> 1.13; 1000 x 15 at 16 bits 29.8 -> 3.1; 300 x 4 at 8 bits
 // 0.91 -> 0.57; 64 x 2 at 16 bits 0.75 -> 0.56.  With 256 chains, where making the records
 // takes the whole chip's issue slots too: 784 x 10 at 8 bits 1.38 -> 1.45, at 16 bits 3.2 -> 2.35.
+// With the short chain to the gammas instead of the fixed order's ~90 dependent fp64 instructions, at 8 bits:
+// 784 x 10 0.889 -> 0.870, 300 x 4 0.570 -> 0.477, 64 x 2 0.499 -> 0.407, 1024 x 15 0.954 -> 0.875, 784 x 16 1.090 -> 0.973.
 #include <algorithm>
 
 #include "halp_device.hpp"
