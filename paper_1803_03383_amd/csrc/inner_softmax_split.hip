@@ -137,9 +137,13 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     // The step's gammas come from the short chain of softmax_fused.hpp, which has its classes in other lanes:
     // what is made one class per lane of the first sixteen goes there through LDS's lane exchange, beside the
     // trip of the sums.
-    const int rc = soft_class(lane);
-    const bool live_f = rc < K;
-    const bool fused = soft_covers(dscale, aB, inv_s);
+    // Not at 16 bits with eight strips per lane, where the class waves' registers are the most and a step got longer with
+    // it: us per step, short chain / fixed order, K = 10: 10000 one chain 3.52 / 3.32, five 3.70 / 3.49, 6500 three 3.13 / 3.09;
+    // with four strips 2000 x 10 2.15 / 2.16, 4000 x 5 2.46 / 2.47.
+    constexpr bool kShort = !(BITS == 16 && UPL == 8);
+    const int rc = kShort ? soft_class(lane) : lc;
+    const bool live_f = kShort ? rc < K : live;
+    const bool fused = kShort && soft_covers(dscale, aB, inv_s);
     const double k2 = __dmul_rn(aB, inv_s);
     auto to_lane = [&](int src, int v) { return __builtin_amdgcn_ds_bpermute(src << 2, v); };
     auto to_lane64 = [&](int src, uint64_t v) {
@@ -167,6 +171,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     SoftDraw dr_n{};
     double from_n = 0.0;
     auto draw_fused = [&]() {
+      if constexpr (!kShort) return;
       const float ph = __builtin_bit_cast(float, to_lane(rc, __builtin_bit_cast(int, (float)a0_n)));
       const double p = __builtin_bit_cast(double, to_lane64(rc, __builtin_bit_cast(uint64_t, p0_n)));
       dr_n = soft_draw<true>(live_f, p, ph, (uint32_t)to_lane(rc, (int)word_n), k2);
@@ -208,12 +213,12 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
           old[s & 1] = v;
           int hi = 0;
           if (__builtin_expect_with_probability(
-                  fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
+                  kShort && fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
             const int g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
             s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
             n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
           } else {  // in the fixed order of roundings, classes in the first lanes
-            const long long Dc = (long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D);
+            const long long Dc = kShort ? (long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D) : D;
             const double moved = __dmul_rn(dscale, (double)Dc);
             const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
             // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
