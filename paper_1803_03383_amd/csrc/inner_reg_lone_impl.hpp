@@ -123,15 +123,13 @@ struct Strip<8> {
     return __builtin_bit_cast(int, __builtin_bit_cast(ushort2r, sat ^ wrapped) >> (ushort2r)(15));
   }
   static __device__ __forceinline__ unsigned int counted(int acc) { return (unsigned int)(acc & 0xFFFF) + ((unsigned int)acc >> 16); }
-  // x^T z of a strip, times 2^b, added to acc
+  // x^T z of a strip, times 2^b, added to acc.  The saturating form, in which a zero to start from needs no register;
+  // a lane's sum is at most 2^26.  (The instruction is the compiler's to place: a dot's result wants three wait states
+  // before another kind of dot reads it, which the compiler keeps only between dots that it knows of)
   static __device__ __forceinline__ int dot(int x, int z, int acc) {
-    return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2r, x), __builtin_bit_cast(short2r, z), acc, false);
+    return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2r, x), __builtin_bit_cast(short2r, z), acc, true);
   }
-  static __device__ __forceinline__ int dot(int x, int z) {  // as an instruction: the compiler's form wants a zeroed register
-    int r;
-    asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "v"(z));
-    return r;
-  }
+  static __device__ __forceinline__ int dot(int x, int z) { return dot(x, z, 0); }
   // the row value and the addend of a record from the strip's two bytes (at `at` bytes into a fragment) and
   // the 16 rounding bits of step s; add: what the record adds to them
   static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t word, int s, int add, int* x, int* c) {
