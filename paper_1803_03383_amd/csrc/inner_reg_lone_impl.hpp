@@ -352,8 +352,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     // the gammas that the chain wave leaves in s_hi; a coordinate was clamped where the sums with and
     // without saturation differ.  The records of window w are taken out of the ring in period w + 1
     // and gone through in period w + 2, when the chain wave's stores have landed for certain.
-    unsigned int n_lane = 0;    // this lane's count of clamped coordinates
-    unsigned int n_gclamp = 0;  // clamped gammas
+    unsigned long long n_lane = 0;  // this lane's count of clamped coordinates: up to 16 of a step, of up to 2^32 steps
+    unsigned int n_gclamp = 0;      // clamped gammas
     RecV r[kWin][NQ];
     auto take = [&](int64_t w) __attribute__((always_inline)) {
 #pragma unroll
@@ -418,11 +418,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     };
     if (s_fold) run(std::true_type{});
     else run(std::false_type{});
-    const unsigned int total = (unsigned int)wave_sum_i32(lane < LANES ? (int)n_lane : 0);
-    if (lane == 0) {
-      s_cnt[0] = total;
-      s_cnt[1] = n_gclamp;
-    }
+    if (lane < LANES) atomicAdd(&s_cnt[0], n_lane);  // (it stood at 0 behind P0)
+    if (lane == 0) s_cnt[1] = n_gclamp;
     __syncthreads();  // the counters
     return;
   }

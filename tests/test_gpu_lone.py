@@ -5,6 +5,7 @@ import pytest
 
 import paper_1803_03383_amd as hp
 import test_gpu_svrg
+from gpu_util import GpuProblem
 from oracle import ref
 from test_gpu_parity import _inner_case, _oracle_inner, _run_inner
 
@@ -85,3 +86,18 @@ def test_sixteen_bits_one_to_eight_strips_per_lane(loss, d, lam, T, mu):
 def test_full_precision_chain_wave(loss, d, lam, R, T):
     """One, two and four float4s per lane, whole and ragged rows, the L2 term, epochs around windows and batches."""
     test_gpu_svrg.test_inner_loop_matches_the_oracle(loss, 120, d, lam, R, T, 0)
+
+
+@pytest.mark.parametrize("d,b", [(1024, 8), (512, 16)])
+def test_more_than_two_to_the_32_clamped_coordinates(d, b):
+    """Rows of zeros and an offset that pushes every coordinate out of the box in every step: d T clamps."""
+    T = 2 ** 32 // d + 21
+    P = GpuProblem(np.zeros((1, 4, d), np.float32), np.zeros((1, 4, d), np.int8), np.zeros((1, 4), np.float32),
+                   b=b, T=T, alpha=0.02, mu=0.2, delta_d=1.0, seed=5)
+    lowest = -2 ** (b - 1)
+    P.put("z", np.full((1, 1, d), lowest))
+    P.put("h", np.full((1, 1, d), 2 ** (2 * b - 1) - 1 if b == 8 else 2 ** 30))
+    P.put("scales", np.full((1, 8), 1.0) * (np.arange(8) < 6))
+    P.h.inner_loop(3)
+    assert (P.get("z") == lowest).all()
+    assert P.get("counters")[0].tolist() == [T * d, 0, 0, 0]
