@@ -10,7 +10,9 @@ int launch_inner_reg_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s)
 int launch_inner_reg_helped_b8(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_helped_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_lone_b8(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
-int launch_inner_reg_lone_b16(const InArgs& a, int upl, int R, bool pair, hipStream_t s);
+int launch_inner_reg_lone_b8_l2(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
+int launch_inner_reg_lone_b16(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
+int launch_inner_reg_lone_b16_l2(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
 
 namespace {
 
@@ -130,8 +132,10 @@ int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   const Lone lone = lone_shape(h);
   const bool lone_forced = h.inner_helpers == 3 && p.b == 8;
   if (lone.upl > 0 && (lone_forced || (h.inner_helpers == 0 && h.inner_waves == 0 && lone_pays(h, lone)))) {
-    if (p.b == 16) return launch_inner_reg_lone_b16(a, lone.upl, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);
-    return launch_inner_reg_lone_b8(a, lone.upl, lone.lanes, p.R, (int64_t)p.R > (int64_t)h.num_cus, s);  // more chains than CUs: the build with at most 128 registers
+    const bool pair = (int64_t)p.R > (int64_t)h.num_cus;  // the build with at most 128 registers
+    const auto launch = p.b == 8 ? (p.lambda > 0 ? launch_inner_reg_lone_b8_l2 : launch_inner_reg_lone_b8)
+                                 : (p.lambda > 0 ? launch_inner_reg_lone_b16_l2 : launch_inner_reg_lone_b16);
+    return launch(a, lone.upl, lone.lanes, p.R, pair, s);
   }
   if (h.inner_helpers == 3) return HALP_ERR_UNSUPPORTED;
   Shape sh = pick_shape(p, auto_waves(h));

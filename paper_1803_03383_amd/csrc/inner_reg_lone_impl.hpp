@@ -20,7 +20,8 @@
 //           else is the same integer in both, so results are those of the other kernels bit for bit
 //   update  z is kept as 2^b z: n = -gamma x + r - h~, z <- saturating (z + n) with the low b bits
 //           cleared -- the saturation of the 16-bit (b = 8) or 32-bit add is the box.  Three
-//           instructions per strip
+//           instructions per strip.  An L2 draw cl takes -cl z along in the addend, r - h~ - cl z, made
+//           while the dot is under way: two more instructions per strip in every step of an epoch that has draws
 // Whatever does not depend on z is made by the helpers, up to two windows of 8 steps ahead, and
 // handed over through LDS as one record per lane and step: per strip the sign-extended row
 // values and r - h~.  A helper serves one or two of the strips of every lane: it draws their Philox
@@ -39,7 +40,8 @@
 // The chain wave is wave 0; the helpers and the service wave are placed on the other three
 // SIMDs (waves w and w + 4 of a workgroup share a SIMD: wave 4 only keeps the barriers).
 //
-// This header holds the kernel template, inner_reg_lone_b8.hip and inner_reg_lone_b16.hip instantiate it.
+// This header holds the kernel template, inner_reg_lone_b8.hip and inner_reg_lone_b16.hip instantiate it, and the
+// same with _l2 the builds for lambda > 0.
 #pragma once
 
 #include "inner_reg_impl.hpp"
@@ -92,7 +94,9 @@ struct Strip<8> {
   using Z = int8_t;
   using H = int16_t;
   static constexpr int kMask = (int)0xFF00FF00;
-  static constexpr int kSmallLow = -64, kSmallHigh = 62;  // high parts of -h~ that may ride in the records
+  // high parts of -h~ that may ride in the records: n stays inside its word; with L2 draws of up to kMaxDraw
+  static constexpr int kSmallLow = -64, kSmallHigh = 62;
+  static constexpr int kMaxDraw = 32, kSmallLowReg = -48, kSmallHighReg = 46;
   // n = -gamma x + c; g: kMagicHi - gamma, whose low half is -gamma
   static __device__ __forceinline__ int mad(int x, int g, int c) {
     const short2r gp = short2r{(short)g, (short)g};
@@ -151,6 +155,7 @@ struct Strip<16> {
   using H = int32_t;
   static constexpr int kMask = (int)0xFFFF0000;
   static constexpr int kSmallLow = -16000, kSmallHigh = 16000;
+  static constexpr int kMaxDraw = 4096, kSmallLowReg = -14000, kSmallHighReg = 14000;
   // The 24-bit multiplier takes g = kMagicHi - gamma as it is, i.e. kOffset - gamma; the records carry
   // c - kOffset x, and everything is exact modulo 2^32, where n lies.
   static constexpr int kOffset = kMagicHi & 0xFFFFFF;
@@ -174,7 +179,8 @@ struct Strip<16> {
 
 // LANES: lanes that share a row of z, 64 or 16 (four copies of the same work in a wave).
 // PAIR: built for several workgroups per CU (more chains than CUs), at most 128 registers per lane.
-template <int BITS, int LOSS, int UPL, int LANES, bool PAIR>
+// REG: lambda > 0, steps may have L2 draws.
+template <int BITS, int LOSS, int UPL, int LANES, bool PAIR, bool REG>
 __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner_reg_lone_kernel(InArgs a) {
   static_assert((UPL == 2 && (LANES == 64 || BITS == 8)) || (LANES == 64 && (UPL == 4 || UPL == 8 || (UPL == 1 && BITS == 16))), "the forms that are launched");
   using S = Strip<BITS>;
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 
   __shared__ __attribute__((aligned(16))) int s_idx[2 * kBatch];
   __shared__ __attribute__((aligned(16))) double s_c[2 * kBatch];  // kDraw - rho
-  __shared__ __attribute__((aligned(16))) short s_creg[2 * kBatch];
+  __shared__ __attribute__((aligned(16))) short s_ncl[REG ? 2 * kBatch : 8];  // L2 draws, negated
   constexpr bool kMargins = LOSS != HALP_LOSS_SQUARED;
   __shared__ __attribute__((aligned(16))) float s_phi[kMargins ? 2 * kBatch : 4];
   __shared__ __attribute__((aligned(16))) float s_y[logistic_c<LOSS> ? 2 * kBatch : 4];
@@ -251,17 +257,19 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   const double delta_m = sc[0], inv_s = sc[5];
   const double dscale = __dmul_rn(a.delta_d, delta_m);
   const double aB = a.hyper[2 * chain];  // B = 1: alpha / 1
-  const bool use_reg = a.lambda > 0;
   constexpr bool logistic = LOSS == HALP_LOSS_LOGISTIC;
   constexpr bool need_phi = LOSS != HALP_LOSS_SQUARED;
   const bool lp = a.lp != 0;
   const double al = __dmul_rn(aB, a.lambda);
+  // a draw is at most floor(al 2^b) + 1 (larger ones: every step in the fixed order, in wide arithmetic)
+  const bool reg_small = REG && al * (double)(1 << BITS) < (double)S::kMaxDraw;
 
   if (tid < 4) s_cnt[tid] = 0;
 
   // z of a lane's strips times 2^b, the coordinates that exist, and the high part of -h~; true where every
   // high part is small.  With -h~ = 2^b hh + hl, 0 <= hl < 2^b, and every hh in [-64, 62] (16 bits: [-16000, 16000]),
-  // n = -gamma x + r - h~ fits its word of 2 b bits (|gamma x| <= 2^(2b-2), 0 <= r < 2^b).
+  // n = -gamma x + r - h~ fits its word of 2 b bits (|gamma x| <= 2^(2b-2), 0 <= r < 2^b); with an L2 draw
+  // cl <= 32 (4096) n has another cl z, |cl z| <= 2^12 (2^27), and hh lies in [-48, 46] ([-14000, 14000]).
   auto load_z = [&](int (&zp)[UPL], int (&mask)[UPL], int (&hh)[UPL]) -> bool {
     bool small = true;
 #pragma unroll
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         zv[e] = ok ? (int)zg[ok ? j : 0] << BITS : 0;
         mv[e] = ok ? S::kMask : 0;
         hv[e] = ok ? (int)((-(int64_t)hg[ok ? j : 0]) >> BITS) : 0;
-        small = small && hv[e] >= S::kSmallLow && hv[e] <= S::kSmallHigh;
+        small = small && hv[e] >= (REG ? S::kSmallLowReg : S::kSmallLow) && hv[e] <= (REG ? S::kSmallHighReg : S::kSmallHigh);
       }
       zp[u] = S::join(zv[0], zv[1]);
       mask[u] = S::join(mv[0], mv[1]);
@@ -288,16 +296,20 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     if constexpr (decltype(fold_tag)::value) return S::add_sat(z, n) & mask;
     else return S::clamp_up(S::shifted(n, S::add(hh, S::high(z)))) & mask;
   };
-  // the same of a step with an L2 draw (rare), in wide arithmetic on the coordinates; g here is -gamma itself
-  auto step_strip_reg = [&](int z, int x, int g, int cl, int c, int hh, int mask, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
+  // the addend of a step with an L2 draw; ncl: -cl
+  auto with_draw = [&](int z, int ncl, int c) __attribute__((always_inline)) -> int { return S::mad(S::high(z), ncl, c); };
+  // z <- Q(z - gamma x - h~ - cl z) in wide arithmetic on the coordinates, for draws of any size (steps in the
+  // fixed order); g here is -gamma itself
+  using Wide = typename std::conditional<BITS == 8, int, int64_t>::type;
+  auto step_strip_reg = [&](int z, int x, int g, int ncl, int c, int hh, int mask, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
     int zn[2] = {0, 0};
     const int cc = S::addend(c, x);
 #pragma unroll
     for (int e = 0; e < CT; ++e) {
-      const int64_t zk = S::value(z, e) >> BITS, xk = S::value(x, e);
-      const int64_t hr = (decltype(fold_tag)::value ? 0 : (int64_t)S::value(hh, e) << BITS) + S::value(cc, e);
-      const int64_t zuk = zk + ((g * xk - cl * zk + hr) >> BITS);
-      const int64_t zc = zuk < QMIN ? QMIN : (zuk > QMAX ? QMAX : zuk);
+      const Wide zk = S::value(z, e) >> BITS, xk = S::value(x, e);
+      const Wide hr = (decltype(fold_tag)::value ? 0 : (Wide)S::value(hh, e) << BITS) + S::value(cc, e);
+      const Wide zuk = zk + ((g * xk + ncl * zk + hr) >> BITS);
+      const Wide zc = zuk < QMIN ? QMIN : (zuk > QMAX ? QMAX : zuk);
       if (clamped) *clamped += (S::value(mask, e) != 0 && zuk != zc) ? 1 : 0;
       zn[e] = (int)zc << BITS;
     }
@@ -337,15 +349,15 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       s_c[half + 4 * lane + 1] = magic(rg.y);
       s_c[half + 4 * lane + 2] = magic(rg.z);
       s_c[half + 4 * lane + 3] = magic(rg.w);
-      if (use_reg) {
+      if constexpr (REG) {
         const U4 rr = stream_block(seed, kReg, a.epoch, blk);
         const double two_b = (double)(1 << BITS);
         short4 cv;
-        cv.x = (short)quantize_real(al, two_b, rr.x, 0.0, (double)QMAX, nullptr);
-        cv.y = (short)quantize_real(al, two_b, rr.y, 0.0, (double)QMAX, nullptr);
-        cv.z = (short)quantize_real(al, two_b, rr.z, 0.0, (double)QMAX, nullptr);
-        cv.w = (short)quantize_real(al, two_b, rr.w, 0.0, (double)QMAX, nullptr);
-        *reinterpret_cast<short4*>(&s_creg[half + 4 * lane]) = cv;
+        cv.x = (short)-quantize_real(al, two_b, rr.x, 0.0, (double)QMAX, nullptr);
+        cv.y = (short)-quantize_real(al, two_b, rr.y, 0.0, (double)QMAX, nullptr);
+        cv.z = (short)-quantize_real(al, two_b, rr.z, 0.0, (double)QMAX, nullptr);
+        cv.w = (short)-quantize_real(al, two_b, rr.w, 0.0, (double)QMAX, nullptr);
+        *reinterpret_cast<short4*>(&s_ncl[half + 4 * lane]) = cv;
       }
     };
     // Clamped coordinates: this wave holds a z of its own and takes it through the steps once more, with
@@ -354,6 +366,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     // and gone through in period w + 2, when the chain wave's stores have landed for certain.
     unsigned long long n_lane = 0;  // this lane's count of clamped coordinates: up to 16 of a step, of up to 2^32 steps
     unsigned int n_gclamp = 0;      // clamped gammas
+    unsigned int n_reg = 0;         // steps with an L2 draw
     RecV r[kWin][NQ];
     auto take = [&](int64_t w) __attribute__((always_inline)) {
 #pragma unroll
@@ -362,30 +375,37 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         for (int q = 0; q < NQ; ++q) r[s][q] = *rec_at((int)(w & (kSlots - 1)), s, q);
     };
     int part = 0;  // of s_hi, the next to be counted
-    auto count_steps = [&](int64_t w, int steps, auto full_tag, auto fold_tag) __attribute__((always_inline)) {
-      constexpr bool FULL = decltype(full_tag)::value;  // eight steps, none of them with an L2 draw
+    // kind_tag: 0 no L2 draws, 1 draws of up to kMaxDraw, in eight steps; 2 whatever there is, in `steps` of them
+    auto count_steps = [&](int64_t w, int steps, auto kind_tag, auto fold_tag) __attribute__((always_inline)) {
+      constexpr int KIND = decltype(kind_tag)::value;
+      const int base = (int)((w * kWin) & kMask);
       const int4r h0 = *reinterpret_cast<const int4r*>(&s_hi[part][0]), h1 = *reinterpret_cast<const int4r*>(&s_hi[part][4]);
       const int hi[kWin] = {h0[0], h0[1], h0[2], h0[3], h1[0], h1[1], h1[2], h1[3]};
+      int4r nc = int4r{0, 0, 0, 0};
+      if constexpr (KIND == 1) nc = *reinterpret_cast<const int4r*>(&s_ncl[base]);
       int acc = 0;  // at most 8 UPL per half and window
       int wide = 0;
 #pragma unroll
       for (int s = 0; s < kWin; ++s) {
-        if (FULL || s < steps) {
-          const int cl = !FULL && use_reg ? __builtin_amdgcn_readfirstlane((int)s_creg[(int)((w * kWin + s) & kMask)]) : 0;
+        if (KIND < 2 || s < steps) {
+          const int pair = nc[s / 2];
+          int ncl = (s & 1) ? pair >> 16 : (int)(short)pair;
+          if constexpr (KIND == 2) ncl = REG ? __builtin_amdgcn_readfirstlane((int)s_ncl[REG ? base + s : 0]) : 0;
           const int g = min(max(hi[s], kMagicHi - QMAX), kMagicHi - QMIN);
           int x[UPL], cr[UPL];
           split_record(r[s], x, cr);
 #pragma unroll
           for (int u = 0; u < UPL; ++u) {
-            if (!FULL && cl != 0) {
-              zs[u] = step_strip_reg(zs[u], x[u], g - kMagicHi, cl, cr[u], hh[u], mask[u], fold_tag, &wide);
+            const int c = KIND == 1 ? with_draw(zs[u], ncl, cr[u]) : cr[u];
+            if (KIND == 2 && ncl != 0) {
+              zs[u] = step_strip_reg(zs[u], x[u], g - kMagicHi, ncl, cr[u], hh[u], mask[u], fold_tag, &wide);
             } else if constexpr (decltype(fold_tag)::value) {
-              const int n = S::mad(x[u], g, cr[u]);
+              const int n = S::mad(x[u], g, c);
               const int sat = S::add_sat(zs[u], n);
               acc = S::add(acc, S::clamped(sat, S::add(zs[u], n)));
               zs[u] = sat & mask[u];
             } else {
-              const int v = S::shifted(S::mad(x[u], g, cr[u]), S::add(hh[u], S::high(zs[u])));
+              const int v = S::shifted(S::mad(x[u], g, c), S::add(hh[u], S::high(zs[u])));
               acc = S::add(acc, S::outside(v));  // (none where no coordinate is: |v| <= 67 there)
               zs[u] = S::clamp_up(v) & mask[u];
             }
@@ -397,10 +417,12 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     auto count_window = [&](int64_t w, auto fold_tag) __attribute__((always_inline)) {
       const int64_t left = T - w * kWin;
       const int steps = (int)(left < kWin ? left : kWin);
-      if (left >= kWin && !use_reg) count_steps(w, kWin, std::true_type{}, fold_tag);
-      else count_steps(w, steps, std::false_type{}, fold_tag);
+      if (left >= kWin && (!REG || reg_small)) count_steps(w, kWin, std::integral_constant<int, REG ? 1 : 0>{}, fold_tag);
+      else count_steps(w, steps, std::integral_constant<int, 2>{}, fold_tag);
       const int hi = s_hi[part][lane & (kWin - 1)];
       n_gclamp += (unsigned int)__builtin_popcountll(__ballot(lane < steps && (hi < kMagicHi - QMAX || hi > kMagicHi - QMIN)));
+      if constexpr (REG)
+        n_reg += (unsigned int)__builtin_popcountll(__ballot(lane < steps && s_ncl[(int)((w * kWin) & kMask) + (lane & (kWin - 1))] != 0));
       part = part == kHis - 1 ? 0 : part + 1;
     };
     fill_batch(0);
@@ -419,7 +441,10 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     if (s_fold) run(std::true_type{});
     else run(std::false_type{});
     if (lane < LANES) atomicAdd(&s_cnt[0], n_lane);  // (it stood at 0 behind P0)
-    if (lane == 0) s_cnt[1] = n_gclamp;
+    if (lane == 0) {
+      s_cnt[1] = n_gclamp;
+      s_cnt[2] = n_reg;
+    }
     __syncthreads();  // the counters
     return;
   }
@@ -551,7 +576,6 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   const bool direct = LANES == 16 || k1 * (double)d * (double)(1 << (2 * BITS - 2)) < 0x1p22;
   const double scale_one = BITS == 8 ? 0x1p-8 : 1.0;  // at 8 bits the dot is with 2^8 z
   const double scale_t = -k1 * scale_one;
-  unsigned int n_reg = 0;  // steps with an L2 draw
   __syncthreads();  // P0
   __syncthreads();  // P1: the records of windows 0 and 1 are in place
   __builtin_amdgcn_s_setprio(3);
@@ -561,11 +585,13 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     RecV rec[NQ];
     double c, dl0;
     float phi, y;
+    int ncl;
   };
   auto load_step = [&](Step& st, int slot, int base, int s) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) st.rec[q] = *rec_at(slot, s, q);
     st.c = s_c[base + s];
+    if constexpr (REG) st.ncl = s_ncl[base + s];
     if constexpr (need_phi) st.phi = s_phi[base + s];
     if constexpr (logistic) {
       st.y = s_y[base + s];
@@ -660,24 +686,21 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       asm("v_cvt_i32_f64 %0, -%1" : "=v"(nf) : "v"(fl));  // saturates
       const int ng = min(max(nf, -QMAX), -QMIN);
       s_hi[part][s] = kMagicHi + min(max(nf, -(1 << 20)), 1 << 20);
-      const int cl = use_reg ? __builtin_amdgcn_readfirstlane(s_creg[k]) : 0;
-      n_reg += cl != 0 ? 1u : 0u;
+      const int ncl = REG ? __builtin_amdgcn_readfirstlane((int)s_ncl[REG ? k : 0]) : 0;
 #pragma unroll
       for (int u = 0; u < UPL; ++u)
-        zp[u] = cl == 0 ? step_strip(zp[u], x[u], kMagicHi + ng, cr[u], hh[u], mask[u], fold_tag)
-                        : step_strip_reg(zp[u], x[u], ng, cl, cr[u], hh[u], mask[u], fold_tag, nullptr);
+        zp[u] = ncl == 0 ? step_strip(zp[u], x[u], kMagicHi + ng, cr[u], hh[u], mask[u], fold_tag)
+                         : step_strip_reg(zp[u], x[u], ng, ncl, cr[u], hh[u], mask[u], fold_tag, nullptr);
     }
   };
 
   // A whole window of fused steps; false (and z as it was) where one of them came too close to an integer.
-  auto window = [&](int64_t t0, int slot, int part, auto reg_tag, auto fold_tag, auto direct_tag) __attribute__((always_inline)) -> bool {
-    constexpr bool REGW = decltype(reg_tag)::value;  // some step of the window may have c_lambda != 0
+  auto window = [&](int64_t t0, int slot, int part, auto fold_tag, auto direct_tag) __attribute__((always_inline)) -> bool {
     const int base = (int)(t0 & kMask);
     const int next_base = (base + kWin) & kMask;  // (any window has its place in the ring, also past the end of the epoch)
     int zsave[UPL];
 #pragma unroll
     for (int u = 0; u < UPL; ++u) zsave[u] = zp[u];
-    unsigned int nr = 0;
     uint32_t nearest = 0xFFFFFFFFu;  // the least of the window's low words
     int hi_even = 0;
     const int next_slot = (slot + 1) & (kSlots - 1);
@@ -692,6 +715,10 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       __builtin_amdgcn_sched_barrier(0);
       if (s + kAhead < kWin) load_step(ahead[s % kAhead], slot, base, s + kAhead);
       else load_step(ahead[s % kAhead], next_slot, next_base, s + kAhead - kWin);
+      if constexpr (REG) {
+#pragma unroll
+        for (int u = 0; u < UPL; ++u) cr[u] = with_draw(zp[u], st.ncl, cr[u]);
+      }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (need_phi) t = __fma_rn(moved(t, st.phi, st.y, st.dl0), -k2, st.c);
       else if constexpr (!DIRECT) t = __fma_rn(t, -k1, st.c);
@@ -703,35 +730,15 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const int g = min(max(hi, kMagicHi - QMAX), kMagicHi - QMIN);
       if (s & 1) *reinterpret_cast<int2r*>(&s_hi[part][s - 1]) = int2r{hi_even, hi};
       else hi_even = hi;
-      int cl = 0;
-      if (REGW) {
-        cl = __builtin_amdgcn_readfirstlane((int)s_creg[base + s]);
-        nr += cl != 0 ? 1u : 0u;
-      }
-      if (!REGW || cl == 0) {
 #pragma unroll
-        for (int u = 0; u < UPL; ++u) zp[u] = step_strip(zp[u], x[u], g, cr[u], hh[u], mask[u], fold_tag);
-      } else {
-#pragma unroll
-        for (int u = 0; u < UPL; ++u)
-          zp[u] = step_strip_reg(zp[u], x[u], g - kMagicHi, cl, cr[u], hh[u], mask[u], fold_tag, nullptr);
-      }
+      for (int u = 0; u < UPL; ++u) zp[u] = step_strip(zp[u], x[u], g, cr[u], hh[u], mask[u], fold_tag);
     }
     if (__builtin_expect(__ballot(nearest <= 2 * kNear) != 0, 0)) {
 #pragma unroll
       for (int u = 0; u < UPL; ++u) zp[u] = zsave[u];
       return false;
     }
-    n_reg += nr;
     return true;
-  };
-  // true if some step of the window at tt has an L2 draw (rare: alpha lambda 2^b is tiny)
-  auto any_creg = [&](int64_t tt) -> bool {
-    if (!use_reg) return false;
-    const int base = (int)(tt & kMask);
-    const int4 c = *reinterpret_cast<const int4*>(&s_creg[base]);
-    const int any = c.x | c.y | c.z | c.w;
-    return __builtin_amdgcn_readfirstlane(any) != 0;
   };
   auto run = [&](auto fold_tag, auto direct_tag) __attribute__((always_inline)) {
     int slot = 0, part = 0;
@@ -745,29 +752,17 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       part = part == kHis - 1 ? 0 : part + 1;
       t0 += kWin;
     };
+    const bool fused = fused_ok && (!REG || reg_small);
     while (t0 < T) {
-      // Windows of fused steps without an L2 draw, in a loop of their own: the registers that the steps'
-      // records arrive in are carried round it, and a copy anywhere would wait for them
-      bool again = false;
-      if (fused_ok) {
+      // Windows of fused steps, in a loop of their own: the registers that the steps' records arrive in are
+      // carried round it, and a copy anywhere would wait for them
+      if (fused) {
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
-        while (t0 + kWin <= T && !any_creg(t0)) {
-          if (__builtin_expect(!window(t0, slot, part, std::false_type{}, fold_tag, direct_tag), 0)) {
-            again = true;
-            break;
-          }
-          next_window();
-        }
+        while (t0 + kWin <= T && __builtin_expect(window(t0, slot, part, fold_tag, direct_tag), 1)) next_window();
+        if (t0 >= T) break;
       }
-      if (t0 >= T) break;
-      bool done = false;
-      if (fused_ok && !again && t0 + kWin <= T) {
-#pragma unroll
-        for (int k = 0; k < kAhead; ++k) load_step(ahead[k], slot, (int)(t0 & kMask), k);
-        done = window(t0, slot, part, std::true_type{}, fold_tag, std::false_type{});
-      }
-      if (!done) window_fixed(t0, slot, part, (int)(T - t0 < kWin ? T - t0 : kWin), fold_tag);
+      window_fixed(t0, slot, part, (int)(T - t0 < kWin ? T - t0 : kWin), fold_tag);
       next_window();
     }
     __syncthreads();  // P2: the last gammas are in place
@@ -789,20 +784,19 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         wg[j] = lp ? (float)step : (float)__dadd_rn((double)wg[j], step);  // Alg. 2: w~ = delta w
       }
     }
-  if (lane == 0) s_cnt[2] = n_reg;  // the service wave has the other two
-  __syncthreads();
+  __syncthreads();  // the counters
   if (tid < 4) cnt_out[tid] = tid < 3 ? s_cnt[tid] : 0ull;
 }
 
 // the record ring: windows of 8 steps, 8 UPL bytes per lane and step
 constexpr size_t ring_bytes(int upl, int lanes) { return (size_t)kSlots * kWin * upl * 8 * lanes; }
 
-template <int BITS, int UPL, int LANES, bool PAIR>
+template <int BITS, int UPL, int LANES, bool PAIR, bool REG>
 int launch_one(const InArgs& a, int R, hipStream_t s) {
   const dim3 grid(R), block(64 * waves_of(UPL, LANES));
 #define HALP_LONE(LOSS_)                                                                          \
   do {                                                                                            \
-    auto kern = inner_reg_lone_kernel<BITS, LOSS_, UPL, LANES, PAIR>;                             \
+    auto kern = inner_reg_lone_kernel<BITS, LOSS_, UPL, LANES, PAIR, REG>;                        \
     const size_t smem = ring_bytes(UPL, LANES);                                     \
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                  \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) \
@@ -814,6 +808,19 @@ int launch_one(const InArgs& a, int R, hipStream_t s) {
   else HALP_LONE(HALP_LOSS_LOGISTIC);
 #undef HALP_LONE
   return hip_ok(hipGetLastError());
+}
+
+template <int BITS, bool REG>
+int launch_shape(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s) {
+  if constexpr (BITS == 8) {
+    if (upl == 2 && lanes == 16) return launch_one<8, 2, 16, true, REG>(a, R, s);
+  } else {
+    if (upl == 1) return launch_one<16, 1, 64, true, REG>(a, R, s);
+  }
+  if (upl == 2) return pair ? launch_one<BITS, 2, 64, true, REG>(a, R, s) : launch_one<BITS, 2, 64, false, REG>(a, R, s);
+  if (upl == 4) return pair ? launch_one<BITS, 4, 64, true, REG>(a, R, s) : launch_one<BITS, 4, 64, false, REG>(a, R, s);
+  if (upl == 8) return launch_one<BITS, 8, 64, false, REG>(a, R, s);
+  return HALP_ERR_UNSUPPORTED;
 }
 
 }  // namespace innerlone

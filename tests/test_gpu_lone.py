@@ -101,3 +101,47 @@ def test_more_than_two_to_the_32_clamped_coordinates(d, b):
     P.h.inner_loop(3)
     assert (P.get("z") == lowest).all()
     assert P.get("counters")[0].tolist() == [T * d, 0, 0, 0]
+
+
+@pytest.mark.parametrize("loss,d,b", [
+    (hp.LOSS_SQUARED, 40, 8), (hp.LOSS_SQUARED, 200, 8), (hp.LOSS_LOGISTIC, 500, 8), (hp.LOSS_SQUARED, 1000, 8),
+    (hp.LOSS_SQUARED, 64, 16), (hp.LOSS_LOGISTIC, 120, 16), (hp.LOSS_SQUARED, 256, 16), (hp.LOSS_SQUARED, 500, 16),
+])
+@pytest.mark.parametrize("draw", [0.4, 1.0, 1.1, 10.0])
+@pytest.mark.parametrize("inside", [True, False])
+def test_l2_draws_at_the_edges_of_the_words(loss, d, b, draw, inside):
+    """Every term of the update at its largest: rows of +-q_max and -2^(b-1), z at the ends of its box, gamma clamped,
+    draws just below and above 32 (16 bits: 4096), where the fused steps end, and far above; high parts of -h~ at the
+    ends of what rides in the records, and one past them."""
+    N, T, seed = 40, 261, 11
+    rng = np.random.default_rng(seed + d)
+    q, largest = 2 ** (b - 1) - 1, 32 if b == 8 else 4096
+    X = rng.choice(np.array([-1.0, 1.0], np.float32), size=(N, d))
+    y = (X @ rng.standard_normal(d).astype(np.float32) * 50.0).astype(np.float32)
+    if loss == hp.LOSS_LOGISTIC:
+        y = np.where(y >= 0, 1.0, -1.0).astype(np.float32)
+    Xq = ref.quantize_data(X, 1.0 / q, b)
+    Xq[rng.random((N, d)) < 0.1] = -q - 1
+    alpha, mu = 0.5, 2000.0
+    lam = (draw * largest - 0.25) / (alpha * 2 ** b)
+    prob = ref.make_problem(N, d, loss=loss, b=b, alpha=alpha, mu=mu, lam=lam, delta_d=1.0 / q, seed=seed)
+    w = (rng.standard_normal((1, d)) * 3.0).astype(np.float32)
+    phi, g, _ = ref.full_gradient(prob, X, y, w)
+    phi = phi.astype(np.float32)
+    sc, h, _ = ref.recenter(prob, g.astype(np.float32), 3)
+    lo, hi = (-48, 46) if b == 8 else (-14000, 14000)
+    hh = rng.choice([lo, lo, hi, hi, 0], size=d)
+    if not inside:
+        hh[rng.integers(d)] = rng.choice([lo - 1, hi + 1])
+    h = -(hh * 2 ** b + rng.choice([0, 2 ** b - 1], size=d)).reshape(np.shape(h)).astype(np.asarray(h).dtype)
+    out = ref.inner_loop(prob, Xq, phi, y, h, sc, 3, T)
+    assert out["counters"][0] > 0 and (loss == hp.LOSS_LOGISTIC or out["counters"][1] > 0)
+    assert out["counters"][2] == T
+    P = GpuProblem(X, Xq, y, loss=loss, b=b, T=T, alpha=alpha, mu=mu, lam=lam, delta_d=1.0 / q, seed=seed, w0=w)
+    P.put("phi", phi); P.put("h", h); P.put("scales", sc)
+    P.h.set_option(hp.OPT_INNER_VARIANT, 2)
+    if b == 8:
+        P.h.set_option(hp.OPT_INNER_HELPERS, 3)
+    P.h.inner_loop(3)
+    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
+    assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
