@@ -27,8 +27,8 @@
 // values and r - h~.  A helper serves one or two of the strips of every lane: it draws their Philox
 // blocks, requests the row fragments kSets - 1 windows ahead and writes its dwords of the records.
 // Where -h~ / 2^b is not small in every coordinate, n leaves its word: the records then carry only
-// the low b bits of -h~ and the chain wave adds the rest behind the shift (FOLD = false; five
-// instructions per strip).  A service wave refills the 256-step batches of step-indexed draws
+// the low b bits of -h~, z is kept as it is and the chain wave adds the rest behind the shift (FOLD = false;
+// five instructions per strip, the sum of z and that rest being made beforehand).  A service wave refills the 256-step batches of step-indexed draws
 // (sample indices, rounding draws of gamma and of the L2 term, margins and labels of the
 // sampled rows) and counts the clamped coordinates: the chain wave stores the gammas of a window in
 // LDS and the service wave, which holds a z of its own, takes it through the same steps with and
@@ -113,14 +113,14 @@ struct Strip<8> {
     return __builtin_bit_cast(int, (__builtin_bit_cast(short2r, n) >> (short2r)(8)) + __builtin_bit_cast(short2r, k));
   }
   static __device__ __forceinline__ int high(int z) { return __builtin_bit_cast(int, __builtin_bit_cast(short2r, z) >> (short2r)(8)); }
-  static __device__ __forceinline__ int clamp_up(int v) {  // clamped to the box, times 2^b
-    const short2r c = __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(short2r, v), (short2r)(-128)), (short2r)(127));
-    return __builtin_bit_cast(int, c << (short2r)(8));
+  static __device__ __forceinline__ int clamp(int v) {  // to the box
+    return __builtin_bit_cast(int, __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(short2r, v), (short2r)(-128)), (short2r)(127)));
   }
-  // coordinates of v outside the box
-  static __device__ __forceinline__ int outside(int v) {
-    const ushort2r t = __builtin_bit_cast(ushort2r, __builtin_bit_cast(short2r, v) + short2r{128, 128}) >> (ushort2r)(8);
-    return __builtin_bit_cast(int, __builtin_elementwise_min(t, (ushort2r)(1)));
+  // coordinates in which a and b differ (a minimum with a 1 that the compiler knows becomes a comparison per half)
+  static __device__ __forceinline__ int differ(int a, int b) {
+    int ones = 0x00010001;
+    asm("" : "+s"(ones));
+    return __builtin_bit_cast(int, __builtin_elementwise_min(__builtin_bit_cast(ushort2r, a ^ b), __builtin_bit_cast(ushort2r, ones)));
   }
   // coordinates in which the sum of z and n leaves its word: its sign there is not that of the saturated sum
   static __device__ __forceinline__ int clamped(int sat, int wrapped) {
@@ -134,11 +134,15 @@ struct Strip<8> {
     return __builtin_amdgcn_sdot2(__builtin_bit_cast(short2r, x), __builtin_bit_cast(short2r, z), acc, true);
   }
   static __device__ __forceinline__ int dot(int x, int z) { return dot(x, z, 0); }
-  // the row value and the addend of a record from the strip's two bytes (at `at` bytes into a fragment) and
-  // the 16 rounding bits of step s; add: what the record adds to them
-  static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t word, int s, int add, int* x, int* c) {
+  // what takes the strip's bytes (strip `at` of a fragment) out of it and leaves zeros for coordinates that do not exist
+  static __device__ __forceinline__ uint32_t take(int at, bool ok0, bool ok1) {
+    return (ok0 ? (at ? 0x0200u : 0x0000u) : 0x0C00u) | (ok1 ? (at ? 0x03000000u : 0x01000000u) : 0x0C000000u) | 0x000C000Cu;
+  }
+  // the row value and the addend of a record from the fragment and the 16 rounding bits of step s; add: what the
+  // record adds to them
+  static __device__ __forceinline__ void record(uint32_t frag, int /*at*/, uint32_t take, uint32_t word, int s, int add, int* x, int* c) {
     // the bytes go to the high bytes of the halves and come back down with their signs
-    const uint32_t up = __builtin_amdgcn_perm(0u, frag, at ? 0x030C020Cu : 0x010C000Cu);
+    const uint32_t up = __builtin_amdgcn_perm(0u, frag, take);
     const uint32_t rp = __builtin_amdgcn_perm(0u, word, (s & 1) ? 0x0C030C02u : 0x0C010C00u);
     *x = __builtin_bit_cast(int, __builtin_bit_cast(short2r, up) >> (short2r)(8));
     *c = __builtin_bit_cast(int, __builtin_bit_cast(short2r, rp) + __builtin_bit_cast(short2r, add));
@@ -164,12 +168,13 @@ struct Strip<16> {
   static __device__ __forceinline__ int add(int z, int n) { return (int)((uint32_t)z + (uint32_t)n); }
   static __device__ __forceinline__ int shifted(int n, int k) { return (n >> 16) + k; }
   static __device__ __forceinline__ int high(int z) { return z >> 16; }
-  static __device__ __forceinline__ int clamp_up(int v) { return min(max(v, -32768), 32767) << 16; }
-  static __device__ __forceinline__ int outside(int v) { return (uint32_t)(v + 32768) > 65535u ? 1 : 0; }
+  static __device__ __forceinline__ int clamp(int v) { return min(max(v, -32768), 32767); }
+  static __device__ __forceinline__ int differ(int a, int b) { return (int)min((uint32_t)(a ^ b), 1u); }
   static __device__ __forceinline__ int clamped(int sat, int wrapped) { return (int)((uint32_t)(sat ^ wrapped) >> 31); }
   static __device__ __forceinline__ unsigned int counted(int acc) { return (unsigned int)acc; }
-  static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t word, int s, int add, int* x, int* c) {
-    *x = at ? (int)frag >> 16 : (int)(short)frag;
+  static __device__ __forceinline__ uint32_t take(int /*at*/, bool ok0, bool /*ok1*/) { return ok0 ? 16 : 0; }  // bits
+  static __device__ __forceinline__ void record(uint32_t frag, int at, uint32_t take, uint32_t word, int s, int add, int* x, int* c) {
+    *x = __builtin_amdgcn_sbfe((int)frag, (uint32_t)(16 * at), take);
     *c = mad24(*x, -kOffset, (int)((s & 1) ? word >> 16 : word & 0xFFFFu) + add);
   }
   static __device__ __forceinline__ int addend(int c, int x) { return mad24(x, kOffset, c); }
@@ -266,60 +271,76 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 
   if (tid < 4) s_cnt[tid] = 0;
 
-  // z of a lane's strips times 2^b, the coordinates that exist, and the high part of -h~; true where every
+  // z of a lane's strips (zeros past the row, where no record changes them) and the high part of -h~; true where every
   // high part is small.  With -h~ = 2^b hh + hl, 0 <= hl < 2^b, and every hh in [-64, 62] (16 bits: [-16000, 16000]),
   // n = -gamma x + r - h~ fits its word of 2 b bits (|gamma x| <= 2^(2b-2), 0 <= r < 2^b); with an L2 draw
   // cl <= 32 (4096) n has another cl z, |cl z| <= 2^12 (2^27), and hh lies in [-48, 46] ([-14000, 14000]).
-  auto load_z = [&](int (&zp)[UPL], int (&mask)[UPL], int (&hh)[UPL]) -> bool {
+  auto load_z = [&](int (&zp)[UPL], int (&hh)[UPL]) -> bool {
     bool small = true;
 #pragma unroll
     for (int u = 0; u < UPL; ++u) {
-      int zv[2] = {0, 0}, mv[2] = {0, 0}, hv[2] = {0, 0};
+      int zv[2] = {0, 0}, hv[2] = {0, 0};
 #pragma unroll
       for (int e = 0; e < CT; ++e) {
         const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
         const bool ok = j < d;
-        zv[e] = ok ? (int)zg[ok ? j : 0] << BITS : 0;
-        mv[e] = ok ? S::kMask : 0;
+        zv[e] = ok ? (int)zg[ok ? j : 0] : 0;
         hv[e] = ok ? (int)((-(int64_t)hg[ok ? j : 0]) >> BITS) : 0;
         small = small && hv[e] >= (REG ? S::kSmallLowReg : S::kSmallLow) && hv[e] <= (REG ? S::kSmallHighReg : S::kSmallHigh);
       }
       zp[u] = S::join(zv[0], zv[1]);
-      mask[u] = S::join(mv[0], mv[1]);
       hh[u] = S::join(hv[0], hv[1]);
     }
     return small;
   };
-  // z <- Q(z - gamma x - h~) of a strip; g: kMagicHi - gamma.  fold: c holds r - h~, else r + hl
-  auto step_strip = [&](int z, int x, int g, int c, int hh, int mask, auto fold_tag) __attribute__((always_inline)) -> int {
+  // z <- Q(z - gamma x - h~) of a strip; g: kMagicHi - gamma.  fold: c holds r - h~ and z is kept times 2^b, else c
+  // holds r + hl and hh goes to z beforehand (left to itself the compiler adds the two one after the other behind
+  // the shift, which waits for gamma)
+  auto begin_strip = [&](int z, int hh, auto fold_tag) __attribute__((always_inline)) -> int {
+    if constexpr (decltype(fold_tag)::value) return z;
+    int zb = S::add(hh, z);
+    if constexpr (BITS == 8) asm("" : "+v"(zb));  // (at 16 bits the registers are worth more)
+    return zb;
+  };
+  auto step_strip = [&](int zb, int x, int g, int c, auto fold_tag) __attribute__((always_inline)) -> int {
     const int n = S::mad(x, g, c);
-    if constexpr (decltype(fold_tag)::value) return S::add_sat(z, n) & mask;
-    else return S::clamp_up(S::shifted(n, S::add(hh, S::high(z)))) & mask;
+    if constexpr (decltype(fold_tag)::value) return S::add_sat(zb, n) & S::kMask;
+    else return S::clamp(S::shifted(n, zb));
   };
   // the addend of a step with an L2 draw; ncl: -cl
-  auto with_draw = [&](int z, int ncl, int c) __attribute__((always_inline)) -> int { return S::mad(S::high(z), ncl, c); };
+  auto with_draw = [&](int z, int ncl, int c, auto fold_tag) __attribute__((always_inline)) -> int {
+    return S::mad(decltype(fold_tag)::value ? S::high(z) : z, ncl, c);
+  };
   // z <- Q(z - gamma x - h~ - cl z) in wide arithmetic on the coordinates, for draws of any size (steps in the
   // fixed order); g here is -gamma itself
   using Wide = typename std::conditional<BITS == 8, int, int64_t>::type;
-  auto step_strip_reg = [&](int z, int x, int g, int ncl, int c, int hh, int mask, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
+  auto step_strip_reg = [&](int z, int x, int g, int ncl, int c, int hh, auto fold_tag, int* clamped) __attribute__((always_inline)) -> int {
+    constexpr int kShift = decltype(fold_tag)::value ? BITS : 0;
     int zn[2] = {0, 0};
     const int cc = S::addend(c, x);
 #pragma unroll
     for (int e = 0; e < CT; ++e) {
-      const Wide zk = S::value(z, e) >> BITS, xk = S::value(x, e);
+      const Wide zk = S::value(z, e) >> kShift, xk = S::value(x, e);
       const Wide hr = (decltype(fold_tag)::value ? 0 : (Wide)S::value(hh, e) << BITS) + S::value(cc, e);
       const Wide zuk = zk + ((g * xk + ncl * zk + hr) >> BITS);
       const Wide zc = zuk < QMIN ? QMIN : (zuk > QMAX ? QMAX : zuk);
-      if (clamped) *clamped += (S::value(mask, e) != 0 && zuk != zc) ? 1 : 0;
-      zn[e] = (int)zc << BITS;
+      if (clamped) *clamped += zuk != zc ? 1 : 0;
+      zn[e] = (int)zc << kShift;
     }
-    return S::join(zn[0], zn[1]) & mask;
+    return S::join(zn[0], zn[1]);
+  };
+  // z as it is <-> as the steps keep it
+  auto keep_z = [&](int (&zp)[UPL], auto fold_tag) __attribute__((always_inline)) {
+    if constexpr (decltype(fold_tag)::value) {
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) zp[u] = S::join(S::value(zp[u], 0) << BITS, S::value(zp[u], 1) << BITS);
+    }
   };
 
   if (is_service) {
     // ============================ service wave ============================
-    int zs[UPL], mask[UPL], hh[UPL];
-    (void)load_z(zs, mask, hh);
+    int zs[UPL], hh[UPL];
+    (void)load_z(zs, hh);
     // draws that depend on the step number only, 256 steps per batch
     auto fill_batch = [&](int64_t bb) {
       const int half = (int)(bb & 1) * kBatch;
@@ -394,20 +415,41 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
           const int g = min(max(hi[s], kMagicHi - QMAX), kMagicHi - QMIN);
           int x[UPL], cr[UPL];
           split_record(r[s], x, cr);
+          // (all strips go through one instruction before the next: one strip after the other, each would wait for
+          // its own results; at 16 bits there are not the registers for it)
+          constexpr int G = BITS == 8 ? UPL : 1;
+          auto next = [&]() __attribute__((always_inline)) { if constexpr (BITS == 8) __builtin_amdgcn_sched_barrier(0); };
 #pragma unroll
-          for (int u = 0; u < UPL; ++u) {
-            const int c = KIND == 1 ? with_draw(zs[u], ncl, cr[u]) : cr[u];
+          for (int u = 0; u < UPL; u += G) {
+            int n[G], v[G];
             if (KIND == 2 && ncl != 0) {
-              zs[u] = step_strip_reg(zs[u], x[u], g - kMagicHi, ncl, cr[u], hh[u], mask[u], fold_tag, &wide);
-            } else if constexpr (decltype(fold_tag)::value) {
-              const int n = S::mad(x[u], g, c);
-              const int sat = S::add_sat(zs[u], n);
-              acc = S::add(acc, S::clamped(sat, S::add(zs[u], n)));
-              zs[u] = sat & mask[u];
+#pragma unroll
+              for (int k = 0; k < G; ++k)
+                zs[u + k] = step_strip_reg(zs[u + k], x[u + k], g - kMagicHi, ncl, cr[u + k], hh[u + k], fold_tag, &wide);
+              continue;
+            }
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+              n[k] = S::mad(x[u + k], g, KIND == 1 ? with_draw(zs[u + k], ncl, cr[u + k], fold_tag) : cr[u + k]);
+            if constexpr (decltype(fold_tag)::value) {
+#pragma unroll
+              for (int k = 0; k < G; ++k) {
+                v[k] = S::add_sat(zs[u + k], n[k]);
+                acc = S::add(acc, S::clamped(v[k], S::add(zs[u + k], n[k])));
+                zs[u + k] = v[k] & S::kMask;
+              }
             } else {
-              const int v = S::shifted(S::mad(x[u], g, c), S::add(hh[u], S::high(zs[u])));
-              acc = S::add(acc, S::outside(v));  // (none where no coordinate is: |v| <= 67 there)
-              zs[u] = S::clamp_up(v) & mask[u];
+#pragma unroll
+              for (int k = 0; k < G; ++k) zs[u + k] = begin_strip(zs[u + k], hh[u + k], fold_tag);
+              next();
+#pragma unroll
+              for (int k = 0; k < G; ++k) v[k] = S::shifted(n[k], zs[u + k]);
+              next();
+#pragma unroll
+              for (int k = 0; k < G; ++k) zs[u + k] = S::clamp(v[k]);
+              next();
+#pragma unroll
+              for (int k = 0; k < G; ++k) acc = S::add(acc, S::differ(v[k], zs[u + k]));
             }
           }
         }
@@ -430,6 +472,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     __syncthreads();  // P0: the first two batches are in place
     __syncthreads();  // P1: the records of windows 0 and 1 are in place
     auto run = [&](auto fold_tag) __attribute__((always_inline)) {
+      keep_z(zs, fold_tag);
       for (int64_t w = 0; w < nwin + 2; ++w) {
         if (w >= 2) count_window(w - 2, fold_tag);
         if (w >= 1 && w <= nwin) take(w - 1);
@@ -458,6 +501,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const int u0 = LANES == 16 ? g0 >> 4 : first_strip;
       int hlp[SPH];  // what a record adds to the rounding bits: the low b bits of -h~, or the whole of it
       int hfp[SPH];  // where every -h~ / 2^b is small
+      uint32_t take[SPH];
 #pragma unroll
       for (int i = 0; i < SPH; ++i) {
         int hl[2] = {0, 0}, hf[2] = {0, 0};
@@ -471,6 +515,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         }
         hlp[i] = S::join(hl[0], hl[1]);
         hfp[i] = S::join(hf[0], hf[1]);
+        take[i] = S::take(i, CT * (g0 + i) < d, CT * (g0 + i) + 1 < d);
       }
       // The rows of a window: its eight sample indices in two LDS reads (every entry of the index ring is
       // a valid row at any time, so windows past the end of the epoch fetch rows that are never used),
@@ -505,8 +550,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
 #pragma unroll
-          for (int i = 0; i < SPH; ++i)  // (what lies past the row's end is kept out of z by the chain wave)
-            S::record(fr[s], i, pick(zn[i], (uint32_t)(s >> 1)), s, hlp[i], &xw[s * kStep + i], &cw[s * kStep + i]);
+          for (int i = 0; i < SPH; ++i)
+            S::record(fr[s], i, take[i], pick(zn[i], (uint32_t)(s >> 1)), s, hlp[i], &xw[s * kStep + i], &cw[s * kStep + i]);
         }
       };
       __syncthreads();  // P0: the first two batches are in place
@@ -563,10 +608,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   }
 
   // ============================== chain wave ==============================
-  int zp[UPL], mask[UPL], hh[UPL];
-  const bool hh_small = load_z(zp, mask, hh);
-  const bool fold = __ballot(!hh_small) == 0;  // uniform
-  if (lane == 0) s_fold = fold ? 1 : 0;
+  int zp[UPL], hh[UPL];
+  const bool hh_small = load_z(zp, hh);
   // The fused form stands for the fixed order of roundings while nothing underflows on the way.  `direct`: and
   // no partial sum of the matrix instruction is so large that its last place matters (|t| <= 2^22), so that it
   // may do the multiply-add too; else it adds up the whole number x^T z, and the multiply-add follows.
@@ -574,8 +617,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   auto normal = [](double v) { return v > 1e-200 && v < 1e200; };
   const bool fused_ok = normal(dscale) && normal(aB) && normal(__dmul_rn(dscale, aB)) && normal(inv_s) && normal(k2) && normal(k1);
   const bool direct = LANES == 16 || k1 * (double)d * (double)(1 << (2 * BITS - 2)) < 0x1p22;
-  const double scale_one = BITS == 8 ? 0x1p-8 : 1.0;  // at 8 bits the dot is with 2^8 z
-  const double scale_t = -k1 * scale_one;
+  const bool fold = __ballot(!hh_small) == 0;  // uniform
+  if (lane == 0) s_fold = fold ? 1 : 0;
   __syncthreads();  // P0
   __syncthreads();  // P1: the records of windows 0 and 1 are in place
   __builtin_amdgcn_s_setprio(3);
@@ -601,7 +644,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
   constexpr int kAhead = logistic ? 1 : 2;  // (a step with exp in it is long enough for one, and needs the registers)
   Step ahead[kAhead];
 
-  // x^T z of a step's row: the sum over the 16 lanes of a row of lanes, divided by scale_one
+  // x^T z of a step's row: the sum over the 16 lanes of a row of lanes; at 8 bits with fold x^T (2^8 z)
   auto fold16 = [](int v) {
     v += dpp_quad_swap1(v);
     v += dpp_quad_swap2(v);
@@ -609,7 +652,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     v += dpp_row_mirror(v);
     return v;
   };
-  auto row_dot = [&](const int (&x)[UPL]) __attribute__((always_inline)) -> double {
+  auto row_dot = [&](const int (&x)[UPL], auto fold_tag) __attribute__((always_inline)) -> double {
     if constexpr (BITS == 8) {
       int v;
       if constexpr (UPL == 2) {
@@ -628,15 +671,18 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       // products, or sums of two less 2^16, fit 32 bits; each is cut into its low 16 bits and the rest, and the
       // two kinds are folded apart (the instructions of one fill the wait states of the other)
       int lo = 0, hi = 0;
+      int z[UPL];
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) z[u] = decltype(fold_tag)::value ? zp[u] >> 16 : zp[u];
       if constexpr (UPL == 1) {
-        const int p = mad24(x[0], zp[0] >> 16, 0);
+        const int p = mad24(x[0], z[0], 0);
         lo = p & 0xFFFF;
         hi = p >> 16;
       } else {
         hi = UPL / 2;
 #pragma unroll
         for (int u = 0; u < UPL; u += 2) {
-          const int p = mad24(x[u], zp[u] >> 16, mad24(x[u + 1], zp[u + 1] >> 16, -65536));
+          const int p = mad24(x[u], z[u], mad24(x[u + 1], z[u + 1], -65536));
           lo += p & 0xFFFF;
           hi += p >> 16;
         }
@@ -646,7 +692,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       return __fma_rn((double)hi, 65536.0, (double)lo);
     }
   };
-  // scale * (the whole x^T z times 2^b) + add
+  auto scale_one = [](auto fold_tag) { return BITS == 8 && decltype(fold_tag)::value ? 0x1p-8 : 1.0; };
+  // scale * (the sum of row_dot) + add
   auto whole_dot = [&](double row, double scale, double add) -> double {
     if (LANES == 16) return __fma_rn(row, scale, add);
     return __builtin_amdgcn_mfma_f64_4x4x4f64(row, scale, add, 0, 0, 0);
@@ -675,7 +722,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       for (int q = 0; q < NQ; ++q) r[q] = *rec_at(slot, s, q);
       int x[UPL], cr[UPL];
       split_record(r, x, cr);
-      const double D = whole_dot(row_dot(x), scale_one, 0.0);
+      const double D = whole_dot(row_dot(x, fold_tag), scale_one(fold_tag), 0.0);
       const int k = base + s;
       const double diff = moved(D, kMargins ? s_phi[kMargins ? k : 0] : 0.f, logistic ? s_y[logistic ? k : 0] : 0.f,
                                 logistic ? s_dl0[logistic ? k : 0] : 0.0);
@@ -689,8 +736,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       const int ncl = REG ? __builtin_amdgcn_readfirstlane((int)s_ncl[REG ? k : 0]) : 0;
 #pragma unroll
       for (int u = 0; u < UPL; ++u)
-        zp[u] = ncl == 0 ? step_strip(zp[u], x[u], kMagicHi + ng, cr[u], hh[u], mask[u], fold_tag)
-                         : step_strip_reg(zp[u], x[u], ng, ncl, cr[u], hh[u], mask[u], fold_tag, nullptr);
+        zp[u] = ncl == 0 ? step_strip(begin_strip(zp[u], hh[u], fold_tag), x[u], kMagicHi + ng, cr[u], fold_tag)
+                         : step_strip_reg(zp[u], x[u], ng, ncl, cr[u], hh[u], fold_tag, nullptr);
     }
   };
 
@@ -710,15 +757,18 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       int x[UPL], cr[UPL];
       split_record(st.rec, x, cr);
       constexpr bool DIRECT = decltype(direct_tag)::value && !need_phi;
-      double t = DIRECT ? whole_dot(row_dot(x), scale_t, st.c) : whole_dot(row_dot(x), scale_one, 0.0);
+      double t = DIRECT ? whole_dot(row_dot(x, fold_tag), -k1 * scale_one(fold_tag), st.c)
+                        : whole_dot(row_dot(x, fold_tag), scale_one(fold_tag), 0.0);
       // (held in place: the scheduler would sink the reads to where their latency is not covered)
       __builtin_amdgcn_sched_barrier(0);
       if (s + kAhead < kWin) load_step(ahead[s % kAhead], slot, base, s + kAhead);
       else load_step(ahead[s % kAhead], next_slot, next_base, s + kAhead - kWin);
       if constexpr (REG) {
 #pragma unroll
-        for (int u = 0; u < UPL; ++u) cr[u] = with_draw(zp[u], st.ncl, cr[u]);
+        for (int u = 0; u < UPL; ++u) cr[u] = with_draw(zp[u], st.ncl, cr[u], fold_tag);
       }
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) zp[u] = begin_strip(zp[u], hh[u], fold_tag);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (need_phi) t = __fma_rn(moved(t, st.phi, st.y, st.dl0), -k2, st.c);
       else if constexpr (!DIRECT) t = __fma_rn(t, -k1, st.c);
@@ -731,7 +781,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       if (s & 1) *reinterpret_cast<int2r*>(&s_hi[part][s - 1]) = int2r{hi_even, hi};
       else hi_even = hi;
 #pragma unroll
-      for (int u = 0; u < UPL; ++u) zp[u] = step_strip(zp[u], x[u], g, cr[u], hh[u], mask[u], fold_tag);
+      for (int u = 0; u < UPL; ++u) zp[u] = step_strip(zp[u], x[u], g, cr[u], fold_tag);
     }
     if (__builtin_expect(__ballot(nearest <= 2 * kNear) != 0, 0)) {
 #pragma unroll
@@ -741,6 +791,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     return true;
   };
   auto run = [&](auto fold_tag, auto direct_tag) __attribute__((always_inline)) {
+    keep_z(zp, fold_tag);
     int slot = 0, part = 0;
     int64_t t0 = 0;
     auto next_window = [&]() {
@@ -766,10 +817,19 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       next_window();
     }
     __syncthreads();  // P2: the last gammas are in place
+    if constexpr (decltype(fold_tag)::value) {
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) zp[u] = S::high(zp[u]);
+    }
   };
-  if (!fold) run(std::false_type{}, std::false_type{});
-  else if (direct && !need_phi) run(std::true_type{}, std::bool_constant<!need_phi>{});
-  else run(std::true_type{}, std::false_type{});
+  using Direct = std::bool_constant<!need_phi>;
+  if (need_phi || direct) {
+    if (fold) run(std::true_type{}, Direct{});
+    else run(std::false_type{}, Direct{});
+  } else {
+    if (fold) run(std::true_type{}, std::false_type{});
+    else run(std::false_type{}, std::false_type{});
+  }
 
   // ---- w~ <- w~ + delta_m z (option I); hand z out
 #pragma unroll
@@ -778,7 +838,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
     for (int e = 0; e < CT; ++e) {
       const int j = CT * strip_of<UPL, LANES>(u, lane) + e;
       if (lane < LANES && j < d) {
-        const int zk = S::value(zp[u], e) >> BITS;
+        const int zk = S::value(zp[u], e);
         zg[j] = (ZT)zk;
         const double step = __dmul_rn(delta_m, (double)zk);
         wg[j] = lp ? (float)step : (float)__dadd_rn((double)wg[j], step);  // Alg. 2: w~ = delta w
