@@ -169,7 +169,11 @@ struct Strip<16> {
   static __device__ __forceinline__ int shifted(int n, int k) { return (n >> 16) + k; }
   static __device__ __forceinline__ int high(int z) { return z >> 16; }
   static __device__ __forceinline__ int clamp(int v) { return min(max(v, -32768), 32767); }
-  static __device__ __forceinline__ int differ(int a, int b) { return (int)min((uint32_t)(a ^ b), 1u); }
+  static __device__ __forceinline__ int differ(int a, int b) {
+    uint32_t one = 1;
+    asm("" : "+s"(one));
+    return (int)min((uint32_t)(a ^ b), one);
+  }
   static __device__ __forceinline__ int clamped(int sat, int wrapped) { return (int)((uint32_t)(sat ^ wrapped) >> 31); }
   static __device__ __forceinline__ unsigned int counted(int acc) { return (unsigned int)acc; }
   static __device__ __forceinline__ uint32_t take(int /*at*/, bool ok0, bool /*ok1*/) { return ok0 ? 16 : 0; }  // bits
