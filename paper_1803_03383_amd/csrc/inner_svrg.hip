@@ -508,10 +508,13 @@ SvShape pick_shape(const halp_handle& h) {
 // loss), with it / without: d = 64 512 chains 81 / 121, 1280 112 / 143, 1536 170 / 143; d = 200 1 chain 70 / 235, 512 80 / 234,
 // 1280 112 / 201, 2048 198 / 211; d = 512 1 chain 92 / 249, 512 107 / 265 (two workgroups fit a CU; 600 chains would take two
 // turns: 267 / 268); d = 1000 256 157 / 294.  Logistic: d = 60 1280 443 / 471, d = 200 1280 445 / 534, d = 512 512 205 / 601.
+// The L2 term costs it two instructions per coordinate: squared loss with lambda > 0, d = 64 1280 116 / 138, d = 128 1280
+// 117 / 155, 1536 182 / 155, 2048 215 / 191 (without L2 158 / 156, 185 / 190), d = 200 2048 218 / 245.
 bool lone_pays(const halp_handle& h) {
   const int d = h.p.d;
   if (h.inner_waves > 0 || d > 1024) return false;
-  const int per_cu = d <= 64 ? 5 : (d <= 256 ? 8 : (d <= 512 ? 2 : 1));
+  const bool few = d <= 64 || (d <= 128 && h.p.lambda > 0 && h.p.loss == HALP_LOSS_SQUARED);
+  const int per_cu = few ? 5 : (d <= 256 ? 8 : (d <= 512 ? 2 : 1));
   return (int64_t)h.p.R <= (int64_t)h.num_cus * per_cu;
 }
 
