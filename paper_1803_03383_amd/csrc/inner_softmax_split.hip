@@ -200,7 +200,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
           p0_n = softmax(a0_n);
           draw_fused();
           phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(idxn, s) * K + lc];  // step t + 8
-          unsigned long long* w = words + (s & 1) * kKC * kWordStride + (live_f ? rc : 0) * kWordStride;
+          unsigned long long* w = words + (s & 1) * kKC * kWordStride + (kShort && !live_f ? 0 : rc) * kWordStride;
           unsigned long long v = old[s & 1];
           for (int spin = 0; n_timeout == 0; ++spin) {  // after one wait ran out, none is tried again
             if (live_f) v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -211,25 +211,32 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
           }
           const long long D = (long long)(v - old[s & 1] - ((unsigned long long)P << 56));
           old[s & 1] = v;
-          int hi = 0;
-          if (__builtin_expect_with_probability(
-                  kShort && fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
-            const int g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
-            s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
-            n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
-          } else {  // in the fixed order of roundings, classes in the first lanes
-            const long long Dc = kShort ? (long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D) : D;
-            const double moved = __dmul_rn(dscale, (double)Dc);
+          double f = 0.0, fc = 0.0;  // gamma in the fixed order of roundings, classes in the first lanes
+          auto fixed = [&](double moved) __attribute__((always_inline)) {
             const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
             // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
             const double beta = __dmul_rn(aB, __dadd_rn(p1, -p0));
-            const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
-            const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
+            f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
+            fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
             if (live) s_ng[s & 1][lane] = (int)(-fc);
-            n_gclamp += (live && f != fc) ? 1u : 0u;
+          };
+          int g = 0, hi = 0;
+          if constexpr (kShort) {
+            if (__builtin_expect_with_probability(
+                    fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
+              g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
+              s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
+            } else {
+              g = hi;
+              fixed(__dmul_rn(dscale, (double)(long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D)));
+            }
+          } else {
+            fixed(__dmul_rn(dscale, (double)D));
           }
           if (lane == 0) s_cl[s & 1] = cl;
           lds_barrier();  // gamma is out; the class waves update z
+          if constexpr (kShort) n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
+          n_gclamp += (live && f != fc) ? 1u : 0u;
           n_reg += (lane == 0 && cl != 0) ? 1u : 0u;
         }
       }
