@@ -186,17 +186,21 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
           }
         }
       };
-      auto fetch_rec = [&](int it) {
+      auto fetch_rec = [&](AheadRec(&r)[SOFT ? 4 : 1], int it) {
         it = min(it, niter - 1);  // past the segment's end its last rows are repeated
         const int tl = MANY ? it / nchunk : it;
         const int mb = MANY ? (it - tl * nchunk) * rows : 0;
         const int64_t o = ((int64_t)tl * B + min(mb + m0, B - 1)) * kAheadK + c0;
 #pragma unroll
-        for (int e = 0; e < (SOFT ? 4 : 1); ++e) rn[e] = rec[o + e];
+        for (int e = 0; e < (SOFT ? 4 : 1); ++e) r[e] = rec[o + e];
         if (!SOFT && a.loss == HALP_LOSS_LOGISTIC) yn = rec[o + 1].phi;
       };
-      fetch_rec(0);
+      // The short chain's draws of an iteration are made while the gammas of the one before are used.  With chunks that
+      // is not long enough for the trip of the records, which are asked for two iterations ahead there
+      const bool far = MANY && fused;
+      fetch_rec(rn, 0);
       draw();
+      if (far) fetch_rec(rn, 1);
       __syncthreads();
       int ch = 0;
       for (int it = 0; it < niter; ++it) {
@@ -220,22 +224,24 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
           int8_t* gp = s_gam + c0 * kGamStride + (m0 & 3) * 16 + (m0 >> 2);
           bool done = false;
           if constexpr (SOFT) {
-            if (fused) {
-              double delta[4], ex[4], sum = 0.0;
+            // NE: classes per lane that may exist (of those past it the gammas are 0 and stay so)
+            auto short_chain = [&](auto ne_tag) __attribute__((always_inline)) {
+              constexpr int NE = decltype(ne_tag)::value;
+              double delta[NE], ex[NE], sum = 0.0;
 #pragma unroll
-              for (int e = 0; e < 4; ++e) delta[e] = __fma_rn(dscale, (double)D[e], -from[e]);  // 0 past the classes
+              for (int e = 0; e < NE; ++e) delta[e] = __fma_rn(dscale, (double)D[e], -from[e]);  // 0 past the classes
 #pragma unroll
-              for (int e = 0; e < 4; ++e) ex[e] = exp_short(delta[e]);
+              for (int e = 0; e < NE; ++e) ex[e] = exp_short(delta[e]);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) sum = __fma_rn(sd[e].p0, ex[e], sum);
+              for (int e = 0; e < NE; ++e) sum = __fma_rn(sd[e].p0, ex[e], sum);
               sum += bank_swap_f64(sum);
               sum += half_swap_f64(sum);
               double y = __builtin_amdgcn_rcp(sum);
               y = __fma_rn(__fma_rn(-sum, y, 1.0), y, y);
               bool bad = !(sum > 0x1p-4);
-              int hi[4];
+              int hi[NE];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
+              for (int e = 0; e < NE; ++e) {
                 const uint64_t bits = __builtin_bit_cast(uint64_t, __fma_rn(sd[e].kp * ex[e], y, sd[e].c));
                 hi[e] = (int)(bits >> 32);
                 bad = bad || sd[e].wide || !(__builtin_fabs(delta[e]) <= 64.0) || (c0 + e < K && (uint32_t)bits <= 2 * kSoftNear);
@@ -243,23 +249,29 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
               done = __ballot(bad) == 0;
               if (__builtin_expect_with_probability(done, 1, 1.0)) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (int e = 0; e < NE; ++e) {
                   const bool in = m0 < nrow && c0 + e < K;
                   const int g = min(max(hi[e], kSoftMagicHi + QMIN), kSoftMagicHi + QMAX);
                   n_gclamp += (in && g != hi[e]) ? 1u : 0u;
                   gp[e * kGamStride] = in ? (int8_t)(g & 0xFF) : (int8_t)0;
                 }
               }
-            }
+            };
+            if (fused && MANY && K == 2) short_chain(std::integral_constant<int, MANY ? 2 : 4>{});
+            else if (fused) short_chain(std::integral_constant<int, 4>{});
           }
           if (!done) {  // in the fixed order of roundings
+            AheadRec rf[SOFT ? 4 : 1];
+#pragma unroll
+            for (int e = 0; e < (SOFT ? 4 : 1); ++e) rf[e] = rn[e];
+            if (far) fetch_rec(rf, it);
             double diff[4];
             if constexpr (SOFT) {
               double v[4], ex[4];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 const double moved = __dmul_rn(dscale, (double)D[e]);
-                v[e] = c0 + e < K ? (lp ? moved : __dadd_rn((double)rn[e].phi, moved)) : -INFINITY;
+                v[e] = c0 + e < K ? (lp ? moved : __dadd_rn((double)rf[e].phi, moved)) : -INFINITY;
               }
               double mx = fmax(fmax(v[0], v[1]), fmax(v[2], v[3]));
               mx = fmax(mx, bank_swap_f64(mx));
@@ -271,21 +283,21 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
               sum = __dadd_rn(sum, bank_swap_f64(sum));
               sum = __dadd_rn(sum, half_swap_f64(sum));
 #pragma unroll
-              for (int e = 0; e < 4; ++e) diff[e] = __dadd_rn(__ddiv_rn(ex[e], sum), -rn[e].p0);
+              for (int e = 0; e < 4; ++e) diff[e] = __dadd_rn(__ddiv_rn(ex[e], sum), -rf[e].p0);
             } else {
-              const double a0 = (double)rn[0].phi, moved = __dmul_rn(dscale, (double)D[0]);
+              const double a0 = (double)rf[0].phi, moved = __dmul_rn(dscale, (double)D[0]);
               if (a.loss == HALP_LOSS_SQUARED) {
                 // Algorithm 4: (phi + Delta - y) - (phi - y) = Delta; Algorithm 2: (x^T w - y) - (phi - y)
                 diff[0] = lp ? __dadd_rn(moved, -a0) : moved;
               } else {
                 const double y = (double)yn, a1 = lp ? moved : __dadd_rn(a0, moved);
-                diff[0] = __dadd_rn(__ddiv_rn(-y, __dadd_rn(1.0, halp_exp(__dmul_rn(y, a1)))), -rn[0].p0);
+                diff[0] = __dadd_rn(__ddiv_rn(-y, __dadd_rn(1.0, halp_exp(__dmul_rn(y, a1)))), -rf[0].p0);
               }
             }
 #pragma unroll
             for (int e = 0; e < (SOFT ? 4 : 1); ++e) {
               const double beta = __dmul_rn(aB, diff[e]);
-              const double rho = __dmul_rn((double)rn[e].rho, 0x1p-32);
+              const double rho = __dmul_rn((double)rf[e].rho, 0x1p-32);
               const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), rho));
               const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
               const bool in = m0 < nrow && c0 + e < K;
@@ -295,8 +307,13 @@ __global__ __launch_bounds__(64 * kWaves) void inner_softmax_mfma_kernel(InArgs 
           }
         }
         lds_barrier();  // gamma is out
-        fetch_rec(it + 1);
-        draw();
+        if (far) {
+          draw();
+          fetch_rec(rn, it + 2);
+        } else {
+          fetch_rec(rn, it + 1);
+          draw();
+        }
         if (MANY) ch = ch + 1 == nchunk ? 0 : ch + 1;
       }
     }
