@@ -7,6 +7,7 @@ import paper_1803_03383_amd as hp
 import test_gpu_svrg
 from gpu_util import GpuProblem
 from oracle import ref
+from test_gpu_lpsvrg import _lp_case
 from test_gpu_parity import _inner_case, _oracle_inner, _run_inner
 
 pytestmark = pytest.mark.gpu
@@ -145,3 +146,43 @@ def test_l2_draws_at_the_edges_of_the_words(loss, d, b, draw, inside):
     P.h.inner_loop(3)
     assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
     assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
+
+
+@pytest.mark.parametrize("loss,d,b,lam", [
+    (hp.LOSS_SQUARED, 64, 16, 0.0), (hp.LOSS_LOGISTIC, 50, 16, 1e-3),     # one strip per lane
+    (hp.LOSS_SQUARED, 100, 16, 1e-3), (hp.LOSS_LOGISTIC, 128, 16, 0.0),   # two
+    (hp.LOSS_SQUARED, 256, 16, 0.0), (hp.LOSS_LOGISTIC, 200, 16, 1e-3),   # four
+    (hp.LOSS_LOGISTIC, 60, 8, 5e-2), (hp.LOSS_SQUARED, 100, 8, 5e-2),     # rows in 16 lanes; two strips
+    (hp.LOSS_LOGISTIC, 256, 8, 0.0), (hp.LOSS_LOGISTIC, 512, 8, 5e-2),    # two, four
+])
+@pytest.mark.parametrize("lp", [False, True])
+def test_more_chains_than_cus(loss, d, b, lam, lp):
+    """The builds held to 128 registers, over shared data, the library's choice at 300 chains: every chain against one
+    wave per chain, chains around the count of CUs against the oracle."""
+    N, T, R, seed, alpha, delta = 100, 61, 300, 19, 0.02, 2.0 ** (-6 if b == 8 else -13)
+    if lp:
+        case = _lp_case(loss, N, d, 1, 1, b, 1, seed, alpha, delta)
+        lam = 0.0
+    else:
+        case = _inner_case(loss, N, d, 1, 1, b, lam, 1, T, seed, mu=0.2)
+    mk = lambda r: ref.make_problem(N, d, loss=loss, b=b, alpha=alpha, mu=0.2, lam=lam, delta_d=case["dd"], seed=900 + r,
+                                    algorithm=ref.ALG_LPSVRG if lp else ref.ALG_HALP, delta=delta if lp else 0.0)
+    X, Xq, y, phi, w = (case[k][0] for k in ("X", "Xq", "y", "phi", "w"))
+    h, sc = case["h"][0], case["scales"][0]
+    z0 = case["z"][0] if lp else np.zeros((1, d), np.int32)
+    res = []
+    for helpers in (0, 2):  # 2: no helper waves, i.e. not this form
+        P = GpuProblem(X, Xq, y, R=R, loss=loss, b=b, T=T, alpha=alpha, mu=0.2, lam=lam, delta_d=case["dd"], seed=900,
+                       share_data=True, w0=np.repeat(w[None], R, axis=0),
+                       algorithm=hp.ALG_LPSVRG if lp else hp.ALG_HALP, delta=delta if lp else 0.0)
+        for name, v in (("phi", phi), ("h", h), ("scales", sc), ("z", z0)):
+            P.put(name, np.repeat(np.asarray(v)[None], R, axis=0))
+        P.h.set_option(hp.OPT_INNER_HELPERS, helpers)
+        P.h.inner_loop(3)
+        res.append([P.get(k).copy() for k in ("z", "w", "counters")])
+    for a, c in zip(*res):
+        assert np.array_equal(a, c)
+    for r in (0, 255, 256, R - 1):
+        out = ref.inner_loop(mk(r), Xq, phi, y, h, sc, 3, T, z0=z0)
+        assert np.array_equal(res[0][0][r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(res[0][2][r].astype(np.uint64), out["counters"])
