@@ -568,7 +568,7 @@ def main():
              (args.inner_helpers == 0 and args.inner_waves == 0 and R <= per_cu * 256)))
     helped = (not lone and args.algorithm != "svrg" and args.inner_helpers in (0, 1)
               and args.inner_waves in (0, 2, 4) and d <= 1024 and (R <= 5 * 256 or args.inner_helpers == 1))
-    svrg_lone = args.inner_waves == 0 and R <= (1 if d > 512 else (2 if d > 256 else (8 if d > 64 else 5))) * 256
+    svrg_lone = d <= 1024 and args.inner_waves == 0 and R <= (1 if d > 512 else (2 if d > 256 else (8 if d > 64 else 5))) * 256
     inner_kernel = ("inner_svrg_lone_kernel" if svrg_lone else "inner_svrg_kernel") if args.algorithm == "svrg" else (
         "inner_reg_lone_kernel" if lone else ("inner_reg_helped_kernel" if helped else "inner_reg_kernel"))
     alu_achieved = updates * laneops / (inner_ms * 1e-3)
