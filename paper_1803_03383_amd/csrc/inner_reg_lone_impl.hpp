@@ -472,16 +472,16 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
       part = part == kHis - 1 ? 0 : part + 1;
     };
     fill_batch(0);
-    fill_batch(1);
-    __syncthreads();  // P0: the first two batches are in place
+    __syncthreads();  // P0: the first batch is in place
     __syncthreads();  // P1: the records of windows 0 and 1 are in place
     auto run = [&](auto fold_tag) __attribute__((always_inline)) {
       keep_z(zs, fold_tag);
       for (int64_t w = 0; w < nwin + 2; ++w) {
         if (w >= 2) count_window(w - 2, fold_tag);
         if (w >= 1 && w <= nwin) take(w - 1);
-        // window w = 32 m + 1: every reader has left batch m - 1, whose half takes batch m + 1
-        if ((w & (kBatch / kWin - 1)) == 1 && w > 1 && w < nwin) fill_batch(w / (kBatch / kWin) + 1);
+        // window w = 32 m + 1: every reader has left batch m - 1, whose half takes batch m + 1 (the first to read indices
+        // out of it are the helpers in period 32 m + 27; an epoch that ends before then has nobody who does)
+        if ((w & (kBatch / kWin - 1)) == 1 && w < nwin) fill_batch(w / (kBatch / kWin) + 1);
         if (w <= nwin) __syncthreads();  // w = nwin: P2, the last gammas are in place
       }
     };
@@ -521,8 +521,8 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
         hfp[i] = S::join(hf[0], hf[1]);
         take[i] = S::take(i, CT * (g0 + i) < d, CT * (g0 + i) + 1 < d);
       }
-      // The rows of a window: its eight sample indices in two LDS reads (every entry of the index ring is
-      // a valid row at any time, so windows past the end of the epoch fetch rows that are never used),
+      // The rows of a window: its eight sample indices in two LDS reads (every entry that is read is a valid row, also
+      // for windows past the end of the epoch, whose rows are never used),
       // then one multiply-add for the address and one load per step.
       const unsigned char* const frag = Xq + (g0 < U ? 2 * g0 : 0);  // lanes past the row re-read its first bytes
       auto request = [&](uint32_t (&dst)[kWin], int64_t win) {
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(64 * waves_of(UPL, LANES), PAIR ? 4 : 2) void inner
             S::record(fr[s], i, take[i], pick(zn[i], (uint32_t)(s >> 1)), s, hlp[i], &xw[s * kStep + i], &cw[s * kStep + i]);
         }
       };
-      __syncthreads();  // P0: the first two batches are in place
+      __syncthreads();  // P0: the first batch is in place
       if (s_fold) {
 #pragma unroll
         for (int i = 0; i < SPH; ++i) hlp[i] = hfp[i];

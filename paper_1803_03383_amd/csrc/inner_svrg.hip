@@ -276,12 +276,12 @@ __global__ __launch_bounds__(64 * sv_waves(NV), PAIR ? 4 : 2) void inner_svrg_lo
       }
     };
     fill_batch(0);
-    fill_batch(1);
-    __syncthreads();  // P0: the first two batches are in place
+    __syncthreads();  // P0: the first batch is in place
     __syncthreads();  // P1: windows 0 and 1 are in the ring
     for (int64_t w = 0; w < nwin; ++w) {
-      // window w = 32 m: every reader has left batch m - 1, whose half takes batch m + 1
-      if ((w & (kBatch / kWin - 1)) == 0 && w > 0) fill_batch(w / (kBatch / kWin) + 1);
+      // window w = 32 m: every reader has left batch m - 1, whose half takes batch m + 1 (the first to read indices out
+      // of it are the helpers in period 32 m + 27 or later; an epoch that ends before then has nobody who does)
+      if ((w & (kBatch / kWin - 1)) == 0) fill_batch(w / (kBatch / kWin) + 1);
       __syncthreads();
     }
     return;
