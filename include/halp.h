@@ -208,7 +208,8 @@ typedef struct {
                                     1024 coordinates (HALP_ERR_UNSUPPORTED elsewhere); 0 takes
                                     it, and its 16-bit twin for rows up to 512 coordinates, up
                                     to one chain per CU, two for up to 256 strips of 16 rounding
-                                    bits, three to six for up to 128.  Results do not
+                                    bits, three to six for up to 128 (logistic rows of up to 64
+                                    coordinates not between two and three).  Results do not
                                     depend on it                                              */
 
 #define HALP_OPT_EXCHANGE_POLL_DELAY 11 /* split minibatch loop: sleeps of 256 cycles between a
