@@ -77,17 +77,18 @@ Lone lone_shape(const halp_handle& h) {
 // rows and steps, shared data), what runs without it / this form, in three kinds of epoch: -h~ rides in the records; it
 // does not (mu = 8); lambda = 0.01 with alpha = 0.1, a draw in every fourth step at 8 bits and in every one at 16:
 //   8 bits, squared    d = 64    256 chains 141/80 141/92 158/87, 1280 202/145 201/174 224/175, 1536 202/169 202/211 225/206
-//                      d = 128   520 144/126 145/148 161/147, 768 145/127 145/149 161/148, 900 147/147 without the others
+//                      d = 128   520 144/126 145/148 161/147, 768 145/127 145/149 161/148, 900 (first kind alone) 147/147
 //                      d = 256   256 132/85 131/99 194/92, 1024 206/153 208/179 224/177, 1536 276/231 278/267 311/273
 //                      d = 512   256 157/112 159/134 230/126 (two workgroups fit a CU; 600 chains would take two turns)
 //                      d = 1024  256 244/172 245/209 337/200 (one fits)
-//   8 bits, logistic   d = 64    256 243/194 244/203 262/203, 768 493/596 per 2000 steps in us, 1024 393/364 391/391 416/389
+//   8 bits, logistic   d = 64    256 243/194 244/203 262/203, 768 (first kind) 247/298, 1024 393/364 391/391 416/389
 //                      d = 256   520 394/220 394/241 417/249, 1024 442/410 437/438 456/426; d = 1024 256 349/275 349/304 451/301
 //   16 bits, squared   d = 64    520 158/100 158/103 172/120, 1536 224/167 221/171 244/181
 //                      d = 128   520 212/122 212/126 235/138, 1536 265/241 266/241 295/257; d = 256 256 213/128 206/129 225/133
 //                      d = 512   256 240/186 233/194 242/197
-//   16 bits, logistic  d = 64    768 518/648 per 2000 steps in us, 1024 410/354 408/365 431/358; d = 128 1024 482/423 484/425 500/435
+//   16 bits, logistic  d = 64    768 (first kind) 259/324, 1024 410/354 408/365 431/358; d = 128 1024 482/423 484/425 500/435
 // So 1536 chains of up to 64 coordinates and 768 of 65 .. 128 lose 2 - 5 % where -h~ is large and gain 12 - 17 % where it is not.
+// (Epochs of a few steps take 2 - 4 us more than without it, up to 40 steps; 150 at 512 coordinates of 16 bits.)
 bool lone_pays(const halp_handle& h, Lone sh) {
   const bool logistic = h.p.loss == HALP_LOSS_LOGISTIC;
   const int64_t R = h.p.R, cus = h.num_cus;
