@@ -28,10 +28,10 @@
 // blocks, requests the row fragments kSets - 1 windows ahead and writes its dwords of the records.
 // Where -h~ / 2^b is not small in every coordinate, n leaves its word: the records then carry only
 // the low b bits of -h~, z is kept as it is and the chain wave adds the rest behind the shift (FOLD = false;
-// five instructions per strip, the sum of z and that rest being made beforehand).  A service wave refills the 256-step batches of step-indexed draws
-// (sample indices, rounding draws of gamma and of the L2 term, margins and labels of the
-// sampled rows) and counts the clamped coordinates: the chain wave stores the gammas of a window in
-// LDS and the service wave, which holds a z of its own, takes it through the same steps with and
+// five instructions per strip, the sum of z and that rest being made beforehand).  A service wave refills the
+// 256-step batches of step-indexed draws (sample indices, rounding draws of gamma and of the L2 term, margins and
+// labels of the sampled rows), counts the steps with an L2 draw and the clamped coordinates: the chain wave stores
+// the gammas of a window in LDS and the service wave, which holds a z of its own, takes it through the same steps with and
 // without saturation.  One barrier per window orders every hand-over: in period w the chain wave
 // consumes window w out of a ring of four and requests the first records of window w + 1 before the
 // barrier, the helpers make window w + 2, and the service wave takes the records of window w - 1 out
