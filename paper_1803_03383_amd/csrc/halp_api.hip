@@ -226,6 +226,7 @@ int halp_create(halp_handle** out, const halp_params* p) {
   if (const size_t bytes = plan_inner_softmax_split(*h)) {
     if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), bytes),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
+    if (prepare_inner_softmax_split(*h) != HALP_OK) { halp_destroy(h); return HALP_ERR_HIP; }
   }
   if (const size_t bytes = plan_inner_softmax_mfma(*h) + plan_inner_softmax(*h)) {  // one of them at most
     if (hip_fail(hipMalloc(&h->ahead_ws, bytes), "hipMalloc(ahead_ws)")) { halp_destroy(h); return HALP_ERR_HIP; }

@@ -19,9 +19,11 @@ struct U4 {
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64 multiplies
 // whose high halves are mixed with the neighbouring counter words and a Weyl
 // sequence of round keys.
-__device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
+template <int FIRST, int END>  // rounds FIRST .. END - 1 of the ten
+__device__ __forceinline__ U4 philox_rounds(U4 c, uint64_t seed) {
+  uint32_t k0 = (uint32_t)seed + FIRST * 0x9E3779B9u, k1 = (uint32_t)(seed >> 32) + FIRST * 0xBB67AE85u;
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
+  for (int r = FIRST; r < END; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * c.x;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c.z;
     U4 n;
@@ -34,6 +36,10 @@ __device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
     k1 += 0xBB67AE85u;
   }
   return c;
+}
+
+__device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
+  return philox_rounds<0, 10>(c, (uint64_t)k1 << 32 | k0);
 }
 
 // Block `blk` of the word stream of a purpose: counter (lo(blk), hi(blk), epoch, purpose).

@@ -93,6 +93,7 @@ int inner_softmax_supported(const halp_handle& h);
 int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t s);
 // sets how many chains a launch takes; bytes of workspace (exchange words and z), 0 for other kernels' shapes
 size_t plan_inner_softmax_split(halp_handle& h);
+int prepare_inner_softmax_split(const halp_handle& h);  // once, after the workspace's allocation
 int inner_softmax_split_supported(const halp_handle& h);  // softmax, a chain cut across workgroups
 int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t s);
 size_t plan_inner_softmax_mfma(halp_handle& h);  // as plan_inner_softmax, the minibatch kernel on the matrix cores

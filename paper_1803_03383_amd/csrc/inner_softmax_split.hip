@@ -7,13 +7,13 @@
 // in registers for the whole epoch; a class wave loads its fragment of the sampled row itself,
 // eight steps ahead.
 //
-// The only thing the workgroups of a chain share is x_i^T z_c.  A class wave adds its part to
-// the class's 64-bit word in device memory with one device-scope atomic: the part in the low
-// 56 bits, a 1 in the top byte.  The service waves read the K words until every top byte has
-// moved by P since the word's last use (two sets of words, by step parity; words are never
-// reset, both fields are taken as differences modulo 2^64), so arrival, sum and hand-over are
-// one trip out and one trip back.  Integer sums: the order of arrival does not matter.  Every
-// workgroup then evaluates the same K gammas.
+// The only thing the workgroups of a chain share is x_i^T z_c.  The class waves leave their parts
+// in LDS, and the service wave adds them to the classes' 64-bit words in device memory with one
+// device-scope atomic instruction: the part in the low 56 bits, a 1 in the top byte.  It then reads
+// the K words until every top byte has moved by P since the word's last use (two sets of words, by
+// step parity; words are never reset, both fields are taken as differences modulo 2^64), so
+// arrival, sum and hand-over are one trip out and one trip back.  Integer sums: the order of
+// arrival does not matter.  Every workgroup then evaluates the same K gammas.
 //
 // A wait has a limit: on a device whose CUs other work holds, some of a chain's workgroups may not
 // get to run while the others wait.  z therefore goes to a workspace, and only a chain none of
@@ -21,16 +21,22 @@
 // from the z they came with (one launch of workgroups that read a flag where there are none).
 //
 // One step:
-//   class waves   x_i^T z_c over the slice, DPP fold, one atomic add per class; meanwhile
-//                 (the trip takes ~0.7 us) the next window's Philox blocks, one strip at a time
-//   service wave  rounding draws and the softmax of the margins for the next step, then polls,
-//                 softmax after the offset, gamma_c into LDS                             | barrier
+//   class waves   x_i^T z_c over the slice, DPP fold, the part into LDS                    | barrier
+//   service wave  adds the parts, makes part of the draws and of the softmax of the margins of
+//                 a later step, polls, softmax after the offset, gamma_c into LDS
+//   class waves   (the trip takes 0.5-0.7 us) a share of the next window's Philox blocks,
+//                 what of the update needs no gamma                                        | barrier
 //   class waves   integer update of their rows
 //
-// What bounds it: latency.  Per step ~0.1 us dot and fold, 0.6-0.9 us for the exchange (P = 4
-// .. 32: ~0.01 us per atomic on one word; one word per 256 bytes, since atomics of different
-// waves on one line queue up: 10 waves on one line took 2.6 us at P = 20 instead of 1.0), ~0.35 us
-// for the fp64 softmax and quantizer, the rest barrier and update.
+// What bounds it: latency, most of it the exchange.  One wave adds all classes at once because
+// atomics of different waves queue up: with one atomic per class wave, words 256 bytes apart, a step of
+// nothing but the exchange took 1.10 us at P = 4 and 1.57 at P = 20, this way 0.85 and 0.89 (K = 10,
+// the parts on one XCD).  The atomics, and the first read behind them, are served by the memory
+// a page of 4096 bytes is homed in: 0.23 us for the nearest, 0.36 for the farthest of the eight that
+// alternate, so a chain's words lie in the page nearest to its XCD, which halp_create finds by timing
+// (find_near): 1100 x 5 three chains 1.66 -> 1.38 us per step.  us per step, one atomic per class wave -> now:
+// 10000 x 10 8 bits one chain 3.06 -> 2.00, five 3.52 -> 2.32, 16 bits five 3.86 -> 2.83; 4000 x 5 five chains 2.06 -> 1.51;
+// 2000 x 10 1.89 -> 1.54; 1100 x 2 1.27 -> 1.20.
 #include <algorithm>
 
 #include "halp_device.hpp"
@@ -43,7 +49,6 @@ namespace {
 constexpr int kWin = 8;          // steps per Philox window
 constexpr int kIdxRing = 64;     // sample indices are drawn 64 steps at a time
 constexpr int kKC = 16;          // classes are padded to one DPP row
-constexpr int kWordStride = 32;  // 64-bit words between two classes' exchange words (256 bytes)
 
 __device__ __forceinline__ int mad24(int a, int b, int c) {
   int r;
@@ -57,9 +62,44 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Exchange words: sixteen chains to eight pages of 4096 bytes, 256 bytes each in the page that lies nearest.
+constexpr int kPage = 4096, kPages = 8, kChainsPerPage = 16, kPageWords = kPage / 8;
+
+__host__ __device__ __forceinline__ size_t split_words(int chains) {
+  return (size_t)((chains + kChainsPerPage - 1) / kChainsPerPage) * kPages * kPageWords;
+}
+
+__device__ __forceinline__ unsigned long long* words_of(unsigned long long* xbuf, int local, int page) {
+  return xbuf + (int64_t)(local / kChainsPerPage * kPages + page) * kPageWords +
+         (local % kChainsPerPage) * (kPageWords / kChainsPerPage);
+}
+
+// Workgroup x (on XCD x) finds the page of the first eight with the shortest atomics: near[x].
+__global__ void find_near(unsigned long long* xbuf, int* near) {
+  if (threadIdx.x != 0) return;
+  long long best = INT64_MAX;
+  int at = 0;
+  for (int p = 0; p < kPages; ++p) {
+    unsigned long long* w = xbuf + (int64_t)p * kPageWords + blockIdx.x * 16;
+    long long least = INT64_MAX;
+    for (int i = 0; i < 8; ++i) {
+      const long long t0 = clock64();
+      const unsigned long long v = __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("" ::"v"((uint32_t)v) : "memory");
+      const long long dt = clock64() - t0;
+      least = dt < least ? dt : least;
+    }
+    if (least < best) {
+      best = least;
+      at = p;
+    }
+  }
+  near[blockIdx.x] = blockIdx.x < 8 ? at : 0;
+}
+
 template <int BITS, int UPL, int CPW, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs a, int P, int chain0, int nchains,
-                                                                        int same_xcd, unsigned long long* xbuf,
+                                                                        int same_xcd, const int* near, unsigned long long* xbuf,
                                                                         int spin_limit) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
   using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
@@ -95,7 +135,8 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
   unsigned long long* cnt_out = reinterpret_cast<unsigned long long*>(a.counters + (int64_t)chain * 4);
   if (sc[7] != 0.0) return;  // converged or unusable gradient: no-op; the counters were cleared before the launch
 
-  unsigned long long* words = xbuf + (int64_t)local * 2 * kKC * kWordStride;  // [parity][class][kWordStride]
+  unsigned long long* words = words_of(xbuf, local, near[same_xcd ? blockIdx.x & 7 : 8]);  // [parity][class]: a 128-byte line per parity
+  __shared__ long long s_part[kKC];  // this workgroup's x_i^T z_c
   __shared__ int s_idx[2][kIdxRing];
   __shared__ int s_ng[2][kKC];  // -gamma_c
   __shared__ int s_cl[2];       // c_lambda
@@ -118,14 +159,11 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     const double aB = a.hyper[2 * chain];  // alpha / B, B = 1
     const double al = __dmul_rn(aB, a.lambda);
     unsigned int n_gclamp = 0, n_reg = 0, n_timeout = spin_limit < 0 ? 1u : 0u;
-    const int lc = min(lane, K - 1);
+    const int c16 = lane & 15;
+    const int lc = min(c16, K - 1);
     const bool live = lane < K;
 
-    const int i0v = draw_idx(0);
-    s_idx[0][lane] = i0v;
-    float phir[kWin];
-#pragma unroll
-    for (int s = 0; s < kWin; ++s) phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(i0v, s) * K + lc];
+    s_idx[0][lane] = draw_idx(0);
     __syncthreads();
 
     auto softmax = [&](double v) {  // this lane's class probability
@@ -135,49 +173,62 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       return __ddiv_rn(e, row_sum_f64(e));
     };
     // The step's gammas come from the short chain of softmax_fused.hpp, which has its classes in other lanes:
-    // what is made one class per lane of the first sixteen goes there through LDS's lane exchange, beside the
-    // trip of the sums.
-    // Not at 16 bits with eight strips per lane, where the class waves' registers are the most and a step got longer with
-    // it: us per step, short chain / fixed order, K = 10: 10000 one chain 3.52 / 3.32, five 3.70 / 3.49, 6500 three 3.13 / 3.09;
-    // with four strips 2000 x 10 2.15 / 2.16, 4000 x 5 2.46 / 2.47.
-    constexpr bool kShort = !(BITS == 16 && UPL == 8);
-    const int rc = kShort ? soft_class(lane) : lc;
-    const bool live_f = kShort ? rc < K : live;
-    const bool fused = kShort && soft_covers(dscale, aB, inv_s);
+    // what is made one class per lane of a row of sixteen goes there through LDS's lane exchange, beside the
+    // trip of the sums.  (16 bits with eight strips per lane, which kept the fixed order while this wave also drew
+    // every step's words: 10000 x 10 five chains 2.88 us per step with the fixed order, 2.83 with the short chain.)
+    const int rc = soft_class(lane);
+    const bool live_f = rc < K;
+    const bool fused = soft_covers(dscale, aB, inv_s);
     const double k2 = __dmul_rn(aB, inv_s);
-    auto to_lane = [&](int src, int v) { return __builtin_amdgcn_ds_bpermute(src << 2, v); };
-    auto to_lane64 = [&](int src, uint64_t v) {
-      return (uint64_t)(uint32_t)to_lane(src, (int)(uint32_t)v) | ((uint64_t)(uint32_t)to_lane(src, (int)(v >> 32)) << 32);
+    auto from_lane = [&](int src, int v) { return __builtin_amdgcn_ds_bpermute(src << 2, v); };
+    auto from_lane64 = [&](int src, uint64_t v) {
+      return (uint64_t)(uint32_t)from_lane(src, (int)(uint32_t)v) | ((uint64_t)(uint32_t)from_lane(src, (int)(v >> 32)) << 32);
     };
-    // rounding word of gamma_c (lanes 0..15: word t K + c) and of the L2 draw (lane 16: word t) of
-    // a step, one Philox evaluation
-    double rho_n = 0.0;
-    uint32_t word_n = 0;
-    int cl_n = 0;
-    auto draw_scalars = [&](int64_t t) {
-      const bool reg = lane == 16;
-      const uint64_t n = reg ? (uint64_t)t : (uint64_t)t * (uint64_t)K + (uint64_t)lc;
-      const U4 r = stream_block(seed, reg ? kReg : kGamma, a.epoch, n >> 2);
-      const uint32_t w = pick(r, (uint32_t)(n & 3));
-      rho_n = __dmul_rn((double)w, 0x1p-32);
-      word_n = w;
-      cl_n = 0;
-      if (use_reg)
-        cl_n = __builtin_amdgcn_readlane(
-            (int)quantize_real(al, (double)(1 << BITS), w, 0.0, (double)QMAX, nullptr), 16);
+    // What a step needs and does not follow from z is made for four steps at a time, one to a row of 16 lanes: the
+    // margins of the row, their softmax, the rounding words of gamma (class c of step t: word t K + c).  Half 0 are the first
+    // four steps of a window, half 1 the others.
+    float ph_req[2], ph[2];
+    double p0q[2];
+    uint32_t word[2];
+    auto request_phi = [&](int half, int64_t win) {
+      const int tn = (int)((win + 4 * half) & (2 * kIdxRing - 1)) + (lane >> 4);
+      ph_req[half] = phi[(int64_t)s_idx[tn >> 6][tn & (kIdxRing - 1)] * K + lc];
     };
-    double a0_n = (double)phir[0], p0_n = softmax(a0_n);
-    draw_scalars(0);
+    // in three stages, so that none is longer than the trip that it runs beside
+    U4 mk_word{};
+    double mk_v = 0.0;
+    auto make_half = [&](int half, int64_t win, int stage) __attribute__((always_inline)) {
+      if (stage == 0) {
+        const uint64_t n = (uint64_t)(win + 4 * half + (lane >> 4)) * (uint64_t)K + (uint64_t)lc;
+        mk_word = philox_rounds<0, 4>(U4{(uint32_t)(n >> 2), (uint32_t)(n >> 34), a.epoch, (uint32_t)kGamma}, seed);
+        const double val = c16 < K ? (double)ph_req[half] : -INFINITY;
+        mk_v = __dadd_rn(val, -row_max_f64(val));
+      } else if (stage == 1) {
+        mk_word = philox_rounds<4, 7>(mk_word, seed);
+        mk_v = c16 < K ? halp_exp(mk_v) : 0.0;
+      } else {
+        const uint32_t n3 = ((uint32_t)(win + 4 * half + (lane >> 4)) * (uint32_t)K + (uint32_t)lc) & 3;
+        word[half] = pick(philox_rounds<7, 10>(mk_word, seed), n3);
+        p0q[half] = __ddiv_rn(mk_v, row_sum_f64(mk_v));
+        ph[half] = ph_req[half];
+      }
+    };
+    request_phi(0, 0);
+    request_phi(1, 0);
+#pragma unroll
+    for (int stage = 0; stage < 3; ++stage) make_half(0, 0, stage);
+    request_phi(0, kWin);
     SoftDraw dr_n{};
     double from_n = 0.0;
-    auto draw_fused = [&]() {
-      if constexpr (!kShort) return;
-      const float ph = __builtin_bit_cast(float, to_lane(rc, __builtin_bit_cast(int, (float)a0_n)));
-      const double p = __builtin_bit_cast(double, to_lane64(rc, __builtin_bit_cast(uint64_t, p0_n)));
-      dr_n = soft_draw<true>(live_f, p, ph, (uint32_t)to_lane(rc, (int)word_n), k2);
-      from_n = lp && live_f ? (double)ph : 0.0;  // Algorithm 2: x^T w is the whole margin
+    auto draw_fused = [&](int s) __attribute__((always_inline)) {  // step s of the window
+      const int src = 16 * (s & 3) + rc, half = s >> 2;
+      const float p = __builtin_bit_cast(float, from_lane(src, __builtin_bit_cast(int, ph[half])));
+      const double q = __builtin_bit_cast(double, from_lane64(src, __builtin_bit_cast(uint64_t, p0q[half])));
+      dr_n = soft_draw<true>(live_f, q, p, (uint32_t)from_lane(src, (int)word[half]), k2);
+      from_n = lp && live_f ? (double)p : 0.0;  // Algorithm 2: x^T w is the whole margin
     };
-    draw_fused();
+    draw_fused(0);
+    int cl64 = 0;  // lane l: the L2 draw of step 64 k + l
     unsigned long long old[2] = {0, 0};
 
     for (int64_t t0 = 0; t0 < T; t0 += kWin) {
@@ -185,22 +236,27 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
         const int64_t blk = (t0 / kIdxRing) + 1;
         s_idx[blk & 1][lane] = draw_idx(blk);
       }
-      const int tn = (int)((t0 + kWin) & (2 * kIdxRing - 1)) + (lane & 7);
-      const int idxn = s_idx[tn >> 6][tn & (kIdxRing - 1)];
+      if (use_reg && (t0 & (kIdxRing - 1)) == 0) {
+        const uint64_t n = (uint64_t)t0 + (uint64_t)lane;
+        const uint32_t w = pick(stream_block(seed, kReg, a.epoch, n >> 2), (uint32_t)(n & 3));
+        cl64 = (int)quantize_real(al, (double)(1 << BITS), w, 0.0, (double)QMAX, nullptr);
+      }
 #pragma unroll
       for (int s = 0; s < kWin; ++s) {
         const int64_t t = t0 + s;
         if (t < T) {
-          const double a0 = a0_n, p0 = p0_n, rho = rho_n, from = from_n;
+          const double from = from_n;
           const SoftDraw dr = dr_n;
-          const int cl = cl_n;
-          // beside the class waves' dots and the trip of their sums: all that does not need them
-          draw_scalars(t + 1);
-          a0_n = (double)phir[(s + 1) % kWin];
-          p0_n = softmax(a0_n);
-          draw_fused();
-          phir[s] = phi[(int64_t)__builtin_amdgcn_readlane(idxn, s) * K + lc];  // step t + 8
-          unsigned long long* w = words + (s & 1) * kKC * kWordStride + (kShort && !live_f ? 0 : rc) * kWordStride;
+          const int cl = use_reg ? __builtin_amdgcn_readlane(cl64, (int)(t & (kIdxRing - 1))) : 0;
+          unsigned long long* w = words + (s & 1) * kKC + (live_f ? rc : 0);
+          lds_barrier();  // the workgroup's parts are in LDS
+          if (live_f && soft_first_copy(lane))
+            __hip_atomic_fetch_add(w, (1ull << 56) + (unsigned long long)s_part[rc], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+          // beside the trip of the sums: all that does not need them
+          if (s < 3) make_half(1, t0, s);
+          if (s >= 4 && s < 7) make_half(0, t0 + kWin, s - 4);
+          draw_fused((s + 1) % kWin);
           unsigned long long v = old[s & 1];
           for (int spin = 0; n_timeout == 0; ++spin) {  // after one wait ran out, none is tried again
             if (live_f) v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -211,8 +267,15 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
           }
           const long long D = (long long)(v - old[s & 1] - ((unsigned long long)P << 56));
           old[s & 1] = v;
+          // a window ahead, and behind the polls, which would wait for them
+          if (s == 2) request_phi(1, t0 + kWin);
+          if (s == 6) request_phi(0, t0 + 2 * kWin);
           double f = 0.0, fc = 0.0;  // gamma in the fixed order of roundings, classes in the first lanes
           auto fixed = [&](double moved) __attribute__((always_inline)) {
+            const int src = 16 * (s & 3) + lc, half = s >> 2;
+            const double a0 = (double)__builtin_bit_cast(float, from_lane(src, __builtin_bit_cast(int, ph[half])));
+            const double p0 = __builtin_bit_cast(double, from_lane64(src, __builtin_bit_cast(uint64_t, p0q[half])));
+            const double rho = __dmul_rn((double)(uint32_t)from_lane(src, (int)word[half]), 0x1p-32);
             const double p1 = softmax(lp ? moved : __dadd_rn(a0, moved));
             // beta_c = alpha (p_c(phi + x^T z) - p_c(phi)), gamma_c = Q_(delta_s, b)(beta_c)
             const double beta = __dmul_rn(aB, __dadd_rn(p1, -p0));
@@ -220,22 +283,18 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
             fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
             if (live) s_ng[s & 1][lane] = (int)(-fc);
           };
-          int g = 0, hi = 0;
-          if constexpr (kShort) {
-            if (__builtin_expect_with_probability(
-                    fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
-              g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
-              s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
-            } else {
-              g = hi;
-              fixed(__dmul_rn(dscale, (double)(long long)to_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D)));
-            }
+          int g, hi = 0;
+          if (__builtin_expect_with_probability(
+                  fused && soft_gamma<true>(dr, live_f, live_f ? __fma_rn(dscale, (double)D, -from) : 0.0, &hi), 1, 1.0)) {
+            g = min(max(hi, kSoftMagicHi - QMAX), kSoftMagicHi - QMIN);
+            s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
           } else {
-            fixed(__dmul_rn(dscale, (double)D));
+            g = hi;
+            fixed(__dmul_rn(dscale, (double)(long long)from_lane64((lc & 3) + 16 * (lc >> 2), (uint64_t)D)));
           }
           if (lane == 0) s_cl[s & 1] = cl;
           lds_barrier();  // gamma is out; the class waves update z
-          if constexpr (kShort) n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
+          n_gclamp += (live_f && soft_first_copy(lane) && g != hi) ? 1u : 0u;
           n_gclamp += (live && f != fc) ? 1u : 0u;
           n_reg += (lane == 0 && cl != 0) ? 1u : 0u;
         }
@@ -308,6 +367,9 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     for (int cc = 0; cc < CPW; ++cc)
 #pragma unroll
       for (int u = 0; u < UPL; ++u) draw_block(zrn[cc][u], cc, u, 0u);
+    constexpr int kBlocks = CPW * UPL;  // a window's blocks
+    static_assert(kBlocks == 4 || kBlocks % 8 == 0);
+    U4 half_block{};
     unsigned long long n_zclamp = 0;
     __syncthreads();  // the first 64 indices are in LDS
     {
@@ -355,16 +417,25 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
 #pragma unroll
           for (int cc = 0; cc < CPW; ++cc) {
             const long long D = BITS == 8 ? (long long)wave_fold_i32((int)acc[cc]) : wave_fold_i64((long long)acc[cc]);
-            if (lane == 63)
-              __hip_atomic_fetch_add(&words[((s & 1) * kKC + cls0 + cc) * kWordStride],
-                                     (1ull << 56) + (unsigned long long)D, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 63) s_part[cls0 + cc] = D;
           }
+          lds_barrier();
           // while the sums travel: blocks of the next window, and what of the update needs no gamma
 #pragma unroll
-          for (int q = 0; q < (CPW * UPL + 7) / 8; ++q) {
-            const int ub = s * ((CPW * UPL + 7) / 8) + q;
-            if (ub < CPW * UPL) draw_block(zrn[ub / UPL][ub % UPL], ub / UPL, ub % UPL, (uint32_t)(t0 >> 3) + 1u);
+          for (int q = 0; q < kBlocks / 8; ++q) {
+            const int ub = s * (kBlocks / 8) + q;
+            draw_block(zrn[ub / UPL][ub % UPL], ub / UPL, ub % UPL, (uint32_t)(t0 >> 3) + 1u);
+          }
+          if constexpr (kBlocks % 8 != 0) {  // four blocks to eight steps: half of one each
+            const int ub = s / 2;
+            if (s % 2 == 0) {
+              half_block = philox_rounds<0, 5>(U4{(uint32_t)((cls0 + ub / UPL) * U + s0 + ub % UPL), (uint32_t)(t0 >> 3) + 1u,
+                                                  a.epoch, (uint32_t)kZround}, seed);
+            } else {
+              const U4 r = philox_rounds<5, 10>(half_block, seed);
+              zrn[ub / UPL][ub % UPL][0] = r.x; zrn[ub / UPL][ub % UPL][1] = r.y;
+              zrn[ub / UPL][ub % UPL][2] = r.z; zrn[ub / UPL][ub % UPL][3] = r.w;
+            }
           }
           S2 crp[CPW][PK ? UPL : 1], zh[CPW][PK ? UPL : 1];
           int hr[CPW][PK ? 1 : CPL];
@@ -449,7 +520,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
       XT* __restrict__ zg =
-          reinterpret_cast<XT*>(xbuf + (int64_t)nchains * 2 * kKC * kWordStride) + ((int64_t)local * K + cls0 + cc) * d;
+          reinterpret_cast<XT*>(xbuf + split_words(nchains)) + ((int64_t)local * K + cls0 + cc) * d;
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
         int zk;
@@ -462,7 +533,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
   }
 }
 
-using Kernel = void (*)(InArgs, int, int, int, int, unsigned long long*, int);
+using Kernel = void (*)(InArgs, int, int, int, int, const int*, unsigned long long*, int);
 
 int classes_per_wave(int K) { return K > 15 ? 2 : 1; }
 int block_threads(int K) { return 64 * (K / classes_per_wave(K) + 1); }
@@ -486,15 +557,16 @@ struct SplitShape {
   int upl, P;  // strips per lane, workgroups per chain
 };
 
-// Four strips per lane; eight where four would need more than 24 workgroups per chain (a longer
-// queue at the exchange words and a longer first arrival cost more than a second helping of
-// strips) and a wave has the registers.  us per step, N = 7500, five chains, K = 10, 4 / 8 strips:
-// 16 bits, d = 2000 2.2 / 2.3, 6500 3.2 / 2.8, 10000 4.3 / 3.1; 8 bits, where eight
-// strips spill 26 registers, 2000 1.9 / 2.6, 10000 3.0 / 3.4, 15000 3.5 / 3.8; K = 5, d = 4001 1.9 / 1.9.  Two strips
-// were nowhere the faster ones.
+// Four strips per lane; eight where four would need more workgroups than an XCD has CUs (32) and a wave has the
+// registers, or where beyond 24 the chains would no longer fit the device one workgroup to a CU.
+// us per step, 4 / 8 strips: 16 bits 6500 x 10 (26 workgroups with four strips) three chains 2.08 / 2.44, 8000 x 10 (32) 2.10 / 2.42,
+// 6500 x 5 1.70 / 1.86; 8 bits 15000 x 10 (30) 2.40 / 2.87; past 32 workgroups (40) 10000 x 10 16 bits 2.47 / 2.50, 20000 x 10
+// 8 bits 2.83 / 3.04, but 10000 x 3 16 bits 2.00 / 1.73 and 20000 x 4 8 bits 2.30 / 1.99.
 SplitShape pick_shape(const halp_params& p) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
-  const int upl = p.K < 12 && (U + 255) / 256 > 24 ? 8 : 4;
+  const int P4 = (U + 255) / 256;
+  const bool four = p.K >= 12 || P4 <= 24 || (P4 <= 32 && (int64_t)p.R * P4 <= 256);
+  const int upl = four ? 4 : 8;
   const int P = (U + 64 * upl - 1) / (64 * upl);
   return SplitShape{upl, P};
 }
@@ -504,18 +576,11 @@ Kernel kernel_for(const halp_params& p) {
   return p.b == 8 ? kernel_for<8>(p.K, upl) : kernel_for<16>(p.K, upl);
 }
 
-size_t split_words(int chains) { return (size_t)chains * 2 * kKC * kWordStride; }
-
-// The words begin at an odd multiple of 4096 bytes, so that a chain's two sets, 4096 bytes each, lie in
-// different aligned blocks of 8192.  us per step with the words at an even multiple and at an odd one:
-// d = 4000, K = 10, 8 bits, 5 chains 2.44 and 2.17, 32 chains 2.69 and 2.32; d = 10000, K = 10, 5 chains 3.0-3.2 and 2.8;
-// d = 2500, K = 10, 16 bits, 25 chains 2.55 and 2.21; d = 1100, K = 5, 5 chains 1.74 and 1.57 (medians; the rest of the
-// address changes little).  What an allocation gives by itself goes by its size: from 2 MB on always even.
-constexpr size_t kPage = 4096;
-unsigned long long* words_at(void* ws) {
-  const uintptr_t page = (reinterpret_cast<uintptr_t>(ws) + kPage - 1) / kPage;
-  return reinterpret_cast<unsigned long long*>((page | 1) * kPage);
+// A workspace: the nearest pages [9], from its first whole page; the exchange words, from the next; z.
+int* near_at(void* ws) {
+  return reinterpret_cast<int*>((reinterpret_cast<uintptr_t>(ws) + kPage - 1) / kPage * kPage);
 }
+unsigned long long* words_at(void* ws) { return reinterpret_cast<unsigned long long*>(near_at(ws)) + kPageWords; }
 
 }  // namespace
 
@@ -540,6 +605,11 @@ size_t plan_inner_softmax_split(halp_handle& h) {
   return 2 * kPage + split_words(h.split_chains) * sizeof(long long) + (size_t)h.split_chains * p.K * p.d * (p.b / 8);
 }
 
+int prepare_inner_softmax_split(const halp_handle& h) {
+  hipLaunchKernelGGL(find_near, dim3(9), dim3(64), 0, 0, words_at(h.batch_xbuf), near_at(h.batch_xbuf));
+  return hip_ok(hipGetLastError());
+}
+
 int inner_softmax_split_supported(const halp_handle& h) {
   if (h.split_chains == 0) return HALP_ERR_UNSUPPORTED;
   return !h.bound || !h.buf.Xq || !h.batch_xbuf ? HALP_ERR_NOT_BOUND : HALP_OK;
@@ -553,13 +623,14 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   const int P = pick_shape(p).P;
   const Kernel kernel = kernel_for(p);
   unsigned long long* xbuf = words_at(h.batch_xbuf);
+  const int* near = near_at(h.batch_xbuf);
   const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for
   for (int c0 = 0; c0 < p.R; c0 += h.split_chains) {
     const int nc = std::min(h.split_chains, p.R - c0);
     const int same = P * ((nc + 7) / 8) <= h.split_workgroups / 8 && h.num_cus % 8 == 0;
     launch_split_prepare(reinterpret_cast<long long*>(xbuf), (int)split_words(nc), h.buf.counters + 4 * (int64_t)c0, 4 * nc, s);
     hipLaunchKernelGGL(kernel, dim3(same ? 8 * ((nc + 7) / 8) * P : nc * P), dim3(block_threads(p.K)), 0, s, a, P, c0,
-                       nc, same, xbuf, h.spin_limit);
+                       nc, same, near, xbuf, h.spin_limit);
     int r = hip_ok(hipGetLastError());
     if (r == HALP_OK) r = launch_split_finish(a, h.buf.scales, xbuf + split_words(nc), c0, nc, report, p.b, s);
     if (r != HALP_OK) return r;

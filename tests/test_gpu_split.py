@@ -22,6 +22,9 @@ SOFTMAX_CASES = [
     (40, 2047, 12, 16, 0.0, 1, 40, 500.0),    # ... saturating
     (30, 1300, 16, 16, 1e-2, 1, 30, 0.05),    # ... two classes to a wave
     (30, 10000, 10, 16, 1e-4, 1, 20, 0.05),   # as many workgroups per chain as the ten-class set takes
+    (30, 6500, 10, 16, 1e-2, 1, 13, 0.05),    # four strips per lane with 26 workgroups
+    (20, 6500, 4, 16, 0.0, 10, 9, 0.05),      # ... which ten chains would not fit one to a CU: eight strips
+    (20, 8193, 3, 16, 1e-2, 1, 67, 0.05),     # past 32 workgroups
     (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than one workgroup to a CU holds
     (30, 2500, 12, 8, 1e-2, 70, 9, 0.05),     # more chains than are in flight at once
     (30, 1100, 4, 8, 0.0, 1, 1, 0.05),
