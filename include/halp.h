@@ -56,9 +56,10 @@ extern "C" {
 #define HALP_ERR_ALIGN (-6)       /* pointer or stride alignment requirement not met    */
 #define HALP_ERR_TOO_LARGE (-7)   /* beyond the fixed scratch of halp_full_gradient_static */
 #define HALP_ERR_EXCHANGE_TIMEOUT (-8) /* halp_get_stats: a cross-workgroup wait of a minibatch
-                                     chain cut across workgroups ran out; that chain's w~ was
-                                     left as it was before the loop (status -2).  Softmax chains
-                                     are run again instead, see HALP_OPT_EXCHANGE_SPIN_LIMIT */
+                                     chain of the chunked form (HALP_OPT_INNER_PARTS) ran out; that
+                                     chain's w~ was left as it was before the loop (status -2).
+                                     Other chains are run again instead, see
+                                     HALP_OPT_EXCHANGE_SPIN_LIMIT */
 
 /* scalar loss l_i of the linear model (Sec. 4); labels y as noted */
 #define HALP_LOSS_SQUARED 0  /* l(a) = (a - y)^2 / 2,        y: float               */
@@ -133,7 +134,9 @@ typedef struct {
                              -2 exchange wait ran out (w~ unchanged)                        */
   int32_t inner_variant;  /* kernel that ran the last inner loop: 1 general (softmax rows past the
                              register-resident kernels: its form cut across workgroups, unless the
-                             general one was asked for by option), 2 register-resident */
+                             general one was asked for by option; K = 1 with 65 to 128 rows per
+                             step on rows past them: the full-step form, likewise), 2
+                             register-resident */
   uint64_t n_clamped_z, n_clamped_gamma, n_reg_draws;
   float ms_full_gradient, ms_recenter, ms_inner_loop; /* mean per halp_epoch over timed_epochs */
   int32_t timed_epochs;   /* halp_epoch calls averaged (the last 32 at most since timing was set) */
@@ -173,7 +176,7 @@ typedef struct {
 #define HALP_OPT_INNER_PARTS 7   /* workgroups per chain of the minibatch (B > 1) register inner
                                     loop.  0 (default): the library's choice, the full-step form
                                     (the row cut across up to 16 workgroups, rows of a step held in
-                                    registers) where it applies; 1, 2, 4, 8: the chunked form with
+                                    registers, B up to 128) where it applies; 1, 2, 4, 8: the chunked form with
                                     that many workgroups.  The workgroups of a chain meet once per
                                     step in device memory and wait for each other (bounded; a wait
                                     that runs out is reported in counters[3]), so more than one
@@ -183,10 +186,11 @@ typedef struct {
 #define HALP_OPT_EXCHANGE_SPIN_LIMIT 8 /* polls after which a workgroup of a chain cut across
                                     workgroups (minibatch loop, softmax rows past the
                                     register-resident kernels) stops waiting for the others for
-                                    good (default 2^20, about a second).  A minibatch chain then
-                                    ends with counters[3] = 1, status -2 and w~ unchanged; a
-                                    softmax chain is run again by the general kernel, in the
-                                    same launch sequence, and only takes longer.  -1: never
+                                    good (default 2^20, about a second).  The chain is then run
+                                    again by the general kernel, in the same launch sequence, and
+                                    only takes longer; a minibatch chain of the chunked form
+                                    (HALP_OPT_INNER_PARTS) ends with counters[3] = 1, status -2
+                                    and w~ unchanged.  -1: never
                                     wait, and chains of either kind end with status -2: for
                                     tests of that path                                     */
 
@@ -228,8 +232,8 @@ typedef struct {
  * library's own device workspace on the current device, held until halp_destroy: partial sums of
  * the gradient pass; for softmax with B = 1 on rows up to 1024 coordinates, and for 8-bit minibatches
  * of softmax or of more than 64 rows, records made ahead of the steps (64 MB, 4 MB a chain where
- * that is more, at most 1 GB, less where T is small); for wider softmax rows with B = 1 a second z
- * of the chains in flight.                                                             */
+ * that is more, at most 1 GB, less where T is small); for wider softmax rows with B = 1, and for
+ * minibatches with K = 1, a second z of the chains in flight.                                                             */
 int halp_create(halp_handle** out, const halp_params* p);
 int halp_destroy(halp_handle* h);
 

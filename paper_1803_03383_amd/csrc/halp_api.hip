@@ -116,13 +116,16 @@ int launch_cut_in_order(const halp_handle& h, hipStream_t s, F&& launch) {
   return r;
 }
 
+int launch_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
+  if (inner_batch_parts(h) == 1) return launch_inner_batch(h, epoch, s);
+  return launch_cut_in_order(h, s, [&] { return launch_inner_batch(h, epoch, s); });
+}
+
 int launch_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
+  if (inner_batch_wide_takes(h)) return launch_batch(h, epoch, s);
   if (batch_family(h.p))
     return h.p.b == 8 ? launch_inner_softmax_mfma(h, epoch, s) : launch_inner_softmax_batch(h, epoch, s);
-  if (h.p.B > 1) {
-    if (inner_batch_parts(h) == 1) return launch_inner_batch(h, epoch, s);
-    return launch_cut_in_order(h, s, [&] { return launch_inner_batch(h, epoch, s); });
-  }
+  if (h.p.B > 1) return launch_batch(h, epoch, s);
   return h.p.loss == HALP_LOSS_SOFTMAX ? launch_inner_softmax(h, epoch, s) : launch_inner_reg(h, epoch, s);
 }
 
@@ -131,6 +134,8 @@ int launch_inner(const halp_handle& h, int variant, uint32_t epoch, hipStream_t 
   // softmax rows past the register kernels, unless the general kernel was asked for
   if (variant == 1 && h.inner_variant == 0 && inner_softmax_split_supported(h) == HALP_OK)
     return launch_cut_in_order(h, s, [&] { return launch_inner_softmax_split(h, epoch, s); });
+  // minibatches of 65 .. 128 rows on rows past the kernels for wide minibatches, likewise
+  if (variant == 1 && h.inner_variant == 0 && inner_batch_wide_takes(h)) return launch_batch(h, epoch, s);
   return variant == 2 ? launch_reg(h, epoch, s) : launch_inner_generic(h, epoch, TraceBufs{}, s);
 }
 
@@ -219,8 +224,7 @@ int halp_create(halp_handle** out, const halp_params* p) {
   }
   // exchange buffers of the split minibatch inner loop, where it can apply
   if (p->K == 1 && p->B > 1 && (int64_t)p->R * 2 <= h->num_cus) {
-    const size_t slots = (size_t)p->R * 2 * kBatchSlots;
-    if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), slots * 64 * sizeof(long long)),
+    if (hip_fail(hipMalloc(reinterpret_cast<void**>(&h->batch_xbuf), inner_batch_workspace(*p)),
                  "hipMalloc(batch_xbuf)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }
   if (const size_t bytes = plan_inner_softmax_split(*h)) {

@@ -108,6 +108,8 @@ size_t inner_generic_workspace_bytes(const halp_params& p);
 int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& tr, hipStream_t s, bool redo = false);
 int inner_batch_supported(const halp_handle& h);
 int inner_batch_parts(const halp_handle& h);  // workgroups per chain, where supported
+bool inner_batch_wide_takes(const halp_handle& h);  // 65 .. 128 rows per step
+size_t inner_batch_workspace(const halp_params& p);
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_svrg_supported(const halp_handle& h);
 int launch_inner_svrg(const halp_handle& h, uint32_t epoch, hipStream_t s);

@@ -1,13 +1,11 @@
 // Inner loop of Algorithm 4 (LM-HALP) with a minibatch of B rows per step (K = 1):
 // all rows of a step see the same z, each has its own gamma, z is quantized once per step.
 //
-// One workgroup per chain, or -- when chains are few -- P workgroups per chain, each holding
-// a slice of the coordinates.  The P partial dots of a row then meet in global memory once
-// per step: every workgroup adds its 64 partial sums, with one device-scope atomic each, to the
-// rows' words, which also count the additions, waits (bounded) until all P are there and goes on
-// alone; the update needs nothing from the others.  (One trip out and one back, 64 words read per
-// poll whatever P is.  A word per part, published by a store and polled until all P carry the
-// step's tag: 2.9 us of a 5.5 us step at d = 4096, 16 bits, B = 64; this form: 4.6 us per step.)
+// One workgroup per chain, its waves side by side along the row; or P workgroups per chain, each holding a
+// slice of the coordinates (only where HALP_OPT_INNER_PARTS asks for it).  The P partial dots of a row
+// then meet in global memory once per step: every workgroup adds its 64 partial sums, with one device-scope atomic
+// each, to the rows' words, which also count the additions, waits (bounded) until all P are there and goes on
+// alone; the update needs nothing from the others.
 //
 // A thread owns the coordinates of one 4/8/16-byte fragment of a row (CPT of them)
 // with z, h~ and the window's Philox words in registers.  A step:
@@ -21,27 +19,18 @@
 // Wave 0 also draws the indices two steps ahead and gathers the margins and labels of the
 // next step's rows.  The barriers wait for LDS only, loads stay in flight across them.
 //
-// Chunked form: the waves of a workgroup sit side by side along the row.  The B rows of a
-// step (512 KB at B = 64, d = 4096, b = 16: a CU's register file) cannot stay on chip, so
+// The B rows of a step (512 KB at B = 64, d = 4096, b = 16: a CU's register file) cannot stay on chip, so
 // they travel twice, in chunks of 8 through two register buffers: from HBM for the dots,
-// from L2 for the update.  Full-step form: see the kernel template below.
-#include "halp_device.hpp"
-#include "inner_args.hpp"
+// from L2 for the update.  The full-step form, which keeps them in registers, is inner_batch_cut.hip.
+#include <algorithm>
+
+#include "inner_batch.hpp"
 
 namespace halp {
 namespace {
 
 constexpr int kMaxB = 64;   // rows per step: one per service lane
 constexpr int kChunk = 8;   // rows in flight per worker thread
-constexpr int kRowsPerWave = 16;    // full-step form: rows of a step one wave takes at most
-
-typedef short short2v __attribute__((ext_vector_type(2)));
-
-// workgroup barrier that waits for this wave's LDS traffic only: global loads may stay in
-// flight across it (their registers are waited for where they are used)
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 __device__ __forceinline__ int mad24(int a, int b, int c) {
   int r;
@@ -49,37 +38,8 @@ __device__ __forceinline__ int mad24(int a, int b, int c) {
   return r;
 }
 
-// Sums of 8 values over the 64 lanes of a wave at once: v[m] is this lane's share of sum m.
-// Three exchange steps inside each group of 8 lanes (partner lane ^ 7, ^ 2, ^ 1) halve the
-// number of values a lane carries while doubling the lanes each covers, leaving lane l with
-// sum l % 8 over its group; three more (lane ^ 8, ^ 16, ^ 32) add the groups.  Every lane
-// returns the complete sum number l % 8.  Integer sums: the order does not matter.
-__device__ __forceinline__ int wave_sums8_i32(const int (&v)[8], int lane) {
-  const bool f2 = (lane & 4) != 0, f1 = (lane & 2) != 0, f0 = (lane & 1) != 0;
-  int w[4], u[2];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) w[m] = (f2 ? v[m + 4] : v[m]) + dpp_half_mirror(f2 ? v[m] : v[m + 4]);
-#pragma unroll
-  for (int m = 0; m < 2; ++m) u[m] = (f1 ? w[m + 2] : w[m]) + dpp_quad_swap2(f1 ? w[m] : w[m + 2]);
-  int r = (f0 ? u[1] : u[0]) + dpp_quad_swap1(f0 ? u[0] : u[1]);
-  r += __builtin_amdgcn_update_dpp(0, r, 0x128, 0xF, 0xF, false);  // row_ror:8 = lane ^ 8
-  r += __builtin_amdgcn_ds_swizzle(r, 0x401F);                      // lane ^ 16
-  r += __shfl_xor(r, 32);
-  return r;
-}
-
-__device__ __forceinline__ double logistic_dl(double a, double y) {
-  return __ddiv_rn(-y, __dadd_rn(1.0, halp_exp(__dmul_rn(y, a))));
-}
-
 // NDW: dwords of a row per thread; KT: most waves of the workgroup.
-// FS, the full-step form: a workgroup holds ONE slice of 64 NDW dwords of the row, and its
-// nwk waves of z all hold that same slice and split the ROWS of the step between them (16
-// each at most).  A wave keeps its rows' fragments in registers, loaded a whole step ahead, so
-// the rows are read from memory once and a wave's per-row work covers a quarter of the batch.
-// The price: the waves add up their sums over rows through LDS before the update, which each
-// of them then performs on its own copy of z (same inputs, same result).
-template <int BITS, int NDW, int KT, bool FS>
+template <int BITS, int NDW, int KT>
 __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk, int P, long long* xbuf,
                                                               int spin_limit, int poll_delay) {
   using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
@@ -109,16 +69,11 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
   }
   // polls of the other workgroups' sums before a wait is given up for good; below 0: never wait
   unsigned int n_timeout = spin_limit < 0 ? 1u : 0u;
-  constexpr int kWarm = 8;   // cache lines of the widest slice (64 threads of 16 bytes)
-  uint32_t warm[kWarm] = {};  // full-step form: what wave 0 reads to warm the caches, never used
 
   __shared__ int s_idx[4][kMaxB];            // sampled rows of steps t .. t+2, slot = step % 4
   __shared__ int s_part[2][16][kMaxB];       // per wave and row: low / high partial dot
   __shared__ int s_gam[kMaxB];               // gamma_m
-  __shared__ int s_acc[FS ? 4 : 1][FS ? 2 * CPT : 1][64];  // full-step form: the waves' sums over their rows
   __shared__ int s_cl;                       // c_lambda of the step
-  __shared__ uint32_t s_rw[2][kMaxB];        // full-step form: rounding words of gamma_m and the L2
-  __shared__ int s_cln[2];                   // draw of the next step, made by wave 1 for wave 0
   __shared__ unsigned long long s_cnt[3];
   if (tid < 3) s_cnt[tid] = 0;
   const bool use_reg = a.lambda > 0;
@@ -128,11 +83,6 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
   // of its own for them would put two waves on one SIMD and halve every wave's registers.)
   const bool svc = wave == 0;
   const int wv = wave;        // this wave's place among the nwk waves that hold z
-  const bool worker = true;
-  // Full-step form with more than one wave: what can be drawn ahead (the next step's rounding
-  // words, the indices two steps ahead) is drawn by wave 1 while wave 0 runs the scalar stage.
-  const bool helper = FS && nwk > 1 && wave == 1;
-  const bool self_prepare = !(FS && nwk > 1);
   const uint32_t N = (uint32_t)a.N;
   const float* __restrict__ phi = a.phi + (int64_t)chain * a.N;
   const float* __restrict__ y = reinterpret_cast<const float*>(a.y) + (int64_t)chain * a.y_chain_stride;
@@ -176,12 +126,8 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
     const HT* __restrict__ hg = reinterpret_cast<const HT*>(a.h) + (int64_t)chain * d;
     XT* __restrict__ zg = reinterpret_cast<XT*>(a.z) + (int64_t)chain * d;
     float* __restrict__ wg = a.w + (int64_t)chain * d;
-    // chunked form: the waves of a workgroup (and the workgroups of a chain) hold consecutive
-    // slices; full-step form: one slice per workgroup, the same in all its waves
-    const int j0 = !worker ? d : (FS ? (part * 64 + lane) * CPT : (part * 64 * nwk + wv * 64 + lane) * CPT);
-    // full-step form: the rows of a step are dealt to the waves in runs of 8 or 16
-    const int rpw = FS ? 8 * ((((B + nwk - 1) / nwk) + 7) / 8) : 0;
-    const int row0 = FS && worker ? wv * rpw : 0;
+    // the waves of a workgroup (and the workgroups of a chain) hold consecutive slices
+    const int j0 = (part * 64 * nwk + wv * 64 + lane) * CPT;
     const bool active = j0 < d;
     // Rows are padded to whole 8-byte groups; a 16-byte fragment is only used when rows are
     // 16-byte multiples (checked on the host), so a fragment that starts below d lies inside
@@ -226,27 +172,8 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
       for (int r = 0; r < kChunk; ++r)  // the row number is uniform: scalar address arithmetic
         load_frag(dst[r], __builtin_amdgcn_readlane(mine, r));
     };
-    // FS: the fragments of all rows of this step and of the next one
-    constexpr int RPW = FS ? kRowsPerWave : 1;
-    // Full-step form with fragments of at most 8 bytes: three register sets, the rows of a step
-    // are requested two steps before their dots (a step ahead is less than a trip to memory for
-    // a random row, and a workgroup whose rows are late makes every workgroup of the chain wait)
-    constexpr bool kDeep = FS && NDW <= 2;
-    uint32_t xc[RPW][NDW], xn[RPW][NDW], xf[kDeep ? RPW : 1][NDW];
-    auto load_step = [&](uint32_t (&dst)[RPW][NDW], const int* idx) {
-      // lane r fetches the index of the wave's row r (one LDS read for all); rows past B
-      // repeat the last one and are not used
-      const int mine = idx[min(row0 + (lane & (RPW - 1)), B - 1)];
-#pragma unroll
-      for (int r = 0; r < RPW; ++r) load_frag(dst[r], __builtin_amdgcn_readlane(mine, r));
-    };
     __syncthreads();
-    if (FS) {
-      if (worker) load_step(xc, s_idx[0]);
-      if (kDeep && worker) load_step(xn, s_idx[1]);
-    } else {
-      load_chunk(xa, s_idx[0], 0);
-    }
+    load_chunk(xa, s_idx[0], 0);
 
     // wave 0: the rounding word of gamma_m and the L2 draw of a step, made a step ahead
     uint32_t rw_next = 0;
@@ -262,7 +189,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
     };
     if (svc) draw_scalars(0);
 
-    auto one_step = [&](int64_t t, uint32_t (&cur)[RPW][NDW], uint32_t (&nxt)[RPW][NDW]) {
+    auto one_step = [&](int64_t t) {
       const int* idx = s_idx[t & 3];
       // wave 0: what the scalar stage needs and does not depend on the dots — margins and
       // labels of the next step's rows (used after the next barrier pair), the rounding word
@@ -272,48 +199,22 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
       int cl_draw = 0;
       if (svc) {
         if (P == 1) {
-          const int inx = self_prepare ? i_next : s_idx[(t + 1) & 3][min(lane, B - 1)];
+          const int inx = i_next;
           phi_n = need_phi ? phi[inx] : 0.f;
           y_n = a.loss == HALP_LOSS_LOGISTIC ? y[inx] : 0.f;
         } else if (shipper) {  // gathered after the last step's gamma (before the loop for step 0)
           phi_n = phi_g;
           y_n = y_g;
         }  // the other parts receive them with the sums below
-        if (self_prepare || t == 0) {  // drawn during the previous step (or before the first)
-          rw = rw_next;
-          cl_draw = cl_next;
-        } else {
-          rw = s_rw[t & 1][lane];
-          cl_draw = s_cln[t & 1];
-        }
+        rw = rw_next;  // drawn during the previous step (or before the first)
+        cl_draw = cl_next;
         n_reg += (lane == 0 && cl_draw != 0) ? 1u : 0u;
       }
       // What wave 0 prepares for later steps: with several workgroups per chain it runs while
       // the wave waits for the others' sums, else here, while the other waves take the dots.
-      auto prepare_ahead = [&]() {
-        draw_scalars(t + 1);
-        if (FS) {  // the indices two steps ahead (slot (t + 2) % 4 was last read in step t - 2)
-          const int i2 = draw_idx(t + 2);
-          if (row) s_idx[(t + 2) & 3][lane] = i2;
-          i_next = i2;
-          // Touch this workgroup's slice of those rows, one row per lane and one load per
-          // cache line: the address translations and the lines are on their way into L2 a step
-          // before the other waves ask for them.  The values are not used (taken up a step
-          // later, so that nothing here waits for them).
-#pragma unroll
-          for (int k = 0; k < kWarm; ++k) asm volatile("" ::"v"(warm[k]));
-          const int64_t part_off = (int64_t)part * 64 * NDW * 4;
-          const int slice = (int)min((int64_t)64 * NDW * 4, row_bytes - part_off);
-          if (!kDeep && slice >= 4) {  // kDeep: the rows themselves are requested at that distance
-            const unsigned char* wp = Xq + (int64_t)i2 * row_bytes + part_off;
-#pragma unroll
-            for (int k = 0; k < kWarm; ++k)  // unconditional, the last line repeated
-              warm[k] = *reinterpret_cast<const uint32_t*>(wp + min(k * 128, slice - 4));
-          }
-        }
-      };
-      if (svc && P == 1 && self_prepare) prepare_ahead();
-      if (worker && (t & 7) == 0) {
+      auto prepare_ahead = [&]() { draw_scalars(t + 1); };
+      if (svc && P == 1) prepare_ahead();
+      if ((t & 7) == 0) {
         if (kPark) {
 #pragma unroll
           for (int q = 0; q < UPL / 4; ++q) {
@@ -332,7 +233,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
             zr[u] = zround_block(seed, a.epoch, strip0 + (uint32_t)u, (uint32_t)(t >> 3));
         }
       }
-      if (kPark && worker && (t & 1) == 0) {  // the block word that serves steps t and t + 1
+      if (kPark && (t & 1) == 0) {  // the block word that serves steps t and t + 1
 #pragma unroll
         for (int q = 0; q < UPL / 4; ++q) {
           const uint4 v = s_zr[(((int)(t & 7) >> 1) * (UPL / 4) + q) * nworkers + wtid];
@@ -381,30 +282,17 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
         const int slo = wave_sums8_i32(lo, lane);  // row m0 + lane % 8
         const int shi = BITS == 16 ? wave_sums8_i32(hi, lane) : 0;
         if (lane < kChunk && m0 + lane < B) {
-          s_part[0][FS ? 0 : wv][m0 + lane] = slo;  // full-step form: one wave per row, one slot
-          if (BITS == 16) s_part[1][FS ? 0 : wv][m0 + lane] = shi;
+          s_part[0][wv][m0 + lane] = slo;
+          if (BITS == 16) s_part[1][wv][m0 + lane] = shi;
         }
       };
-      if constexpr (FS) {
-        if (worker) {
-#pragma unroll
-          for (int c0 = 0; c0 < RPW; c0 += kChunk)
-            if (c0 < rpw && row0 + c0 < B) dots(reinterpret_cast<uint32_t(&)[kChunk][NDW]>(cur[c0]), row0 + c0);
-        }
-      } else {
-        for (int m0 = 0; m0 < B; m0 += 2 * kChunk) {
-          load_chunk(xb, idx, m0 + kChunk);
-          dots(xa, m0);
-          load_chunk(xa, idx, m0 + 2 * kChunk < B ? m0 + 2 * kChunk : 0);
-          if (m0 + kChunk < B) dots(xb, m0 + kChunk);
-        }
+      for (int m0 = 0; m0 < B; m0 += 2 * kChunk) {
+        load_chunk(xb, idx, m0 + kChunk);
+        dots(xa, m0);
+        load_chunk(xa, idx, m0 + 2 * kChunk < B ? m0 + 2 * kChunk : 0);
+        if (m0 + kChunk < B) dots(xb, m0 + kChunk);
       }
       lds_barrier();  // the partial dots of this step are in LDS
-      if (helper) {
-        prepare_ahead();
-        s_rw[(t + 1) & 1][lane] = rw_next;
-        if (lane == 0) s_cln[(t + 1) & 1] = cl_next;
-      }
       if (svc) {
         // l'(phi_m) does not depend on the dots: evaluated here, ahead of the wait for the other
         // workgroups' sums, so that only l'(phi_m + x_m^T z) follows it
@@ -417,7 +305,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
           asm volatile("" : "+v"(dl0));  // stays where it is written
         }
         long long D = 0;
-        for (int w2 = 0; w2 < (FS ? 1 : nwk); ++w2) {
+        for (int w2 = 0; w2 < nwk; ++w2) {
           const long long lo = s_part[0][w2][min(lane, B - 1)];
           const long long hi = BITS == 8 ? 0 : s_part[1][w2][min(lane, B - 1)];
           D += lo + hi * 256;
@@ -443,7 +331,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
           const bool want_phi = receiver && need_phi, want_y = receiver && logistic;
           if (logistic) dl0 = logistic_dl(a0, yi);  // behind the publish, ahead of the wait
           asm volatile("" : "+v"(dl0));
-          if (self_prepare) prepare_ahead();
+          prepare_ahead();
           // polls that start before the additions can be back only add traffic
           if (n_timeout == 0) {
             for (int i = 0; i < poll_delay; ++i) __builtin_amdgcn_s_sleep(4);
@@ -488,7 +376,7 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
           n_gclamp += hit ? 1u : 0u;
         }
         if (lane == 0) s_cl = cl_draw;
-        if (!FS) {  // indices two steps ahead (slot (t + 2) % 4 was last read in step t - 2)
+        {  // indices two steps ahead (slot (t + 2) % 4 was last read in step t - 2)
           const int i2 = draw_idx(t + 2);
           if (row) s_idx[(t + 2) & 3][lane] = i2;
           i_next = i2;
@@ -497,14 +385,10 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
       }
       lds_barrier();  // gamma is out
       if (svc && shipper) {  // margins and labels of the rows two steps on, shipped with the next step's sums
-        const int i2 = self_prepare ? i_next : s_idx[(t + 2) & 3][min(lane, B - 1)];
+        const int i2 = i_next;
         phi_g = need_phi ? phi[i2] : 0.f;
         y_g = a.loss == HALP_LOSS_LOGISTIC ? y[i2] : 0.f;
       }
-      // Full-step form: this wave's rows of the next step, requested only now -- what wave 0
-      // read from memory for the scalar stage (margins, the other workgroups' sums) must not
-      // queue behind them -- and in flight through the update and the next step's start.
-      if (FS) load_step(nxt, s_idx[(t + (kDeep ? 2 : 1)) & 3]);  // kDeep: `nxt` is the set two steps on
       // ---- pass 2: sum_m gamma_m x_m per coordinate (low / high byte of gamma apart at 16 bits)
       int acc[CPT], acch[CPT];
 #pragma unroll
@@ -547,49 +431,13 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
           }
         }
       };
-      if constexpr (FS) {
-        if (worker) {
-#pragma unroll
-          for (int c0 = 0; c0 < RPW; c0 += kChunk)
-            if (c0 < rpw && row0 + c0 < B)
-              accumulate(reinterpret_cast<uint32_t(&)[kChunk][NDW]>(cur[c0]), row0 + c0);
-          // this wave's sums over its rows, for the other waves
-#pragma unroll
-          for (int k = 0; k < CPT; ++k) {
-            s_acc[wv][k][lane] = acc[k];
-            if (BITS == 16) s_acc[wv][CPT + k][lane] = acch[k];
-          }
-        }
-        lds_barrier();  // every wave's sums are in LDS
-        if (worker) {
-#pragma unroll
-          for (int k = 0; k < CPT; ++k) {
-            int pa[4], ph[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {  // every group's slot is read (unused ones hold old sums)
-              pa[g] = s_acc[g][k][lane];
-              ph[g] = BITS == 16 ? s_acc[g][CPT + k][lane] : 0;
-            }
-            acc[k] = 0;
-            acch[k] = 0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {  // the same order in every wave
-              if (g < nwk) {
-                acc[k] += pa[g];
-                acch[k] += ph[g];
-              }
-            }
-          }
-        }
-      } else {
-        const int* idn = s_idx[(t + 1) & 3];
-        for (int m0 = 0; m0 < B; m0 += 2 * kChunk) {
-          load_chunk(xb, idx, m0 + kChunk);
-          accumulate(xa, m0);
-          if (m0 + 2 * kChunk < B) load_chunk(xa, idx, m0 + 2 * kChunk);
-          else load_chunk(xa, idn, 0);
-          accumulate(xb, m0 + kChunk);
-        }
+      const int* idn = s_idx[(t + 1) & 3];
+      for (int m0 = 0; m0 < B; m0 += 2 * kChunk) {
+        load_chunk(xb, idx, m0 + kChunk);
+        accumulate(xa, m0);
+        if (m0 + 2 * kChunk < B) load_chunk(xa, idx, m0 + 2 * kChunk);
+        else load_chunk(xa, idn, 0);
+        accumulate(xb, m0 + kChunk);
       }
       // ---- u = z - sum gamma x - h~ - c_lambda z in (delta_i, 2b); z = Q_(delta_m, b)(u)
       const int cl = use_reg ? s_cl : 0;
@@ -603,38 +451,17 @@ __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk,
         const long long v = -(long long)hv[k] - (long long)cl * (long long)z[k] - gsum;
         const long long zu = (long long)z[k] + ((v + re) >> BITS);
         const long long zc = zu > QMAX ? QMAX : (zu < QMIN ? QMIN : zu);
-        n_zclamp += (ok[k] && zu != zc && (!FS || wv == 0)) ? 1u : 0u;  // the copies of z count once
+        n_zclamp += (ok[k] && zu != zc) ? 1u : 0u;
         z[k] = ok[k] ? (int)zc : 0;
       }
     };
-    if constexpr (kDeep) {  // three register sets in rotation: rows of steps t, t + 1 and the set being filled
-      auto& x0 = xc;
-      auto& x1 = xn;
-      auto& x2 = reinterpret_cast<uint32_t(&)[RPW][NDW]>(xf);
-      int64_t t = 0;
-      for (; t + 2 < T; t += 3) {
-        one_step(t, x0, x2);
-        one_step(t + 1, x1, x0);
-        one_step(t + 2, x2, x1);
-      }
-      if (t < T) one_step(t, x0, x2);
-      if (t + 1 < T) one_step(t + 1, x1, x0);
-    } else if (FS) {  // the two register sets trade places from step to step
-      int64_t t = 0;
-      for (; t + 1 < T; t += 2) {
-        one_step(t, xc, xn);
-        one_step(t + 1, xn, xc);
-      }
-      if (t < T) one_step(t, xc, xn);
-    } else {
-      for (int64_t t = 0; t < T; ++t) one_step(t, xc, xn);
-    }
+    for (int64_t t = 0; t < T; ++t) one_step(t);
 
     // ---- w~ <- w~ + delta_m z (option I; Algorithm 2: w~ = delta z); hand z out
     const double delta_m = sc[0];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
-      if (ok[k] && (!FS || wv == 0)) {
+      if (ok[k]) {
         const int j = j0 + k;
         zg[j] = (XT)z[k];
         if (P == 1) {  // several workgroups per chain: split_finish applies the offset
@@ -688,10 +515,10 @@ __global__ void split_prepare(long long* xbuf, int nwords, uint64_t* counters, i
   if (k < ncounters) counters[k] = 0;
 }
 
-template <int BITS, int NDW, int KT, bool FS>
+template <int BITS, int NDW, int KT>
 int launch_kt(const InArgs& a, int nwk, int P, long long* xbuf, int spin_limit, int poll_delay, dim3 grid, dim3 block,
               size_t smem, hipStream_t s) {
-  auto kern = inner_batch_kernel<BITS, NDW, KT, FS>;
+  auto kern = inner_batch_kernel<BITS, NDW, KT>;
   if (smem > 0 && hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                       hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)smem) != hipSuccess)
@@ -775,35 +602,28 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
     if (most_any < 1) most_any = 1;
   }
   if (h.inner_parts == 0) {
-    // full-step form: the widest fragment the alignment allows whose slices (one workgroup
-    // each) are few enough to be resident together; up to 4 waves share the rows of a step
+    // full-step form (inner_batch_cut.hip): slices, one workgroup each, few enough to be resident together
     const int epd = 32 / p.b;
     const bool al16 = row_bytes % 16 == 0 && reinterpret_cast<uintptr_t>(h.buf.Xq) % 16 == 0;
     const int ndw_max = (al16 && p.b == 16) ? 4 : 2;  // 8 coordinates per thread at most
     auto fits = [&](int ndw, int& P) {
       const int cpt = ndw * epd;
       P = (p.d + 64 * cpt - 1) / (64 * cpt);
-      if (P > most_any) return false;
-      // several workgroups pay for an exchange per step.  us per step, cut and on one workgroup: steps of
-      // 16 KB of rows 3.1 - 4.2 and 3.2 - 4.2 (five shapes, none slower cut), 32 KB 3.7 and 3.9, 64 KB 3.0 - 4.3 and
-      // 5.0 - 9.7
-      if (P > 1 && (int64_t)p.B * row_bytes < 16 * 1024) return false;
+      if (P > most_any || !inner_batch_cut_takes(p.B, ndw)) return false;
       return (int64_t)((p.d + cpt - 1) / cpt) * ndw * 4 <= row_bytes;  // fragments inside the row
     };
-    int rg = (p.B + 7) / 8;
-    if (rg > 4) rg = 4;
     // A chain cut across workgroups: the narrowest fragment of at least four coordinates whose
-    // slices are few enough -- more, narrower slices shorten both passes over the rows of a step.  us per
-    // step, B = 64: 4096 x 16 bits 5.7 with 8 slices, 4.2 with 16; 2048 x 16 bits 5.6 / 4.4 with 4 / 8; 1024 x 16
-    // bits 5.0 / 4.3 with 2 / 4; 4096 x 8 bits 4.5 / 3.6 with 8 / 16.
-    for (int ndw = p.b == 16 ? 2 : 1; ndw <= ndw_max; ndw *= 2) {
-      int P;
-      if (fits(ndw, P) && P > 1) return BtLaunch{true, ndw, rg, P};
-    }
-    for (int ndw = ndw_max; ndw >= 1; ndw /= 2) {
-      int P;
-      if (fits(ndw, P)) return BtLaunch{true, ndw, rg, P};
-    }
+    // slices are few enough -- more, narrower slices shorten both passes over the rows of a step.  us per step, 4096 x 16
+    // bits, B = 64, N = 100 000: 3.4 with 8 slices, 2.9 with 16; 4096 x 8 bits, N = 400 000: 2.65 and 2.40.
+    // One workgroup where the widest fragment lets it hold the row, for the smaller steps (no exchange).  us per step, one
+    // workgroup and two: 8 bits d = 300 B = 4 1.14 / 1.58, 500 B = 64 1.81 / 1.86, 500 B = 128 2.77 / 2.50;
+    // 16 bits 500 B = 4 1.49 / 1.81, 300 B = 32 1.82 / 2.00, 500 B = 64 2.57 / 2.33.
+    int P = 1;
+    const bool alone = p.B <= (p.b == 8 ? 64 : 32) && fits(ndw_max, P) && P == 1;
+    for (int ndw = p.b == 16 ? 2 : 1; ndw <= ndw_max && !alone; ndw *= 2)
+      if (fits(ndw, P) && P > 1) return BtLaunch{true, ndw, 0, P};
+    for (int ndw = ndw_max; ndw >= 1; ndw /= 2)
+      if (fits(ndw, P)) return BtLaunch{true, ndw, 0, P};
   }
   int P = 1;
   if (h.inner_parts > 0) {
@@ -813,14 +633,26 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
   return BtLaunch{false, sh.ndw, (sh.nwk + P - 1) / P, P};
 }
 
+// 65 .. 128 rows per step: only where the full-step form takes them
+bool inner_batch_wide_takes(const halp_handle& h) {
+  const halp_params& p = h.p;
+  if (p.K != 1 || p.B <= kMaxB || p.algorithm == HALP_ALG_SVRG || (p.b == 8 && p.d > 131071)) return false;
+  return h.bound && h.buf.Xq && h.inner_parts == 0 && pick_launch(h, h.buf.ldxq * (p.b / 8)).fs;
+}
+
+size_t inner_batch_workspace(const halp_params& p) {
+  return std::max((size_t)p.R * 2 * kBatchSlots * 64 * sizeof(long long), inner_batch_cut_workspace(p));
+}
+
 int inner_batch_parts(const halp_handle& h) { return pick_launch(h, h.buf.ldxq * (h.p.b / 8)).P; }
 
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   const halp_params& p = h.p;
-  const int rc = inner_batch_supported(h);
+  const int rc = p.B > kMaxB ? (inner_batch_wide_takes(h) ? HALP_OK : HALP_ERR_UNSUPPORTED) : inner_batch_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
   const BtLaunch L = pick_launch(h, h.buf.ldxq * (p.b / 8));
+  if (L.fs) return launch_inner_batch_cut(h, a, L.ndw, L.P, s);
   const int nwk = L.nwk, P = L.P;
   const int nwaves = nwk;
   const dim3 grid(p.R * P), block(64 * nwaves);
@@ -830,22 +662,19 @@ int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   }
   // parked Philox blocks: 128 bytes per worker thread at 8 strips per thread (120 KB at most)
   const size_t smem = L.ndw == 4 ? (size_t)64 * nwk * 128 : 0;
-#define HALP_BT(BITS_, NDW_, FS_)                                                                  \
-  if (p.b == BITS_ && L.ndw == NDW_ && L.fs == FS_) {                                              \
-    if (nwaves <= 4)                                                                               \
-      return launch_kt<BITS_, NDW_, 4, FS_>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);         \
-    if (nwaves <= 8)                                                                               \
-      return launch_kt<BITS_, NDW_, 8, FS_>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);         \
-    if (FS_) return HALP_ERR_UNSUPPORTED;                                                          \
-    if (nwaves <= 12)                                                                              \
-      return launch_kt<BITS_, NDW_, 12, FS_>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);        \
-    return launch_kt<BITS_, NDW_, 16, FS_>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);          \
+#define HALP_BT(BITS_, NDW_)                                                                                               \
+  if (p.b == BITS_ && L.ndw == NDW_) {                                                                                     \
+    if (nwaves <= 4)                                                                                                       \
+      return launch_kt<BITS_, NDW_, 4>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);         \
+    if (nwaves <= 8)                                                                                                       \
+      return launch_kt<BITS_, NDW_, 8>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);         \
+    if (nwaves <= 12)                                                                                                      \
+      return launch_kt<BITS_, NDW_, 12>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);        \
+    return launch_kt<BITS_, NDW_, 16>(a, nwk, P, h.batch_xbuf, h.spin_limit, h.poll_delay, grid, block, smem, s);          \
   }
   auto launch_loop = [&]() -> int {
-    HALP_BT(8, 1, true) HALP_BT(8, 2, true) HALP_BT(8, 4, true)
-    HALP_BT(16, 1, true) HALP_BT(16, 2, true) HALP_BT(16, 4, true)
-    HALP_BT(8, 1, false) HALP_BT(8, 2, false) HALP_BT(8, 4, false)
-    HALP_BT(16, 1, false) HALP_BT(16, 2, false) HALP_BT(16, 4, false)
+    HALP_BT(8, 1) HALP_BT(8, 2) HALP_BT(8, 4)
+    HALP_BT(16, 1) HALP_BT(16, 2) HALP_BT(16, 4)
     return HALP_ERR_UNSUPPORTED;
   };
 #undef HALP_BT

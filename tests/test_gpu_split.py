@@ -96,6 +96,60 @@ def test_softmax_split_on_two_streams():
     assert not np.any(second.get("scales")[:, 7])
 
 
+FULL_STEP_CASES = [
+    # loss, N, d, B, b, lam, R, T, mu: rows of a step in registers, dealt to waves by 2, 4, 8 or 16
+    (hp.LOSS_SQUARED, 300, 257, 2, 8, 0.0, 1, 70, 0.05),      # one coordinate past a slice, one wave with rows
+    (hp.LOSS_LOGISTIC, 300, 600, 3, 16, 1e-2, 2, 40, 0.05),   # ragged waves, cut at a small step
+    (hp.LOSS_LOGISTIC, 300, 1030, 7, 8, 1e-2, 1, 130, 0.05),  # five slices, L2 draws past 64 steps
+    (hp.LOSS_SQUARED, 300, 512, 9, 16, 0.0, 3, 33, 0.05),     # four rows to a wave; the widest row of one workgroup
+    (hp.LOSS_SQUARED, 300, 513, 32, 8, 0.0, 1, 27, 500.0),    # ... saturating
+    (hp.LOSS_LOGISTIC, 200, 2050, 33, 16, 1e-2, 1, 20, 0.05), # eight rows to a wave
+    (hp.LOSS_LOGISTIC, 200, 30, 63, 8, 0.0, 2, 31, 0.05),
+    (hp.LOSS_SQUARED, 200, 1025, 65, 8, 1e-2, 1, 21, 0.05),   # sixteen, past the kernels for wide minibatches
+    (hp.LOSS_LOGISTIC, 150, 4096, 128, 16, 1e-5, 1, 9, 0.05),
+    (hp.LOSS_LOGISTIC, 150, 2000, 128, 8, 0.0, 2, 11, 500.0), # ... saturating
+    (hp.LOSS_LOGISTIC, 150, 5000, 100, 16, 0.0, 1, 4, 0.05),  # too wide a fragment for sixteen rows: the general kernel
+    (hp.LOSS_SQUARED, 100, 700, 5, 16, 0.0, 1, 1, 0.05),
+    (hp.LOSS_SQUARED, 100, 700, 5, 16, 0.0, 1, 0, 0.05),
+]
+
+
+@pytest.mark.parametrize("loss,N,d,B,b,lam,R,T,mu", FULL_STEP_CASES)
+def test_minibatch_full_step_bit_exact(loss, N, d, B, b, lam, R, T, mu):
+    seed = 210 + d + B
+    case = _inner_case(loss, N, d, 1, B, b, lam, R, T, seed, mu=mu)
+    P = _run_inner(case, loss, 1, B, b, lam, R, T, seed, 0, mu=mu)
+    P.h.inner_loop(3)
+    z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+    for r in range(R):
+        prob = case["mk"](r)
+        out = ref.inner_loop(prob, case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, T)
+        assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
+        assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+    if mu > 100:
+        assert cnt[0, 0] > 0
+
+
+@pytest.mark.parametrize("B", [16, 96])
+def test_minibatch_full_step_waits_that_run_out(B):
+    """A limit of no polls at all: chains whose wait ran out are run by the general kernel, from the z they came
+    with; waits switched off: the model stays as it was and the statistics call says so."""
+    loss, N, d, b, T, seed = hp.LOSS_LOGISTIC, 200, 2048, 16, 15, 31
+    case = _inner_case(loss, N, d, 1, B, b, 0.0, 1, T, seed, mu=0.05)
+    P = _run_inner(case, loss, 1, B, b, 0.0, 1, T, seed, 0, mu=0.05)
+    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], case["h"][0], case["scales"][0], 3, T)
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 0)
+    P.h.inner_loop(3)
+    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
+    assert P.get("scales")[0, 7] == 0.0
+    P.put("w", case["w"]); P.st["z"].zero_()
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, -1)
+    P.h.inner_loop(3)
+    assert np.array_equal(P.get("w"), case["w"].reshape(1, 1, d))
+    assert P.get("scales")[0, 7] == -2.0
+
+
 def test_softmax_and_minibatch_chains_cut_on_two_streams():
     """Softmax chains in 224 workgroups, minibatch chains cut into 128 behind them,
     softmax chains again, with wait limits far below a launch's run time: each waits for the one before it."""
