@@ -1,12 +1,13 @@
 // Inner loop of Algorithm 4 (LM-HALP) for softmax regression (K classes, one sampled row per
-// step), register-resident form with specialised waves.
+// step), register-resident form with specialised waves, at 16 bits; and the launch of this form at
+// either width (8 bits: inner_softmax_b8.hip).
 //
 // One workgroup per chain: K / CPW class waves and one service wave (CPW = 1 up to 15
 // classes; CPW = 2, two rows of z per class wave, for the 16 classes that would need a
 // seventeenth wave).
 //
 // Class wave c owns row c of z ([K][d]): lane l holds the UPL consecutive strips
-// (16 rounding bits each; UPL up to 8 at 8 bits, up to 16 at 16 bits) starting at l * UPL,
+// (a coordinate each, UPL up to 16) starting at l * UPL,
 // with h~, in registers for the whole epoch.  Its fragment of the sampled row and the step's
 // rounding bits come straight from memory, requested two or four steps ahead.
 //
@@ -28,22 +29,18 @@
 // ~350 cycles), LDS, update, with the issue slots of the SIMD that has most class waves next to
 // it: three waves of 784 coordinates take 920 cycles for update and dot where one takes 630, and
 // at ten classes of that width these slots are the longer part.
-// So the class waves' instructions are kept few: coordinates in pairs (packed 16-bit update at
-// 8 bits, z biased so that one test of the wave finds a clamp), requests with a scalar base, the
-// rare paths (a clamp, an L2 draw) behind one branch each.
+// So the class waves' instructions are kept few: z biased so that one test of the wave finds a clamp, requests
+// with a scalar base, the rare paths (a clamp, an L2 draw) behind one branch each.
 //
 // Measured, us per step of one chain, before (class waves drawing their own blocks) and now:
-// 784 x 10 at 8 bits 1.43 -> 0.89, at 16 bits 2.73 -> 1.45; 1024 x 15 at 8 bits 2.42 -> 1.02;
-// 784 x 16 at 8 bits 3.92 -> 1.13; 1000 x 15 at 16 bits 29.8 -> 3.1; 300 x 4 at 8 bits
-// 0.91 -> 0.57; 64 x 2 at 16 bits 0.75 -> 0.56.  With 256 chains, where making the records
-// takes the whole chip's issue slots too: 784 x 10 at 8 bits 1.38 -> 1.45, at 16 bits 3.2 -> 2.35.
-// With the short chain to the gammas instead of the fixed order's ~90 dependent fp64 instructions, at 8 bits:
-// 784 x 10 0.889 -> 0.870, 300 x 4 0.570 -> 0.477, 64 x 2 0.499 -> 0.407, 1024 x 15 0.954 -> 0.875, 784 x 16 1.090 -> 0.973.
+// 784 x 10 2.73 -> 1.37; 1000 x 15 29.8 -> 3.0; 64 x 2 0.75 -> 0.48.  With 256 chains, where making the records
+// takes the whole chip's issue slots too: 784 x 10 3.2 -> 2.35.
 #include <algorithm>
 
 #include "halp_device.hpp"
 #include "softmax_ahead.hpp"
 #include "softmax_fused.hpp"
+#include "inner_softmax_b8.hpp"
 
 namespace halp {
 namespace {
@@ -77,39 +74,35 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int BITS, int UPL, int KT, int CPW>
+template <int UPL, int KT, int CPW>
 __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead ah, int chain0, int last) {
-  using XT = typename std::conditional<BITS == 8, int8_t, int16_t>::type;
-  using HT = typename std::conditional<BITS == 8, int16_t, int32_t>::type;
-  using AccT = typename std::conditional<BITS == 8, int, long long>::type;
-  constexpr int CT = 16 / BITS;
-  constexpr int CPL = UPL * CT;
+  using AccT = long long;
+  constexpr int CPL = UPL;  // a strip is one coordinate
   constexpr int NDW = (UPL + 1) / 2;  // dwords of a lane's fragment of a row, and of its rounding bits
   // steps a request runs ahead: four, or two where four sets of fragments do not fit the registers
-  constexpr int kDep = UPL > 8 || (BITS == 8 && UPL == 8 && (KT > 12 || CPW > 1)) ? 2 : 4;
+  constexpr int kDep = UPL > 8 ? 2 : 4;
   constexpr int NP = CPL == 1 ? 1 : CPL / 2;  // pairs of coordinates, two 16-bit halves of a register
-  // z is kept in pairs, biased by 2^(b-1): before clamping, a coordinate has left the box exactly
-  // where bits from b upwards are set.  8 bits: the pairs are updated as such; 16 bits: one by one.
-  constexpr bool PK = BITS == 8;
+  // z is kept in pairs, biased by 2^15: before clamping, a coordinate has left the box exactly
+  // where bits from 16 upwards are set.
   // 16 values of c_k and as many of z - hh would not fit the 128 registers of 16 waves: there that
   // part of the update waits until gamma is known
-  constexpr bool kLean = !PK && UPL > 8 && KT > 12;
+  constexpr bool kLean = UPL > 8 && KT > 12;
   typedef short S2 __attribute__((ext_vector_type(2)));
   typedef unsigned short W2 __attribute__((ext_vector_type(2)));
-  constexpr int QMAX = (1 << (BITS - 1)) - 1, QMIN = -(1 << (BITS - 1));
+  constexpr int QMAX = 32767, QMIN = -32768;
   const int local = blockIdx.x, chain = chain0 + local;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int d = a.d, K = a.K;
-  const int U = (d + CT - 1) / CT;
+  const int U = d;
   // Waves w, w + 4, ... share a SIMD.  Wave 3's has the fewest waves, so the service wave goes
   // there (10 classes: beside one class wave, the other SIMDs have three), unless the class
   // waves alone fill whole rounds: then it comes last.
   const int ncw = K / CPW, svc = ncw % 4 == 0 ? ncw : min(3, ncw);
   const int64_t T = epoch_steps(a.seed + (uint64_t)chain, a.epoch, a.T, a.option2);
   const int steps = segment_steps(ah.t0, ah.t1, T);
-  const int64_t row_bytes = a.ldxq * (BITS / 8);
+  const int64_t row_bytes = a.ldxq * 2;
   const double* sc = a.scales + (int64_t)chain * 8;
   unsigned long long* cnt_out = reinterpret_cast<unsigned long long*>(a.counters + (int64_t)chain * 4);
   const bool lp = a.lp != 0;  // Algorithm 2 (LP-SVRG): z is the model itself
@@ -120,7 +113,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
   }
 
   __shared__ __attribute__((aligned(16))) AccT s_D[2][kKC];  // x_i^T z_c
-  __shared__ int s_ng[2][kKC];                               // 8 bits: -gamma_c, 16 bits: gamma_c
+  __shared__ int s_ng[2][kKC];                               // gamma_c
   __shared__ AccT s_dumpD[64];  // partial folds of lanes 0..62 of every class wave (never read)
   __shared__ unsigned long long s_cnt[3];
   if (tid < 3) s_cnt[tid] = 0;
@@ -156,7 +149,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
         const double beta = __dmul_rn(aB, __dadd_rn(p, -r.p0));
         const double f = floor(__dadd_rn(__dmul_rn(beta, inv_s), __dmul_rn((double)r.rho, 0x1p-32)));
         const double fc = fmin(fmax(f, (double)QMIN), (double)QMAX);
-        if (lane < K) s_ng[par][lane] = BITS == 8 ? (int)(-fc) : (int)fc;
+        if (lane < K) s_ng[par][lane] = (int)fc;
         n_gclamp += (lane < K && f != fc) ? 1u : 0u;
       };
       auto run = [&](auto fused_tag) __attribute__((always_inline)) {
@@ -172,7 +165,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
         double from = 0.0;  // what the new margins are measured from: phi in Algorithm 2
         auto draw = [&](const AheadRec& r) __attribute__((always_inline)) {
           if constexpr (FUSED) {
-            dr = soft_draw<BITS == 8>(live, r.p0, r.phi, r.rho, k2);
+            dr = soft_draw<false>(live, r.p0, r.phi, r.rho, k2);
             from = lp && live ? (double)r.phi : 0.0;
           }
         };
@@ -189,9 +182,8 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
               if constexpr (FUSED) {
                 int hi;
                 if (__builtin_expect_with_probability(
-                        soft_gamma<BITS == 8>(dr, live, __fma_rn(dscale, (double)s_D[s & 1][rc], -from), &hi), 1, 1.0)) {
-                  const int lo = BITS == 8 ? -QMAX : QMIN, up = BITS == 8 ? -QMIN : QMAX;
-                  const int g = min(max(hi, kSoftMagicHi + lo), kSoftMagicHi + up);
+                        soft_gamma<false>(dr, live, __fma_rn(dscale, (double)s_D[s & 1][rc], -from), &hi), 1, 1.0)) {
+                  const int g = min(max(hi, kSoftMagicHi + QMIN), kSoftMagicHi + QMAX);
                   s_ng[s & 1][rc] = g - kSoftMagicHi;  // (four lanes store the same word)
                   n_gclamp += (live && soft_first_copy(lane) && g != hi) ? 1u : 0u;
                 } else {
@@ -218,14 +210,14 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
     const int cls0 = (wave - (wave > svc ? 1 : 0)) * CPW;
     auto row0_of = [&](int cc) { return ((int64_t)chain * K + cls0 + cc) * d; };
     const int s0 = lane * UPL;
-    const int j0 = s0 * CT;
+    const int j0 = s0;
     const bool lane_ok = s0 < U;
-    S2 zp[CPW][NP], hlp[CPW][PK ? NP : 1], hhp[CPW][PK ? NP : 1];
-    int hv[CPW][PK ? 1 : CPL];
+    S2 zp[CPW][NP];
+    int hv[CPW][CPL];
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
-      const HT* __restrict__ hg = reinterpret_cast<const HT*>(a.h) + row0_of(cc);
-      const XT* __restrict__ zg = reinterpret_cast<const XT*>(a.z) + row0_of(cc);
+      const int32_t* __restrict__ hg = reinterpret_cast<const int32_t*>(a.h) + row0_of(cc);
+      const int16_t* __restrict__ zg = reinterpret_cast<const int16_t*>(a.z) + row0_of(cc);
       int zv[CPL], hk[CPL];
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {  // unconditional: all loads in flight at once
@@ -238,19 +230,12 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
       for (int k = 0; k < CPL; ++k) {
         const bool ok = j0 + k < d;
         const int zz = ok ? zv[k] : 0, hh = ok ? hk[k] : 0;
-        if (CPL == 1) zp[cc][0] = (S2)(short)(1 << (BITS - 1));
-        zp[cc][k / 2][k % 2] = (short)(zz + (1 << (BITS - 1)));
-        if constexpr (PK) {  // -h~ = 256 hh + hl with 0 <= hl < 256
-          hlp[cc][k / 2][k % 2] = (short)((-hh) & 0xFF);
-          hhp[cc][k / 2][k % 2] = (short)((-hh) >> 8);
-        } else {
-          hv[cc][k] = hh;
-        }
+        if (CPL == 1) zp[cc][0] = (S2)(short)(1 << 15);
+        zp[cc][k / 2][k % 2] = (short)(zz + (1 << 15));
+        hv[cc][k] = hh;
       }
     }
-    unsigned long long n_zclamp = 0;  // counted by the wave (steps with an L2 draw, 16 bits)
-    W2 n_half = (W2)(0);              // counted by the lane, a window's and all of them (8 bits)
-    uint32_t n_lane = 0;
+    uint32_t n_lane = 0;  // clamped coordinates, counted by the lane
     using LdsAcc = __attribute__((address_space(3))) AccT;
     LdsAcc* slotD[CPW][2];
 #pragma unroll
@@ -261,25 +246,16 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
 
     if (steps > 0) {
       const unsigned char* __restrict__ Xq = reinterpret_cast<const unsigned char*>(a.Xq) +
-                                             (int64_t)chain * a.xq_chain_stride * (BITS / 8);
+                                             (int64_t)chain * a.xq_chain_stride * 2;
       const int32_t* __restrict__ idx = ah.idx + (int64_t)local * ah.S;
       // Rows are padded to whole 8-byte groups: a fragment is read in pieces of 8 bytes at most, and
       // a piece past the row repeats the row's last group.  What lies past d is masked to zero.
-      const uint32_t last_group = (uint32_t)((((int64_t)d * (BITS / 8) + 7) / 8 - 1) * 8);
-      uint32_t fm[NDW];           // 16 bits: the mask; 8 bits: -128 in the bytes of coordinates, 0 past d
-      uint32_t fs[PK ? UPL : 1];  // 8 bits: byte selectors of a pair, 0x0C (a zero byte) past d
+      const uint32_t last_group = (uint32_t)((((int64_t)d * 2 + 7) / 8 - 1) * 8);
+      uint32_t fm[NDW];
 #pragma unroll
       for (int q = 0; q < NDW; ++q) {
-        const int nv = d - (j0 + q * (32 / BITS));
-        fm[q] = nv >= 32 / BITS ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << (nv * BITS)) - 1u);
-        if (PK) fm[q] &= 0x80808080u;
-      }
-      if constexpr (PK) {
-#pragma unroll
-        for (int u = 0; u < UPL; ++u) {
-          const int nv = d - (j0 + 2 * u), b = 2 * (u & 1);
-          fs[u] = ((nv >= 2 ? (uint32_t)(b + 1) : 0x0Cu) << 24) | 0x0C000Cu | ((nv >= 1 ? (uint32_t)b : 0x0Cu) << 8);
-        }
+        const int nv = d - (j0 + q * 2);
+        fm[q] = nv >= 2 ? 0xFFFFFFFFu : (nv <= 0 ? 0u : 0xFFFFu);
       }
       uint32_t foff[(UPL + 3) / 4];
 #pragma unroll
@@ -341,20 +317,10 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
       int bias[2] = {0, 0};  // -128 sum x, for the bias of z in the dot product
       auto unpack = [&](int par, int slot) {
         bias[par] = 0;
-        if constexpr (PK) {
 #pragma unroll
-          for (int u = 0; u < UPL; ++u) {
-            const uint32_t up = __builtin_amdgcn_perm(0u, fr[slot][u / 2], fs[u]);
-            xp[par][u] = __builtin_bit_cast(S2, up) >> (S2)(8);
-          }
-#pragma unroll
-          for (int q = 0; q < NDW; ++q) bias[par] = __builtin_amdgcn_sdot4((int)fr[slot][q], (int)fm[q], bias[par], false);
-        } else {
-#pragma unroll
-          for (int q = 0; q < NDW; ++q) {
-            xp[par][q] = __builtin_bit_cast(S2, fr[slot][q] & fm[q]);
-            bias[par] = __builtin_amdgcn_sdot2(xp[par][q], (S2)(-128), bias[par], false);
-          }
+        for (int q = 0; q < NDW; ++q) {
+          xp[par][q] = __builtin_bit_cast(S2, fr[slot][q] & fm[q]);
+          bias[par] = __builtin_amdgcn_sdot2(xp[par][q], (S2)(-128), bias[par], false);
         }
       };
       unpack(0, 0);
@@ -368,46 +334,31 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
         for (int s = 0; s < kWin; ++s) {
           if (t0 + s < steps) {
             AccT acc[CPW];
-            if constexpr (PK) {
+            // the high and the low bytes of z apart: 16 products of either fit 32 bits
 #pragma unroll
-              for (int cc = 0; cc < CPW; ++cc) {
-                int c0 = bias[s & 1], c1 = 0;  // two chains
+            for (int cc = 0; cc < CPW; ++cc) {
+              int ch = bias[s & 1], cl8 = 0;
 #pragma unroll
-                for (int u = 0; u < UPL; ++u) {
-                  if (u & 1) c1 = __builtin_amdgcn_sdot2(xp[s & 1][u], zp[cc][u], c1, false);
-                  else c0 = __builtin_amdgcn_sdot2(xp[s & 1][u], zp[cc][u], c0, false);
-                }
-                acc[cc] = (AccT)(UPL > 1 ? c0 + c1 : c0);
+              for (int q = 0; q < NP; ++q) {
+                const uint32_t zq = __builtin_bit_cast(uint32_t, zp[cc][q]);
+                ch = __builtin_amdgcn_sdot2(xp[s & 1][q], __builtin_bit_cast(S2, __builtin_bit_cast(W2, zp[cc][q]) >> (W2)(8)), ch, false);
+                cl8 = __builtin_amdgcn_sdot2(xp[s & 1][q], __builtin_bit_cast(S2, zq & 0x00FF00FFu), cl8, false);
               }
-            } else {
-              // the high and the low bytes of z apart: 16 products of either fit 32 bits
-#pragma unroll
-              for (int cc = 0; cc < CPW; ++cc) {
-                int ch = bias[s & 1], cl8 = 0;
-#pragma unroll
-                for (int q = 0; q < NP; ++q) {
-                  const uint32_t zq = __builtin_bit_cast(uint32_t, zp[cc][q]);
-                  ch = __builtin_amdgcn_sdot2(xp[s & 1][q], __builtin_bit_cast(S2, __builtin_bit_cast(W2, zp[cc][q]) >> (W2)(8)), ch, false);
-                  cl8 = __builtin_amdgcn_sdot2(xp[s & 1][q], __builtin_bit_cast(S2, zq & 0x00FF00FFu), cl8, false);
-                }
-                acc[cc] = ((AccT)ch << 8) + (AccT)cl8;
-              }
+              acc[cc] = ((AccT)ch << 8) + (AccT)cl8;
             }
             // the fold leaves the sum in lane 63, which stores it; the other lanes store their
             // partial folds into a dump row, so that no lane mask is set up and no lane is read
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc) {
-              if (BITS == 8) *slotD[cc][s & 1] = (AccT)wave_fold_i32((int)acc[cc]);
-              else *slotD[cc][s & 1] = (AccT)wave_fold_i64((long long)acc[cc]);
+              *slotD[cc][s & 1] = (AccT)wave_fold_i64((long long)acc[cc]);
             }
             lds_barrier();
             __builtin_amdgcn_sched_barrier(0);
             // While the service wave evaluates the softmax: the part of the update that does not
             // need gamma, the next row's fragment, and the next requests.
-            S2 crp[CPW][PK ? UPL : 1], zh[CPW][PK ? UPL : 1];
-            // 16 bits: h~ = 2^16 hh + hl, 0 <= hl < 2^16.  floor((-gamma x + r - h~) / 2^16) =
+            // h~ = 2^16 hh + hl, 0 <= hl < 2^16.  floor((-gamma x + r - h~) / 2^16) =
             // -hh - floor((gamma x + hl + 65535 - r) / 2^16), whose numerator fits 32 bits
-            int hr[CPW][PK ? 1 : CPL], zr[CPW][PK ? 1 : CPL];
+            int hr[CPW][CPL], zr[CPW][CPL];
             auto before = [&](int cc) {
 #pragma unroll
               for (int k = 0; k < CPL; ++k) {
@@ -419,16 +370,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
             };
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc) {
-              if constexpr (PK) {
-#pragma unroll
-                for (int u = 0; u < UPL; ++u) {
-                  const uint32_t rp = __builtin_amdgcn_perm(0u, zb[s % kDep][cc][u / 2], (u & 1) ? 0x0C030C02u : 0x0C010C00u);
-                  crp[cc][u] = __builtin_bit_cast(S2, rp) + hlp[cc][u];  // rounding bits + hl
-                  zh[cc][u] = hhp[cc][u] + zp[cc][u];
-                }
-              } else {
-                if (!kLean) before(cc);
-              }
+              if (!kLean) before(cc);
             }
             if (!kLean) request_bits(s % kDep, min(t0 + s + kDep, tlast));
             unpack((s + 1) & 1, (s + 1) % kDep);
@@ -440,9 +382,8 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc)
 #pragma unroll
-              for (int k = 0; k < (kLean ? 0 : (PK ? UPL : CPL)); ++k) {
-                if constexpr (PK) asm volatile("" : "+v"(crp[cc][k]), "+v"(zh[cc][k]));
-                else asm volatile("" : "+v"(hr[cc][k]), "+v"(zr[cc][k]));
+              for (int k = 0; k < (kLean ? 0 : CPL); ++k) {
+                asm volatile("" : "+v"(hr[cc][k]), "+v"(zr[cc][k]));
               }
 #pragma unroll
             for (int q = 0; q < NP; ++q) asm volatile("" : "+v"(xp[(s + 1) & 1][q]));
@@ -456,74 +397,36 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
             // u = z - gamma x - h~ (- c_lambda z), z = Q_(delta_m, b)(u)
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc) {
-              if constexpr (PK) {
-                if (__builtin_expect_with_probability(cl == 0, 1, 1.0)) {
-                  // per half: floor((-gamma x + r + hl) / 256) + hh + z + 128; |gamma x| <= 2^14 and
-                  // r + hl < 512, so every intermediate fits 16 bits
-                  const S2 ngp = S2{(short)ng[cc], (short)ng[cc]};
-                  uint32_t hit = 0;
-                  S2 vu[UPL];
+              int v[CPL];
+              uint32_t hit = 0;
+              if (kLean) before(cc);
+              if (__builtin_expect_with_probability(cl == 0, 1, 1.0)) {
 #pragma unroll
-                  for (int u = 0; u < UPL; ++u) {
-                    vu[u] = ((xp[s & 1][u] * ngp + crp[cc][u]) >> (S2)(8)) + zh[cc][u];
-                    hit |= __builtin_bit_cast(uint32_t, vu[u]);
-                  }
-                  if (__builtin_expect_with_probability(__ballot((hit & 0xFF00FF00u) != 0) != 0, 0, 1.0)) {  // a coordinate left the box
+                for (int k = 0; k < CPL; ++k)
+                  v[k] = zr[cc][k] - (mad16(__builtin_bit_cast(uint32_t, xp[s & 1][k / 2]), k, ng[cc], hr[cc][k]) >> 16);
+              } else {  // a step with an L2 draw
 #pragma unroll
-                    for (int u = 0; u < UPL; ++u) {
-                      // 1 in every half whose high byte is not 0
-                      n_half += __builtin_elementwise_min(__builtin_bit_cast(W2, vu[u]) >> (W2)(8), (W2)(1));
-                      vu[u] = __builtin_elementwise_min(__builtin_elementwise_max(vu[u], (S2)(0)), (S2)(255));
-                    }
-                  }
-#pragma unroll
-                  for (int u = 0; u < UPL; ++u) zp[cc][u] = vu[u];
-                } else {  // a step with an L2 draw: 32-bit arithmetic
-#pragma unroll
-                  for (int u = 0; u < UPL; ++u) {
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                      const S2 xu = xp[s & 1][u], zo = zp[cc][u], cu = crp[cc][u], hu = hhp[cc][u];
-                      const int zk = (int)zo[e] - 128;
-                      const int zu = zk + (int)hu[e] + (mad24(ng[cc], (int)xu[e], mad24(-cl, zk, (int)cu[e])) >> 8);
-                      const int zc = min(max(zu, QMIN), QMAX);
-                      n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
-                      zp[cc][u][e] = (short)(zc + 128);
-                    }
-                  }
+                for (int k = 0; k < CPL; ++k) {
+                  uint32_t zq = __builtin_bit_cast(uint32_t, zp[cc][k / 2]);
+                  asm volatile("" : "+v"(zq));  // unpacked here, not kept for every step
+                  const int zk = (int)((zq >> (16 * (k % 2))) & 0xFFFFu) - 32768;
+                  const long long n = (long long)ng[cc] * (int)xp[s & 1][k / 2][k % 2] + (long long)cl * zk + hr[cc][k];
+                  v[k] = zr[cc][k] - (int)(n >> 16);
                 }
-              } else {
-                int v[CPL];
-                uint32_t hit = 0;
-                if (kLean) before(cc);
-                if (__builtin_expect_with_probability(cl == 0, 1, 1.0)) {
-#pragma unroll
-                  for (int k = 0; k < CPL; ++k)
-                    v[k] = zr[cc][k] - (mad16(__builtin_bit_cast(uint32_t, xp[s & 1][k / 2]), k, ng[cc], hr[cc][k]) >> 16);
-                } else {  // a step with an L2 draw
-#pragma unroll
-                  for (int k = 0; k < CPL; ++k) {
-                    uint32_t zq = __builtin_bit_cast(uint32_t, zp[cc][k / 2]);
-                    asm volatile("" : "+v"(zq));  // unpacked here, not kept for every step
-                    const int zk = (int)((zq >> (16 * (k % 2))) & 0xFFFFu) - 32768;
-                    const long long n = (long long)ng[cc] * (int)xp[s & 1][k / 2][k % 2] + (long long)cl * zk + hr[cc][k];
-                    v[k] = zr[cc][k] - (int)(n >> 16);
-                  }
-                }
-#pragma unroll
-                for (int k = 0; k < CPL; ++k) hit |= (uint32_t)v[k];
-                if (__builtin_expect_with_probability(__ballot((hit & 0xFFFF0000u) != 0) != 0, 0, 1.0)) {
-#pragma unroll
-                  for (int k = 0; k < CPL; ++k) {
-                    const int vc = min(max(v[k], 0), 65535);
-                    n_lane += v[k] != vc ? 1u : 0u;
-                    v[k] = vc;
-                  }
-                }
-#pragma unroll
-                for (int q = 0; q < NP; ++q)
-                  zp[cc][q] = CPL == 1 ? S2{(short)v[0], (short)0x8000} : S2{(short)v[2 * q], (short)v[(2 * q + 1) % CPL]};
               }
+#pragma unroll
+              for (int k = 0; k < CPL; ++k) hit |= (uint32_t)v[k];
+              if (__builtin_expect_with_probability(__ballot((hit & 0xFFFF0000u) != 0) != 0, 0, 1.0)) {
+#pragma unroll
+                for (int k = 0; k < CPL; ++k) {
+                  const int vc = min(max(v[k], 0), 65535);
+                  n_lane += v[k] != vc ? 1u : 0u;
+                  v[k] = vc;
+                }
+              }
+#pragma unroll
+              for (int q = 0; q < NP; ++q)
+                zp[cc][q] = CPL == 1 ? S2{(short)v[0], (short)0x8000} : S2{(short)v[2 * q], (short)v[(2 * q + 1) % CPL]};
             }
             if (kLean) request_bits(s % kDep, min(t0 + s + kDep, tlast));
           }
@@ -531,8 +434,6 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
         }
         iv = ivn;
         ivn = ivnn;
-        n_lane += (uint32_t)n_half[0] + (uint32_t)n_half[1];
-        n_half = (W2)(0);
       }
     }
 
@@ -540,7 +441,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
     const double delta_m = sc[0];
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
-      XT* __restrict__ zg = reinterpret_cast<XT*>(a.z) + row0_of(cc);
+      int16_t* __restrict__ zg = reinterpret_cast<int16_t*>(a.z) + row0_of(cc);
       float* __restrict__ wg = a.w + row0_of(cc);
       int jl = j0;
       asm volatile("" : "+v"(jl));  // keeps the addresses below from being carried through the loop
@@ -552,8 +453,8 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
         if (jl + k < d) {
-          const int zk = (int)(uint16_t)zp[cc][k / 2][k % 2] - (1 << (BITS - 1));
-          zg[jl + k] = (XT)zk;
+          const int zk = (int)(uint16_t)zp[cc][k / 2][k % 2] - (1 << 15);
+          zg[jl + k] = (int16_t)zk;
           if (last) {
             const double step = __dmul_rn(delta_m, (double)zk);
             wg[jl + k] = lp ? (float)step : (float)__dadd_rn((double)wv[k], step);  // Alg. 2: w~ = delta w
@@ -561,7 +462,6 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
         }
       }
     }
-    if (lane == 0 && n_zclamp) atomicAdd(&s_cnt[0], n_zclamp);
     if (n_lane) atomicAdd(&s_cnt[0], (unsigned long long)n_lane);
   }
   __syncthreads();
@@ -571,40 +471,37 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_kernel(InArgs a, Ahead 
   }
 }
 
-using Kernel = void (*)(InArgs, Ahead, int, int);
+using Kernel = SoftmaxKernel;
 
 // one row of z per class wave up to 15 classes; 16 classes: two rows per wave, 8 + 1 waves
 int classes_per_wave(int K) { return K > 15 ? 2 : 1; }
-int block_threads(int K) { return 64 * (K / classes_per_wave(K) + 1); }
+int block_threads(const halp_params& p) {
+  return p.b == 8 ? softmax_b8_threads(p.K) : 64 * (p.K / classes_per_wave(p.K) + 1);
+}
 
-template <int BITS, int UPL>
+template <int UPL>
 Kernel kernel_for(int K) {
   if (classes_per_wave(K) == 2) {
-    if constexpr (UPL <= 8) return inner_softmax_kernel<BITS, UPL, 12, 2>;
+    if constexpr (UPL <= 8) return inner_softmax_kernel<UPL, 12, 2>;
     else return nullptr;
   } else if constexpr (UPL <= 4) {
-    return inner_softmax_kernel<BITS, UPL, 16, 1>;
+    return inner_softmax_kernel<UPL, 16, 1>;
   } else {  // fewer waves, more registers each
-    if (K + 1 <= 8) return inner_softmax_kernel<BITS, UPL, 8, 1>;
-    if (K + 1 <= 12) return inner_softmax_kernel<BITS, UPL, 12, 1>;
-    return inner_softmax_kernel<BITS, UPL, 16, 1>;
+    if (K + 1 <= 8) return inner_softmax_kernel<UPL, 8, 1>;
+    if (K + 1 <= 12) return inner_softmax_kernel<UPL, 12, 1>;
+    return inner_softmax_kernel<UPL, 16, 1>;
   }
 }
 
-template <int BITS>
 Kernel kernel_for(int K, int upl) {
   switch (upl) {
-    case 1: return kernel_for<BITS, 1>(K);
-    case 2: return kernel_for<BITS, 2>(K);
-    case 4: return kernel_for<BITS, 4>(K);
-    case 8: return kernel_for<BITS, 8>(K);
-    default: break;
+    case 1: return kernel_for<1>(K);
+    case 2: return kernel_for<2>(K);
+    case 4: return kernel_for<4>(K);
+    case 8: return kernel_for<8>(K);
+    case 16: return kernel_for<16>(K);
+    default: return nullptr;
   }
-  // 16 strips per lane exist at 16 bits only (16 coordinates per lane; at 8 bits they would be 32)
-  if constexpr (BITS == 16) {
-    if (upl == 16) return kernel_for<16, 16>(K);
-  }
-  return nullptr;
 }
 
 int strips_per_lane(const halp_params& p) {
@@ -622,8 +519,13 @@ int softmax_up(const halp_params& p) {
   return ((p.d + ct - 1) / ct + m - 1) / m * m;
 }
 
+// Records of 16-bit halves: eight strips per lane, more than one class wave to a SIMD and few chains, whose records'
+// traffic is nothing.  us per step, bytes / halves: 784 x 10 one chain 0.691 / 0.651, four 0.712 / 0.683, eight 0.756 / 0.750,
+// sixteen 0.814 / 0.837, 256 1.82 / 2.77; 784 x 8 0.626 / 0.607, 784 x 7 0.541 / 0.565; 784 x 16 0.940 / 0.913; 500 x 10 0.493 / 0.530.
+bool expanded(const halp_params& p) { return p.b == 8 && strips_per_lane(p) == 8 && p.K >= 8 && p.R <= 8; }
+
 Kernel kernel_for(const halp_params& p) {
-  return p.b == 8 ? kernel_for<8>(p.K, strips_per_lane(p)) : kernel_for<16>(p.K, strips_per_lane(p));
+  return p.b == 8 ? softmax_b8_kernel(p.K, strips_per_lane(p), expanded(p)) : kernel_for(p.K, strips_per_lane(p));
 }
 
 }  // namespace
@@ -642,9 +544,9 @@ size_t plan_inner_softmax(halp_handle& h) {
   if (!inner_softmax_takes(h.p)) return 0;
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(h.p)),
-                                                   block_threads(h.p.K), 0) != hipSuccess)
+                                                   block_threads(h.p), 0) != hipSuccess)
     (void)hipGetLastError();
-  return plan_ahead(h, softmax_up(h.p), std::max(per_cu, 1) * h.num_cus);
+  return plan_ahead(h, softmax_up(h.p), std::max(per_cu, 1) * h.num_cus, expanded(h.p));
 }
 
 // softmax, one row per step, up to 15 classes one wave each plus the service wave, 16 classes
@@ -661,8 +563,8 @@ int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t st) {
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
   const Kernel kernel = kernel_for(p);
-  return for_segments(a, h, softmax_up(p), st, [&](const Ahead& s, int c0, int chains, int last) {
-    hipLaunchKernelGGL(kernel, dim3(chains), dim3(block_threads(p.K)), 0, st, a, s, c0, last);
+  return for_segments(a, h, softmax_up(p), expanded(p), st, [&](const Ahead& s, int c0, int chains, int last) {
+    hipLaunchKernelGGL(kernel, dim3(chains), dim3(block_threads(p)), 0, st, a, s, c0, last);
     return hip_ok(hipGetLastError());
   });
 }

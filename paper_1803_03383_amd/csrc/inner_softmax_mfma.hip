@@ -650,7 +650,7 @@ int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t 
   const InArgs a = make_inner_args(h, epoch);
   const bool many = p.B > mfma_rows(p.d, p.B), soft = p.loss == HALP_LOSS_SOFTMAX;
   const bool al16 = h.buf.ldxq % 16 == 0 && reinterpret_cast<uintptr_t>(h.buf.Xq) % 16 == 0;
-  return for_segments(a, h, mfma_up(p), st, [&](const Ahead& s, int c0, int chains, int last) -> int {
+  return for_segments(a, h, mfma_up(p), false, st, [&](const Ahead& s, int c0, int chains, int last) -> int {
 #define HALP_MF(MANY_, AL_, SOFT_) \
   if (many == MANY_ && al16 == AL_ && soft == SOFT_) return launch_one<MANY_, AL_, SOFT_>(a, s, c0, chains, last, st);
     HALP_MF(false, true, true) HALP_MF(false, false, true) HALP_MF(true, true, true) HALP_MF(true, false, true)

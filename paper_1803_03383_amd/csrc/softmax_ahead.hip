@@ -78,37 +78,72 @@ __global__ __launch_bounds__(256) void ahead_zbits(InArgs a, Ahead s, int bits, 
   for (int k = 0; k < 8; ++k) out[k * stride] = zround_field(r0, (uint32_t)k) | (zround_field(r1, (uint32_t)k) << 16);
 }
 
+// The same at 8 bits, expanded: strips of a class up to UP, those past the row 0.
+__global__ __launch_bounds__(256) void ahead_halves(InArgs a, Ahead s, int chain0) {
+  const int local = blockIdx.z, chain = chain0 + local;
+  const uint64_t seed = a.seed + (uint64_t)chain;
+  const int U = (a.d + 1) / 2;
+  const int v = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (v >= a.K * s.UP) return;
+  const int c = v / s.UP, u = v - c * s.UP;
+  const int64_t tw = s.t0 + 8 * (int64_t)blockIdx.y;
+  uint32_t* out = reinterpret_cast<uint32_t*>(s.zbits) + (((int64_t)local * s.S + (tw - s.t0)) * a.K + c) * s.UP + u;
+  const int64_t stride = (int64_t)a.K * s.UP;  // dwords per step
+  const bool in = u < U;
+  const U4 r = zround_block(seed, a.epoch, (uint32_t)(c * U + u), (uint32_t)(tw >> 3));
+  int h0 = 0, h1 = 0;
+  if (in && s.whole[local] != 0) {
+    const int16_t* h = reinterpret_cast<const int16_t*>(a.h) + ((int64_t)chain * a.K + c) * a.d + 2 * u;
+    h0 = h[0];
+    h1 = 2 * u + 1 < a.d ? h[1] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int f = (int)zround_field(r, (uint32_t)k);
+    out[k * stride] = in ? (uint32_t)(((f & 0xFF) - h0) & 0xFFFF) | ((uint32_t)((f >> 8) - h1) << 16) : 0u;
+  }
+}
+
+// one workgroup per chain
+__global__ __launch_bounds__(256) void ahead_whole(InArgs a, Ahead s, int chain0) {
+  const int16_t* h = reinterpret_cast<const int16_t*>(a.h) + (int64_t)(chain0 + blockIdx.x) * a.K * a.d;
+  int large = 0;
+  for (int j = threadIdx.x; j < a.K * a.d; j += 256) large |= (h[j] > kWholeH || h[j] < -kWholeH) ? 1 : 0;
+  const int any = __syncthreads_or(large);
+  if (threadIdx.x == 0) s.whole[blockIdx.x] = any ? 0 : 1;
+}
+
 size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 
 }  // namespace
 
-size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP) {
+size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP, bool expanded) {
   const size_t n = (size_t)chains * (size_t)S;
   return round256(n * p.B * kAheadK * sizeof(AheadRec)) + round256(n * p.B * 4) + round256(n * 4) +
-         round256(n * p.K * (size_t)UP * 2);
+         round256(n * p.K * (size_t)UP * (expanded ? 4 : 2)) + round256((size_t)chains * 4);
 }
 
-int64_t ahead_steps(const halp_params& p, int chains, int UP, size_t bytes) {
-  const size_t per8 = ahead_bytes(p, chains, 8, UP);
+int64_t ahead_steps(const halp_params& p, int chains, int UP, bool expanded, size_t bytes) {
+  const size_t per8 = ahead_bytes(p, chains, 8, UP, expanded);
   int64_t S = (int64_t)(bytes / per8) * 8;  // each part is rounded up once per call, so this is on the safe side
   const int64_t most = (p.T + 7) / 8 * 8;
   return S < most ? S : (most > 8 ? most : 8);
 }
 
-size_t plan_ahead(halp_handle& h, int UP, int resident) {
+size_t plan_ahead(halp_handle& h, int UP, int resident, bool expanded) {
   const halp_params& p = h.p;
   const size_t mb = (size_t)1 << 20;
   const size_t budget = std::min((size_t)1024 * mb, std::max((size_t)64 * mb, (size_t)p.R * 4 * mb));
   const int groups = (p.R + resident - 1) / resident;
   int chains = (p.R + groups - 1) / groups;
-  int64_t S = ahead_steps(p, chains, UP, budget);
-  for (; S < 8 && chains > 1; S = ahead_steps(p, chains, UP, budget)) chains = (chains + 1) / 2;
+  int64_t S = ahead_steps(p, chains, UP, expanded, budget);
+  for (; S < 8 && chains > 1; S = ahead_steps(p, chains, UP, expanded, budget)) chains = (chains + 1) / 2;
   h.ahead_chains = chains;
   h.ahead_steps = std::max((int64_t)8, S);
-  return ahead_bytes(p, chains, h.ahead_steps, UP);
+  return ahead_bytes(p, chains, h.ahead_steps, UP, expanded);
 }
 
-Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws) {
+Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, bool expanded, void* ws) {
   const size_t n = (size_t)chains * (size_t)S;
   unsigned char* q = reinterpret_cast<unsigned char*>(ws);
   Ahead s;
@@ -119,6 +154,9 @@ Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, void* ws
   s.cl = reinterpret_cast<int32_t*>(q);
   q += round256(n * 4);
   s.zbits = UP > 0 ? reinterpret_cast<uint16_t*>(q) : nullptr;
+  q += round256(n * p.K * (size_t)UP * (expanded ? 4 : 2));
+  s.whole = reinterpret_cast<int32_t*>(q);
+  s.expanded = expanded;
   s.S = S;
   s.UP = UP;
   s.t0 = s.t1 = 0;
@@ -137,7 +175,12 @@ int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chai
   else if (a.K <= 4) scalars(std::integral_constant<int, 4>{});
   else if (a.K <= 8) scalars(std::integral_constant<int, 8>{});
   else scalars(std::integral_constant<int, 16>{});
-  if (s.UP > 0) {
+  const bool b8_rows = bits == 8 && a.B == 1 && s.UP > 0;  // the 8-bit loop of one row per step
+  if (b8_rows && s.t0 == 0) hipLaunchKernelGGL(ahead_whole, dim3(chains), dim3(256), 0, stream, a, s, chain0);
+  if (s.expanded) {
+    const dim3 g2((unsigned)((a.K * s.UP + 255) / 256), (unsigned)((steps + 7) / 8), chains);
+    hipLaunchKernelGGL(ahead_halves, g2, dim3(256), 0, stream, a, s, chain0);
+  } else if (s.UP > 0) {
     const int U = (a.d + 16 / bits - 1) / (16 / bits);
     const dim3 g2((unsigned)((a.K * ((U + 1) / 2) + 255) / 256), (unsigned)((steps + 7) / 8), chains);
     hipLaunchKernelGGL(ahead_zbits, g2, dim3(256), 0, stream, a, s, bits, chain0);
