@@ -26,7 +26,8 @@
 //                 a later step, polls, softmax after the offset, gamma_c into LDS
 //   class waves   (the trip takes 0.5-0.7 us) a share of the next window's Philox blocks,
 //                 what of the update needs no gamma                                        | barrier
-//   class waves   integer update of their rows
+//   class waves   integer update of their rows (8 bits: two packed instructions per strip, as in
+//                 inner_softmax_b8.hip; what saturated is counted, and the next row unpacked, during the trip)
 //
 // What bounds it: latency, most of it the exchange.  One wave adds all classes at once because
 // atomics of different waves queue up: with one atomic per class wave, words 256 bytes apart, a step of
@@ -36,11 +37,14 @@
 // alternate, so a chain's words lie in the page nearest to its XCD, which halp_create finds by timing
 // (find_near): 1100 x 5 three chains 1.66 -> 1.38 us per step.  us per step, one atomic per class wave -> now:
 // 10000 x 10 8 bits one chain 3.06 -> 2.00, five 3.52 -> 2.32, 16 bits five 3.86 -> 2.83; 4000 x 5 five chains 2.06 -> 1.51;
-// 2000 x 10 1.89 -> 1.54; 1100 x 2 1.27 -> 1.20.
+// 2000 x 10 1.89 -> 1.54; 1100 x 2 1.27 -> 1.20.  With the update in saturated halves at 8 bits, where it was done in
+// unsaturated ones, clamps counted by ballots before the next dot: one chain of 10000 x 10 1.99 -> 1.82, five 2.31 -> 2.15, 2000 x 10
+// 1.54 -> 1.37, 1100 x 2 1.20 -> 1.03, 256 chains of 1100 x 10 8.9 -> 8.2; where nothing is clamped 2-8 %.
 #include <algorithm>
 
 #include "halp_device.hpp"
 #include "inner_args.hpp"
+#include "softmax_ahead.hpp"
 #include "softmax_fused.hpp"
 
 namespace halp {
@@ -109,6 +113,7 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
   constexpr int NDW = UPL / 2;      // dwords of a lane's row fragment
   constexpr bool PK = BITS == 8;    // 8 bits: the two coordinates of a strip as halves of one register
   typedef short S2 __attribute__((ext_vector_type(2)));
+  typedef unsigned short W2 __attribute__((ext_vector_type(2)));
   constexpr int QMAX = (1 << (BITS - 1)) - 1, QMIN = -(1 << (BITS - 1));
   // Consecutive workgroups go to the eight XCDs in turn.  Where a chain's parts fit one XCD they
   // are placed there (the exchange is 0.15-0.3 us shorter); results do not depend on it.
@@ -316,11 +321,18 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     // whatever lies past d is masked to zero, so that z stays zero there.
     const int64_t off0 = s0 < U ? (int64_t)s0 * 2 : 0;
     const int64_t off1 = UPL == 8 && s0 + 4 < U ? off0 + 8 : off0;
-    uint32_t fm[NDW];
+    uint32_t fm[PK ? 1 : NDW], fs[PK ? UPL : 1];  // 8 bits: byte selectors of a pair, 0x0C (a zero byte) past d
 #pragma unroll
     for (int q = 0; q < NDW; ++q) {
       const int nv = d - (j0 + q * (32 / BITS));
-      fm[q] = nv >= 32 / BITS ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << (nv * BITS)) - 1u);
+      if (!PK) fm[q] = nv >= 32 / BITS ? 0xFFFFFFFFu : (nv <= 0 ? 0u : (1u << (nv * BITS)) - 1u);
+    }
+    if constexpr (PK) {
+#pragma unroll
+      for (int u = 0; u < UPL; ++u) {
+        const int nv = d - (j0 + 2 * u), b = 2 * (u & 1);
+        fs[u] = ((nv >= 2 ? (uint32_t)(b + 1) : 0x0Cu) << 24) | 0x0C000Cu | ((nv >= 1 ? (uint32_t)b : 0x0Cu) << 8);
+      }
     }
     uint32_t fr[kWin][NDW];
     auto request = [&](int s, int i) {
@@ -336,8 +348,10 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
         }
       }
     };
-    // z and h~: 8 bits packed, -h~ = 256 hh + hl with 0 <= hl < 256; 16 bits plain
-    S2 zp[CPW][PK ? UPL : 1], hlp[CPW][PK ? UPL : 1], hhp[CPW][PK ? UPL : 1];
+    // z and h~, 16 bits plain.  8 bits: packed, h~ and 256 z before the step, what was added to it, and their
+    // saturated sum, whose high bytes are z and whose low bytes are cleared beside the exchange (inner_softmax_b8.hip)
+    S2 hp[CPW][PK ? UPL : 1], zq[CPW][PK ? UPL : 1], add[CPW][PK ? UPL : 1], sum[CPW][PK ? UPL : 1];
+    bool whole = true;  // |h~| of this wave's coordinates leaves room for -gamma x + r - h~ in 16 bits
     int z[CPW][PK ? 1 : CPL], hv[CPW][PK ? 1 : CPL];
     auto row_of = [&](int cc) { return ((int64_t)chain * K + cls0 + cc) * d; };
 #pragma unroll
@@ -349,9 +363,11 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
         const int j = min(j0 + k, d - 1);
         const int zk = j0 + k < d ? (int)zg[j] : 0, hk = j0 + k < d ? (int)hg[j] : 0;
         if constexpr (PK) {
-          zp[cc][k / 2][k % 2] = (short)zk;
-          hlp[cc][k / 2][k % 2] = (short)((-hk) & 0xFF);
-          hhp[cc][k / 2][k % 2] = (short)((-hk) >> 8);
+          sum[cc][k / 2][k % 2] = (short)(zk * 256);
+          zq[cc][k / 2] = sum[cc][k / 2];
+          add[cc][k / 2] = (S2)(0);
+          hp[cc][k / 2][k % 2] = (short)hk;
+          whole = whole && hk <= kWholeH && hk >= -kWholeH;
         } else {
           z[cc][k] = zk;
           hv[cc][k] = hk;
@@ -370,7 +386,9 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
     constexpr int kBlocks = CPW * UPL;  // a window's blocks
     static_assert(kBlocks == 4 || kBlocks % 8 == 0);
     U4 half_block{};
-    unsigned long long n_zclamp = 0;
+    unsigned long long n_zclamp = 0;  // counted by the wave (8 bits: by the lane)
+    W2 n_half = (W2)(0), ones = (W2)(1);
+    asm volatile("" : "+v"(ones));  // a value the compiler does not see: one packed minimum per strip
     __syncthreads();  // the first 64 indices are in LDS
     {
       const int iv = s_idx[0][lane & 7];
@@ -378,142 +396,177 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       for (int s = 0; s < kWin; ++s) request(s, __builtin_amdgcn_readlane(iv, s));
     }
 
-    for (int64_t t0 = 0; t0 < T; t0 += kWin) {
+    uint32_t xs[PK ? UPL : 1];  // 8 bits: the row in pairs, a coordinate in the high byte of its half
+    auto unpack = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
-      for (int cc = 0; cc < CPW; ++cc)
+      for (int u = 0; u < (PK ? UPL : 1); ++u) xs[u] = PK ? __builtin_amdgcn_perm(0u, fr[slot][u / 2], fs[PK ? u : 0]) : 0u;
+    };
+    auto run = [&](auto whole_tag) __attribute__((always_inline)) {
+      constexpr bool WHOLE = decltype(whole_tag)::value;
+      for (int64_t t0 = 0; t0 < T; t0 += kWin) {
 #pragma unroll
-        for (int u = 0; u < UPL; ++u)
+        for (int cc = 0; cc < CPW; ++cc)
 #pragma unroll
-          for (int w = 0; w < 4; ++w) zrw[cc][u][w] = zrn[cc][u][w];
-      const int tn = (int)((t0 + kWin) & (2 * kIdxRing - 1)) + (lane & 7);
-      const int idxn = s_idx[tn >> 6][tn & (kIdxRing - 1)];  // rows of the next window
+          for (int u = 0; u < UPL; ++u)
 #pragma unroll
-      for (int s = 0; s < kWin; ++s) {
-        if (t0 + s < T) {
-          uint32_t xw[NDW];
+            for (int w = 0; w < 4; ++w) zrw[cc][u][w] = zrn[cc][u][w];
+        const int tn = (int)((t0 + kWin) & (2 * kIdxRing - 1)) + (lane & 7);
+        const int idxn = s_idx[tn >> 6][tn & (kIdxRing - 1)];  // rows of the next window
 #pragma unroll
-          for (int q = 0; q < NDW; ++q) xw[q] = fr[s][q] & fm[q];
-          S2 xp[PK ? UPL : 1];
-          AccT acc[CPW];
+        for (int s = 0; s < kWin; ++s) {
+          if (t0 + s < T) {
+            uint32_t xw[PK ? 1 : NDW];
+            if constexpr (!PK) {
 #pragma unroll
-          for (int cc = 0; cc < CPW; ++cc) acc[cc] = 0;
-          auto x_of = [&](int k) { return (int)(int16_t)(xw[k / 2] >> (16 * (k % 2))); };  // 16 bits
-          if constexpr (PK) {
+              for (int q = 0; q < NDW; ++q) xw[q] = fr[s][q] & fm[q];
+            }
+            S2 xp[PK ? UPL : 1];
+            AccT acc[CPW];
 #pragma unroll
-            for (int u = 0; u < UPL; ++u) {
-              const uint32_t up = __builtin_amdgcn_perm(0u, xw[u / 2], (u & 1) ? 0x030C020Cu : 0x010C000Cu);
-              xp[u] = __builtin_bit_cast(S2, up) >> (S2)(8);
+            for (int cc = 0; cc < CPW; ++cc) acc[cc] = 0;
+            auto x_of = [&](int k) { return (int)(int16_t)(xw[k / 2] >> (16 * (k % 2))); };  // 16 bits
+            if constexpr (PK) {
 #pragma unroll
               for (int cc = 0; cc < CPW; ++cc)
-                acc[cc] = (AccT)__builtin_amdgcn_sdot2(xp[u], zp[cc][u], (int)acc[cc], false);
+#pragma unroll
+                for (int u = 0; u < UPL; ++u)
+                  acc[cc] = (AccT)__builtin_amdgcn_sdot4((int)xs[u], __builtin_bit_cast(int, sum[cc][u]), (int)acc[cc], false);
+            } else {  // two products of 16-bit factors fit 32 bits; their sums are added in 64
+#pragma unroll
+              for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+                for (int k = 0; k + 1 < CPL; k += 2)
+                  acc[cc] += (AccT)mad24(x_of(k), z[cc][k], mad24(x_of(k + 1), z[cc][k + 1], 0));
             }
-          } else {  // two products of 16-bit factors fit 32 bits; their sums are added in 64
 #pragma unroll
-            for (int cc = 0; cc < CPW; ++cc)
-#pragma unroll
-              for (int k = 0; k + 1 < CPL; k += 2)
-                acc[cc] += (AccT)mad24(x_of(k), z[cc][k], mad24(x_of(k + 1), z[cc][k + 1], 0));
-          }
-#pragma unroll
-          for (int cc = 0; cc < CPW; ++cc) {
-            const long long D = BITS == 8 ? (long long)wave_fold_i32((int)acc[cc]) : wave_fold_i64((long long)acc[cc]);
-            if (lane == 63) s_part[cls0 + cc] = D;
-          }
-          lds_barrier();
-          // while the sums travel: blocks of the next window, and what of the update needs no gamma
-#pragma unroll
-          for (int q = 0; q < kBlocks / 8; ++q) {
-            const int ub = s * (kBlocks / 8) + q;
-            draw_block(zrn[ub / UPL][ub % UPL], ub / UPL, ub % UPL, (uint32_t)(t0 >> 3) + 1u);
-          }
-          if constexpr (kBlocks % 8 != 0) {  // four blocks to eight steps: half of one each
-            const int ub = s / 2;
-            if (s % 2 == 0) {
-              half_block = philox_rounds<0, 5>(U4{(uint32_t)((cls0 + ub / UPL) * U + s0 + ub % UPL), (uint32_t)(t0 >> 3) + 1u,
-                                                  a.epoch, (uint32_t)kZround}, seed);
-            } else {
-              const U4 r = philox_rounds<5, 10>(half_block, seed);
-              zrn[ub / UPL][ub % UPL][0] = r.x; zrn[ub / UPL][ub % UPL][1] = r.y;
-              zrn[ub / UPL][ub % UPL][2] = r.z; zrn[ub / UPL][ub % UPL][3] = r.w;
+            for (int cc = 0; cc < CPW; ++cc) {
+              const long long D = BITS == 8 ? (long long)wave_fold_i32((int)acc[cc]) : wave_fold_i64((long long)acc[cc]);
+              if (lane == 63) s_part[cls0 + cc] = D;
             }
-          }
-          S2 crp[CPW][PK ? UPL : 1], zh[CPW][PK ? UPL : 1];
-          int hr[CPW][PK ? 1 : CPL];
+            lds_barrier();
+            // while the sums travel: blocks of the next window, and what of the update needs no gamma
 #pragma unroll
-          for (int cc = 0; cc < CPW; ++cc) {
-            if constexpr (PK) {
-#pragma unroll
-              for (int u = 0; u < UPL; ++u) {
-                const uint32_t rp = __builtin_amdgcn_perm(0u, zrw[cc][u][s >> 1], (s & 1) ? 0x0C030C02u : 0x0C010C00u);
-                crp[cc][u] = __builtin_bit_cast(S2, rp) + hlp[cc][u];  // rounding bits + hl
-                zh[cc][u] = hhp[cc][u] + zp[cc][u];
+            for (int q = 0; q < kBlocks / 8; ++q) {
+              const int ub = s * (kBlocks / 8) + q;
+              draw_block(zrn[ub / UPL][ub % UPL], ub / UPL, ub % UPL, (uint32_t)(t0 >> 3) + 1u);
+            }
+            if constexpr (kBlocks % 8 != 0) {  // four blocks to eight steps: half of one each
+              const int ub = s / 2;
+              if (s % 2 == 0) {
+                half_block = philox_rounds<0, 5>(U4{(uint32_t)((cls0 + ub / UPL) * U + s0 + ub % UPL), (uint32_t)(t0 >> 3) + 1u,
+                                                    a.epoch, (uint32_t)kZround}, seed);
+              } else {
+                const U4 r = philox_rounds<5, 10>(half_block, seed);
+                zrn[ub / UPL][ub % UPL][0] = r.x; zrn[ub / UPL][ub % UPL][1] = r.y;
+                zrn[ub / UPL][ub % UPL][2] = r.z; zrn[ub / UPL][ub % UPL][3] = r.w;
               }
-            } else {
-              // h~ = 2^16 hh + hl, 0 <= hl < 2^16: floor((-gamma x + r - h~) / 2^16) =
-              // floor((-gamma x + r - hl) / 2^16) - hh, and that numerator fits 32 bits
-#pragma unroll
-              for (int k = 0; k < CPL; ++k)
-                hr[cc][k] = (int)((zrw[cc][k][s >> 1] >> (16 * (s & 1))) & 0xFFFFu) - (hv[cc][k] & 0xFFFF);
             }
-          }
-          lds_barrier();
-          const int cl = use_reg ? __builtin_amdgcn_readfirstlane(s_cl[s & 1]) : 0;
-#pragma unroll
-          for (int cc = 0; cc < CPW; ++cc) {
-            const int ng = s_ng[s & 1][cls0 + cc];
+            S2 crp[CPW][PK ? UPL : 1];
             if constexpr (PK) {
-              if (cl == 0) {
-                // per half: floor((-gamma x + r + hl) / 256) + hh + z; |gamma x| <= 2^14 and
-                // r + hl < 512, so every intermediate fits 16 bits
-                const S2 ngp = S2{(short)ng, (short)ng};
-                S2 vu[UPL];
-                uint32_t hit = 0;
+#pragma unroll
+              for (int u = 0; u < UPL; ++u) xp[u] = __builtin_bit_cast(S2, xs[u]) >> (S2)(8);
+              unpack((s + 1) % kWin);  // the next row
+              request(s, __builtin_amdgcn_readlane(idxn, s));  // step t + 8
+            }
+            int hr[CPW][PK ? 1 : CPL];
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc) {
+              if constexpr (PK) {
+                uint32_t off[UPL], hit = 0;  // not 0 in the halves that saturated at the last step
 #pragma unroll
                 for (int u = 0; u < UPL; ++u) {
-                  const S2 v = ((xp[u] * ngp + crp[cc][u]) >> (S2)(8)) + zh[cc][u];
-                  const S2 zc = __builtin_elementwise_min(__builtin_elementwise_max(v, (S2)(QMIN)), (S2)(QMAX));
-                  hit |= __builtin_bit_cast(uint32_t, v) ^ __builtin_bit_cast(uint32_t, zc);
-                  vu[u] = v;
-                  zp[cc][u] = zc;
+                  const uint32_t v = __builtin_bit_cast(uint32_t, sum[cc][u]);
+                  off[u] = v ^ __builtin_bit_cast(uint32_t, zq[cc][u] + add[cc][u]);
+                  hit |= off[u];
+                  zq[cc][u] = __builtin_bit_cast(S2, v & 0xFF00FF00u);
+                  const uint32_t rp = __builtin_amdgcn_perm(0u, zrw[cc][u][s >> 1], (s & 1) ? 0x0C030C02u : 0x0C010C00u);
+                  crp[cc][u] = __builtin_bit_cast(S2, rp) - hp[cc][u];  // r - h~
                 }
                 if (__ballot(hit != 0) != 0) {
 #pragma unroll
-                  for (int u = 0; u < UPL; ++u) {
-                    const uint32_t df = __builtin_bit_cast(uint32_t, vu[u]) ^ __builtin_bit_cast(uint32_t, zp[cc][u]);
-                    n_zclamp += (unsigned long long)__builtin_popcountll(__ballot((df & 0xFFFFu) != 0)) +
-                                (unsigned long long)__builtin_popcountll(__ballot((df >> 16) != 0));
-                  }
+                  for (int u = 0; u < UPL; ++u) n_half += __builtin_elementwise_min(__builtin_bit_cast(W2, off[u]), ones);
                 }
-              } else {  // a step with an L2 draw: 32-bit arithmetic
+              } else {
+                // h~ = 2^16 hh + hl, 0 <= hl < 2^16: floor((-gamma x + r - h~) / 2^16) =
+                // floor((-gamma x + r - hl) / 2^16) - hh, and that numerator fits 32 bits
 #pragma unroll
-                for (int u = 0; u < UPL; ++u) {
-#pragma unroll
-                  for (int e = 0; e < 2; ++e) {
-                    const S2 xu = xp[u], zu2 = zp[cc][u], cu = crp[cc][u], hu = hhp[cc][u];
-                    const int zk = (int)zu2[e];
-                    const int zu = zk + (int)hu[e] + (mad24(ng, (int)xu[e], mad24(-cl, zk, (int)cu[e])) >> 8);
-                    const int zc = min(max(zu, QMIN), QMAX);
-                    n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
-                    zp[cc][u][e] = (short)zc;
-                  }
-                }
-              }
-            } else {
-#pragma unroll
-              for (int k = 0; k < CPL; ++k) {
-                int num = mad24(ng, x_of(k), hr[cc][k]);
-                if (cl != 0) num = mad24(-cl, z[cc][k], num);
-                const int zu = z[cc][k] + (num >> 16) - (hv[cc][k] >> 16);
-                const int zc = min(max(zu, QMIN), QMAX);
-                n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
-                z[cc][k] = zc;
+                for (int k = 0; k < CPL; ++k)
+                  hr[cc][k] = (int)((zrw[cc][k][s >> 1] >> (16 * (s & 1))) & 0xFFFFu) - (hv[cc][k] & 0xFFFF);
               }
             }
+            lds_barrier();
+            const int cl = use_reg ? __builtin_amdgcn_readfirstlane(s_cl[s & 1]) : 0;
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc) {
+              const int ng = s_ng[s & 1][cls0 + cc];
+              if constexpr (PK) {
+                if constexpr (WHOLE) {
+                  const S2 ngp = S2{(short)ng, (short)ng};
+#pragma unroll
+                  for (int u = 0; u < UPL; ++u) {
+                    add[cc][u] = xp[u] * ngp + crp[cc][u];
+                    sum[cc][u] = __builtin_elementwise_add_sat(zq[cc][u], add[cc][u]);
+                  }
+                }
+                if (!WHOLE || __builtin_expect_with_probability(cl != 0, 0, 1.0)) {
+                  // a step with an L2 draw, or an h~ past kWholeH: 32-bit arithmetic
+#pragma unroll
+                  for (int u = 0; u < UPL; ++u) {
+                    int zc[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                      const S2 xu = xp[u], zo = zq[cc][u], hu = hp[cc][u];
+                      const int zk = (int)zo[e] >> 8;
+                      int ad = 0;  // r - h~
+                      if constexpr (WHOLE) {
+                        const S2 cu = crp[cc][u];
+                        ad = (int)cu[e];
+                      } else {
+                        ad = (int)((zrw[cc][u][s >> 1] >> (16 * (s & 1) + 8 * e)) & 0xFFu) - (int)hu[e];
+                      }
+                      const int zu = zk + (mad24(ng, (int)xu[e], mad24(-cl, zk, ad)) >> 8);
+                      zc[e] = min(max(zu, QMIN), QMAX);
+                      n_zclamp += zu != zc[e] ? 1 : 0;
+                    }
+                    sum[cc][u] = S2{(short)(zc[0] * 256), (short)(zc[1] * 256)};
+                    add[cc][u] = sum[cc][u] - zq[cc][u];  // nothing left to count
+                  }
+                }
+              } else {
+#pragma unroll
+                for (int k = 0; k < CPL; ++k) {
+                  int num = mad24(ng, x_of(k), hr[cc][k]);
+                  if (cl != 0) num = mad24(-cl, z[cc][k], num);
+                  const int zu = z[cc][k] + (num >> 16) - (hv[cc][k] >> 16);
+                  const int zc = min(max(zu, QMIN), QMAX);
+                  n_zclamp += (unsigned long long)__builtin_popcountll(__ballot(zu != zc));
+                  z[cc][k] = zc;
+                }
+              }
+            }
+            if constexpr (!PK) request(s, __builtin_amdgcn_readlane(idxn, s));  // step t + 8
           }
-          request(s, __builtin_amdgcn_readlane(idxn, s));  // step t + 8
+          __builtin_amdgcn_sched_barrier(0);  // keep one step's temporaries from overlapping the next's
         }
-        __builtin_amdgcn_sched_barrier(0);  // keep one step's temporaries from overlapping the next's
+        if constexpr (PK) {
+          n_zclamp += (unsigned long long)n_half[0] + (unsigned long long)n_half[1];
+          n_half = (W2)(0);
+        }
       }
+    };
+    if constexpr (PK) {
+      unpack(0);
+      if (__ballot(!whole) == 0) run(std::true_type{});
+      else run(std::false_type{});
+#pragma unroll
+      for (int cc = 0; cc < CPW; ++cc)  // the last step's
+#pragma unroll
+        for (int u = 0; u < UPL; ++u) {
+          const uint32_t off = __builtin_bit_cast(uint32_t, sum[cc][u]) ^ __builtin_bit_cast(uint32_t, zq[cc][u] + add[cc][u]);
+          n_zclamp += ((off & 0xFFFFu) != 0 ? 1 : 0) + ((off >> 16) != 0 ? 1 : 0);
+        }
+    } else {
+      run(std::true_type{});
     }
 
     // ---- hand z out (on to a.z, and w~ <- w~ + delta_m z: split_finish)
@@ -524,12 +577,12 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
 #pragma unroll
       for (int k = 0; k < CPL; ++k) {
         int zk;
-        if constexpr (PK) zk = (int)zp[cc][k / 2][k % 2];
+        if constexpr (PK) zk = (int)sum[cc][k / 2][k % 2] >> 8;
         else zk = z[cc][k];
         if (j0 + k < d) zg[j0 + k] = (XT)zk;
       }
     }
-    if (lane == 0 && n_zclamp) atomicAdd(&cnt_out[0], n_zclamp);  // wave-wide count
+    if ((PK || lane == 0) && n_zclamp) atomicAdd(&cnt_out[0], n_zclamp);
   }
 }
 
@@ -560,12 +613,12 @@ struct SplitShape {
 // Four strips per lane; eight where four would need more workgroups than an XCD has CUs (32) and a wave has the
 // registers, or where beyond 24 the chains would no longer fit the device one workgroup to a CU.
 // us per step, 4 / 8 strips: 16 bits 6500 x 10 (26 workgroups with four strips) three chains 2.08 / 2.44, 8000 x 10 (32) 2.10 / 2.42,
-// 6500 x 5 1.70 / 1.86; 8 bits 15000 x 10 (30) 2.40 / 2.87; past 32 workgroups (40) 10000 x 10 16 bits 2.47 / 2.50, 20000 x 10
-// 8 bits 2.83 / 3.04, but 10000 x 3 16 bits 2.00 / 1.73 and 20000 x 4 8 bits 2.30 / 1.99.
+// 6500 x 5 1.70 / 1.86; 8 bits 15000 x 10 (30) 2.40 / 2.87; past 32 workgroups (40) 10000 x 8 16 bits 2.42 / 2.23, 10000 x 3
+// 2.00 / 1.73, 20000 x 4 8 bits 2.30 / 1.99.  At 8 bits eight strips spill from eight class waves on: 20000 x 10 2.69 / 3.02.
 SplitShape pick_shape(const halp_params& p) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
   const int P4 = (U + 255) / 256;
-  const bool four = p.K >= 12 || P4 <= 24 || (P4 <= 32 && (int64_t)p.R * P4 <= 256);
+  const bool four = p.K >= 12 || P4 <= 24 || ((P4 <= 32 || (p.b == 8 && p.K >= 8)) && (int64_t)p.R * P4 <= 256);
   const int upl = four ? 4 : 8;
   const int P = (U + 64 * upl - 1) / (64 * upl);
   return SplitShape{upl, P};

@@ -25,11 +25,29 @@ SOFTMAX_CASES = [
     (30, 6500, 10, 16, 1e-2, 1, 13, 0.05),    # four strips per lane with 26 workgroups
     (20, 6500, 4, 16, 0.0, 10, 9, 0.05),      # ... which ten chains would not fit one to a CU: eight strips
     (20, 8193, 3, 16, 1e-2, 1, 67, 0.05),     # past 32 workgroups
+    (20, 16500, 5, 8, 1e-2, 1, 21, 0.05),     # ... eight strips at 8 bits
+    (20, 16500, 9, 8, 0.0, 1, 11, 500.0),     # ... four
     (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than one workgroup to a CU holds
     (30, 2500, 12, 8, 1e-2, 70, 9, 0.05),     # more chains than are in flight at once
     (30, 1100, 4, 8, 0.0, 1, 1, 0.05),
     (30, 1100, 4, 8, 0.0, 1, 0, 0.05),
 ]
+
+
+@pytest.mark.parametrize("d,K,mu", [(1101, 3, 0.05), (2300, 13, 500.0), (1300, 16, 0.05)])
+def test_softmax_split_with_large_h(d, K, mu):
+    """8 bits, h~ over all of its 16 bits in some waves' coordinates: the sum of a step past 16 bits."""
+    loss, N, b, lam, T, seed = hp.LOSS_SOFTMAX, 40, 8, 1e-2, 70, 190
+    case = _inner_case(loss, N, d, K, 1, b, lam, 1, T, seed, mu=mu)
+    h = np.random.default_rng(seed).integers(-16000, 16001, size=case["h"].shape)
+    h[0].flat[d // 3] = -32768
+    h[0].flat[-1] = 32767
+    case["h"] = h
+    P = _run_inner(case, loss, K, 1, b, lam, 1, T, seed, 0, mu=mu)
+    P.h.inner_loop(3)
+    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], h[0], case["scales"][0], 3, T)
+    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
+    assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
 
 
 @pytest.mark.parametrize("N,d,K,b,lam,R,T,mu", SOFTMAX_CASES)
