@@ -20,10 +20,10 @@
 // again only after every workgroup of the chain has read it: its next addition follows this step's gamma, hence
 // everyone's share of the step after.
 //
-// What bounds it: latency.  At 4096 x 16 bits, B = 64, N = 50 000 a step takes 2.5 us: the exchange ~1.0, the scalars
-// ~0.35, the passes over 8 rows per wave, four barriers.  It grows with the size of the data (3.5 us at N = 1e6, 8 GB),
-// at 8 rows per step as at 64, whether the rows are requested two steps ahead or five, before the exchange or behind it:
-// the page translations of random rows, which the atomics and polls of the same CU queue behind.
+// What bounds it: latency.  At 4096 x 16 bits, B = 64 a step takes 2.5 us: the exchange ~1.0, the scalars
+// ~0.35, the passes over 8 rows per wave, four barriers.  Rows requested behind gamma instead of beside the exchange: 0.3 us
+// more; requested three to five steps ahead: the same.  All parts of a chain on one XCD: 4096 x 8 bits 0.13 us less, 4096 x
+// 16 bits at 8 GB of rows 0.7 us more, the others the same: not done.
 // The form before had four waves of 16 rows with a copy of z each, all draws and updates repeated in every wave.  us per
 // step, that form -> this one: 4096 x 16 bits B = 64 N = 200 000 4.40 -> 2.72, 4096 x 8 bits 3.73 -> 2.26, 1024 x 16
 // bits 4.33 -> 2.35, 512 x 8 bits B = 16 3.20 -> 1.5, 128 x 8 bits B = 4 3.65 -> 1.1; small steps of several slices, on one workgroup
