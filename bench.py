@@ -252,7 +252,7 @@ def c5_full_gradient(hp, inp, torch, reps=5):
                              steps_per_s=T / (s.ms_inner_loop * 1e-3),
                              us_per_step=s.ms_inner_loop / T * 1e3,
                              row_bytes_per_step=64 * d * 2,
-                             traffic=measured_traffic("inner_batch_kernel", "c5"),
+                             traffic=measured_traffic("inner_batch_cut_kernel", "c5"),
                              traffic_source=traffic_source("c5"),
                              exchange_timeouts=int(st["counters"][:, 3].sum().item()))
     h.close()
