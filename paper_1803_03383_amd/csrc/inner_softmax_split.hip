@@ -606,6 +606,8 @@ Kernel kernel_for(int K, int upl) {
   return cpw == 1 ? kernel_for<BITS, 8, 1>(waves) : nullptr;
 }
 
+constexpr int kMaxWorkgroups = 127;  // of a chain: its additions are counted in the top byte of an exchange word
+
 struct SplitShape {
   int upl, P;  // strips per lane, workgroups per chain
 };
@@ -615,17 +617,18 @@ struct SplitShape {
 // us per step, 4 / 8 strips: 16 bits 6500 x 10 (26 workgroups with four strips) three chains 2.08 / 2.44, 8000 x 10 (32) 2.10 / 2.42,
 // 6500 x 5 1.70 / 1.86; 8 bits 15000 x 10 (30) 2.40 / 2.87; past 32 workgroups (40) 10000 x 8 16 bits 2.42 / 2.23, 10000 x 3
 // 2.00 / 1.73, 20000 x 4 8 bits 2.30 / 1.99.  At 8 bits eight strips spill from eight class waves on: 20000 x 10 2.69 / 3.02.
-SplitShape pick_shape(const halp_params& p) {
+// Past kMaxWorkgroups four strips have no launch at all, so the row goes to eight while these fit.
+SplitShape pick_shape(const halp_params& p, int num_cus) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
   const int P4 = (U + 255) / 256;
-  const bool four = p.K >= 12 || P4 <= 24 || ((P4 <= 32 || (p.b == 8 && p.K >= 8)) && (int64_t)p.R * P4 <= 256);
+  const bool four = p.K >= 12 || P4 <= 24 ||
+                    ((P4 <= 32 || (p.b == 8 && p.K >= 8 && P4 <= kMaxWorkgroups)) && (int64_t)p.R * P4 <= num_cus);
   const int upl = four ? 4 : 8;
   const int P = (U + 64 * upl - 1) / (64 * upl);
   return SplitShape{upl, P};
 }
 
-Kernel kernel_for(const halp_params& p) {
-  const int upl = pick_shape(p).upl;
+Kernel kernel_for(const halp_params& p, int upl) {
   return p.b == 8 ? kernel_for<8>(p.K, upl) : kernel_for<16>(p.K, upl);
 }
 
@@ -647,10 +650,10 @@ size_t plan_inner_softmax_split(halp_handle& h) {
   if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return 0;
   if (inner_softmax_takes(p)) return 0;          // the register kernel has the shape
   if (p.b == 8 && p.d > 131071) return 0;        // int32 dot products stay exact
-  const int P = pick_shape(p).P;
-  if (P > 127 || P > h.num_cus) return 0;  // top byte of an exchange word; all workgroups of a chain resident
+  const auto [upl, P] = pick_shape(p, h.num_cus);
+  if (P > kMaxWorkgroups || P > h.num_cus) return 0;  // all workgroups of a chain resident
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(p)),
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(p, upl)),
                                                    block_threads(p.K), 0) != hipSuccess)
     (void)hipGetLastError();
   h.split_workgroups = std::max(per_cu, 1) * h.num_cus;
@@ -673,8 +676,8 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   const int rc = inner_softmax_split_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const int P = pick_shape(p).P;
-  const Kernel kernel = kernel_for(p);
+  const auto [upl, P] = pick_shape(p, h.num_cus);
+  const Kernel kernel = kernel_for(p, upl);
   unsigned long long* xbuf = words_at(h.batch_xbuf);
   const int* near = near_at(h.batch_xbuf);
   const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for

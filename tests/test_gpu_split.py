@@ -67,6 +67,36 @@ def test_softmax_split_bit_exact(N, d, K, b, lam, R, T, mu):
         assert cnt[0, 0] > 0
 
 
+WIDEST_CASES = [
+    # d, K, b, R: workgroups of a chain on both sides of the 127 that an exchange word counts
+    (65024, 9, 8, 1),     # 127 with four strips per lane
+    (65025, 9, 8, 1),     # 128 with four: eight strips
+    (65600, 8, 8, 2),
+    (130048, 8, 8, 1),    # 127 with eight
+    (65024, 3, 16, 1),
+]
+
+
+@pytest.mark.parametrize("d,K,b,R", WIDEST_CASES)
+def test_softmax_split_takes_the_widest_rows(d, K, b, R):
+    """Such chains are cut (with waits switched off they end without a result, which the general kernel's never do)
+    and give the oracle's bits."""
+    loss, N, T, seed = hp.LOSS_SOFTMAX, 6, 3, 70
+    case = _inner_case(loss, N, d, K, 1, b, 0.0, R, T, seed, mu=0.05)
+    P = _run_inner(case, loss, K, 1, b, 0.0, R, T, seed, 0, mu=0.05)
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, -1)
+    P.h.inner_loop(3)
+    assert np.all(P.get("scales")[:, 7] == -2.0)
+    P.put("scales", case["scales"])
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 1 << 20)
+    P.h.inner_loop(3)
+    for r in range(R):
+        out = ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r],
+                             case["scales"][r], 3, T)
+        assert np.array_equal(P.get("z")[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(P.get("counters")[r].astype(np.uint64), out["counters"])
+
+
 def test_softmax_split_algorithm_2():
     loss, N, d, K, b, T, seed = hp.LOSS_SOFTMAX, 50, 1200, 5, 8, 60, 9
     case = _lp_case(loss, N, d, K, 1, b, 1, seed, 0.02, 2.0 ** -7)
