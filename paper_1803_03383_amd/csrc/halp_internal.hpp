@@ -50,6 +50,7 @@ struct halp_handle {
   int64_t ahead_steps = 0;       // steps per segment
   int split_chains = 0;          // softmax chains cut across workgroups: chains per launch, 0: not that kernel's shape
   int split_workgroups = 0;      // ... and workgroups the device holds at once
+  bool split_lean = false;       // ... of the form with fewer registers
   // launches of chains cut across workgroups, listed under a lock (halp_api.hip)
   mutable hipEvent_t cut_event = nullptr;             // behind the last one
   mutable int cut_device = 0;

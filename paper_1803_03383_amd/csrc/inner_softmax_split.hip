@@ -101,7 +101,8 @@ __global__ void find_near(unsigned long long* xbuf, int* near) {
   near[blockIdx.x] = blockIdx.x < 8 ? at : 0;
 }
 
-template <int BITS, int UPL, int CPW, int WAVES>
+// LEAN: at most 128 registers, for chains that share a CU (plan_inner_softmax_split).
+template <int BITS, int UPL, int CPW, int WAVES, bool LEAN>
 __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs a, int P, int chain0, int nchains,
                                                                         int same_xcd, const int* near, unsigned long long* xbuf,
                                                                         int spin_limit) {
@@ -375,8 +376,15 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
       }
     }
     uint32_t zrw[CPW][UPL][4], zrn[CPW][UPL][4];  // this window's rounding words and the next one's
+    // LEAN: a strip's number is opaque at the place of use.  The products of a block's first two rounds do not change from
+    // window to window, and are carried through the loop otherwise, in 20 registers of the 154; made anew they cost 2 % of a step.
+    auto strip = [&](int cc, int u) {
+      uint32_t n = (uint32_t)((cls0 + cc) * U + s0 + u);
+      if constexpr (LEAN) asm volatile("" : "+v"(n));
+      return n;
+    };
     auto draw_block = [&](uint32_t (&dst)[4], int cc, int u, uint32_t win) {
-      const U4 r = zround_block(seed, a.epoch, (uint32_t)((cls0 + cc) * U + s0 + u), win);
+      const U4 r = zround_block(seed, a.epoch, strip(cc, u), win);
       dst[0] = r.x; dst[1] = r.y; dst[2] = r.z; dst[3] = r.w;
     };
 #pragma unroll
@@ -453,8 +461,8 @@ __global__ __launch_bounds__(64 * WAVES) void inner_softmax_split_kernel(InArgs 
             if constexpr (kBlocks % 8 != 0) {  // four blocks to eight steps: half of one each
               const int ub = s / 2;
               if (s % 2 == 0) {
-                half_block = philox_rounds<0, 5>(U4{(uint32_t)((cls0 + ub / UPL) * U + s0 + ub % UPL), (uint32_t)(t0 >> 3) + 1u,
-                                                    a.epoch, (uint32_t)kZround}, seed);
+                half_block = philox_rounds<0, 5>(U4{strip(ub / UPL, ub % UPL), (uint32_t)(t0 >> 3) + 1u, a.epoch,
+                                                    (uint32_t)kZround}, seed);
               } else {
                 const U4 r = philox_rounds<5, 10>(half_block, seed);
                 zrn[ub / UPL][ub % UPL][0] = r.x; zrn[ub / UPL][ub % UPL][1] = r.y;
@@ -593,9 +601,9 @@ int block_threads(int K) { return 64 * (K / classes_per_wave(K) + 1); }
 
 template <int BITS, int UPL, int CPW>
 Kernel kernel_for(int waves) {
-  if (waves <= 8) return inner_softmax_split_kernel<BITS, UPL, CPW, 8>;
-  if (waves <= 12) return inner_softmax_split_kernel<BITS, UPL, CPW, 12>;
-  if constexpr (UPL * CPW <= 4) return inner_softmax_split_kernel<BITS, UPL, CPW, 16>;
+  if (waves <= 8) return inner_softmax_split_kernel<BITS, UPL, CPW, 8, false>;
+  if (waves <= 12) return inner_softmax_split_kernel<BITS, UPL, CPW, 12, false>;
+  if constexpr (UPL * CPW <= 4) return inner_softmax_split_kernel<BITS, UPL, CPW, 16, false>;
   else return nullptr;
 }
 
@@ -628,7 +636,8 @@ SplitShape pick_shape(const halp_params& p, int num_cus) {
   return SplitShape{upl, P};
 }
 
-Kernel kernel_for(const halp_params& p, int upl) {
+Kernel kernel_for(const halp_params& p, int upl, bool lean) {
+  if (lean) return inner_softmax_split_kernel<8, 4, 1, 16, true>;
   return p.b == 8 ? kernel_for<8>(p.K, upl) : kernel_for<16>(p.K, upl);
 }
 
@@ -650,13 +659,30 @@ size_t plan_inner_softmax_split(halp_handle& h) {
   if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return 0;
   if (inner_softmax_takes(p)) return 0;          // the register kernel has the shape
   if (p.b == 8 && p.d > 131071) return 0;        // int32 dot products stay exact
-  const auto [upl, P] = pick_shape(p, h.num_cus);
+  const SplitShape shape = pick_shape(p, h.num_cus);
+  const int P = shape.P;
   if (P > kMaxWorkgroups || P > h.num_cus) return 0;  // all workgroups of a chain resident
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(p, upl)),
-                                                   block_threads(p.K), 0) != hipSuccess)
-    (void)hipGetLastError();
-  h.split_workgroups = std::max(per_cu, 1) * h.num_cus;
+  const int waves = block_threads(p.K) / 64;
+  auto per_cu = [&](bool lean, int threads) {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(kernel_for(p, shape.upl, lean)),
+                                                     threads, 0) != hipSuccess)
+      (void)hipGetLastError();
+    return std::max(n, 1);
+  };
+  auto launches = [&](int workgroups) { return (p.R + workgroups / P - 1) / (workgroups / P); };
+  h.split_workgroups = per_cu(false, 64 * waves) * h.num_cus;
+  // 8 bits, four strips, up to seven classes: the form with 128 registers, of which a CU holds more workgroups than of the one
+  // with 154, where it saves a launch.  us per step, 154 registers / 128: 256 chains of 1100 x 4 4.8 / 2.4, x 5 5.2 / 3.0,
+  // x 7 5.8 / 3.1, 128 of 3000 x 4 5.9 / 2.5; with as many launches either way 154 are 2 - 3 % faster.
+  if (p.b == 8 && shape.upl == 4 && waves <= 8) {
+    // What a CU holds whichever SIMDs their waves go to.  (Going by the occupancy of workgroups of 5 to 7 waves, two to a
+    // CU, 256 chains of 1100 x 5 took 5.3 in two launches: the second workgroup waited for the first.)
+    const int plain = std::max(per_cu(false, 256) / ((waves + 3) / 4), 1) * h.num_cus;
+    const int lean = per_cu(true, 64 * waves) * h.num_cus;
+    h.split_lean = launches(lean) < launches(plain);
+    h.split_workgroups = h.split_lean ? lean : plain;
+  }
   h.split_chains = std::min(p.R, h.split_workgroups / P);
   return 2 * kPage + split_words(h.split_chains) * sizeof(long long) + (size_t)h.split_chains * p.K * p.d * (p.b / 8);
 }
@@ -677,7 +703,7 @@ int launch_inner_softmax_split(const halp_handle& h, uint32_t epoch, hipStream_t
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
   const auto [upl, P] = pick_shape(p, h.num_cus);
-  const Kernel kernel = kernel_for(p, upl);
+  const Kernel kernel = kernel_for(p, upl, h.split_lean);
   unsigned long long* xbuf = words_at(h.batch_xbuf);
   const int* near = near_at(h.batch_xbuf);
   const bool report = h.spin_limit < 0;  // waits switched off: their outcome is what is asked for

@@ -29,25 +29,28 @@ SOFTMAX_CASES = [
     (20, 16500, 9, 8, 0.0, 1, 11, 500.0),     # ... four
     (30, 1100, 4, 8, 0.0, 70, 9, 0.05),       # more chains than one workgroup to a CU holds
     (30, 2500, 12, 8, 1e-2, 70, 9, 0.05),     # more chains than are in flight at once
+    (30, 1100, 7, 8, 1e-2, 100, 17, 500.0),   # more workgroups than CUs: the form with fewer registers, saturating
+    (20, 1101, 3, 8, 0.0, 300, 9, 0.05),      # ... four workgroups to a CU
     (30, 1100, 4, 8, 0.0, 1, 1, 0.05),
     (30, 1100, 4, 8, 0.0, 1, 0, 0.05),
 ]
 
 
-@pytest.mark.parametrize("d,K,mu", [(1101, 3, 0.05), (2300, 13, 500.0), (1300, 16, 0.05)])
-def test_softmax_split_with_large_h(d, K, mu):
+@pytest.mark.parametrize("d,K,R,mu", [(1101, 3, 1, 0.05), (2300, 13, 1, 500.0), (1300, 16, 1, 0.05), (1100, 6, 90, 0.05)])
+def test_softmax_split_with_large_h(d, K, R, mu):
     """8 bits, h~ over all of its 16 bits in some waves' coordinates: the sum of a step past 16 bits."""
     loss, N, b, lam, T, seed = hp.LOSS_SOFTMAX, 40, 8, 1e-2, 70, 190
-    case = _inner_case(loss, N, d, K, 1, b, lam, 1, T, seed, mu=mu)
+    case = _inner_case(loss, N, d, K, 1, b, lam, R, T, seed, mu=mu)
     h = np.random.default_rng(seed).integers(-16000, 16001, size=case["h"].shape)
     h[0].flat[d // 3] = -32768
     h[0].flat[-1] = 32767
     case["h"] = h
-    P = _run_inner(case, loss, K, 1, b, lam, 1, T, seed, 0, mu=mu)
+    P = _run_inner(case, loss, K, 1, b, lam, R, T, seed, 0, mu=mu)
     P.h.inner_loop(3)
-    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], h[0], case["scales"][0], 3, T)
-    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
-    assert np.array_equal(P.get("counters")[0].astype(np.uint64), out["counters"])
+    for r in {0, R - 1}:
+        out = ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], h[r], case["scales"][r], 3, T)
+        assert np.array_equal(P.get("z")[r].astype(np.int32), out["z"])
+        assert np.array_equal(P.get("counters")[r].astype(np.uint64), out["counters"])
 
 
 @pytest.mark.parametrize("N,d,K,b,lam,R,T,mu", SOFTMAX_CASES)
@@ -373,6 +376,7 @@ MANY_CHAINS = [
     # d, K, few, many: one chain to a CU at most, then four times as many
     (64, 2, 256, 1024),    # rows in registers
     (1100, 2, 64, 256),    # a chain cut across workgroups
+    (1100, 4, 64, 256),    # ... of five waves, which fewer registers let share a CU
 ]
 
 
