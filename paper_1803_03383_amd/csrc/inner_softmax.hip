@@ -521,8 +521,12 @@ int softmax_up(const halp_params& p) {
 
 // Records of 16-bit halves: eight strips per lane, more than one class wave to a SIMD and few chains, whose records'
 // traffic is nothing.  us per step, bytes / halves: 784 x 10 one chain 0.691 / 0.651, four 0.712 / 0.683, eight 0.756 / 0.750,
-// sixteen 0.814 / 0.837, 256 1.82 / 2.77; 784 x 8 0.626 / 0.607, 784 x 7 0.541 / 0.565; 784 x 16 0.940 / 0.913; 500 x 10 0.493 / 0.530.
-bool expanded(const halp_params& p) { return p.b == 8 && strips_per_lane(p) == 8 && p.K >= 8 && p.R <= 8; }
+// sixteen 0.814 / 0.837, 256 1.82 / 2.77; 784 x 8 0.626 / 0.607, 784 x 7 0.541 / 0.565; 500 x 10 0.493 / 0.530; 16 classes, 784 and
+// 1024 coordinates: one chain 0.939 / 0.898 and 0.945 / 0.908, four 0.948 / 0.941 and 0.954 / 0.960, eight 0.992 / 1.035 and
+// 1.055 / 1.122.
+bool expanded(const halp_params& p) {
+  return p.b == 8 && strips_per_lane(p) == 8 && p.K >= 8 && p.R <= (p.K > 15 ? 4 : 8);
+}
 
 Kernel kernel_for(const halp_params& p) {
   return p.b == 8 ? softmax_b8_kernel(p.K, strips_per_lane(p), expanded(p)) : kernel_for(p.K, strips_per_lane(p));

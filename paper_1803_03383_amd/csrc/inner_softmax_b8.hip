@@ -7,7 +7,7 @@
 // packed instructions per strip,
 //   n = -gamma x + (r - h~),   u = 256 z + n saturated to 16 bits,   256 z = u with its low byte cleared,
 // since floor over 2^8 is clearing the low byte and the box [-128, 127] is what saturation keeps.  It needs
-// |gamma x| + |r - h~| < 2^15: chains with an |h~| past kWholeH take a second loop, with h~ in two parts.
+// |gamma x| + |r - h~| < 2^15: class waves with an |h~| past kWholeH take a second loop, in 32-bit arithmetic.
 // What saturated is found by the sum without saturation and counted behind one branch.
 //
 // The row wave fetches the sampled rows and leaves them in LDS for all class waves, a coordinate in the high byte of
@@ -275,6 +275,21 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
     // rows cls0 .. cls0 + CPW - 1 of z
     const int cls0 = (wave - (wave > svc ? 1 : 0)) * CPW;
     auto row0_of = [&](int cc) { return ((int64_t)chain * K + cls0 + cc) * d; };
+    auto load_h = [&](int cc, int (&hk)[CPL]) {  // h~ of the lane's coordinates (past d the last one's)
+      const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(j0 + k, d - 1)];
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(hk[k]));
+    };
+    uint32_t large = 0;  // not 0 where a coordinate leaves no room for -gamma x + r - h~ in 16 bits
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) {
+      int hk[CPL];
+      load_h(cc, hk);
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) large |= hk[k] > kWholeH || hk[k] < -kWholeH ? 1u : 0u;
+    }
     // 256 z before the step; what was added to it; their saturated sum, whose high bytes are z and whose low bytes are
     // cleared later, beside the softmax
     S2 zq[CPW][UPL], add[CPW][UPL], sum[CPW][UPL];
@@ -313,18 +328,13 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
 
     auto run = [&](auto whole_tag) __attribute__((always_inline)) {
       constexpr bool WHOLE = decltype(whole_tag)::value;
-      // h~ of the lane's coordinates, where the records do not hold it
-      constexpr bool kH = !EXP || !WHOLE;
+      constexpr bool kH = !EXP || !WHOLE;  // where the records do not hold h~
       S2 hp[CPW][kH ? UPL : 1];
       if constexpr (kH) {
 #pragma unroll
         for (int cc = 0; cc < CPW; ++cc) {
-          const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
           int hk[CPL];
-#pragma unroll
-          for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(j0 + k, d - 1)];
-#pragma unroll
-          for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(hk[k]));
+          load_h(cc, hk);
 #pragma unroll
           for (int k = 0; k < CPL; ++k) hp[cc][k / 2][k % 2] = (short)(j0 + k < d ? hk[k] : 0);
         }
@@ -419,7 +429,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
                 for (int u = 0; u < UPL; ++u) n_half += __builtin_elementwise_min(__builtin_bit_cast(W2, off[u]), ones);
               }
             }
-            S2 crp[CPW][UPL];  // r - h~, or without WHOLE r alone
+            S2 crp[CPW][UPL];  // r - h~, or without WHOLE r alone (EXP: r - h~ modulo 2^16)
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc)
 #pragma unroll
@@ -460,7 +470,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
                 }
               }
               if (!WHOLE || __builtin_expect_with_probability(cl != 0, 0, 1.0)) {
-                // a step with an L2 draw, or h~ in two parts: 32-bit arithmetic
+                // a step with an L2 draw, or an h~ past kWholeH: 32-bit arithmetic
 #pragma unroll
                 for (int u = 0; u < UPL; ++u) {
                   int zc[2];
@@ -471,7 +481,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
                     int ad = EXP && !lane_ok ? 0 : (int)cu[e];
                     if constexpr (!WHOLE) {
                       const S2 hu = hp[cc][u];
-                      ad -= (int)hu[e];
+                      ad = (EXP ? ((int)cu[e] + (int)hu[e]) & 0xFF : ad) - (int)hu[e];
                     }
                     const int zu = zk + (mad24(ng[cc], (int)xu[e], mad24(-cl, zk, ad)) >> 8);
                     zc[e] = min(max(zu, QMIN), QMAX);
@@ -490,7 +500,8 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
       }
     };
     if (steps > 0) {
-      if (ah.whole[local] != 0) run(std::true_type{});
+      // (said to be the rule: otherwise the compiler spills registers of this loop for the other's.  1024 x 16 one chain 0.91, not 0.99)
+      if (__builtin_expect_with_probability(__ballot(large != 0) == 0, 1, 1.0)) run(std::true_type{});
       else run(std::false_type{});
     }
 
@@ -537,7 +548,6 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
   }
 }
 
-// K / CPW class waves, the service wave, the row wave (15 classes: no room for it, the service wave takes the rows)
 // K / CPW class waves, the service wave, the row wave (15 classes: no room for it, the service wave takes the rows)
 template <int UPL, bool EXP>
 SoftmaxKernel kernel_for(int K) {

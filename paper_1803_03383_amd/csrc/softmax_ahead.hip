@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void ahead_zbits(InArgs a, Ahead s, int bits, 
   for (int k = 0; k < 8; ++k) out[k * stride] = zround_field(r0, (uint32_t)k) | (zround_field(r1, (uint32_t)k) << 16);
 }
 
-// The same at 8 bits, expanded: strips of a class up to UP, those past the row 0.
+// The same at 8 bits, expanded: r - h~ modulo 2^16; strips of a class up to UP, those past the row 0.
 __global__ __launch_bounds__(256) void ahead_halves(InArgs a, Ahead s, int chain0) {
   const int local = blockIdx.z, chain = chain0 + local;
   const uint64_t seed = a.seed + (uint64_t)chain;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void ahead_halves(InArgs a, Ahead s, int chain
   const bool in = u < U;
   const U4 r = zround_block(seed, a.epoch, (uint32_t)(c * U + u), (uint32_t)(tw >> 3));
   int h0 = 0, h1 = 0;
-  if (in && s.whole[local] != 0) {
+  if (in) {
     const int16_t* h = reinterpret_cast<const int16_t*>(a.h) + ((int64_t)chain * a.K + c) * a.d + 2 * u;
     h0 = h[0];
     h1 = 2 * u + 1 < a.d ? h[1] : 0;
@@ -104,15 +104,6 @@ __global__ __launch_bounds__(256) void ahead_halves(InArgs a, Ahead s, int chain
   }
 }
 
-// one workgroup per chain
-__global__ __launch_bounds__(256) void ahead_whole(InArgs a, Ahead s, int chain0) {
-  const int16_t* h = reinterpret_cast<const int16_t*>(a.h) + (int64_t)(chain0 + blockIdx.x) * a.K * a.d;
-  int large = 0;
-  for (int j = threadIdx.x; j < a.K * a.d; j += 256) large |= (h[j] > kWholeH || h[j] < -kWholeH) ? 1 : 0;
-  const int any = __syncthreads_or(large);
-  if (threadIdx.x == 0) s.whole[blockIdx.x] = any ? 0 : 1;
-}
-
 size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 
 }  // namespace
@@ -120,7 +111,7 @@ size_t round256(size_t n) { return (n + 255) / 256 * 256; }
 size_t ahead_bytes(const halp_params& p, int chains, int64_t S, int UP, bool expanded) {
   const size_t n = (size_t)chains * (size_t)S;
   return round256(n * p.B * kAheadK * sizeof(AheadRec)) + round256(n * p.B * 4) + round256(n * 4) +
-         round256(n * p.K * (size_t)UP * (expanded ? 4 : 2)) + round256((size_t)chains * 4);
+         round256(n * p.K * (size_t)UP * (expanded ? 4 : 2));
 }
 
 int64_t ahead_steps(const halp_params& p, int chains, int UP, bool expanded, size_t bytes) {
@@ -154,8 +145,6 @@ Ahead ahead_layout(const halp_params& p, int chains, int64_t S, int UP, bool exp
   s.cl = reinterpret_cast<int32_t*>(q);
   q += round256(n * 4);
   s.zbits = UP > 0 ? reinterpret_cast<uint16_t*>(q) : nullptr;
-  q += round256(n * p.K * (size_t)UP * (expanded ? 4 : 2));
-  s.whole = reinterpret_cast<int32_t*>(q);
   s.expanded = expanded;
   s.S = S;
   s.UP = UP;
@@ -175,8 +164,6 @@ int launch_ahead(const InArgs& a, const Ahead& s, int bits, int chain0, int chai
   else if (a.K <= 4) scalars(std::integral_constant<int, 4>{});
   else if (a.K <= 8) scalars(std::integral_constant<int, 8>{});
   else scalars(std::integral_constant<int, 16>{});
-  const bool b8_rows = bits == 8 && a.B == 1 && s.UP > 0;  // the 8-bit loop of one row per step
-  if (b8_rows && s.t0 == 0) hipLaunchKernelGGL(ahead_whole, dim3(chains), dim3(256), 0, stream, a, s, chain0);
   if (s.expanded) {
     const dim3 g2((unsigned)((a.K * s.UP + 255) / 256), (unsigned)((steps + 7) / 8), chains);
     hipLaunchKernelGGL(ahead_halves, g2, dim3(256), 0, stream, a, s, chain0);

@@ -24,8 +24,7 @@ struct Ahead {
   int32_t* idx;     // [chain][step][rows]
   int32_t* cl;      // [chain][step] c_lambda
   uint16_t* zbits;  // [chain][step][class][UP] rounding bits of the strips, or null; expanded: two 16-bit halves
-                    // per strip (8 bits), r - h~ of its coordinates where whole is set, r where it is not
-  int32_t* whole;   // [chain] every |h~| is at most kWholeH
+                    // per strip (8 bits), r - h~ of its coordinates
   bool expanded;
   int64_t S;        // steps per segment, a multiple of 8 (buffer dimension)
   int UP;           // strips per class, padded

@@ -18,6 +18,7 @@ CASES = [
     (515, 13, 1e-2, 9, 40, 0.05),    # records of bytes
     (900, 7, 1e-2, 2, 90, 500.0),
     (513, 16, 0.0, 9, 30, 0.05),
+    (1024, 16, 1e-2, 5, 30, 500.0),  # ... records of bytes from five chains on
     (300, 15, 1e-2, 1, 70, 0.05),    # four strips per lane, no row wave
     (129, 4, 1e-2, 1, 70, 500.0),    # two
     (3, 2, 1e-2, 2, 70, 0.05),       # one strip per lane, the row in two lanes
@@ -25,18 +26,22 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("large", ["none", "last chain", "one class"])
 @pytest.mark.parametrize("d,K,lam,R,T,mu", CASES)
 def test_softmax_8bit_bit_exact(d, K, lam, R, T, mu, large):
     loss, N, b, seed = hp.LOSS_SOFTMAX, 50, 8, 330 + d + K
     case = _inner_case(loss, N, d, K, 1, b, lam, R, T, seed, mu=mu)
-    if large:  # the last chain's h~ over all of its 16 bits, the others' up to the largest that the records hold
+    if large != "none":  # the last chain's h~ over all of its 16 bits, or one class's; the others' up to what the records hold
         rng = np.random.default_rng(seed)
         for r in range(R):
-            top = 32768 if r == R - 1 else 16000
-            h = rng.integers(-top, top, size=case["h"][r].shape)
-            h.flat[0] = -top
-            h.flat[-1] = top - 1
+            rows = slice(0, K if large == "last chain" else 1)
+            h = rng.integers(-16000, 16000, size=case["h"][r].shape)
+            h.flat[0] = -16000
+            h.flat[-1] = 15999
+            if r == R - 1:
+                h[rows] = rng.integers(-32768, 32768, size=h[rows].shape)
+                h[rows].flat[0] = -32768
+                h[rows].flat[-1] = 32767
             case["h"][r] = h
     P = _run_inner(case, loss, K, 1, b, lam, R, T, seed, 2, mu=mu)
     P.h.inner_loop(3)
@@ -47,7 +52,7 @@ def test_softmax_8bit_bit_exact(d, K, lam, R, T, mu, large):
         assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
         assert np.array_equal(w[r], ref.apply_offset(prob, case["scales"][r], out["z"], case["w"][r]))
         assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
-    if mu > 100 or (large and d * K > 16):
+    if mu > 100 or (large != "none" and d * K > 16):
         assert cnt[R - 1, 0] > 0
 
 
