@@ -48,6 +48,7 @@ struct halp_handle {
   void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
   int ahead_chains = 0;          // chains per launch of those loops
   int64_t ahead_steps = 0;       // steps per segment
+  bool softmax_dense = false;    // ... 8 bits, one row per step: the form with a wave less
   int split_chains = 0;          // softmax chains cut across workgroups: chains per launch, 0: not that kernel's shape
   int split_workgroups = 0;      // ... and workgroups the device holds at once
   bool split_lean = false;       // ... of the form with fewer registers

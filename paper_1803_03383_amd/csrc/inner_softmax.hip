@@ -475,8 +475,8 @@ using Kernel = SoftmaxKernel;
 
 // one row of z per class wave up to 15 classes; 16 classes: two rows per wave, 8 + 1 waves
 int classes_per_wave(int K) { return K > 15 ? 2 : 1; }
-int block_threads(const halp_params& p) {
-  return p.b == 8 ? softmax_b8_threads(p.K) : 64 * (p.K / classes_per_wave(p.K) + 1);
+int block_threads(const halp_params& p, bool dense) {
+  return p.b == 8 ? softmax_b8_threads(p.K, dense) : 64 * (p.K / classes_per_wave(p.K) + 1);
 }
 
 template <int UPL>
@@ -528,8 +528,8 @@ bool expanded(const halp_params& p) {
   return p.b == 8 && strips_per_lane(p) == 8 && p.K >= 8 && p.R <= (p.K > 15 ? 4 : 8);
 }
 
-Kernel kernel_for(const halp_params& p) {
-  return p.b == 8 ? softmax_b8_kernel(p.K, strips_per_lane(p), expanded(p)) : kernel_for(p.K, strips_per_lane(p));
+Kernel kernel_for(const halp_params& p, bool dense) {
+  return p.b == 8 ? softmax_b8_kernel(p.K, strips_per_lane(p), expanded(p), dense) : kernel_for(p.K, strips_per_lane(p));
 }
 
 }  // namespace
@@ -545,12 +545,29 @@ bool inner_softmax_takes(const halp_params& p) {
 // 0.75, 1024 chains 2.24 and 0.87; 64 x 10, 512 chains 1.52 and 0.89; 300 x 5, 1024 chains 3.54 and 2.21
 // (two launches of 512: even shares, 768 and 256 took 2.97); 784 x 5, 1024 chains 4.0 either way.
 size_t plan_inner_softmax(halp_handle& h) {
-  if (!inner_softmax_takes(h.p)) return 0;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(h.p)),
-                                                   block_threads(h.p), 0) != hipSuccess)
-    (void)hipGetLastError();
-  return plan_ahead(h, softmax_up(h.p), std::max(per_cu, 1) * h.num_cus, expanded(h.p));
+  const halp_params& p = h.p;
+  if (!inner_softmax_takes(p)) return 0;
+  auto resident = [&](bool dense, int threads) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel_for(p, dense)),
+                                                     threads, 0) != hipSuccess)
+      (void)hipGetLastError();
+    return std::max(per_cu, 1);
+  };
+  int chains = resident(false, block_threads(p, false)) * h.num_cus;
+  // 8 bits: the form without a row wave where it saves a launch.  A row wave makes the step of few chains shorter (784 x 3 0.485
+  // instead of 0.502), but may be the fifth wave of a workgroup.  us per step, with a row wave / without: 64 x 3 2048 chains 1.84 /
+  // 1.39, 64 x 7 768 1.33 / 0.79, 64 x 11 1024 2.58 / 1.62, 300 x 3 2048 1.85 / 1.76, 784 x 3 768 1.98 / 1.34, 784 x 7 1024 4.38 / 3.45.
+  if (p.b == 8 && p.K < 15 && !expanded(p)) {
+    auto launches = [&](int n) { return (p.R + n - 1) / n; };
+    const int waves = block_threads(p, false) / 64;
+    // what a CU holds whichever SIMDs their waves go to
+    const int plain = std::max(resident(false, 256) / ((waves + 3) / 4), 1) * h.num_cus;
+    const int dense = resident(true, block_threads(p, true)) * h.num_cus;
+    h.softmax_dense = launches(dense) < launches(plain);
+    chains = h.softmax_dense ? dense : plain;
+  }
+  return plan_ahead(h, softmax_up(p), chains, expanded(p));
 }
 
 // softmax, one row per step, up to 15 classes one wave each plus the service wave, 16 classes
@@ -566,9 +583,9 @@ int launch_inner_softmax(const halp_handle& h, uint32_t epoch, hipStream_t st) {
   const int rc = inner_softmax_supported(h);
   if (rc != HALP_OK) return rc;
   const InArgs a = make_inner_args(h, epoch);
-  const Kernel kernel = kernel_for(p);
+  const Kernel kernel = kernel_for(p, h.softmax_dense);
   return for_segments(a, h, softmax_up(p), expanded(p), st, [&](const Ahead& s, int c0, int chains, int last) {
-    hipLaunchKernelGGL(kernel, dim3(chains), dim3(block_threads(p)), 0, st, a, s, c0, last);
+    hipLaunchKernelGGL(kernel, dim3(chains), dim3(block_threads(p, h.softmax_dense)), 0, st, a, s, c0, last);
     return hip_ok(hipGetLastError());
   });
 }

@@ -57,7 +57,10 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int UPL, int KT, int CPW, bool EXP, bool ROW>
+// Who fetches the rows: a wave of its own or the service wave, for all class waves, or every class wave for itself.
+enum class Rows { kOwn, kService, kEach };
+
+template <int UPL, int KT, int CPW, bool EXP, Rows ROWS>
 __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahead ah, int chain0, int last) {
   constexpr int CPL = 2 * UPL;
   constexpr int NDW = (UPL + 1) / 2;          // dwords of a lane's fragment of a row
@@ -90,7 +93,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
 
   __shared__ __attribute__((aligned(16))) int s_D[2][kKC];  // x_i^T z_c
   __shared__ int s_ng[2][kKC];                              // -gamma_c
-  __shared__ __attribute__((aligned(16))) uint32_t s_x[2][UPL * 64];  // the row in pairs, by step parity
+  __shared__ __attribute__((aligned(16))) uint32_t s_x[2][ROWS == Rows::kEach ? 1 : UPL * 64];  // the row in pairs, by step parity
   __shared__ int s_dumpD[64];  // partial folds of lanes 0..62 of every class wave (never read)
   __shared__ unsigned long long s_cnt[3];
   if (tid < 3) s_cnt[tid] = 0;
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
     // every class wave waits for this one at the step's second barrier: it goes first
     // wherever it shares a SIMD with class waves
     __builtin_amdgcn_s_setprio(3);
-    if constexpr (!ROW) start_rows();
+    if constexpr (ROWS == Rows::kService) start_rows();
     __syncthreads();
     if (steps > 0) {
       const AheadRec* __restrict__ rec = ah.rec + (int64_t)local * ah.S * kAheadK;
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
             n_reg += (lane < kWin && t0 + lane < steps && cln != 0) ? 1u : 0u;
             cln = clv[min(t0 + kWin + (lane & 7), tlast)];
           }
-          if constexpr (!ROW) window_rows(t0);
+          if constexpr (ROWS == Rows::kService) window_rows(t0);
 #pragma unroll
           for (int s = 0; s < kWin; ++s) {
             if (t0 + s < steps) {
@@ -243,10 +246,10 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
               lds_barrier();  // gamma is out; the class waves update z
               rr[s % kDep] = rec[(int64_t)min(t0 + s + kDep, tlast) * kAheadK + rc];
               draw(rr[(s + 1) % kDep]);
-              if constexpr (!ROW) next_row(s);
+              if constexpr (ROWS == Rows::kService) next_row(s);
             }
           }
-          if constexpr (!ROW) window_end();
+          if constexpr (ROWS == Rows::kService) window_end();
         }
       };
       if (soft_covers(dscale, aB, inv_s)) run(std::true_type{});
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
       if (n_gclamp) atomicAdd(&s_cnt[1], (unsigned long long)n_gclamp);
       if (n_reg) atomicAdd(&s_cnt[2], (unsigned long long)n_reg);
     }
-  } else if (ROW && wave == ncw + 1) {
+  } else if (ROWS == Rows::kOwn && wave == ncw + 1) {
     // ========================================================================= row wave
     start_rows();
     __syncthreads();
@@ -387,11 +390,25 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
           }
         }
       };
-      fetch_row(0);
+      auto unpack = [&](int par, int slot) {
+#pragma unroll
+        for (int u = 0; u < UPL; ++u) xs[par][u] = __builtin_amdgcn_perm(0u, fr[slot][u / 2], fs[u]);
+      };
+      if constexpr (ROWS == Rows::kEach) {
+        iv = idx[min(lane & 7, tlast)];
+        ivn = idx[min(kWin + (lane & 7), tlast)];
+#pragma unroll
+        for (int s = 0; s < kDep; ++s) request_row(s, __builtin_amdgcn_readlane(iv, s));
+        unpack(0, 0);
+        request_row(0, __builtin_amdgcn_readlane(iv, kDep));
+      } else {
+        fetch_row(0);
+      }
 
       for (int t0 = 0; t0 < steps; t0 += kWin) {
         const int clc = clw;
         if (use_reg) clw = clv[min(t0 + kWin + (lane & 7), tlast)];
+        if constexpr (ROWS == Rows::kEach) window_rows(t0);
 #pragma unroll
         for (int s = 0; s < kWin; ++s) {
           if (t0 + s < steps) {
@@ -444,7 +461,12 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
               }
             if constexpr (EXP) request_bits((s + kDep - 1) % kDep, min(t0 + s + kDep - 1, tlast));  // the last step's slot
             else request_bits(s % kDep, min(t0 + s + kDep, tlast));
-            fetch_row((s + 1) & 1);
+            if constexpr (ROWS == Rows::kEach) {
+              unpack((s + 1) & 1, (s + 1) % kDep);
+              request_row((s + 1) % kDep, __builtin_amdgcn_readlane(s + 1 + kDep < kWin ? iv : ivn, (s + 1 + kDep) % kWin));
+            } else {
+              fetch_row((s + 1) & 1);
+            }
             // all of it stays in front of the barrier
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc)
@@ -497,6 +519,7 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
         }
         n_lane += (uint32_t)n_half[0] + (uint32_t)n_half[1];
         n_half = (W2)(0);
+        if constexpr (ROWS == Rows::kEach) window_end();
       }
     };
     if (steps > 0) {
@@ -548,32 +571,36 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
   }
 }
 
-// K / CPW class waves, the service wave, the row wave (15 classes: no room for it, the service wave takes the rows)
+// K / CPW class waves, the service wave, the row wave.  dense: without the row wave, for workgroups that share a CU
+// (plan_inner_softmax): of up to two strips per lane every class wave fetches for itself, of more the service wave for all, as
+// it does for 15 classes, which leave no room for a row wave.
 template <int UPL, bool EXP>
-SoftmaxKernel kernel_for(int K) {
-  if (K > 15) return inner_softmax_b8_kernel<UPL, 12, 2, EXP, true>;  // two rows to a wave, 8 + 2 waves
-  if (K == 15) return inner_softmax_b8_kernel<UPL, 16, 1, EXP, false>;
+SoftmaxKernel kernel_for(int K, bool dense) {
+  if (K > 15) return inner_softmax_b8_kernel<UPL, 12, 2, EXP, Rows::kOwn>;  // two rows to a wave, 8 + 2 waves
+  if constexpr (!EXP)
+    if (dense) return inner_softmax_b8_kernel<UPL, 16, 1, EXP, (UPL <= 2 ? Rows::kEach : Rows::kService)>;
+  if (K == 15) return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kService>;
   if constexpr (UPL <= 4) {
-    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, true>;
+    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kOwn>;
   } else {  // fewer waves, more registers each
     if constexpr (!EXP)
-      if (K + 2 <= 8) return inner_softmax_b8_kernel<UPL, 8, 1, EXP, true>;
-    if (K + 2 <= 12) return inner_softmax_b8_kernel<UPL, 12, 1, EXP, true>;
-    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, true>;
+      if (K + 2 <= 8) return inner_softmax_b8_kernel<UPL, 8, 1, EXP, Rows::kOwn>;
+    if (K + 2 <= 12) return inner_softmax_b8_kernel<UPL, 12, 1, EXP, Rows::kOwn>;
+    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kOwn>;
   }
 }
 
 }  // namespace
 
-int softmax_b8_threads(int K) { return 64 * (K > 15 ? K / 2 + 2 : (K == 15 ? 16 : K + 2)); }
+int softmax_b8_threads(int K, bool dense) { return 64 * (K > 15 ? K / 2 + 2 : K + (dense || K == 15 ? 1 : 2)); }
 
-SoftmaxKernel softmax_b8_kernel(int K, int upl, bool expanded) {
-  if (expanded) return upl == 8 ? kernel_for<8, true>(K) : nullptr;
+SoftmaxKernel softmax_b8_kernel(int K, int upl, bool expanded, bool dense) {
+  if (expanded) return upl == 8 ? kernel_for<8, true>(K, false) : nullptr;
   switch (upl) {
-    case 1: return kernel_for<1, false>(K);
-    case 2: return kernel_for<2, false>(K);
-    case 4: return kernel_for<4, false>(K);
-    default: return kernel_for<8, false>(K);
+    case 1: return kernel_for<1, false>(K, dense);
+    case 2: return kernel_for<2, false>(K, dense);
+    case 4: return kernel_for<4, false>(K, dense);
+    default: return kernel_for<8, false>(K, dense);
   }
 }
 

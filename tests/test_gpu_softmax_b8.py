@@ -23,6 +23,10 @@ CASES = [
     (129, 4, 1e-2, 1, 70, 500.0),    # two
     (3, 2, 1e-2, 2, 70, 0.05),       # one strip per lane, the row in two lanes
     (1, 3, 0.0, 1, 9, 0.05),
+    (100, 3, 1e-2, 1030, 9, 0.05),   # without a row wave, for more chains to a CU: every class wave fetches for itself
+    (200, 7, 0.0, 600, 9, 500.0),    # ... two strips
+    (300, 4, 1e-2, 800, 9, 0.05),    # ... the service wave for all, four strips
+    (600, 3, 1e-2, 520, 17, 500.0),  # ... eight
 ]
 
 

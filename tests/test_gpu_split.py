@@ -375,6 +375,7 @@ def test_softmax_split_chains_whose_waits_run_out_are_run_again(N, d, K, b, lam,
 MANY_CHAINS = [
     # d, K, few, many: one chain to a CU at most, then four times as many
     (64, 2, 256, 1024),    # rows in registers
+    (64, 3, 512, 2048),    # ... with a row wave the workgroup would have five waves
     (1100, 2, 64, 256),    # a chain cut across workgroups
     (1100, 4, 64, 256),    # ... of five waves, which fewer registers let share a CU
 ]
