@@ -610,6 +610,13 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
       const int cpt = ndw * epd;
       P = (p.d + 64 * cpt - 1) / (64 * cpt);
       if (P > most_any || !inner_batch_cut_takes(p.B, ndw)) return false;
+      // Few small steps: a chain cut across workgroups takes three launches more, some 10 us.  us per epoch of 1, 3, 6 and 12
+      // steps, one workgroup (the chunked form) / cut: rows of 600 bytes, B = 2, 64 chains 12 / 21, 19 / 24, 30 / 29, 51 / 38; of 2048 bytes
+      // (8 bits, B = 2) 14 / 20, 23 / 24, 35 / 28, 61 / 37; (16 bits, 64 chains) 13 / 21, 21 / 24, 33 / 29, 57 / 40; of 4096, 64
+      // chains 16 / 23, 25 / 27, 39 / 33, 67 / 44; of 6000, 1 and 4 steps 21 / 21, 35 / 26; of 1200, 4 and 5 steps 23 / 26, 26 / 28.  Steps of 16 KB of rows: cut at once,
+      // 1024 x 16 bits B = 8 25 / 22, 31 / 27.
+      const int64_t least_steps = row_bytes <= 1536 ? 6 : (row_bytes <= 4096 ? 4 : 0);
+      if (P > 1 && p.T < least_steps && (int64_t)p.B * row_bytes < 16 * 1024) return false;
       return (int64_t)((p.d + cpt - 1) / cpt) * ndw * 4 <= row_bytes;  // fragments inside the row
     };
     // A chain cut across workgroups: the narrowest fragment of at least four coordinates whose

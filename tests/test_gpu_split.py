@@ -182,6 +182,33 @@ def test_minibatch_full_step_bit_exact(loss, N, d, B, b, lam, R, T, mu):
         assert cnt[0, 0] > 0
 
 
+SHORT_EPOCHS = [
+    # d, B, b, T, cut: chains are cut across workgroups from so many steps on, by bytes of a row, or at once
+    (700, 3, 8, 5, False), (700, 3, 8, 6, True),
+    (1500, 2, 16, 3, False), (1500, 2, 16, 4, True),
+    (3000, 2, 16, 1, True),
+    (1024, 16, 8, 1, True),
+]
+
+
+@pytest.mark.parametrize("d,B,b,T,cut", SHORT_EPOCHS)
+def test_minibatch_chains_of_short_epochs(d, B, b, T, cut):
+    """With waits switched off a chain that is cut ends without a result; otherwise both give the oracle's bits."""
+    loss, N, seed = hp.LOSS_LOGISTIC, 100, 90 + d
+    case = _inner_case(loss, N, d, 1, B, b, 0.0, 2, T, seed, mu=0.05)
+    P = _run_inner(case, loss, 1, B, b, 0.0, 2, T, seed, 0, mu=0.05)
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, -1)
+    P.h.inner_loop(3)
+    assert np.all(P.get("scales")[:, 7] == (-2.0 if cut else 0.0))
+    P.put("scales", case["scales"]); P.put("w", case["w"]); P.st["z"].zero_()
+    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 1 << 20)
+    P.h.inner_loop(3)
+    for r in range(2):
+        out = ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r], 3, T)
+        assert np.array_equal(P.get("z")[r].astype(np.int32), out["z"]), f"chain {r}"
+        assert np.array_equal(P.get("counters")[r].astype(np.uint64), out["counters"])
+
+
 @pytest.mark.parametrize("B", [16, 96])
 def test_minibatch_full_step_waits_that_run_out(B):
     """A limit of no polls at all: chains whose wait ran out are run by the general kernel, from the z they came
