@@ -6,7 +6,7 @@
 namespace halp {
 
 int launch_inner_reg_b8(const InArgs& a, int nw, int upl, int R, bool packed, hipStream_t s);
-int launch_inner_reg_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
+int launch_inner_reg_b16(const InArgs& a, int nw, int upl, int R, bool few, hipStream_t s);
 int launch_inner_reg_helped_b8(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_helped_b16(const InArgs& a, int nw, int upl, int R, hipStream_t s);
 int launch_inner_reg_lone_b8(const InArgs& a, int upl, int lanes, int R, bool pair, hipStream_t s);
@@ -173,7 +173,7 @@ int launch_inner_reg(const halp_handle& h, uint32_t epoch, hipStream_t s) {
   const bool many = (int64_t)p.R >= 8 * (int64_t)h.num_cus;
   const bool packed = p.b == 8 && sh.nw == 1 && (h.inner_packed == 1 || (h.inner_packed == 0 && many));
   return p.b == 8 ? launch_inner_reg_b8(a, sh.nw, sh.upl, p.R, packed, s)
-                  : launch_inner_reg_b16(a, sh.nw, sh.upl, p.R, s);
+                  : launch_inner_reg_b16(a, sh.nw, sh.upl, p.R, 2 * (int64_t)p.R <= h.num_cus, s);
 }
 
 }  // namespace halp

@@ -53,7 +53,7 @@ typedef short short2r __attribute__((ext_vector_type(2)));  // the two coordinat
 constexpr int kLossSquaredWithMargins = 3;
 
 // PKF: the 8-bit strips are updated as packed 16-bit halves (one wave per chain only).
-template <int BITS, int LOSS, int UPL, int NWT, bool PKF = false>
+template <int BITS, int LOSS, int UPL, int NWT, bool PKF = false, bool FREE = false>
 __global__ __launch_bounds__(64 * NWT) void inner_reg_kernel(InArgs a) {
   static_assert(!PKF || (BITS == 8 && NWT == 1), "the packed form is built for 8 bits, one wave per chain");
   constexpr bool COUNT = true;  // clamped coordinates are always counted
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(64 * NWT) void inner_reg_kernel(InArgs a) {
     }
     // From eight waves on registers are short: a step reads its own draws, beside its dot.  us per step of one chain, all
     // draws of a window at its start / by the step: 4096 x 16 bits squared 0.765 / 0.720, logistic 1.49 / 1.13 (312 and 150
-    // registers spilled); 8000 x 8 bits 1.13 / 0.94, logistic 1.91 / 1.42.
+    // registers spilled); 8000 x 8 bits 1.13 / 0.94, logistic 1.91 / 1.42.  FREE: the steps' instructions may overlap (see launch_one).
     constexpr bool kOwn = NWT >= 8;
     if (need_phi && !kOwn) {
       const float4 p0 = *reinterpret_cast<const float4*>(&s_phi[base]);
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(64 * NWT) void inner_reg_kernel(InArgs a) {
           }
           z[k] = zc;
         }
-        if constexpr (kOwn) __builtin_amdgcn_sched_barrier(0);  // a step's temporaries end with it
+        if constexpr (kOwn && !FREE) __builtin_amdgcn_sched_barrier(0);  // a step's temporaries end with it
       }
     }
     if (!PK) pack_z();
@@ -545,8 +545,18 @@ __global__ __launch_bounds__(64 * NWT) void inner_reg_kernel(InArgs a) {
 }
 
 template <int BITS, int UPL, int NWT>
-int launch_one(const InArgs& a, int R, bool packed, hipStream_t s) {
+int launch_one(const InArgs& a, int R, bool packed, hipStream_t s, bool few = false) {
   const dim3 grid(R), block(64 * NWT);
+  // Sixteen waves of eight strips at 16 bits, where two windows' rows and a window's rounding words alone take 96 of the 128
+  // registers: with L2 draws and few chains the order of steps is left to the compiler.  us per step of 8000 coordinates, draws
+  // of a window at its start / by the step, steps kept apart / not: one chain 3.83 / 4.33 / 3.42, 128 4.84 / 4.94 / 4.73, 256
+  // 7.2 / 5.95 / 6.5; without the L2 term 3.80 / 3.52 / 3.61, 256 6.7 / 4.5 / 6.3.
+  if constexpr (BITS == 16 && NWT == 16 && UPL == 8) {
+    if (few && a.loss == HALP_LOSS_SQUARED && !a.lp && a.lambda > 0) {
+      hipLaunchKernelGGL((inner_reg_kernel<BITS, HALP_LOSS_SQUARED, UPL, NWT, false, true>), grid, block, 0, s, a);
+      return hip_ok(hipGetLastError());
+    }
+  }
   if constexpr (BITS == 8 && NWT == 1) {
     if (packed) {
       if (a.loss == HALP_LOSS_SQUARED && a.lp)
@@ -569,9 +579,9 @@ int launch_one(const InArgs& a, int R, bool packed, hipStream_t s) {
 
 // every (strips per lane, waves per chain) pair the library launches
 template <int BITS>
-int launch_bits(const InArgs& a, int nw, int upl, int R, bool packed, hipStream_t s) {
+int launch_bits(const InArgs& a, int nw, int upl, int R, bool packed, hipStream_t s, bool few = false) {
 #define HALP_CASE(U_, W_) \
-  if (upl == U_ && nw == W_) return launch_one<BITS, U_, W_>(a, R, packed, s);
+  if (upl == U_ && nw == W_) return launch_one<BITS, U_, W_>(a, R, packed, s, few);
   HALP_CASE(1, 1) HALP_CASE(2, 1) HALP_CASE(4, 1) HALP_CASE(8, 1)
   HALP_CASE(1, 2) HALP_CASE(2, 2) HALP_CASE(4, 2) HALP_CASE(8, 2)
   HALP_CASE(1, 4) HALP_CASE(2, 4) HALP_CASE(4, 4) HALP_CASE(8, 4)
