@@ -689,7 +689,8 @@ size_t plan_inner_softmax_split(halp_handle& h) {
 
 int prepare_inner_softmax_split(const halp_handle& h) {
   hipLaunchKernelGGL(find_near, dim3(9), dim3(64), 0, 0, words_at(h.batch_xbuf), near_at(h.batch_xbuf));
-  return hip_ok(hipGetLastError());
+  const int rc = hip_ok(hipGetLastError());
+  return rc != HALP_OK ? rc : hip_ok(hipStreamSynchronize(0));  // a loop on any stream indexes with what it wrote
 }
 
 int inner_softmax_split_supported(const halp_handle& h) {
