@@ -232,8 +232,9 @@ typedef struct {
  * library's own device workspace on the current device, held until halp_destroy: partial sums of
  * the gradient pass; for softmax with B = 1 on rows up to 1024 coordinates, and for 8-bit minibatches
  * of softmax or of more than 64 rows, records made ahead of the steps (64 MB, 4 MB a chain where
- * that is more, at most 1 GB, less where T is small); for wider softmax rows with B = 1, and for
- * minibatches with K = 1, a second z of the chains in flight.                                                             */
+ * that is more, at most 1 GB, less where T is small; for K = 1 and rows that the full-step form takes
+ * only once HALP_OPT_INNER_PARTS asks for another form); for wider softmax rows with B = 1, and for
+ * minibatches with K = 1, a second z of the chains in flight.                          */
 int halp_create(halp_handle** out, const halp_params* p);
 int halp_destroy(halp_handle* h);
 

@@ -233,7 +233,8 @@ int halp_create(halp_handle** out, const halp_params* p) {
     if (prepare_inner_softmax_split(*h) != HALP_OK) { halp_destroy(h); return HALP_ERR_HIP; }
   }
   if (const size_t bytes = plan_inner_softmax_mfma(*h) + plan_inner_softmax(*h)) {  // one of them at most
-    if (hip_fail(hipMalloc(&h->ahead_ws, bytes), "hipMalloc(ahead_ws)")) { halp_destroy(h); return HALP_ERR_HIP; }
+    if (inner_batch_wide_takes_all(*h)) h->ahead_pending = bytes;
+    else if (hip_fail(hipMalloc(&h->ahead_ws, bytes), "hipMalloc(ahead_ws)")) { halp_destroy(h); return HALP_ERR_HIP; }
   }
   if (p->algorithm != HALP_ALG_SVRG && inner_generic_supported(*p) == HALP_OK &&
       inner_generic_needs_workspace(*p) &&
@@ -336,6 +337,10 @@ int halp_set_option(halp_handle* h, int32_t option, int64_t value) {
       return HALP_OK;
     case HALP_OPT_INNER_PARTS:
       if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8) return HALP_ERR_INVALID;
+      if (value != 0 && h->ahead_pending) {  // the kernel on the matrix cores takes over from the full-step form
+        if (hip_fail(hipMalloc(&h->ahead_ws, h->ahead_pending), "hipMalloc(ahead_ws)")) return HALP_ERR_HIP;
+        h->ahead_pending = 0;
+      }
       h->inner_parts = (int)value;
       return HALP_OK;
     case HALP_OPT_EXCHANGE_SPIN_LIMIT:

@@ -46,6 +46,7 @@ struct halp_handle {
   hipEvent_t ev[kTimedEpochs][4] = {};
   int64_t timed = 0;
   void* ahead_ws = nullptr;      // records made ahead of the softmax inner loops (softmax_ahead.hpp)
+  size_t ahead_pending = 0;      // ... bytes of them, where only HALP_OPT_INNER_PARTS brings them into use
   int ahead_chains = 0;          // chains per launch of those loops
   int64_t ahead_steps = 0;       // steps per segment
   bool softmax_dense = false;    // ... 8 bits, one row per step: the form with a wave less
@@ -111,6 +112,7 @@ int launch_inner_generic(const halp_handle& h, uint32_t epoch, const TraceBufs& 
 int inner_batch_supported(const halp_handle& h);
 int inner_batch_parts(const halp_handle& h);  // workgroups per chain, where supported
 bool inner_batch_wide_takes(const halp_handle& h);  // 65 .. 128 rows per step
+bool inner_batch_wide_takes_all(const halp_handle& h);  // ... and will for every binding
 size_t inner_batch_workspace(const halp_params& p);
 int launch_inner_batch(const halp_handle& h, uint32_t epoch, hipStream_t s);
 int inner_svrg_supported(const halp_handle& h);

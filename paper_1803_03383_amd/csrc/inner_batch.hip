@@ -647,6 +647,13 @@ bool inner_batch_wide_takes(const halp_handle& h) {
   return h.bound && h.buf.Xq && h.inner_parts == 0 && pick_launch(h, h.buf.ldxq * (p.b / 8)).fs;
 }
 
+// ... whatever is bound: at 8 bits a fragment is 8 bytes at most, which lies inside a row of any stride
+bool inner_batch_wide_takes_all(const halp_handle& h) {
+  const halp_params& p = h.p;
+  if (p.K != 1 || p.b != 8 || p.B <= kMaxB || p.algorithm == HALP_ALG_SVRG || p.d > 131071) return false;
+  return h.inner_parts == 0 && pick_launch(h, ((int64_t)p.d + 7) / 8 * 8).fs;
+}
+
 size_t inner_batch_workspace(const halp_params& p) {
   return std::max((size_t)p.R * 2 * kBatchSlots * 64 * sizeof(long long), inner_batch_cut_workspace(p));
 }

@@ -640,13 +640,14 @@ size_t plan_inner_softmax_mfma(halp_handle& h) {
 
 int inner_softmax_mfma_supported(const halp_handle& h) {
   if (!mfma_shape(h.p)) return HALP_ERR_UNSUPPORTED;
-  return (!h.bound || !h.buf.Xq || !h.ahead_ws) ? HALP_ERR_NOT_BOUND : HALP_OK;
+  return (!h.bound || !h.buf.Xq || (!h.ahead_ws && !h.ahead_pending)) ? HALP_ERR_NOT_BOUND : HALP_OK;
 }
 
 int launch_inner_softmax_mfma(const halp_handle& h, uint32_t epoch, hipStream_t st) {
   const halp_params& p = h.p;
   const int rc = inner_softmax_mfma_supported(h);
   if (rc != HALP_OK) return rc;
+  if (!h.ahead_ws) return HALP_ERR_UNSUPPORTED;  // the full-step form has the shape
   const InArgs a = make_inner_args(h, epoch);
   const bool many = p.B > mfma_rows(p.d, p.B), soft = p.loss == HALP_LOSS_SOFTMAX;
   const bool al16 = h.buf.ldxq % 16 == 0 && reinterpret_cast<uintptr_t>(h.buf.Xq) % 16 == 0;

@@ -209,6 +209,31 @@ def test_minibatch_chains_of_short_epochs(d, B, b, T, cut):
         assert np.array_equal(P.get("counters")[r].astype(np.uint64), out["counters"])
 
 
+def test_minibatch_full_step_needs_no_records():
+    """The 64 MB of records belong to the kernel on the matrix cores: a handle whose steps the full-step form takes has
+    them from the time on when an option asks for the other kernel, and both give the oracle's bits."""
+    loss, N, d, B, b, T, seed = hp.LOSS_SQUARED, 60, 300, 100, 8, 200, 53
+    case = _inner_case(loss, N, d, 1, B, b, 0.0, 1, T, seed, mu=0.05)
+    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], case["h"][0], case["scales"][0], 3, T)
+    P = _run_inner(case, loss, 1, B, b, 0.0, 1, T, seed, 2, mu=0.05)
+    P.h.inner_loop(3)  # the library is loaded
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = [torch.cuda.mem_get_info()[0]]
+    idle = hp.Halp(N, d, B=B, T=1 << 20)
+    free.append(torch.cuda.mem_get_info()[0])
+    idle.set_option(hp.OPT_INNER_PARTS, 1)
+    free.append(torch.cuda.mem_get_info()[0])
+    idle.close()
+    assert free[0] - free[1] < 16 << 20 and free[1] - free[2] > 48 << 20
+    for parts in (0, 1, 0):
+        P.h.set_option(hp.OPT_INNER_PARTS, parts)
+        P.put("z", np.zeros((1, 1, d))); P.put("w", case["w"])
+        P.h.inner_loop(3)
+        assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"]), parts
+        assert P.h.get_stats(0).inner_variant == 2
+
+
 @pytest.mark.parametrize("B", [16, 96])
 def test_minibatch_full_step_waits_that_run_out(B):
     """A limit of no polls at all: chains whose wait ran out are run by the general kernel, from the z they came
