@@ -234,23 +234,50 @@ def test_minibatch_full_step_needs_no_records():
         assert P.h.get_stats(0).inner_variant == 2
 
 
-@pytest.mark.parametrize("B", [16, 96])
-def test_minibatch_full_step_waits_that_run_out(B):
+@pytest.mark.parametrize("d,B,b,lam,R", [(2048, 16, 16, 0.0, 1), (2048, 96, 16, 0.0, 1), (1500, 12, 8, 1e-2, 3),
+                                         (2048, 40, 16, 1e-2, 2)])
+def test_minibatch_full_step_waits_that_run_out(d, B, b, lam, R):
     """A limit of no polls at all: chains whose wait ran out are run by the general kernel, from the z they came
-    with; waits switched off: the model stays as it was and the statistics call says so."""
-    loss, N, d, b, T, seed = hp.LOSS_LOGISTIC, 200, 2048, 16, 15, 31
-    case = _inner_case(loss, N, d, 1, B, b, 0.0, 1, T, seed, mu=0.05)
-    P = _run_inner(case, loss, 1, B, b, 0.0, 1, T, seed, 0, mu=0.05)
-    out = ref.inner_loop(case["mk"](0), case["Xq"][0], case["phi"][0], case["y"][0], case["h"][0], case["scales"][0], 3, T)
-    P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, 0)
-    P.h.inner_loop(3)
-    assert np.array_equal(P.get("z")[0].astype(np.int32), out["z"])
-    assert P.get("scales")[0, 7] == 0.0
-    P.put("w", case["w"]); P.st["z"].zero_()
+    with, which is not zero, and so are those of every replay of a captured launch; waits switched off: the model stays
+    as it was and the statistics call says so."""
+    loss, N, T, seed = hp.LOSS_LOGISTIC, 200, 15, 31
+    case = _inner_case(loss, N, d, 1, B, b, lam, R, T, seed, mu=0.05)
+    P = _run_inner(case, loss, 1, B, b, lam, R, T, seed, 0, mu=0.05)
+    z0 = np.random.default_rng(3).integers(-20, 21, size=(R, 1, d))
+    outs = [ref.inner_loop(case["mk"](r), case["Xq"][r], case["phi"][r], case["y"][r], case["h"][r], case["scales"][r],
+                           3, T, z0=z0[r]) for r in range(R)]
+
+    def check():
+        z, w, cnt = P.get("z"), P.get("w"), P.get("counters")
+        assert not np.any(P.get("scales")[:, 7])
+        for r, out in enumerate(outs):
+            assert np.array_equal(z[r].astype(np.int32), out["z"]), f"chain {r}"
+            assert np.array_equal(w[r], ref.apply_offset(case["mk"](r), case["scales"][r], out["z"], case["w"][r]))
+            assert np.array_equal(cnt[r].astype(np.uint64), out["counters"])
+
+    for limit in (0, 1 << 20):
+        P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, limit)
+        P.put("z", z0); P.put("w", case["w"])
+        P.h.inner_loop(3)
+        check()
+        P.h.get_stats(0)
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            P.h.inner_loop(3, stream=torch.cuda.current_stream().cuda_stream)
+        for _ in range(3):
+            P.put("z", z0); P.put("w", case["w"])
+            torch.cuda.synchronize()
+            graph.replay()
+            check()
+    P.put("z", z0); P.put("w", case["w"])
     P.h.set_option(hp.OPT_EXCHANGE_SPIN_LIMIT, -1)
     P.h.inner_loop(3)
-    assert np.array_equal(P.get("w"), case["w"].reshape(1, 1, d))
-    assert P.get("scales")[0, 7] == -2.0
+    assert np.array_equal(P.get("w"), case["w"].reshape(R, 1, d))
+    assert np.all(P.get("scales")[:, 7] == -2.0)
+    with pytest.raises(hp.HalpError) as e:
+        P.h.get_stats(0)
+    assert e.value.code == hp.ERR_EXCHANGE_TIMEOUT
 
 
 def test_softmax_and_minibatch_chains_cut_on_two_streams():
