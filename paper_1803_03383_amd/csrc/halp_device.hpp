@@ -76,6 +76,28 @@ __device__ __forceinline__ uint32_t zround_field(const U4& r, uint32_t t) {
   return (pick(r, f >> 1) >> (16u * (f & 1u))) & 0xFFFFu;
 }
 
+// ---- single instructions ---------------------------------------------------
+
+// a b + c of the low 24 bits of a and b, signed: one full-rate instruction
+__device__ __forceinline__ int mad24(int a, int b, int c) {
+  int r;
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// a lane's 32-bit offset, opaque at the place of use: the load then takes it beside its scalar
+// base, where a widened copy carried through the loop would cost registers and a 64-bit addition
+__device__ __forceinline__ uint32_t lane_off(uint32_t o) {
+  asm volatile("" : "+v"(o));
+  return o;
+}
+
+// workgroup barrier that waits for this wave's LDS traffic only: global loads stay in flight
+// across it (their registers are waited for where they are used)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---- wave-wide sums --------------------------------------------------------
 // Four DPP steps fold each row of 16 lanes (quad swaps, half-row mirror, row
 // mirror); two row broadcasts (lane 15 of rows 0 and 2 into rows 1 and 3, then

@@ -32,12 +32,6 @@ namespace {
 constexpr int kMaxB = 64;   // rows per step: one per service lane
 constexpr int kChunk = 8;   // rows in flight per worker thread
 
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 // NDW: dwords of a row per thread; KT: most waves of the workgroup.
 template <int BITS, int NDW, int KT>
 __global__ __launch_bounds__(64 * KT) void inner_batch_kernel(InArgs a, int nwk, int P, long long* xbuf,

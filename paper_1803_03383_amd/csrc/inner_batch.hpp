@@ -14,12 +14,6 @@ int launch_inner_batch_cut(const halp_handle& h, const InArgs& a, int ndw, int P
 
 typedef short short2v __attribute__((ext_vector_type(2)));
 
-// workgroup barrier that waits for this wave's LDS traffic only: global loads may stay in
-// flight across it (their registers are waited for where they are used)
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Sums of 8 values over the 64 lanes of a wave at once: v[m] is this lane's share of sum m.
 // Three exchange steps inside each group of 8 lanes (partner lane ^ 7, ^ 2, ^ 1) halve the
 // number of values a lane carries while doubling the lanes each covers, leaving lane l with

@@ -32,7 +32,6 @@ using innerreg::kBatch;
 using innerreg::kLossSquaredWithMargins;
 using innerreg::kWin;
 using innerreg::logistic_dl;
-using innerreg::mad24;
 
 constexpr int kRing = 4;    // records in flight per lane
 constexpr int kAhead = 16;  // steps between a row request and the record made from it

@@ -41,12 +41,6 @@ __device__ __forceinline__ double logistic_dl(double a, double y) {
 // a * b + c on the 24-bit multiplier; a and b must fit 24 bits (they are codes of at most
 // 16 bits here).  Written as the instruction because the compiler cannot see the range of
 // a value that comes out of a float conversion and would re-extend it first.
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 typedef short short2r __attribute__((ext_vector_type(2)));  // the two coordinates of an 8-bit strip
 
 // squared loss whose step needs the margin phi_i of w~ (LP-SVRG); a value apart from HALP_LOSS_*

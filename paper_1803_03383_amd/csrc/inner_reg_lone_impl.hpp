@@ -53,7 +53,6 @@ using innerreg::kBatch;
 using innerreg::kLossSquaredWithMargins;
 using innerreg::kWin;
 using innerreg::logistic_dl;
-using innerreg::mad24;
 using innerreg::short2r;
 
 typedef int int4r __attribute__((ext_vector_type(4)));

@@ -48,30 +48,12 @@ namespace {
 constexpr int kWin = 8;   // steps per unrolled window
 constexpr int kKC = 16;   // classes are padded to one DPP row
 
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 // half k & 1 of x (16 bits, signed) times the low half of b, plus c
 __device__ __forceinline__ int mad16(uint32_t x, int k, int b, int c) {
   int r;
   if (k & 1) asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(r) : "v"(x), "v"(b), "v"(c));
   else asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(b), "v"(c));
   return r;
-}
-
-// a lane's 32-bit offset, opaque at the place of use: the load then takes it beside its scalar
-// base, where a widened copy carried through the loop would cost registers and a 64-bit addition
-__device__ __forceinline__ uint32_t lane_off(uint32_t o) {
-  asm volatile("" : "+v"(o));
-  return o;
-}
-
-// workgroup barrier that waits for this wave's LDS traffic only: requests stay in flight across it
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 template <int UPL, int KT, int CPW>

@@ -39,24 +39,6 @@ namespace {
 constexpr int kWin = 8;   // steps per unrolled window
 constexpr int kKC = 16;   // classes are padded to one DPP row
 
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
-// a lane's 32-bit offset, opaque at the place of use: the load then takes it beside its scalar
-// base, where a widened copy carried through the loop would cost registers and a 64-bit addition
-__device__ __forceinline__ uint32_t lane_off(uint32_t o) {
-  asm volatile("" : "+v"(o));
-  return o;
-}
-
-// workgroup barrier that waits for this wave's LDS traffic only: requests stay in flight across it
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Who fetches the rows: a wave of its own or the service wave, for all class waves, or every class wave for itself.
 enum class Rows { kOwn, kService, kEach };
 

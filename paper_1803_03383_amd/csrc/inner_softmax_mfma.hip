@@ -62,16 +62,6 @@ constexpr int kNB = 2;       // blocks of 64 coordinates per owner
 constexpr int kGamStride = 80;   // bytes per class of the gamma buffer (64 + 16: bank spread)
 constexpr size_t kLdsCap = 158 * 1024;
 
-__device__ __forceinline__ void lds_barrier() {  // waits for this wave's LDS traffic only
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 // lane ^ 4 inside rows of 16: banks of four lanes trade places
 __device__ __forceinline__ double bank_swap_f64(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);

@@ -54,18 +54,6 @@ constexpr int kWin = 8;          // steps per Philox window
 constexpr int kIdxRing = 64;     // sample indices are drawn 64 steps at a time
 constexpr int kKC = 16;          // classes are padded to one DPP row
 
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
-// workgroup barrier that waits for this wave's LDS traffic only: row fragments and exchange
-// words stay in flight across it
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Exchange words: sixteen chains to eight pages of 4096 bytes, 256 bytes each in the page that lies nearest.
 constexpr int kPage = 4096, kPages = 8, kChainsPerPage = 16, kPageWords = kPage / 8;
 

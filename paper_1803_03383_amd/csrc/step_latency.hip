@@ -14,12 +14,6 @@
 namespace halp {
 namespace {
 
-__device__ __forceinline__ int mad24(int a, int b, int c) {
-  int r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void step_latency_kernel(int64_t steps, double dscale, double aB,
                                                               double inv_s, uint32_t* out) {
