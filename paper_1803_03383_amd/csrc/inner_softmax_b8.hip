@@ -264,30 +264,25 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
       const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
 #pragma unroll
       for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(j0 + k, d - 1)];
-#pragma unroll
-      for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(hk[k]));
     };
     uint32_t large = 0;  // not 0 where a coordinate leaves no room for -gamma x + r - h~ in 16 bits
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      int hk[CPL];
-      load_h(cc, hk);
-#pragma unroll
-      for (int k = 0; k < CPL; ++k) large |= hk[k] > kWholeH || hk[k] < -kWholeH ? 1u : 0u;
-    }
     // 256 z before the step; what was added to it; their saturated sum, whose high bytes are z and whose low bytes are
     // cleared later, beside the softmax
     S2 zq[CPW][UPL], add[CPW][UPL], sum[CPW][UPL];
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
       const int8_t* __restrict__ zg = reinterpret_cast<const int8_t*>(a.z) + row0_of(cc);
-      int zv[CPL];
+      int zv[CPL], hk[CPL];
+      load_h(cc, hk);
 #pragma unroll
       for (int k = 0; k < CPL; ++k) zv[k] = (int)zg[min(j0 + k, d - 1)];  // all loads in flight at once
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(zv[k]));
+      for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(zv[k]), "+v"(hk[k]));
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) sum[cc][k / 2][k % 2] = (short)(j0 + k < d ? zv[k] * 256 : 0);
+      for (int k = 0; k < CPL; ++k) {
+        large |= hk[k] > kWholeH || hk[k] < -kWholeH ? 1u : 0u;
+        sum[cc][k / 2][k % 2] = (short)(j0 + k < d ? zv[k] * 256 : 0);
+      }
 #pragma unroll
       for (int u = 0; u < UPL; ++u) {
         zq[cc][u] = sum[cc][u];
@@ -320,6 +315,8 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
         for (int cc = 0; cc < CPW; ++cc) {
           int hk[CPL];
           load_h(cc, hk);
+#pragma unroll
+          for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(hk[k]));
 #pragma unroll
           for (int k = 0; k < CPL; ++k) hp[cc][k / 2][k % 2] = (short)(j0 + k < d ? hk[k] : 0);
         }
