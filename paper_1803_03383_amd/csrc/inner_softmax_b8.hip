@@ -13,6 +13,7 @@
 // The row wave fetches the sampled rows and leaves them in LDS for all class waves, a coordinate in the high byte of
 // its half: as such the dot with 256 z is one v_dot4 per strip, whatever the low bytes hold.  With few chains (EXP) the
 // records hold r - h~ in 16-bit halves, with many, whose records' traffic counts, the bytes of r.
+// (15 classes leave no room for a row wave, and more of many chains share a CU without one: kernel_for.)
 //
 // One step:
 //   class waves   x_i^T z_c (v_dot4, DPP fold), one LDS word each                                            | barrier
@@ -22,10 +23,10 @@
 //
 // What bounds it: the dependent chain (~1000 cycles at 64 x 2), and from eight strips per lane and three class waves to a
 // SIMD on the class waves' instructions, of which only multiply-add, saturated addition, dot and fold are on the chain.
-// us per step of one chain, with the update in unsaturated halves (shift, two parts of h~, a test for clamps before
-// the dot) and a row unpacked by every class wave -> now: 784 x 10 0.78 -> 0.65, where the box binds (24 coordinates clamped per
-// step) 0.97 -> 0.69; 1024 x 15 0.93 -> 0.80; 784 x 5 0.62 -> 0.53; 300 x 4 0.484 -> 0.456; 64 x 2 0.420 -> 0.409; 256 chains of 784 x 10
-// 1.97 -> 1.82.
+// us per step of the loop, one chain, with the update in unsaturated halves (shift, two parts of h~, a test for clamps before
+// the dot) and a row unpacked by every class wave -> now: 784 x 10 0.74 -> 0.62; 1024 x 15 0.88 -> 0.75; 784 x 5 0.55 -> 0.50; 300 x 4
+// 0.451 -> 0.443; 64 x 2 0.413 -> 0.403; 256 chains of 784 x 10 1.36 -> 1.32; where the box binds (400 coordinates of 784 x 10
+// clamped per step) 1.05 -> 0.72.
 #include <algorithm>
 
 #include "halp_device.hpp"
@@ -502,8 +503,10 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
       }
     };
     if (steps > 0) {
-      // (said to be the rule: otherwise the compiler spills registers of this loop for the other's.  1024 x 16 one chain 0.91, not 0.99)
-      if (__builtin_expect_with_probability(__ballot(large != 0) == 0, 1, 1.0)) run(std::true_type{});
+      // Two rows to a wave: said to be the rule, otherwise the compiler spills registers of this loop for the other's (1024 x 16 one
+      // chain 0.91 instead of 0.99 us per step; one row to a wave, where the box binds, 0.723 instead of 0.718 at 784 x 10).
+      const bool fits = __ballot(large != 0) == 0;
+      if (CPW > 1 ? __builtin_expect_with_probability(fits, 1, 1.0) : fits) run(std::true_type{});
       else run(std::false_type{});
     }
 
