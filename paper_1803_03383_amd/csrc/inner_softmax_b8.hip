@@ -261,22 +261,19 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
     // rows cls0 .. cls0 + CPW - 1 of z
     const int cls0 = (wave - (wave > svc ? 1 : 0)) * CPW;
     auto row0_of = [&](int cc) { return ((int64_t)chain * K + cls0 + cc) * d; };
-    auto load_h = [&](int cc, int (&hk)[CPL]) {  // h~ of the lane's coordinates (past d the last one's)
-      const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
-#pragma unroll
-      for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(j0 + k, d - 1)];
-    };
-    uint32_t large = 0;  // not 0 where a coordinate leaves no room for -gamma x + r - h~ in 16 bits
     // 256 z before the step; what was added to it; their saturated sum, whose high bytes are z and whose low bytes are
     // cleared later, beside the softmax
     S2 zq[CPW][UPL], add[CPW][UPL], sum[CPW][UPL];
+    uint32_t large = 0;  // not 0 where a coordinate of the wave's rows leaves no room for -gamma x + r - h~ in 16 bits
 #pragma unroll
     for (int cc = 0; cc < CPW; ++cc) {
       const int8_t* __restrict__ zg = reinterpret_cast<const int8_t*>(a.z) + row0_of(cc);
-      int zv[CPL], hk[CPL];
-      load_h(cc, hk);
+      const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
+      int zv[CPL], hk[CPL];  // all loads in flight at once; those of h~ for the test alone: lane after lane
 #pragma unroll
-      for (int k = 0; k < CPL; ++k) zv[k] = (int)zg[min(j0 + k, d - 1)];  // all loads in flight at once
+      for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(64 * k + lane, d - 1)];
+#pragma unroll
+      for (int k = 0; k < CPL; ++k) zv[k] = (int)zg[min(j0 + k, d - 1)];
 #pragma unroll
       for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(zv[k]), "+v"(hk[k]));
 #pragma unroll
@@ -314,8 +311,10 @@ __global__ __launch_bounds__(64 * KT) void inner_softmax_b8_kernel(InArgs a, Ahe
       if constexpr (kH) {
 #pragma unroll
         for (int cc = 0; cc < CPW; ++cc) {
+          const int16_t* __restrict__ hg = reinterpret_cast<const int16_t*>(a.h) + row0_of(cc);
           int hk[CPL];
-          load_h(cc, hk);
+#pragma unroll
+          for (int k = 0; k < CPL; ++k) hk[k] = (int)hg[min(j0 + k, d - 1)];
 #pragma unroll
           for (int k = 0; k < CPL; ++k) asm volatile("" : "+v"(hk[k]));
 #pragma unroll
@@ -562,14 +561,9 @@ SoftmaxKernel kernel_for(int K, bool dense) {
   if constexpr (!EXP)
     if (dense) return inner_softmax_b8_kernel<UPL, 16, 1, EXP, (UPL <= 2 ? Rows::kEach : Rows::kService)>;
   if (K == 15) return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kService>;
-  if constexpr (UPL <= 4) {
-    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kOwn>;
-  } else {  // fewer waves, more registers each
-    if constexpr (!EXP)
-      if (K + 2 <= 8) return inner_softmax_b8_kernel<UPL, 8, 1, EXP, Rows::kOwn>;
+  if constexpr (EXP)  // fewer waves, more registers each (few chains: no matter that fewer share a CU)
     if (K + 2 <= 12) return inner_softmax_b8_kernel<UPL, 12, 1, EXP, Rows::kOwn>;
-    return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kOwn>;
-  }
+  return inner_softmax_b8_kernel<UPL, 16, 1, EXP, Rows::kOwn>;
 }
 
 }  // namespace
