@@ -253,8 +253,7 @@ def c5_full_gradient(hp, inp, torch, reps=5):
                              us_per_step=s.ms_inner_loop / T * 1e3,
                              row_bytes_per_step=64 * d * 2,
                              traffic=measured_traffic("inner_batch_cut_kernel", "c5"),
-                             traffic_source=traffic_source("c5"),
-                             exchange_timeouts=int(st["counters"][:, 3].sum().item()))
+                             traffic_source=traffic_source("c5"))
     h.close()
     del X, y, st, Xq
     torch.cuda.empty_cache()

@@ -120,12 +120,13 @@ typedef struct {
   void* h;            /* out  [R][K][d] int16 / int32 h~ in (delta_i, 2b)               */
   double* scales;     /* out  [R][8]: delta_m, delta_i, delta_s, ||g~||, 1/delta_i, 1/delta_s,
                          f(w~), status (0 ok, 1 gradient exactly zero, -1 not finite, -2 a wait
-                         between the workgroups of a minibatch chain ran out: w~ was not
-                         updated)                                                       */
+                         between the workgroups of a chain left it without a result, see
+                         HALP_OPT_EXCHANGE_SPIN_LIMIT: w~ was not updated)               */
   uint64_t* counters; /* out  [R][4]: coordinates of z clamped by the last inner loop, gammas
                          clamped, steps with a non-zero L2 draw, 1 if a cross-workgroup wait
-                         of a minibatch chain ran out (z is then invalid, w~ is left
-                         unchanged and the status becomes -2)                              */
+                         left the chain without a result (z is then invalid, w~ is left
+                         unchanged and the status becomes -2); 0 for a chain that was run
+                         again after such a wait                                         */
 } halp_buffers;
 
 typedef struct {
@@ -176,10 +177,12 @@ typedef struct {
 #define HALP_OPT_INNER_PARTS 7   /* workgroups per chain of the minibatch (B > 1) register inner
                                     loop.  0 (default): the library's choice, the full-step form
                                     (the row cut across up to 16 workgroups, rows of a step held in
-                                    registers, B up to 128) where it applies; 1, 2, 4, 8: the chunked form with
+                                    registers, B up to 128) where it applies (epochs of a few small
+                                    steps: one workgroup of the chunked form); 1, 2, 4, 8: the
+                                    chunked form with
                                     that many workgroups.  The workgroups of a chain meet once per
-                                    step in device memory and wait for each other (bounded; a wait
-                                    that runs out is reported in counters[3]), so more than one
+                                    step in device memory and wait for each other (bounded, see
+                                    HALP_OPT_EXCHANGE_SPIN_LIMIT), so more than one
                                     is only taken when R times the count is at most the number of
                                     CUs, and launches of two handles in that mode should not
                                     overlap.  Results do not depend on it                       */

@@ -615,10 +615,10 @@ static BtLaunch pick_launch(const halp_handle& h, int64_t row_bytes) {
     };
     // A chain cut across workgroups: the narrowest fragment of at least four coordinates whose
     // slices are few enough -- more, narrower slices shorten both passes over the rows of a step.  us per step, 4096 x 16
-    // bits, B = 64, N = 100 000: 3.4 with 8 slices, 2.9 with 16; 4096 x 8 bits, N = 400 000: 2.65 and 2.40.
+    // bits, B = 64, N = 100 000: 3.14 with 8 slices, 2.51 with 16; 4096 x 8 bits, N = 400 000: 2.26 and 2.00.
     // One workgroup where the widest fragment lets it hold the row, for the smaller steps (no exchange).  us per step, one
-    // workgroup and two: 8 bits d = 300 B = 4 1.14 / 1.58, 500 B = 64 1.81 / 1.86, 500 B = 128 2.77 / 2.50;
-    // 16 bits 500 B = 4 1.49 / 1.81, 300 B = 32 1.82 / 2.00, 500 B = 64 2.57 / 2.33.
+    // workgroup and two: 8 bits d = 300 B = 4 1.11 / 1.59, 500 B = 64 1.75 / 1.74, 500 B = 128 2.72 / 2.38;
+    // 16 bits 500 B = 4 1.42 / 1.69, 300 B = 32 1.76 / 2.00, 500 B = 64 2.52 / 2.23.
     int P = 1;
     const bool alone = p.B <= (p.b == 8 ? 64 : 32) && fits(ndw_max, P) && P == 1;
     for (int ndw = p.b == 16 ? 2 : 1; ndw <= ndw_max && !alone; ndw *= 2)

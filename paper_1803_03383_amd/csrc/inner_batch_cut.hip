@@ -25,10 +25,11 @@
 // more; requested three to five steps ahead: the same.  All parts of a chain on one XCD: 4096 x 8 bits 0.13 us less, 4096 x
 // 16 bits at 8 GB of rows 0.7 us more, the others the same: not done.
 // The form before had four waves of 16 rows with a copy of z each, all draws and updates repeated in every wave.  us per
-// step, that form -> this one: 4096 x 16 bits B = 64 N = 200 000 4.40 -> 2.72, 4096 x 8 bits 3.73 -> 2.26, 1024 x 16
-// bits 4.33 -> 2.35, 512 x 8 bits B = 16 3.20 -> 1.5, 128 x 8 bits B = 4 3.65 -> 1.1; small steps of several slices, on one workgroup
-// before, 1024 x 8 bits B = 4 3.78 -> 1.53; 128 rows, on the kernels of the matrix cores and of class waves or on the general
-// kernel before: 1000 x 8 bits 6.9 -> 2.9, 1024 x 16 bits 95 -> 3.8, 4096 x 8 bits 210 -> 3.4.
+// step of the loop (without the gradient pass; logistic), that form -> this one: 4096 x 16 bits B = 64 N = 10^6 4.55 -> 2.60, N = 200 000
+// 4.20 -> 2.53, 4096 x 8 bits 3.54 -> 1.99, 1024 x 16 bits 4.25 -> 2.18, 512 x 8 bits B = 16 3.14 -> 1.36, 128 x 8 bits B = 4 3.57
+// -> 0.98; small steps of several slices, on one workgroup before, 1024 x 8 bits B = 4 3.70 -> 1.36; 128 rows, on the kernels of the
+// matrix cores and of class waves or on the general kernel before: 1000 x 8 bits 6.5 -> 2.4, 1024 x 16 bits 95 -> 3.2, 4096 x
+// 8 bits 207 -> 2.6.
 #include <algorithm>
 
 #include "inner_batch.hpp"

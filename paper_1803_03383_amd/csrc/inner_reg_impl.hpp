@@ -262,8 +262,8 @@ __global__ __launch_bounds__(64 * NWT) void inner_reg_kernel(InArgs a) {
       dl08[s] = 0.0;
     }
     // From eight waves on registers are short: a step reads its own draws, beside its dot.  us per step of one chain, all
-    // draws of a window at its start / by the step: 4096 x 16 bits squared 0.765 / 0.720, logistic 1.49 / 1.13 (312 and 150
-    // registers spilled); 8000 x 8 bits 1.13 / 0.94, logistic 1.91 / 1.42.  FREE: the steps' instructions may overlap (see launch_one).
+    // draws of a window at its start / by the step: 4096 x 16 bits squared 0.765 / 0.720, logistic 1.48 / 1.12 (312 and 150
+    // registers spilled); 8000 x 8 bits 1.11 / 0.92, logistic 1.90 / 1.41.  FREE: the steps' instructions may overlap (see launch_one).
     constexpr bool kOwn = NWT >= 8;
     if (need_phi && !kOwn) {
       const float4 p0 = *reinterpret_cast<const float4*>(&s_phi[base]);

@@ -32,9 +32,9 @@
 // So the class waves' instructions are kept few: z biased so that one test of the wave finds a clamp, requests
 // with a scalar base, the rare paths (a clamp, an L2 draw) behind one branch each.
 //
-// Measured, us per step of one chain, before (class waves drawing their own blocks) and now:
-// 784 x 10 2.73 -> 1.37; 1000 x 15 29.8 -> 3.0; 64 x 2 0.75 -> 0.48.  With 256 chains, where making the records
-// takes the whole chip's issue slots too: 784 x 10 3.2 -> 2.35.
+// Measured, us per step of one chain, before (class waves drawing their own blocks) and now (the loop and its records):
+// 784 x 10 2.73 -> 1.29; 1000 x 15 29.8 -> 2.9; 64 x 2 0.75 -> 0.47.  With 256 chains, where making the records
+// takes the whole chip's issue slots too: 784 x 10 3.2 -> 2.26.
 #include <algorithm>
 
 #include "halp_device.hpp"
@@ -502,10 +502,9 @@ int softmax_up(const halp_params& p) {
 }
 
 // Records of 16-bit halves: eight strips per lane, more than one class wave to a SIMD and few chains, whose records'
-// traffic is nothing.  us per step, bytes / halves: 784 x 10 one chain 0.691 / 0.651, four 0.712 / 0.683, eight 0.756 / 0.750,
-// sixteen 0.814 / 0.837, 256 1.82 / 2.77; 784 x 8 0.626 / 0.607, 784 x 7 0.541 / 0.565; 500 x 10 0.493 / 0.530; 16 classes, 784 and
-// 1024 coordinates: one chain 0.939 / 0.898 and 0.945 / 0.908, four 0.948 / 0.941 and 0.954 / 0.960, eight 0.992 / 1.035 and
-// 1.055 / 1.122.
+// traffic is nothing.  us per step, bytes / halves: 784 x 10 one chain 0.670 / 0.625, four 0.671 / 0.644, eight 0.698 / 0.695,
+// sixteen 0.738 / 0.766, 256 1.31 / 2.18; 784 x 8 0.596 / 0.580, 784 x 7 0.516 / 0.545; 16 classes, 784 and 1024 coordinates: one chain
+// 0.917 / 0.880 and 0.923 / 0.886, four 0.938 / 0.935 and 0.946 / 0.957, eight 0.994 / 1.017 and 1.032 / 1.107.
 bool expanded(const halp_params& p) {
   return p.b == 8 && strips_per_lane(p) == 8 && p.K >= 8 && p.R <= (p.K > 15 ? 4 : 8);
 }
@@ -523,9 +522,9 @@ bool inner_softmax_takes(const halp_params& p) {
 
 // A launch takes as many chains as the device holds at once: a chain's step is mostly waiting, so
 // several of them to a CU take little longer than one, and launches run one after the other.  us per
-// step of all chains at 8 bits, 256 chains per launch and as many as fit: 64 x 2, 512 chains 1.13 and
-// 0.75, 1024 chains 2.24 and 0.87; 64 x 10, 512 chains 1.52 and 0.89; 300 x 5, 1024 chains 3.54 and 2.21
-// (two launches of 512: even shares, 768 and 256 took 2.97); 784 x 5, 1024 chains 4.0 either way.
+// step of all chains at 8 bits, 256 chains per launch and as many as fit: 64 x 2, 512 chains 0.98 and
+// 0.57, 1024 chains 1.94 and 0.64; 64 x 10, 512 chains 1.13 and 0.69; 300 x 5, 1024 chains 2.33 and 1.81
+// (two launches of 512: even shares, 768 and 256 took a third more); 784 x 5, 1024 chains 3.75 and 2.72.
 size_t plan_inner_softmax(halp_handle& h) {
   const halp_params& p = h.p;
   if (!inner_softmax_takes(p)) return 0;

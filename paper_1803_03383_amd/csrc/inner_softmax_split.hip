@@ -35,11 +35,11 @@
 // the parts on one XCD).  The atomics, and the first read behind them, are served by the memory
 // a page of 4096 bytes is homed in: 0.23 us for the nearest, 0.36 for the farthest of the eight that
 // alternate, so a chain's words lie in the page nearest to its XCD, which halp_create finds by timing
-// (find_near): 1100 x 5 three chains 1.66 -> 1.38 us per step.  us per step, one atomic per class wave -> now:
-// 10000 x 10 8 bits one chain 3.06 -> 2.00, five 3.52 -> 2.32, 16 bits five 3.86 -> 2.83; 4000 x 5 five chains 2.06 -> 1.51;
-// 2000 x 10 1.89 -> 1.54; 1100 x 2 1.27 -> 1.20.  With the update in saturated halves at 8 bits, where it was done in
-// unsaturated ones, clamps counted by ballots before the next dot: one chain of 10000 x 10 1.99 -> 1.82, five 2.31 -> 2.15, 2000 x 10
-// 1.54 -> 1.37, 1100 x 2 1.20 -> 1.03, 256 chains of 1100 x 10 8.9 -> 8.2; where nothing is clamped 2-8 %.
+// (find_near): 1100 x 5 three chains 1.36 -> 1.12 us per step.  us per step of the loop (without the gradient pass; 2000 rows),
+// one atomic per class wave -> the parts added by one wave, words in the nearest page -> at 8 bits the update in saturated
+// halves too, clamps counted beside the exchange: 10000 x 10 8 bits one chain 2.73 -> 1.62 -> 1.44, five 2.76 -> 1.62 -> 1.45; 16
+// bits five 3.15 -> 2.11; 4000 x 5 five chains 1.84 -> 1.28 -> 1.14; 2000 x 10 1.79 -> 1.45 -> 1.27; 1100 x 2 1.25 -> 1.16 ->
+// 0.99; 256 chains of 1100 x 10 7.8 -> 7.0 -> 6.4.
 #include <algorithm>
 
 #include "halp_device.hpp"
@@ -610,9 +610,10 @@ struct SplitShape {
 
 // Four strips per lane; eight where four would need more workgroups than an XCD has CUs (32) and a wave has the
 // registers, or where beyond 24 the chains would no longer fit the device one workgroup to a CU.
-// us per step, 4 / 8 strips: 16 bits 6500 x 10 (26 workgroups with four strips) three chains 2.08 / 2.44, 8000 x 10 (32) 2.10 / 2.42,
-// 6500 x 5 1.70 / 1.86; 8 bits 15000 x 10 (30) 2.40 / 2.87; past 32 workgroups (40) 10000 x 8 16 bits 2.42 / 2.23, 10000 x 3
-// 2.00 / 1.73, 20000 x 4 8 bits 2.30 / 1.99.  At 8 bits eight strips spill from eight class waves on: 20000 x 10 2.69 / 3.02.
+// us per step of the loop, 4 / 8 strips: 16 bits 6500 x 10 (26 workgroups with four strips) three chains 1.71 / 1.99, 8000 x 10 (32)
+// 1.80 / 2.04, 6500 x 5 1.53 / 1.64; 8 bits 15000 x 10 (30) 1.59 / 2.17; past 32 workgroups (40) 10000 x 8 16 bits 1.93 / 1.85,
+// 10000 x 3 1.81 / 1.54, 20000 x 4 8 bits 1.68 / 1.32.  At 8 bits eight strips spill 28 registers with up to seven class waves and 204
+// from eight on: 20000 x 10 1.92 / 2.30.
 // Past kMaxWorkgroups four strips have no launch at all, so the row goes to eight while these fit.
 SplitShape pick_shape(const halp_params& p, int num_cus) {
   const int ct = 16 / p.b, U = (p.d + ct - 1) / ct;
@@ -639,9 +640,9 @@ unsigned long long* words_at(void* ws) { return reinterpret_cast<unsigned long l
 
 // A launch takes as many chains as the device holds workgroups for (a wait that other work makes run
 // out all the same only costs time).  us per step of all chains, one workgroup to a CU and as many as
-// fit (the general kernel): 1100 x 2 at 8 bits, 256 chains 5.55 and 2.04 (8.0), 1024 chains 18.4 and 6.9 (31.7);
-// 1100 x 5, 256 chains 7.0 and 4.2 (9.7); 1100 x 2 at 16 bits, 256 chains 8.9 and 3.0 (7.6).  Where one fits:
-// 1100 x 10, 256 chains 8.1 (18.5); 60000 x 15, 256 chains, two to a launch, 795 (2143).
+// fit (the general kernel): 1100 x 2 at 8 bits, 256 chains 5.3 and 1.25 (7.9), 1024 chains 18.1 and 4.9 (31.7);
+// 1100 x 5, 256 chains 5.8 and 3.0 (9.8); 1100 x 2 at 16 bits, 256 chains 8.7 and 1.63 (7.7).  Where one fits:
+// 1100 x 10, 256 chains 6.2 (18.3).
 size_t plan_inner_softmax_split(halp_handle& h) {
   const halp_params& p = h.p;
   if (p.algorithm == HALP_ALG_SVRG || p.loss != HALP_LOSS_SOFTMAX || p.B != 1 || p.K < 2 || p.K > 16) return 0;
